@@ -28,7 +28,7 @@
 #include <complex>
 #include <vector>
 
-#include "cgemm.h"
+#include "hgemm.h"
 #include "rgemm.h"
 #include "rw_common.h"
 #include "rw_fourier.h"
@@ -374,7 +374,7 @@ static int adjoint_prepare(rwpsf_plan* p, int n_stacks) {
   int st;
   if (!p->d_CxT) {
     const double s_max = p->s_max, k = p->k;
-    const double pref = p->opt.focal_length * k / kTwoPi;
+    const double pref = std::ldexp(p->opt.focal_length * k / kTwoPi, -p->pf_exp);   // the pupils carry 2^pf_exp
     std::vector<float> CxT((size_t)w * nxp, 0.f), CyT((size_t)w * nyp, 0.f);
     for (int f = 0; f < nh; ++f) {
       const double sv = (2.0 * f + 1.0 - N) * s_max / N;

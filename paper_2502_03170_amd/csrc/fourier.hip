@@ -6,8 +6,8 @@
 // to the pixel grid, E_c = C sum_{j,l} P~_c[j,l] e^{i k (s_x[j] x + s_y[l] y)},
 // C = -i f k / 2 pi.  The sample grid is symmetric (s[n-1-j] = -s[j]), so each 1-D
 // transform folds into even and odd parts with real coefficients cos / sin, and the
-// separable transform becomes two real GEMMs on the FP32 matrix cores with half the
-// flops of the complex matrix DFT:
+// separable transform becomes two real GEMMs with half the flops of the complex matrix DFT,
+// run on the F16 matrix cores with split operands at FP32-level accuracy (hgemm.h):
 //   K1  pupil_build_folded   mirror-folded pupils Pf (four parities per folded cell)
 //                     of up to 8 stacks, each cell's P_c formed on the way (FP64
 //                     phase: Gibson-Lanni, Zernike, free phase map, lateral emitter
@@ -17,8 +17,7 @@
 //                     pupil tile is staged (FP64 phase, reduced mod 2 pi, FP32 sincos)
 //   K3  gemm_image    E'_c = A2 T_c (fold along x) for c = x, y, z in one workgroup,
 //                     writing E = -i E' and I = sum_c |E_c|^2 from registers.
-#include "cgemm.h"
-#include "rgemm.h"
+#include "hgemm.h"
 #include "rw_common.h"
 #include "rw_fourier.h"
 
@@ -36,6 +35,28 @@ __global__ void zernike_table_kernel(float* __restrict__ out, int n, int nj) {
   const double cp = r > 0 ? u / r : 1.0, sp = r > 0 ? v / r : 0.0;
   for (int q = 1; q <= nj; ++q)
     out[(size_t)(q - 1) * n * n + cell] = (float)zernike_noll(q, r, cp, sp);
+}
+
+// Plan-time table: one thread per (row r, folded cell f), FP64 sine and cosine.
+__global__ void dft_panel_kernel(_Float16* __restrict__ panel, int rows, int count, int n, int w, double k,
+                                 double s_max, double pitch) {
+  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx >= rows * (w / 2)) return;
+  const int r = idx % rows, f = idx / rows;
+  double v[2] = {0.0, 0.0};
+  if (r < count && f < (n + 1) / 2) {
+    const double ph = k * ((2.0 * f + 1.0 - n) * s_max / n) * ((double)(r - count / 2) * pitch);
+    sincos(ph, &v[1], &v[0]);
+  }
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    const double x = ldexp(v[p], kTabExp);
+    const int kk = 2 * f + p;
+    _Float16* o = panel + ((size_t)(kk / 16 * 4 + kk % 16 / 8) * rows + r) * 8 + kk % 8;
+    const _Float16 hi = (_Float16)(float)x;
+    o[0] = hi;
+    o[(size_t)2 * rows * 8] = (_Float16)(float)(x - (double)(float)hi);
+  }
 }
 
 // --------------------------------------------------------------------------
@@ -181,156 +202,159 @@ __global__ void __launch_bounds__(256) pupil_build_folded_kernel(PupilArgs a, co
 }
 
 // --------------------------------------------------------------------------
-// A operand of K2: rows 2q + ri (q = 2 jf + pj, ri = re/im) and contraction index
-// kk = 2 lf + pl of the folded pupil, with the defocus factor exp(i k s_z z) applied
-// on the way into LDS.  One thread takes one folded cell (jf, lf): its four values
-// share one defocus factor, whose phase is formed and reduced in FP64 (in revolutions)
-// before the FP32 hardware sine and cosine.
+// A operand of K2: the folded pupil with the defocus factor exp(i k s_z z) applied and
+// split into f16 halves on the way into LDS.  Contraction index kk = 2 lf + pl; 32-row
+// blocks hold 16 folded rows q = 2 jf + pj as rows 8 (q/4) + 4 ri + q%4 (ri = re / im), so
+// that an accumulator lane holds 16 consecutive q of one part.  One thread takes a
+// folded cell (jf, lf) with its four parities: its eight values share one defocus factor, whose phase is formed and reduced in FP64 (in revolutions) before the
+// FP32 hardware sine and cosine.
 // --------------------------------------------------------------------------
-template <class Cfg>
+// LDS position of a row within its 32-row block.  The row bits are (pj, jf0, ri, jf1, jf2);
+// position (jf0, jf1 ^ pj, jf2 ^ ri, pj, ri) puts both the eight rows that a read phase
+// covers (all pj, jf0, ri) and the eight that a write phase covers (all jf0, jf1, jf2) in
+// distinct 16-byte columns of the banks.
+struct HgFoldRows {
+  static __device__ __forceinline__ int make(int pj, int ri, int j8) {
+    return (j8 ^ (pj << 1) ^ (ri << 2)) | (pj << 3) | (ri << 4);
+  }
+  static __device__ __forceinline__ int pos(int r) {
+    return make(r & 1, (r >> 2) & 1, ((r >> 1) & 1) | ((r >> 2) & 6));
+  }
+};
+
+// PZ planes share a tile: its BM rows are PZ runs of BM / PZ rows of the same folded pupil
+// rows, each with its own defocus, so that the pupil is read once for all of them.
+template <class Cfg, int PZ>
 struct FoldDefocusLoader {
-  static constexpr int JF = Cfg::BM / 4, LF = Cfg::BK / 2;
-  static constexpr int PER_THREAD = JF * LF / Cfg::NT;
-  static_assert(JF * LF % Cfg::NT == 0, "loader shape");
+  using Rows = HgFoldRows;
+  static constexpr int JF = Cfg::BM / PZ / 4, CELLS = Cfg::BK / 2;
+  static constexpr int TOTAL = JF * CELLS;
+  static constexpr int PER_THREAD = (TOTAL + Cfg::NT - 1) / Cfg::NT;
+  static_assert(JF % 8 == 0, "whole 32-row blocks per plane");
   const float2* Pf;    // [2 nhp][2 nhp] of this stack and component, from folded row jf0
   const double* kszf;  // [nhp][nhp], from row jf0
-  double zrev;         // z / 2 pi, so that k s_z zrev is the phase in revolutions
+  double zrev[PZ];     // z / 2 pi, so that k s_z zrev is the phase in revolutions
   int w, nhp;          // w = 2 nhp
   struct Regs {
-    float4 v0[PER_THREAD], v1[PER_THREAD];
+    float4 v[PER_THREAD][2];   // [pj]: (pl = 0, 1)
     double kz[PER_THREAD];
   };
+  // folded row and cell of task idx: the four cells of a 16-byte piece side by side, then
+  // eight folded rows, then the pieces, then the 32-row blocks
+  static __device__ __forceinline__ void task(int idx, int* jl, int* lc) {
+    *jl = ((idx >> 2) & 7) | (idx / (4 * Cfg::BK) << 3);
+    *lc = (idx & 3) | (((idx >> 5) % (Cfg::BK / 8)) << 2);
+  }
 
   __device__ Regs load(int k0, int tid) const {
     Regs r;
 #pragma unroll
     for (int i = 0; i < PER_THREAD; ++i) {
       const int idx = tid + i * Cfg::NT;
-      const int jl = idx / LF, ll = idx % LF;
-      const size_t off = (size_t)(2 * jl) * w + k0 + 2 * ll;
-      r.v0[i] = *reinterpret_cast<const float4*>(Pf + off);       // pj = 0, pl = 0, 1
-      r.v1[i] = *reinterpret_cast<const float4*>(Pf + off + w);   // pj = 1
-      r.kz[i] = kszf[(size_t)jl * nhp + k0 / 2 + ll];
+      if (TOTAL % Cfg::NT != 0 && idx >= TOTAL) break;
+      int jl, lc;
+      task(idx, &jl, &lc);
+      const float2* p = Pf + (size_t)(2 * jl) * w + k0 + 2 * lc;
+      r.v[i][0] = *reinterpret_cast<const float4*>(p);
+      r.v[i][1] = *reinterpret_cast<const float4*>(p + w);
+      r.kz[i] = kszf[(size_t)jl * nhp + k0 / 2 + lc];
     }
     return r;
   }
-  // LDS tile [row][k]: rows 4 jl + 2 pj + ri, columns 2 ll + pl
-  __device__ void store(float* dst, int tid, const Regs& r) const {
-    const float4* v0 = r.v0;
-    const float4* v1 = r.v1;
-    const double* kz = r.kz;
+  __device__ void store(char* dst, int tid, const Regs& r) const {
 #pragma unroll
     for (int i = 0; i < PER_THREAD; ++i) {
       const int idx = tid + i * Cfg::NT;
-      const int jl = idx / LF, ll = idx % LF;
-      float sn, cs;
-      sincos_rev(kz[i] * zrev, &sn, &cs);
-      float* d = dst + (4 * jl) * Cfg::LDK + 2 * ll;
-      *reinterpret_cast<float2*>(d) = make_float2(v0[i].x * cs - v0[i].y * sn, v0[i].z * cs - v0[i].w * sn);
-      *reinterpret_cast<float2*>(d + Cfg::LDK) =
-          make_float2(v0[i].x * sn + v0[i].y * cs, v0[i].z * sn + v0[i].w * cs);
-      *reinterpret_cast<float2*>(d + 2 * Cfg::LDK) =
-          make_float2(v1[i].x * cs - v1[i].y * sn, v1[i].z * cs - v1[i].w * sn);
-      *reinterpret_cast<float2*>(d + 3 * Cfg::LDK) =
-          make_float2(v1[i].x * sn + v1[i].y * cs, v1[i].z * sn + v1[i].w * cs);
+      if (TOTAL % Cfg::NT != 0 && idx >= TOTAL) break;
+      int jl, lc;
+      task(idx, &jl, &lc);
+      const int piece = 4 * (lc >> 3) + ((lc >> 2) & 1);
+      char* d = dst + (size_t)(piece * Cfg::BM + 32 * (jl >> 3)) * 16 + 4 * (lc & 3);
+#pragma unroll
+      for (int z = 0; z < PZ; ++z) {
+        float sn, cs;
+        sincos_rev(r.kz[i] * zrev[z], &sn, &cs);
+#pragma unroll
+        for (int pj = 0; pj < 2; ++pj)
+#pragma unroll
+          for (int ri = 0; ri < 2; ++ri) {
+            const float4 v = r.v[i][pj];
+            const float x0 = ri ? v.x * sn + v.y * cs : v.x * cs - v.y * sn;
+            const float x1 = ri ? v.z * sn + v.w * cs : v.z * cs - v.w * sn;
+            unsigned hi, lo;
+            hg_split2(x0, x1, &hi, &lo);
+            char* o = d + (z * (Cfg::BM / PZ) + HgFoldRows::make(pj, ri, jl & 7)) * 16;
+            *reinterpret_cast<unsigned*>(o) = hi;
+            *reinterpret_cast<unsigned*>(o + 2 * Cfg::BM * 16) = lo;
+          }
+      }
     }
   }
 };
 
-#ifndef RW_F1_BM
-#define RW_F1_BM 128
-#endif
-#ifndef RW_F1_BN
-#define RW_F1_BN 128
-#endif
-#ifndef RW_F1_BK
-#define RW_F1_BK 16
-#endif
-#ifndef RW_F1_WM
-#define RW_F1_WM 64
-#endif
-#ifndef RW_F1_WN
-#define RW_F1_WN 64
-#endif
-#ifndef RW_F1_OCC
-#define RW_F1_OCC 4
-#endif
-#ifndef RW_F2_BM
-#define RW_F2_BM 128
-#endif
-#ifndef RW_F2_BN
-#define RW_F2_BN 256
-#endif
-#ifndef RW_F2_BK
-#define RW_F2_BK 16
-#endif
-#ifndef RW_F2_WM
-#define RW_F2_WM 64
-#endif
-#ifndef RW_F2_WN
-#define RW_F2_WN 64
-#endif
-#ifndef RW_F2_OCC
-#define RW_F2_OCC 2
-#endif
-using CfgPupil = RgCfg<RW_F1_BM, RW_F1_BN, RW_F1_BK, RW_F1_WM, RW_F1_WN>;
-// image GEMM: 128 x 256 tiles (a whole padded row of re/im columns at 128-pixel width) on
-// eight 64 x 64 waves; launches whose padded width 2 nyp is not a multiple of 256, or
-// that would underfill the GPU, take CfgImageS
-using CfgImage = RgCfg<RW_F2_BM, RW_F2_BN, RW_F2_BK, RW_F2_WM, RW_F2_WN>;
-// pupils whose folded row count 4 nhp is a multiple of 256 take 256-row tiles (8 waves;
-// the y-table tile is then shared by twice the rows)
-using CfgPupilL = RgCfg<256, 128, 16, 64, 64>;
-// outputs of at most 64 pixels per axis are padded to 64 and use half-height tiles
-// (256 rows when the folded row count allows, as above)
-using CfgPupilS = RgCfg<128, 64, 16, 64, 32>;
-using CfgPupilSL = RgCfg<256, 64, 16, 64, 64>;
-using CfgImageS = RgCfg<64, 64, 32, 32, 32>;
-static_assert((4 * kFoldPad) % CfgPupil::BM == 0 && (2 * kFoldPad) % CfgPupil::BK == 0, "pupil GEMM padding");
-static_assert((4 * kFoldPad) % CfgPupilS::BM == 0 && kPadSmall % CfgPupilS::BN == 0 && kPadSmall % CfgImageS::BM == 0 &&
-                  (2 * kPadSmall) % CfgImageS::BN == 0 && (2 * kFoldPad) % CfgImageS::BK == 0,
-              "small-output padding");
-static_assert(kPadY % CfgPupil::BN == 0 && kPadX % CfgImage::BM == 0 && (2 * kPadY) % CfgImage::BN == 0 &&
-                  (2 * kFoldPad) % CfgImage::BK == 0,
-              "image GEMM padding");
+// Measured on 16 stacks of 128 x 128 x 64 at a 256 x 256 pupil (fields and intensity): the
+// call took 1313 us with FP32 MFMA tiles and takes 692 us (pupil GEMM 860 -> 345-400 us, image
+// GEMM 480 -> 310-340 us, whose 0.8 GB of T and 0.47 GB of output are 4 TB/s of HBM); one
+// 201 x 201 image 52 -> 25 us.  The pupil GEMM's pipes hardly overlap: its MFMAs alone need
+// 115 us, without them it takes 257 us, without global loads 247 us; one plane per tile
+// (the pupil then crosses L2 twice as often) 372 us, other tile shapes and occupancies
+// (128 x 128, eight waves, k-stages of 32) 372-450 us.
+// Tiles.  Pupil GEMM: 128 rows of two planes x 128 columns (four 64 x 128 waves, two
+// workgroups per CU), 64 columns for outputs of at most 64 pixels; image GEMM: 128 (n, re /
+// im) rows x 128 pixels m.  Launches that would underfill the GPU take the 64 x 64 tiles.
+using CfgPupil = HgCfg<256, 128, 16, 64, 128>;
+using CfgPupilN = HgCfg<256, 64, 16, 64, 64>;
+using CfgPupilS = HgCfg<64, 64, 32, 32, 32>;
+using CfgImage = HgCfg<128, 128, 32, 64, 64>;
+using CfgImageM = HgCfg<128, 64, 32, 64, 32>;
+using CfgImageS = HgCfg<64, 64, 32, 32, 32>;
+static_assert((4 * kFoldPad) % (CfgPupil::BM / 2) == 0 && (2 * kFoldPad) % 32 == 0, "pupil GEMM padding");
+static_assert(kPadY % CfgPupil::BN == 0 && kPadX % CfgImage::BN == 0 && (2 * kPadSmall) % CfgImage::BM == 0 &&
+                  kPadSmall % CfgPupilS::BN == 0 && kPadSmall % CfgImageS::BN == 0,
+              "output padding");
 
-// K2: T[s][z][c] = (Pf~ B1) with rows 2q + ri, i.e. the complex [2 nhp] x [nyp] matrix
-// T[q][n] = sum_kk Pf~[q][kk] B1[kk][n], B1[2lf][n] = cos(k s_lf y_n), B1[2lf+1][n] = sin(...)
-template <class Cfg, int OCC>
+// K2: T[s][z][c] = (Pf~ B1), i.e. the complex [2 nhp] x [nyp] matrix
+// T[q][n] = sum_kk Pf~[q][kk] B1[kk][n], B1[2lf][n] = cos(k s_lf y_n), B1[2lf+1][n] = sin(...),
+// written as a panel of rows 2n + ri with k = q for K3: a lane's 16 accumulators are the 16
+// consecutive q of one row, and the 64 lanes of a store cover 1 KB without gaps.
+template <class Cfg, int PZ, int OCC>
 __global__ void __launch_bounds__(Cfg::NT, OCC) gemm_pupil_kernel(Gemm1Args a) {
-  extern __shared__ float lds[];
+  extern __shared__ __align__(16) char hlds[];
+  constexpr int BR = Cfg::BM / PZ;   // pupil rows of the tile
   const int w = 2 * a.nhp;
-  const int tiles_m = 2 * w / Cfg::BM;
+  const int tiles_m = 2 * w / BR;
   const int tiles_n = a.nyp / Cfg::BN;
-  const int nblocks = a.nstk * a.nzs * a.nc * tiles_m * tiles_n;
+  const int zgroups = (a.nzs + PZ - 1) / PZ;
+  const int nblocks = a.nstk * zgroups * a.nc * tiles_m * tiles_n;
   int id = xcd_remap(blockIdx.x, nblocks);
   const int tn = id % tiles_n; id /= tiles_n;
   const int tm = id % tiles_m; id /= tiles_m;
-  const int zi = id % a.nzs; id /= a.nzs;
+  const int zi = id % zgroups * PZ; id /= zgroups;
   const int c = id % a.nc; id /= a.nc;
   const int s = id;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wrow = (wave / Cfg::WAVES_N) * Cfg::WM, wcol = (wave % Cfg::WAVES_N) * Cfg::WN;
   const size_t fpp = (size_t)w * w;
-  const int row0 = tm * Cfg::BM, col0 = tn * Cfg::BN;
+  const int row0 = tm * BR, col0 = tn * Cfg::BN;
   const int jf0 = row0 / 4;
 
-  FoldDefocusLoader<Cfg> la;
+  FoldDefocusLoader<Cfg, PZ> la;
   la.Pf = a.Pf + ((size_t)s * a.nc + c) * fpp + (size_t)(2 * jf0) * w;
   la.kszf = a.kszf + (size_t)jf0 * a.nhp;
-  la.zrev = (a.z[a.z0 + zi] + a.zoff[s]) * (1.0 / kTwoPi);
+#pragma unroll
+  for (int z = 0; z < PZ; ++z) la.zrev[z] = (a.z[a.z0 + min(zi + z, a.nzs - 1)] + a.zoff[s]) * (1.0 / kTwoPi);
   la.w = w;
   la.nhp = a.nhp;
-  RRowLoader<Cfg, Cfg::BN> lb;
-  lb.src = a.B1 + (size_t)col0 * w;
-  lb.ld = w;
+  HgPanelLoader<Cfg, Cfg::BN> lb;
+  lb.src = a.B1 + col0;
+  lb.ld = a.nyp;
 
   // The pupil is zero outside the disk (2j+1-n)^2 + (2l+1-n)^2 <= n^2: this row block
   // needs the folded columns lf that its row nearest the centre (largest jf) reaches.
   int k_begin = 0, k_end = w;
   {
     const int n = a.n, nh = (a.n + 1) / 2;
-    const int jf_hi = min(jf0 + Cfg::BM / 4, nh) - 1;
+    const int jf_hi = min(jf0 + BR / 4, nh) - 1;
     if (jf_hi < jf0) {
       k_end = Cfg::BK;   // padding rows only: one (zero) stage
     } else {
@@ -340,94 +364,93 @@ __global__ void __launch_bounds__(Cfg::NT, OCC) gemm_pupil_kernel(Gemm1Args a) {
       k_begin = (2 * lf_lo / Cfg::BK) * Cfg::BK;
     }
   }
-  RgAcc<Cfg> acc;
+  HgAcc<Cfg> acc;
   acc.zero();
-  // unordered: the compiler's interleaving of the defocus arithmetic measured faster here
-  rg_mainloop<Cfg, kOrderFree>(acc, la, lb, k_begin, k_end, lds, tid, wrow, wcol, lane);
+  hg_mainloop<Cfg>(acc, la, lb, k_begin, k_end, hlds, tid, wrow, wcol, lane);
 
-  // rows 2q + ri: registers r and r + 1 (r even) are the re/im parts of one T[q][n]
-  float2* T = a.T + (((size_t)s * a.nzs + zi) * a.nc + c) * (size_t)w * a.nyp;
+  // each wave's rows belong to one plane
+  static_assert(BR % Cfg::WM == 0, "a wave stays within a plane");
+  const int zw = zi + wrow / BR, prow = row0 + wrow % BR;
+  if (zw >= a.nzs) return;
+  uint4* T = a.T + (((size_t)s * a.nzs + zw) * a.nc + c) * (hg_panel_bytes(w, 2 * a.nyp) / 16);
+  const int ri = lane >> 5;
 #pragma unroll
   for (int i = 0; i < Cfg::TM; ++i)
 #pragma unroll
     for (int jj = 0; jj < Cfg::TN; ++jj) {
-      const int col = col0 + rg_col(wcol, jj, lane);
+      const int n = col0 + wcol + 32 * jj + (lane & 31);
+      float v[16];
 #pragma unroll
-      for (int r = 0; r < 16; r += 2) {
-        const int q = (row0 + rg_row(wrow, i, r, lane)) >> 1;
-        T[(size_t)q * a.nyp + col] = make_float2(acc.c[i][jj][r], acc.c[i][jj][r + 1]);
-      }
+      for (int r = 0; r < 16; ++r) v[r] = acc.c[i][jj][r] * a.tscale;
+      uint4 piece[4];
+      hg_split16(v, piece);
+      uint4* o = T + (size_t)(4 * ((prow + 32 * i) / 32)) * (2 * a.nyp) + 2 * n + ri;
+#pragma unroll
+      for (int p = 0; p < 4; ++p) o[(size_t)p * (2 * a.nyp)] = piece[p];
     }
 }
 
-// K3: E'[m][(n, ri)] = sum_kk A2[m][kk] T[kk][(n, ri)] with A2[m][2jf] = pref cos(k s_jf x_m),
-// A2[m][2jf+1] = pref sin(...) for all channels in one workgroup; E = -i E' and
-// I = sum_c |E_c|^2 are written from registers.
-// One channel of an output tile of K3: the GEMM (its first stage already in ra, rb),
-// then the next channel's first stage is loaded, then this channel's fields are stored
-// and its intensity accumulated.  The loads go first so that the wait before they are
-// staged in LDS does not also wait for the stores.
+// K3: E'[(n, ri)][m] = sum_kk T[kk][(n, ri)] A2[kk][m] with A2[2jf][m] = cos(k s_jf x_m),
+// A2[2jf+1][m] = sin(...), for all channels in one workgroup; E = -i E' (times the
+// prefactor) and I = sum_c |E_c|^2 are written from registers: accumulators 4g .. 4g + 3 of
+// a lane are two neighbouring pixels (re, im) of one image row m, one 16-byte store.
+// One channel: the GEMM (its first stage already in ra, rb), then the next channel's first
+// stage is loaded, then this channel's fields are stored and its intensity accumulated.
+// The loads go first so that the wait before they are staged in LDS does not also wait
+// for the stores.
 template <class Cfg, bool FULL, bool HAS_E, class LA, class LB>
-__device__ __forceinline__ void image_channel(const Gemm2Args& a, float* lds, int c, const LA& la, LB& lb,
-                                              typename LA::Regs& ra, typename LB::Regs& rb, const float* tsrc,
-                                              size_t tch, float* E, int row0, int col0, float (*isum)[Cfg::TN][8]) {
+__device__ __forceinline__ void image_channel(const Gemm2Args& a, char* lds, int c, LA& la, const LB& lb,
+                                              typename LA::Regs& ra, typename LB::Regs& rb, const uint4* tsrc,
+                                              size_t tch, float2* E, int row0, int col0,
+                                              float (*isum)[Cfg::TN][8]) {
   const int w = 2 * a.nhp;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wrow = (wave / Cfg::WAVES_N) * Cfg::WM, wcol = (wave % Cfg::WAVES_N) * Cfg::WN;
-  const int ri = lane & 1;   // columns alternate re/im with the lane index
-  RgAcc<Cfg> acc;
+  HgAcc<Cfg> acc;
   acc.zero();
-  rg_mainloop_pre<Cfg, kOrderFull>(acc, la, lb, ra, rb, 0, w, lds, tid, wrow, wcol, lane);
+  hg_mainloop_pre<Cfg>(acc, la, lb, ra, rb, 0, w, lds, tid, wrow, wcol, lane);
   // first stage of the next channel (the last channel reloads its own, unused)
-  lb.src = tsrc + (size_t)min(c + 1, a.nc - 1) * tch;
+  la.src = tsrc + (size_t)min(c + 1, a.nc - 1) * tch;
   ra = la.load(0, tid);
   rb = lb.load(0, tid);
   __builtin_amdgcn_sched_barrier(0);
-
-  // Lane 2t holds Re E' and lane 2t+1 Im E' of one pixel: E = -i E' = (Im E', -Re E'),
-  // so the odd lane writes E.x = v and the even lane E.y = -v.  A DPP swap within lane
-  // pairs gives each lane its partner's value for the intensity.
-  // The store offsets are the same for every channel; keeping them opaque here stops
-  // them from being hoisted out of the channel loop (32 live offsets would spill).
-  int mbase = row0 + rg_row(wrow, 0, 0, lane);
-  asm volatile("" : "+v"(mbase));
 #pragma unroll
   for (int i = 0; i < Cfg::TM; ++i)
 #pragma unroll
     for (int jj = 0; jj < Cfg::TN; ++jj) {
-      const int n = (col0 + rg_col(wcol, jj, lane)) >> 1;
+      const int m = col0 + wcol + 32 * jj + (lane & 31);
+      const int n0 = (row0 + wrow + 32 * i) / 2 + 2 * (lane >> 5);
 #pragma unroll
-      for (int r = 0; r < 8; ++r) {
-        float q[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const int rr = r + 8 * h;
-          const int m = mbase + 32 * i + (rr >> 2) * 8 + (rr & 3);
-          const float v = acc.c[i][jj][rr];
-          const float u = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, false));
-          q[h] = v * v + u * u;
-          if (HAS_E && (FULL || (m < a.nx && n < a.ny))) E[2 * ((size_t)m * a.ny + n) + 1 - ri] = ri ? v : -v;
+      for (int g = 0; g < 4; ++g) {
+        const int n = n0 + 4 * g;
+        // E = -i E' = (Im E', -Re E')
+        const float4 e = make_float4(acc.c[i][jj][4 * g + 1] * a.escale, acc.c[i][jj][4 * g] * -a.escale,
+                                     acc.c[i][jj][4 * g + 3] * a.escale, acc.c[i][jj][4 * g + 2] * -a.escale);
+        isum[i][jj][2 * g] += e.x * e.x + e.y * e.y;
+        isum[i][jj][2 * g + 1] += e.z * e.z + e.w * e.w;
+        if (HAS_E) {
+          float2* o = E + (size_t)m * a.ny + n;
+          if (FULL) {
+            *reinterpret_cast<float4*>(o) = e;
+          } else if (m < a.nx) {
+            if (n < a.ny) o[0] = make_float2(e.x, e.y);
+            if (n + 1 < a.ny) o[1] = make_float2(e.z, e.w);
+          }
         }
-        isum[i][jj][r] += ri ? q[1] : q[0];
       }
     }
 }
 
-// One output tile of K3 for every channel.  FULL: the tile lies inside the nx x ny
-// image, so its stores need no per-lane bounds and run as straight-line code.  The
-// first channel is peeled so that every entry into the channel loop follows a batch of
-// stores issued after the loads it waits for.
+// One output tile of K3 for every channel.  FULL: the tile lies inside the nx x ny image
+// and its rows are 16-byte aligned, so its stores need no per-lane bounds and run as
+// straight-line 16-byte (fields) and 8-byte (intensity) stores.
 template <class Cfg, bool FULL, bool HAS_E>
-__device__ __forceinline__ void image_tile(const Gemm2Args& a, float* lds, int s, int zi, int row0, int col0) {
+__device__ __forceinline__ void image_tile(const Gemm2Args& a, char* lds, int s, int zi, int row0, int col0) {
   const int w = 2 * a.nhp;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wrow = (wave / Cfg::WAVES_N) * Cfg::WM, wcol = (wave % Cfg::WAVES_N) * Cfg::WN;
   const size_t plane = (size_t)a.nx * a.ny;
   const size_t gstk = (size_t)(a.s_base + s), gz = (size_t)(a.z0 + zi);
-  const int ri = lane & 1;
-
-  // intensity of the lane pair's 16 pixels per block: the even lane keeps those of
-  // registers 0-7, the odd lane those of registers 8-15
   float isum[Cfg::TM][Cfg::TN][8];
 #pragma unroll
   for (int i = 0; i < Cfg::TM; ++i)
@@ -436,33 +459,39 @@ __device__ __forceinline__ void image_tile(const Gemm2Args& a, float* lds, int s
 #pragma unroll
       for (int r = 0; r < 8; ++r) isum[i][jj][r] = 0.f;
 
-  RRowLoader<Cfg, Cfg::BM> la;
-  la.src = a.A2 + (size_t)row0 * w;
-  la.ld = w;
-  RColLoader<Cfg, Cfg::BN> lb;
-  const float* tsrc = reinterpret_cast<const float*>(a.T + ((size_t)s * a.nzs + zi) * a.nc * (size_t)w * a.nyp) + col0;
-  const size_t tch = 2 * (size_t)w * a.nyp;   // floats per channel of T
-  lb.src = tsrc;
-  lb.ld = 2 * a.nyp;
+  const size_t tch = hg_panel_bytes(w, 2 * a.nyp) / 16;   // 16-byte pieces per channel of T
+  const uint4* tsrc = a.T + ((size_t)s * a.nzs + zi) * a.nc * tch + row0;
+  HgPanelLoader<Cfg, Cfg::BM> la;
+  la.src = tsrc;
+  la.ld = 2 * a.nyp;
+  HgPanelLoader<Cfg, Cfg::BN> lb;
+  lb.src = a.A2 + col0;
+  lb.ld = a.nxp;
   auto ra = la.load(0, tid);
   auto rb = lb.load(0, tid);
-  float* E0 = HAS_E ? reinterpret_cast<float*>(a.E + (gstk * a.nz + gz) * a.nc * plane) : nullptr;
-  image_channel<Cfg, FULL, HAS_E>(a, lds, 0, la, lb, ra, rb, tsrc, tch, E0, row0, col0, isum);
+  float2* E0 = HAS_E ? a.E + (gstk * a.nz + gz) * a.nc * plane : nullptr;
 #pragma unroll 1
-  for (int c = 1; c < a.nc; ++c)
-    image_channel<Cfg, FULL, HAS_E>(a, lds, c, la, lb, ra, rb, tsrc, tch, HAS_E ? E0 + 2 * c * plane : nullptr,
-                                    row0, col0, isum);
+  for (int c = 0; c < a.nc; ++c)
+    image_channel<Cfg, FULL, HAS_E>(a, lds, c, la, lb, ra, rb, tsrc, tch, HAS_E ? E0 + c * plane : nullptr, row0,
+                                    col0, isum);
   if (a.I) {
     float* I = a.I + (gstk * a.nz + gz) * plane;
 #pragma unroll
     for (int i = 0; i < Cfg::TM; ++i)
 #pragma unroll
       for (int jj = 0; jj < Cfg::TN; ++jj) {
-        const int n = (col0 + rg_col(wcol, jj, lane)) >> 1;
+        const int m = col0 + wcol + 32 * jj + (lane & 31);
+        const int n0 = (row0 + wrow + 32 * i) / 2 + 2 * (lane >> 5);
 #pragma unroll
-        for (int r = 0; r < 8; ++r) {
-          const int m = row0 + rg_row(wrow, i, r + 8 * ri, lane);
-          if (FULL || (m < a.nx && n < a.ny)) I[(size_t)m * a.ny + n] = isum[i][jj][r];
+        for (int g = 0; g < 4; ++g) {
+          const int n = n0 + 4 * g;
+          float* o = I + (size_t)m * a.ny + n;
+          if (FULL) {
+            *reinterpret_cast<float2*>(o) = make_float2(isum[i][jj][2 * g], isum[i][jj][2 * g + 1]);
+          } else if (m < a.nx) {
+            if (n < a.ny) o[0] = isum[i][jj][2 * g];
+            if (n + 1 < a.ny) o[1] = isum[i][jj][2 * g + 1];
+          }
         }
       }
   }
@@ -470,9 +499,9 @@ __device__ __forceinline__ void image_tile(const Gemm2Args& a, float* lds, int s
 
 template <class Cfg, int OCC>
 __global__ void __launch_bounds__(Cfg::NT, OCC) gemm_image_kernel(Gemm2Args a) {
-  extern __shared__ float lds[];
-  const int tiles_m = a.nxp / Cfg::BM;
-  const int tiles_n = 2 * a.nyp / Cfg::BN;
+  extern __shared__ __align__(16) char hlds[];
+  const int tiles_m = 2 * a.nyp / Cfg::BM;
+  const int tiles_n = a.nxp / Cfg::BN;
   const int nblocks = a.nstk * a.nzs * tiles_m * tiles_n;
   int id = xcd_remap(blockIdx.x, nblocks);
   const int tn = id % tiles_n; id /= tiles_n;
@@ -480,17 +509,17 @@ __global__ void __launch_bounds__(Cfg::NT, OCC) gemm_image_kernel(Gemm2Args a) {
   const int zi = id % a.nzs; id /= a.nzs;
   const int s = id;
   const int row0 = tm * Cfg::BM, col0 = tn * Cfg::BN;
-  const bool full = row0 + Cfg::BM <= a.nx && col0 + Cfg::BN <= 2 * a.ny;
+  const bool full = a.vec && row0 + Cfg::BM <= 2 * a.ny && col0 + Cfg::BN <= a.nx;
   if (a.E) {
     if (full)
-      image_tile<Cfg, true, true>(a, lds, s, zi, row0, col0);
+      image_tile<Cfg, true, true>(a, hlds, s, zi, row0, col0);
     else
-      image_tile<Cfg, false, true>(a, lds, s, zi, row0, col0);
+      image_tile<Cfg, false, true>(a, hlds, s, zi, row0, col0);
   } else {
     if (full)
-      image_tile<Cfg, true, false>(a, lds, s, zi, row0, col0);
+      image_tile<Cfg, true, false>(a, hlds, s, zi, row0, col0);
     else
-      image_tile<Cfg, false, false>(a, lds, s, zi, row0, col0);
+      image_tile<Cfg, false, false>(a, hlds, s, zi, row0, col0);
   }
 }
 
@@ -500,6 +529,14 @@ __global__ void __launch_bounds__(Cfg::NT, OCC) gemm_image_kernel(Gemm2Args a) {
 hipError_t launch_zernike_table(float* out, int n, int nj, hipStream_t st) {
   const int cells = n * n;
   hipLaunchKernelGGL(zernike_table_kernel, dim3((cells + 255) / 256), dim3(256), 0, st, out, n, nj);
+  return hipGetLastError();
+}
+
+hipError_t launch_dft_panel(uint4* panel, int rows, int count, int n, int w, double k, double s_max, double pitch,
+                            hipStream_t st) {
+  const int total = rows * (w / 2);
+  hipLaunchKernelGGL(dft_panel_kernel, dim3((total + 255) / 256), dim3(256), 0, st, (_Float16*)panel, rows, count, n, w,
+                     k, s_max, pitch);
   return hipGetLastError();
 }
 
@@ -518,17 +555,17 @@ hipError_t launch_pupil_build_folded(const PupilArgs& a, const float2* Q, const 
   return hipGetLastError();
 }
 
-template <class Cfg, int OCC>
+template <class Cfg, int PZ, int OCC>
 static hipError_t gemm_pupil_launch(const Gemm1Args& a, hipStream_t st) {
-  const int tiles = (4 * a.nhp / Cfg::BM) * (a.nyp / Cfg::BN);
-  const int nblocks = a.nstk * a.nzs * a.nc * tiles;
-  hipLaunchKernelGGL((gemm_pupil_kernel<Cfg, OCC>), dim3(nblocks), dim3(Cfg::NT), Cfg::LDS_BYTES, st, a);
+  const int tiles = (4 * a.nhp * PZ / Cfg::BM) * (a.nyp / Cfg::BN);
+  const int nblocks = a.nstk * ((a.nzs + PZ - 1) / PZ) * a.nc * tiles;
+  hipLaunchKernelGGL((gemm_pupil_kernel<Cfg, PZ, OCC>), dim3(nblocks), dim3(Cfg::NT), Cfg::LDS_BYTES, st, a);
   return hipGetLastError();
 }
 
 template <class Cfg, int OCC>
 static hipError_t gemm_image_launch(const Gemm2Args& a, hipStream_t st) {
-  const int tiles = (a.nxp / Cfg::BM) * (2 * a.nyp / Cfg::BN);
+  const int tiles = (2 * a.nyp / Cfg::BM) * (a.nxp / Cfg::BN);
   const int nblocks = a.nstk * a.nzs * tiles;
   hipLaunchKernelGGL((gemm_image_kernel<Cfg, OCC>), dim3(nblocks), dim3(Cfg::NT), Cfg::LDS_BYTES, st, a);
   return hipGetLastError();
@@ -547,34 +584,31 @@ static int device_cus() {
   return cus[dev];
 }
 
-// The tile height follows the padding the plan chose (multiples of 128, or of 64 for
-// outputs of at most 64 pixels along that axis).  A launch whose large tiles would give
-// fewer than two workgroups per CU (a few planes, e.g. one image) takes the small tiles
-// instead: its time is then set by how many CUs work on it, not by the tile efficiency.
+// A launch whose large tiles would give fewer than two workgroups per CU (a few planes, e.g.
+// one image) takes the small tiles instead: its time is then set by how many CUs work on
+// it, not by the tile efficiency.
 hipError_t launch_gemm_pupil(const Gemm1Args& a, hipStream_t st) {
   const long long work = (long long)a.nstk * a.nzs * a.nc;
   const bool few = work * ((4 * a.nhp + 127) / 128) * ((a.nyp + 127) / 128) < 2LL * device_cus();
-  if (!few && a.nyp % CfgPupilL::BN == 0 && (4 * a.nhp) % CfgPupilL::BM == 0)
-    return gemm_pupil_launch<CfgPupilL, 2>(a, st);
-  if (!few && a.nyp % CfgPupil::BN == 0) return gemm_pupil_launch<CfgPupil, RW_F1_OCC>(a, st);
-  if (!few && (4 * a.nhp) % CfgPupilSL::BM == 0) return gemm_pupil_launch<CfgPupilSL, 2>(a, st);
-  return gemm_pupil_launch<CfgPupilS, 4>(a, st);
+  if (few) return gemm_pupil_launch<CfgPupilS, 1, 2>(a, st);
+  if (a.nyp % 128 == 0) return gemm_pupil_launch<CfgPupil, 2, 2>(a, st);
+  return gemm_pupil_launch<CfgPupilN, 2, 2>(a, st);
 }
 
 hipError_t launch_gemm_image(const Gemm2Args& a, hipStream_t st) {
   const long long work = (long long)a.nstk * a.nzs;
   const bool few = work * ((a.nxp + 127) / 128) * ((2 * a.nyp + 127) / 128) < 2LL * device_cus();
-  if (!few && a.nxp % CfgImage::BM == 0 && (2 * a.nyp) % CfgImage::BN == 0)
-    return gemm_image_launch<CfgImage, RW_F2_OCC>(a, st);
-  return gemm_image_launch<CfgImageS, 4>(a, st);
+  if (few) return gemm_image_launch<CfgImageS, 2>(a, st);
+  if (a.nxp % 128 == 0) return gemm_image_launch<CfgImage, 2>(a, st);
+  return gemm_image_launch<CfgImageM, 2>(a, st);
 }
 
 hipError_t fourier_kernel_attributes() {
-  const void* k[6] = {(const void*)gemm_pupil_kernel<CfgPupil, RW_F1_OCC>, (const void*)gemm_pupil_kernel<CfgPupilS, 4>,
-                      (const void*)gemm_image_kernel<CfgImage, RW_F2_OCC>, (const void*)gemm_image_kernel<CfgImageS, 4>,
-                      (const void*)gemm_pupil_kernel<CfgPupilL, 2>, (const void*)gemm_pupil_kernel<CfgPupilSL, 2>};
-  const int bytes[6] = {CfgPupil::LDS_BYTES, CfgPupilS::LDS_BYTES, CfgImage::LDS_BYTES, CfgImageS::LDS_BYTES,
-                        CfgPupilL::LDS_BYTES, CfgPupilSL::LDS_BYTES};
+  const void* k[6] = {(const void*)gemm_pupil_kernel<CfgPupil, 2, 2>, (const void*)gemm_pupil_kernel<CfgPupilN, 2, 2>,
+                      (const void*)gemm_pupil_kernel<CfgPupilS, 1, 2>, (const void*)gemm_image_kernel<CfgImage, 2>,
+                      (const void*)gemm_image_kernel<CfgImageM, 2>, (const void*)gemm_image_kernel<CfgImageS, 2>};
+  const int bytes[6] = {CfgPupil::LDS_BYTES, CfgPupilN::LDS_BYTES, CfgPupilS::LDS_BYTES,
+                        CfgImage::LDS_BYTES, CfgImageM::LDS_BYTES, CfgImageS::LDS_BYTES};
   for (int i = 0; i < 6; ++i) {
     const hipError_t e = hipFuncSetAttribute(k[i], hipFuncAttributeMaxDynamicSharedMemorySize, bytes[i]);
     if (e != hipSuccess) return e;

@@ -9,14 +9,15 @@
 // and of the folded transforms (jf, lf < nh = ceil(N/2), the mirror-symmetric half):
 //   kszf[jf,lf]   = k s_z                            (FP64)
 //   B1[n][2lf]    = cos(k s_y[lf] y_n),  B1[n][2lf+1] = sin(k s_y[lf] y_n)
-//   A2[m][2jf]    = pref cos(k s_x[jf] x_m),  A2[m][2jf+1] = pref sin(...),  pref = f k / 2 pi
-// (both with the contraction index contiguous)
+//   A2[m][2jf]    = cos(k s_x[jf] x_m),  A2[m][2jf+1] = sin(k s_x[jf] x_m)
+// (split-f16 panels; the prefactor f k / 2 pi is applied with the operand scales)
 // with x_m = (m - nx/2) dx, y_n = (n - ny/2) dy.
 #include <algorithm>
 #include <cmath>
 #include <complex>
 #include <vector>
 
+#include "hgemm.h"
 #include "rw_common.h"
 #include "rw_fourier.h"
 #include "rw_plan.h"
@@ -24,6 +25,40 @@
 namespace rw {
 
 int bessel_plan_init(rwpsf_plan* p);
+
+// Power-of-two scales of the Fourier GEMMs' operands.  Q is scaled in place so that no
+// folded pupil value (a sum over up to four mirrors, each of unit phase factor) exceeds
+// 2^10, and T = Pf B1, bounded by the largest row sum of |Pf|, is brought under 2^15: f16
+// halves then neither overflow nor, down to 2^-13 (Pf) or 2^-18 (T) of the bounds, lose
+// bits to subnormal halves.
+static void fourier_scales(rwpsf_plan* p, std::vector<float2>& Q) {
+  const int N = p->num.n_pupil, np = p->np, nh = (N + 1) / 2;
+  const size_t npp = (size_t)np * np;
+  double cell_max = 0.0, row_max = 0.0;
+  for (int c = 0; c < p->nc; ++c)
+    for (int jf = 0; jf < nh; ++jf) {
+      double row = 0.0;
+      for (int lf = 0; lf < nh; ++lf) {
+        double m = 0.0;
+        for (int j : {jf, N - 1 - jf})
+          for (int l : {lf, N - 1 - lf}) {
+            const float2 q = Q[c * npp + (size_t)j * np + l];
+            m += std::fabs((double)q.x) + std::fabs((double)q.y);
+          }
+        cell_max = std::max(cell_max, m);
+        row += 2.0 * m;
+      }
+      row_max = std::max(row_max, row);
+    }
+  int ec = 0, er = 0;   // cell_max < 2^ec, row_max < 2^er
+  std::frexp(cell_max, &ec);
+  std::frexp(row_max, &er);
+  p->pf_exp = cell_max > 0.0 ? 10 - ec : 0;
+  const int t_exp = row_max > 0.0 ? 15 - (er + p->pf_exp + kTabExp) : 0;
+  p->tscale = (float)std::ldexp(1.0, t_exp);
+  p->escale = (float)std::ldexp(p->opt.focal_length * p->k / kTwoPi, -(p->pf_exp + 2 * kTabExp + t_exp));
+  for (float2& q : Q) q = make_float2(std::ldexp(q.x, p->pf_exp), std::ldexp(q.y, p->pf_exp));
+}
 
 static int fourier_plan_init(rwpsf_plan* p) {
   const int N = p->num.n_pupil, nx = p->grid.nx, ny = p->grid.ny;
@@ -52,30 +87,13 @@ static int fourier_plan_init(rwpsf_plan* p) {
   std::vector<double> kszf((size_t)nhp * nhp, 0.0);
   for (int jf = 0; jf < nh; ++jf)
     for (int lf = 0; lf < nh; ++lf) kszf[(size_t)jf * nhp + lf] = ksz[(size_t)jf * np + lf];
-  std::vector<float> B1((size_t)w * nyp, 0.f), A2T((size_t)w * nxp, 0.f);
-  const double pref = p->opt.focal_length * k / kTwoPi;  // C = -i pref
-  for (int lf = 0; lf < nh; ++lf) {
-    const double sy = (2.0 * lf + 1.0 - N) * s_max / N;
-    for (int n = 0; n < ny; ++n) {
-      const double ph = k * sy * (double)(n - ny / 2) * p->grid.dy_nm;
-      B1[(size_t)n * w + 2 * lf] = (float)std::cos(ph);
-      B1[(size_t)n * w + 2 * lf + 1] = (float)std::sin(ph);
-    }
-  }
-  for (int jf = 0; jf < nh; ++jf) {
-    const double sx = (2.0 * jf + 1.0 - N) * s_max / N;
-    for (int m = 0; m < nx; ++m) {
-      const double ph = k * sx * (double)(m - nx / 2) * p->grid.dx_nm;
-      A2T[(size_t)m * w + 2 * jf] = (float)(pref * std::cos(ph));
-      A2T[(size_t)m * w + 2 * jf + 1] = (float)(pref * std::sin(ph));
-    }
-  }
+  if (p->num.form == RWPSF_FORM_FOURIER) fourier_scales(p, Q);
   int st;
   if ((st = dev_alloc(p, &p->d_Q, 3 * npp))) return st;
   if ((st = dev_alloc(p, &p->d_ksz, npp))) return st;
   if ((st = dev_alloc(p, &p->d_kszf, kszf.size()))) return st;
-  if ((st = dev_alloc(p, &p->d_B1, B1.size()))) return st;
-  if ((st = dev_alloc(p, &p->d_A2T, A2T.size()))) return st;
+  if ((st = dev_alloc(p, &p->d_B1, hg_panel_bytes(w, nyp) / sizeof(uint4)))) return st;
+  if ((st = dev_alloc(p, &p->d_A2, hg_panel_bytes(w, nxp) / sizeof(uint4)))) return st;
   if ((st = dev_alloc(p, &p->d_ztab, (size_t)RWPSF_MAX_ZERNIKE * N * N))) return st;
   if ((st = dev_alloc(p, &p->d_z, (size_t)p->grid.nz))) return st;
   p->P_stacks = kPupilStacks;
@@ -83,16 +101,16 @@ static int fourier_plan_init(rwpsf_plan* p) {
   const bool gemm = p->num.form == RWPSF_FORM_FOURIER;   // the chirp-z form needs no GEMM workspaces
   if (gemm && (st = dev_alloc(p, &p->d_Pf, (size_t)kGemmStacks * 3 * w * w))) return st;
   // plane workspace: whole group of stacks x planes, capped at 1 GiB
-  const size_t plane_bytes = 3 * (size_t)w * nyp * sizeof(float2);
+  const size_t plane_bytes = 3 * hg_panel_bytes(w, 2 * nyp);
   const size_t want = (size_t)kGemmStacks * p->grid.nz;
   p->T_planes = std::max<size_t>(1, std::min(want, ((size_t)1 << 30) / plane_bytes));
-  if (gemm && (st = dev_alloc(p, &p->d_T, p->T_planes * 3 * (size_t)w * nyp))) return st;
+  if (gemm && (st = dev_alloc(p, &p->d_T, p->T_planes * 3 * (size_t)w * nyp / 2))) return st;
 
   if ((st = hip_check(hipMemcpy(p->d_Q, Q.data(), Q.size() * sizeof(float2), hipMemcpyHostToDevice)))) return st;
   if ((st = hip_check(hipMemcpy(p->d_ksz, ksz.data(), ksz.size() * sizeof(double), hipMemcpyHostToDevice)))) return st;
   if ((st = hip_check(hipMemcpy(p->d_kszf, kszf.data(), kszf.size() * sizeof(double), hipMemcpyHostToDevice)))) return st;
-  if ((st = hip_check(hipMemcpy(p->d_B1, B1.data(), B1.size() * sizeof(float), hipMemcpyHostToDevice)))) return st;
-  if ((st = hip_check(hipMemcpy(p->d_A2T, A2T.data(), A2T.size() * sizeof(float), hipMemcpyHostToDevice)))) return st;
+  if ((st = hip_check(launch_dft_panel(p->d_B1, nyp, ny, N, w, k, s_max, p->grid.dy_nm, 0)))) return st;
+  if ((st = hip_check(launch_dft_panel(p->d_A2, nxp, nx, N, w, k, s_max, p->grid.dx_nm, 0)))) return st;
   if ((st = hip_check(hipMemcpy(p->d_z, p->z.data(), p->z.size() * sizeof(double), hipMemcpyHostToDevice)))) return st;
   if ((st = hip_check(launch_zernike_table(p->d_ztab, N, RWPSF_MAX_ZERNIKE, 0)))) return st;
   if ((st = hip_check(fourier_kernel_attributes()))) return st;
@@ -188,6 +206,7 @@ static int fourier_gemms(rwpsf_plan* p, int s_local, int ns, const double* zoff,
   g1.z = p->d_z;
   g1.B1 = p->d_B1;
   g1.T = p->d_T;
+  g1.tscale = p->tscale;
   for (int i = 0; i < ns; ++i) g1.zoff[i] = zoff[i];
   g1.n = p->num.n_pupil;
   g1.nhp = p->nhp;
@@ -201,7 +220,9 @@ static int fourier_gemms(rwpsf_plan* p, int s_local, int ns, const double* zoff,
   if (rc) return rc;
   p->time_end(tr, st);
   Gemm2Args g2{};
-  g2.A2 = p->d_A2T;
+  g2.A2 = p->d_A2;
+  g2.escale = p->escale;
+  g2.vec = p->grid.ny % 2 == 0 && ((uintptr_t)E & 15) == 0 && ((uintptr_t)I & 7) == 0;
   g2.T = p->d_T;
   g2.E = E;
   g2.I = I;

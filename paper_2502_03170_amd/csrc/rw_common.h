@@ -165,12 +165,15 @@ struct rwpsf_plan {
   float2* d_Q = nullptr;        // [3][np][np] ds^2 a e_inf,c / s_z (0 outside)
   int nhp = 0;                  // folded pupil cells per axis, padded (2 nhp = np)
   double* d_kszf = nullptr;     // [nhp][nhp] k * s_z on the folded cells
-  float* d_B1 = nullptr;        // [nyp][2 nhp] cos / sin (k s_y[lf] y_n)
-  float* d_A2T = nullptr;       // [nxp][2 nhp] pref cos / sin (k s_x[jf] x_m), pref = f k / 2 pi
+  uint4* d_B1 = nullptr;        // split-f16 panel of nyp rows n, k = 2lf + p: cos / sin (k s_y[lf] y_n)
+  uint4* d_A2 = nullptr;        // split-f16 panel of nxp rows m, k = 2jf + p: cos / sin (k s_x[jf] x_m)
+  int pf_exp = 0;               // Q and the folded pupils carry 2^pf_exp (Fourier form)
+  float tscale = 1.f;           // power of two that T is multiplied by when it is written
+  float escale = 1.f;           // fields per unit of the image GEMM's accumulators
   float* d_ztab = nullptr;      // [RWPSF_MAX_ZERNIKE][N][N] Noll basis on the pupil cells
   float2* d_P = nullptr;        // workspace [chunk][3][np][np]
   float2* d_Pf = nullptr;       // workspace [chunk][3][2 nhp][2 nhp] folded pupils
-  float2* d_T = nullptr;        // workspace [planes][3][2 nhp][nyp]
+  uint4* d_T = nullptr;         // workspace [planes][3] split-f16 panels of 2 nyp rows 2n + ri, k = q
   size_t T_planes = 0;          // capacity of d_T in stack-planes
   // adjoint (built on first use)
   float* d_CxT = nullptr;       // [2 nhp][nxp] folded x table (prefactor included), pixels contiguous

@@ -29,24 +29,32 @@ using PupilArgs = PupilArgsT<kPupilStacks>;
 static_assert(sizeof(PupilArgs) <= 4000, "kernel arguments are passed by value (4 KB limit)");
 
 // Device operands are zero-padded: np = n rounded up to 64, nxp = nx rounded up
-// to 128, nyp = ny rounded up to 128, and the folded pupil axis nh = ceil(n/2) to
+// to 128, nyp = ny rounded up to 128 (64 for axes of at most 64 pixels), and the folded pupil axis nh = ceil(n/2) to
 // nhp = nh rounded up to 32 (so 2 nhp = np).
+
+// Operands of the two GEMMs are split-f16 panels (hgemm.h).  Their power-of-two scales
+// (fourier_scales) keep the halves in range: Pf carries 2^pf_exp (through Q), the tables
+// 2^kTabExp, and T is rescaled by tscale when it is written.
+constexpr int kTabExp = 6;
 
 struct Gemm1Args {
   const float2* Pf;    // [nstk][nc][2 nhp][2 nhp]
   const double* kszf;  // [nhp][nhp] k s_z on the folded cells
   const double* z;     // plan planes
-  const float* B1;     // [nyp][2 nhp] cos / sin (k s_y[lf] y_n), k contiguous
-  float2* T;           // [nstk][nzs][nc][2 nhp][nyp]
+  const uint4* B1;     // panel of nyp rows n, k = 2lf + p: cos / sin (k s_y[lf] y_n)
+  uint4* T;            // [nstk][nzs][nc] panels of 2 nyp rows 2n + ri, k = q
   double zoff[kGemmStacks];
+  float tscale;
   int n, nhp, nyp, nstk, z0, nzs, nc;   // n: pupil cells per axis
 };
 
 struct Gemm2Args {
-  const float* A2;     // [nxp][2 nhp] pref cos / sin (k s_x[jf] x_m), k contiguous
-  const float2* T;     // [nstk][nzs][nc][2 nhp][nyp]
+  const uint4* A2;     // panel of nxp rows m, k = 2jf + p: cos / sin (k s_x[jf] x_m)
+  const uint4* T;      // [nstk][nzs][nc] panels of 2 nyp rows 2n + ri, k = q
   float2* E;           // [stacks][nz][nc][nx][ny] or null
   float* I;            // [stacks][nz][nx][ny] or null
+  float escale;        // prefactor f k / 2 pi over the operand scales
+  int vec;             // E and I rows allow 16- and 8-byte stores (ny even, aligned outputs)
   int nhp, nxp, nyp, nx, ny, nz, nstk, s_base, z0, nzs, nc;
 };
 
@@ -56,6 +64,10 @@ constexpr int kPadPupil = 64, kPadX = 128, kPadY = 128, kFoldPad = 32, kPadSmall
 inline int pad_axis(int n) { return n <= kPadSmall ? kPadSmall : round_up(n, kPadX); }
 
 hipError_t launch_zernike_table(float* out, int n, int nj, hipStream_t st);
+// DFT table of `count` output pixels (pixel r at (r - count / 2) pitch) as a split-f16 panel
+// of `rows` rows, k = 2f + p: 2^kTabExp {cos, sin}(wavenumber s_f x_r), zero past count and n
+hipError_t launch_dft_panel(uint4* panel, int rows, int count, int n, int w, double wavenumber, double s_max,
+                            double pitch, hipStream_t st);
 hipError_t launch_pupil_build(const PupilArgs& a, const float2* Q, const float* ztab, float2* P,
                               hipStream_t st);
 // Pf [nstk][nc][2 nhp][2 nhp] of the stacks of a (its np field is the stride of Q)
