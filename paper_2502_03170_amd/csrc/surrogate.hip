@@ -16,10 +16,10 @@
 // lo in BF16 and the product is hi*hi + hi*lo + lo*hi (relative error ~1e-5); the
 // fast mode uses hi*hi only.  The forward transposed convolutions run in one fused
 // kernel per sample: the first two as implicit GEMMs on v_mfma_f32_16x16x32_bf16 (same
-// splitting), the last (one output channel) in FP32, activations in LDS.  The backward
-// kernels stage a sample in LDS (FP32).  Weight gradients of the convolutions
+// splitting), the last (one output channel) in FP32, activations in LDS.  Their backward
+// runs in one fused FP32 kernel per sample.  Weight gradients of the convolutions
 // and all bias gradients are reduced over the batch in a fixed order through
-// per-chunk partial sums; training updates FP32 master weights with Adam.
+// partial sums; training updates FP32 master weights with Adam.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -453,35 +453,6 @@ __global__ void sg_relu_mask_kernel(float* __restrict__ g, const float* __restri
   if (i < n) g[i] = h[i] > 0.f ? g[i] : 0.f;
 }
 
-// dY = 2 (y - t) / n and per-block partial sums of (y - t)^2
-__global__ void __launch_bounds__(256) sg_mse_kernel(const float* __restrict__ y, const float* __restrict__ t,
-                                                      size_t n, float* __restrict__ dy,
-                                                      double* __restrict__ partial) {
-  __shared__ double red[256];
-  double s = 0.0;
-  const float scale = 2.f / (float)n;
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) {
-    const float r = y[i] - t[i];
-    dy[i] = scale * r;
-    s += (double)r * r;
-  }
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
-}
-
-__global__ void sg_sum_kernel(const double* __restrict__ partial, int n, double inv, float* __restrict__ out) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    double s = 0.0;
-    for (int i = 0; i < n; ++i) s += partial[i];
-    out[0] = (float)(s * inv);
-  }
-}
-
 // column sums of g [rows][cols] (bias gradients), two levels in a fixed order: chunk
 // blockIdx.y sums its rows in order into part[chunk][col]; sg_colsum_final_kernel sums the
 // chunks in order
@@ -803,91 +774,233 @@ __global__ void __launch_bounds__(256, 2) sg_decoder_kernel(const float* __restr
   }
 }
 
-// dIn[ci, iy, ix] = sum_{co, ky, kx} dOut[co, 2 iy - 1 + ky, 2 ix - 1 + kx] K[ci, co, ky, kx]
-__global__ void __launch_bounds__(256) sg_deconv_bwd_data_kernel(const float* __restrict__ dout,
-                                                                  const float* __restrict__ K, int Ci, int Co,
-                                                                  int H, float* __restrict__ din) {
-  extern __shared__ float sh[];
-  const int HO = 2 * H;
-  float* g = sh;                   // [Co][HO][HO]
-  float* kk = sh + Co * HO * HO;   // [Ci][Co][16]
-  const int b = blockIdx.x;
-  const float* src = dout + (size_t)b * Co * HO * HO;
-  for (int i = threadIdx.x; i < Co * HO * HO; i += 256) g[i] = src[i];
-  for (int i = threadIdx.x; i < Ci * Co * 16; i += 256) kk[i] = K[i];
-  __syncthreads();
-  float* dst = din + (size_t)b * Ci * H * H;
-  for (int o = threadIdx.x; o < Ci * H * H; o += 256) {
-    const int ci = o / (H * H), iy = (o / H) % H, ix = o % H;
-    float s = 0.f;
-    for (int ky = 0; ky < 4; ++ky) {
-      const int oy = 2 * iy - 1 + ky;
-      if (oy < 0 || oy >= HO) continue;
-      for (int kx = 0; kx < 4; ++kx) {
-        const int ox = 2 * ix - 1 + kx;
-        if (ox < 0 || ox >= HO) continue;
-        for (int co = 0; co < Co; ++co) s += g[(co * HO + oy) * HO + ox] * kk[(ci * Co + co) * 16 + ky * 4 + kx];
-      }
-    }
-    dst[o] = s;
-  }
-}
+// ---------------------------------------------------------------- decoder backward
+// Backward of the three transposed convolutions of a sample in one workgroup, with the loss
+// gradient formed on the way: gy = 2 (y - t) / n, then per layer (3, 2, 1) the weight gradient
+//   dK[ci][co][ky][kx] = sum_{iy, ix} in[ci][iy][ix] g[co][2 iy - 1 + ky][2 ix - 1 + kx]
+// and the data gradient gin[ci][iy][ix] = sum_{co, ky, kx} g[co][..][..] K[ci][co][ky][kx],
+// masked by the relu of the layer's input.  Everything stays FP32; the sums run on
+// v_mfma_f32_16x16x4_f32: a weight gradient of one co is the product [ci][pixel] x
+// [pixel][tap], a data gradient [pixel][(co, tap)] x [(co, tap)][ci].  Gradients sit in LDS
+// with a zero border, so that no tap needs a bounds test; rows are padded against bank
+// conflicts.  A workgroup serves a run of samples and keeps the weight and bias gradients in
+// registers; the partial sums of the workgroups are added in a fixed order afterwards.
+// Bound by latency: 256 samples are one workgroup per CU, a chain of six phases.  Measured at
+// 256 samples: 27 us and 5 us for the reduction, against 730 us for the separate kernels (weights 3
+// x 117 us, whose bias sums ran on one thread, their reduction 3 x 64, data 3 x 58, masks).
+constexpr int kBwdThreads = 512;
+constexpr int BX2 = 32 * 32 + 4, BX1 = 16 * 16 + 4, BX0 = 64 + 4;    // channel strides of the layer inputs
+constexpr int BL3 = 74, BL2 = 42, BL1 = 20;                          // row strides of the bordered gradients
+constexpr int BG2 = 34 * BL2, BG1 = 18 * BL1;                        // channel strides of those
+constexpr int BK2 = 8 * 16 + 4, BK1 = 16 * 16 + 4;                   // weight strides per ci
+constexpr int kBwdR0 = (66 * BL3 > DC1 * BG1) ? 66 * BL3 : DC1 * BG1;   // gy, then layer 1's gradient
+constexpr int kBwdX2 = (DC2 * BX2 > 16 * BK1) ? DC2 * BX2 : 16 * BK1;   // d2, then K1
+constexpr int kBwdLdsFloats = kBwdR0 + kBwdX2 + DC2 * BG2 + DC1 * BX1 + DC0 * BX0 + DC1 * BK2;
+constexpr int kConvParams = 16 * 16 * 16 + 16 + 16 * 8 * 16 + 8 + 8 * 16 + 1;   // K1 c1 K2 c2 K3 c3, in layout order
+static_assert(kBwdLdsFloats * 4 <= 160 * 1024, "one workgroup's LDS");
+static_assert(DC0 == 16 && DC1 == 16 && DC2 == 8, "phases below assume these channels");
 
-// Per chunk of samples: partial dK[ci, co, ky, kx] and dbias[co], summed over the chunk's
-// samples in order.  Each sample's input and output gradient are staged in LDS; every
-// thread owns a fixed set of parameters and keeps their sums in LDS.
-__global__ void __launch_bounds__(256) sg_deconv_bwd_weight_kernel(const float* __restrict__ in,
-                                                                    const float* __restrict__ dout, int B,
-                                                                    int chunk, int Ci, int Co, int H,
-                                                                    float* __restrict__ partial) {
-  extern __shared__ float sh[];
-  const int HO = 2 * H, np = Ci * Co * 16, nin = Ci * H * H, nout = Co * HO * HO;
-  float* xs = sh;                  // [Ci][H][H]
-  float* gs = sh + nin;            // [Co][HO][HO]
-  float* accs = gs + nout;         // [np + Co]
+__global__ void __launch_bounds__(kBwdThreads) sg_decoder_bwd_kernel(
+    const float* __restrict__ y, const float* __restrict__ t, const float* __restrict__ h3,
+    const float* __restrict__ d1, const float* __restrict__ d2, const float* __restrict__ K1,
+    const float* __restrict__ K2, const float* __restrict__ K3, int B, int chunk, float* __restrict__ gy,
+    float* __restrict__ g3, float* __restrict__ partial, double* __restrict__ loss_partial) {
+  extern __shared__ float bls[];
+  float* r0 = bls;               // gy [66][BL3]; later layer 1's gradient [16][18][BL1]
+  float* x2 = r0 + kBwdR0;       // d2 [8][BX2]; later K1 [ci][BK1]
+  float* g2 = x2 + kBwdX2;       // layer 2's gradient [8][34][BL2]
+  float* x1 = g2 + DC2 * BG2;    // d1 [16][BX1]
+  float* x0 = x1 + DC1 * BX1;    // h3 [16][BX0]
+  float* k2 = x0 + DC0 * BX0;    // K2 [ci][BK2]
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, g = lane >> 4, r16 = lane & 15;
+  const int ky = r16 >> 2, kx = r16 & 3;   // the lane's tap as a column of a weight gradient
+  const float scale = 2.f / (float)((size_t)B * 4096);
+  f4v_t a3 = {0.f, 0.f, 0.f, 0.f}, a2 = a3, a1[2] = {a3, a3};
+  float b2s = 0.f, b1s[2] = {0.f, 0.f};
+  double lsum = 0.0;
+  for (int i = tid; i < DC1 * 8 * 16; i += kBwdThreads) k2[(i >> 7) * BK2 + (i & 127)] = K2[i];
   const int b0 = blockIdx.x * chunk, b1 = min(B, b0 + chunk);
-  for (int p = threadIdx.x; p < np + Co; p += 256) accs[p] = 0.f;
   for (int b = b0; b < b1; ++b) {
+    __syncthreads();   // the previous sample's (or the staging's) use of the buffers is over
+    for (int i = tid; i < kBwdR0; i += kBwdThreads) r0[i] = 0.f;
+    for (int i = tid; i < DC2 * BG2; i += kBwdThreads) g2[i] = 0.f;
+    for (int i = 4 * tid; i < DC2 * 1024; i += 4 * kBwdThreads)
+      *reinterpret_cast<float4*>(x2 + (i >> 10) * BX2 + (i & 1023)) =
+          *reinterpret_cast<const float4*>(d2 + (size_t)b * DC2 * 1024 + i);
+    for (int i = 4 * tid; i < DC1 * 256; i += 4 * kBwdThreads)
+      *reinterpret_cast<float4*>(x1 + (i >> 8) * BX1 + (i & 255)) =
+          *reinterpret_cast<const float4*>(d1 + (size_t)b * DC1 * 256 + i);
+    for (int i = 4 * tid; i < DC0 * 64; i += 4 * kBwdThreads)
+      *reinterpret_cast<float4*>(x0 + (i >> 6) * BX0 + (i & 63)) =
+          *reinterpret_cast<const float4*>(h3 + (size_t)b * DC0 * 64 + i);
     __syncthreads();
-    const float* xsrc = in + (size_t)b * nin;
-    const float* gsrc = dout + (size_t)b * nout;
-    for (int i = threadIdx.x; i < nin; i += 256) xs[i] = xsrc[i];
-    for (int i = threadIdx.x; i < nout; i += 256) gs[i] = gsrc[i];
-    __syncthreads();
-    for (int p = threadIdx.x; p < np + Co; p += 256) {
-      float s = 0.f;
-      if (p < np) {
-        const int ci = p / (Co * 16), co = (p / 16) % Co, ky = (p / 4) % 4, kx = p % 4;
-        const float* x = xs + ci * H * H;
-        const float* g = gs + co * HO * HO;
-        // output rows oy = 2 iy - 1 + ky inside [0, HO): iy from (1 - ky + 1) / 2 when ky = 0
-        const int iy0 = ky == 0 ? 1 : 0, iy1 = ky == 3 ? H - 1 : H;
-        const int ix0 = kx == 0 ? 1 : 0, ix1 = kx == 3 ? H - 1 : H;
-        for (int iy = iy0; iy < iy1; ++iy) {
-          const float* xr = x + iy * H;
-          const float* gr = g + (2 * iy - 1 + ky) * HO - 1 + kx;
-          for (int ix = ix0; ix < ix1; ++ix) s += xr[ix] * gr[2 * ix];
-        }
-      } else {
-        const float* g = gs + (p - np) * HO * HO;
-        for (int i = 0; i < HO * HO; ++i) s += g[i];
+    for (int i = 4 * tid; i < 4096; i += 4 * kBwdThreads) {
+      const float4 yv = *reinterpret_cast<const float4*>(y + (size_t)b * 4096 + i);
+      const float* tv = t + (size_t)b * 4096 + i;   // (the caller's array: 4-byte aligned)
+      const float e[4] = {yv.x - tv[0], yv.y - tv[1], yv.z - tv[2], yv.w - tv[3]};
+      float* o = r0 + ((i >> 6) + 1) * BL3 + (i & 63) + 1;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        o[q] = scale * e[q];
+        lsum += (double)e[q] * e[q];
       }
-      accs[p] += s;
+      *reinterpret_cast<float4*>(gy + (size_t)b * 4096 + i) =
+          make_float4(scale * e[0], scale * e[1], scale * e[2], scale * e[3]);
+    }
+    __syncthreads();
+    // ---- layer 3 (one output channel).  dK3: rows ci 0-7, row 8 all ones (the bias); the
+    // 1024 pixels split over the waves
+#pragma unroll 4
+    for (int st = 0; st < 32; ++st) {
+      const int px = 128 * w + 4 * st + g, iy = px >> 5, ix = px & 31;
+      const float av = r16 < 8 ? x2[r16 * BX2 + px] : (r16 == 8 ? 1.f : 0.f);
+      a3 = __builtin_amdgcn_mfma_f32_16x16x4f32(av, r0[(2 * iy + ky) * BL3 + 2 * ix + kx], a3, 0, 0, 0);
+    }
+    // gd2: a thread owns the eight channels of two pixels
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int px = tid + kBwdThreads * u, iy = px >> 5, ix = px & 31;
+      float gv[16];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) gv[q] = r0[(2 * iy + (q >> 2)) * BL3 + 2 * ix + (q & 3)];
+#pragma unroll
+      for (int ci = 0; ci < 8; ++ci) {
+        float v = 0.f;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) v = fmaf(gv[q], K3[ci * 16 + q], v);
+        g2[ci * BG2 + (iy + 1) * BL2 + ix + 1] = x2[ci * BX2 + px] > 0.f ? v : 0.f;
+      }
+    }
+    __syncthreads();
+    // gy and d2 are done with: layer 1's gradient and K1 take their place
+    for (int i = tid; i < DC1 * BG1; i += kBwdThreads) r0[i] = 0.f;
+    for (int i = tid; i < DC0 * 256; i += kBwdThreads) x2[(i >> 8) * BK1 + (i & 255)] = K1[i];
+    // ---- layer 2.  dK2: wave w takes co = w
+#pragma unroll 4
+    for (int st = 0; st < 64; ++st) {
+      const int px = 4 * st + g, iy = px >> 4, ix = px & 15;
+      const float bv = g2[w * BG2 + (2 * iy + ky) * BL2 + 2 * ix + kx];
+      a2 = __builtin_amdgcn_mfma_f32_16x16x4f32(x1[r16 * BX1 + px], bv, a2, 0, 0, 0);
+      b2s += bv;
+    }
+    // gd1: wave w takes image rows 2 w, 2 w + 1 (16 pixels each) of all ci
+    f4v_t d[2] = {f4v_t{0.f, 0.f, 0.f, 0.f}, f4v_t{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll 4
+    for (int st = 0; st < 32; ++st) {   // k = 4 st + g: co = st / 4, ky = st % 4, kx = g
+      const float kv = k2[r16 * BK2 + 4 * st + g];
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+        d[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+            g2[(st >> 2) * BG2 + (2 * (2 * w + u) + (st & 3)) * BL2 + 2 * r16 + g], kv, d[u], 0, 0, 0);
+    }
+    __syncthreads();   // layer 1's buffer is zeroed, K1 is staged
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int iy = 2 * w + u, ix = 4 * g + r;
+        r0[r16 * BG1 + (iy + 1) * BL1 + ix + 1] = x1[r16 * BX1 + 16 * iy + ix] > 0.f ? d[u][r] : 0.f;
+      }
+    __syncthreads();
+    // ---- layer 1.  dK1: wave w takes co = 2 w, 2 w + 1
+#pragma unroll 4
+    for (int st = 0; st < 16; ++st) {
+      const int px = 4 * st + g, iy = px >> 3, ix = px & 7;
+      const float av = x0[r16 * BX0 + px];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const float bv = r0[(2 * w + u) * BG1 + (2 * iy + ky) * BL1 + 2 * ix + kx];
+        a1[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv, a1[u], 0, 0, 0);
+        b1s[u] += bv;
+      }
+    }
+    // g3 (before its mask: the basis branch adds to it): waves 0-3 take 16 pixels each
+    if (w < 4) {
+      f4v_t v[2] = {f4v_t{0.f, 0.f, 0.f, 0.f}, f4v_t{0.f, 0.f, 0.f, 0.f}};
+      const int px = 16 * w + r16, iy = px >> 3, ix = px & 7;
+#pragma unroll 4
+      for (int st = 0; st < 64; st += 2)
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+          v[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+              r0[((st + u) >> 2) * BG1 + (2 * iy + ((st + u) & 3)) * BL1 + 2 * ix + g], x2[r16 * BK1 + 4 * (st + u) + g],
+              v[u], 0, 0, 0);
+      *reinterpret_cast<float4*>(g3 + (size_t)b * 1024 + r16 * 64 + 16 * w + 4 * g) =
+          make_float4(v[0][0] + v[1][0], v[0][1] + v[1][1], v[0][2] + v[1][2], v[0][3] + v[1][3]);
     }
   }
+  // ---- this workgroup's partial sums.  The four taps (1, 2) x (1, 2) visit every pixel of a
+  // gradient once, so a bias is the sum of those columns.
   __syncthreads();
-  float* dst = partial + (size_t)blockIdx.x * (np + Co);
-  for (int p = threadIdx.x; p < np + Co; p += 256) dst[p] = accs[p];
+  float* dst = partial + (size_t)blockIdx.x * kConvParams;
+  float* bs = bls;             // bias columns [co][lane]: 8 + 16 rows of 64
+  float* w3 = bls + 24 * 64;   // layer 3's products of the eight waves, [w][16 ci][16 taps]
+  const bool mid = (ky == 1 || ky == 2) && (kx == 1 || kx == 2);
+  bs[w * 64 + lane] = mid ? b2s : 0.f;
+#pragma unroll
+  for (int u = 0; u < 2; ++u) bs[(8 + 2 * w + u) * 64 + lane] = mid ? b1s[u] : 0.f;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int ci = 4 * g + r;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) dst[(ci * 16 + 2 * w + u) * 16 + r16] = a1[u][r];
+    dst[4096 + 16 + (ci * 8 + w) * 16 + r16] = a2[r];
+    w3[(w * 16 + ci) * 16 + r16] = a3[r];
+  }
+  double* ld = reinterpret_cast<double*>(bls + 24 * 64 + 8 * 256);
+  ld[tid] = lsum;
+  __syncthreads();
+  if (tid < 144) {
+    float v = 0.f;
+    for (int q = 0; q < 8; ++q) v += w3[q * 256 + tid];
+    if (tid < 128) dst[4096 + 16 + 2048 + 8 + tid] = v;
+    else w3[tid] = v;   // the bias row
+  }
+  __syncthreads();
+  if (tid == 128) dst[kConvParams - 1] = (w3[133] + w3[134]) + (w3[137] + w3[138]);
+  if (tid < 24) {
+    double v = 0.0;
+    for (int q = 0; q < 64; ++q) v += bs[tid * 64 + q];
+    dst[tid < 8 ? 4096 + 16 + 2048 + tid : 4096 + tid - 8] = (float)v;
+  }
+  for (int h = kBwdThreads / 2; h > 0; h >>= 1) {
+    if (tid < h) ld[tid] += ld[tid + h];
+    __syncthreads();
+  }
+  if (tid == 0) loss_partial[blockIdx.x] = ld[0];
 }
 
-// sum partials [chunks][n] in chunk order
-__global__ void sg_reduce_partials_kernel(const float* __restrict__ partial, int chunks, int n,
-                                          float* __restrict__ out) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= n) return;
+// out[p] = sum over chunks of partial[chunk][p], FP64, in a fixed order (eight runs of chunks,
+// then the runs); the last workgroup sums the loss partials the same way.
+__global__ void __launch_bounds__(256) sg_reduce_partials_kernel(const float* __restrict__ partial, int chunks, int n,
+                                                                 float* __restrict__ out,
+                                                                 const double* __restrict__ loss_partial,
+                                                                 double inv, float* __restrict__ loss) {
+  __shared__ double red[256];
+  const int tid = threadIdx.x, l = tid & 31, run = tid >> 5;
+  const bool lossy = blockIdx.x == gridDim.x - 1;
+  const int p = blockIdx.x * 32 + l;
+  const int per = (chunks + 7) / 8, c0 = run * per, c1 = min(chunks, c0 + per);
   double s = 0.0;
-  for (int c = 0; c < chunks; ++c) s += partial[(size_t)c * n + p];
-  out[p] = (float)s;
+  if (lossy) {
+    for (int c = tid; c < chunks; c += 256) s += loss_partial[c];
+  } else if (p < n) {
+#pragma unroll 8
+    for (int c = c0; c < c1; ++c) s += partial[(size_t)c * n + p];
+  }
+  red[tid] = s;
+  __syncthreads();
+  if (lossy) {
+    for (int h = 128; h > 0; h >>= 1) {
+      if (tid < h) red[tid] += red[tid + h];
+      __syncthreads();
+    }
+    if (tid == 0 && loss) loss[0] = (float)(red[0] * inv);
+  } else if (run == 0 && p < n) {
+    s = red[l];
+    for (int q = 1; q < 8; ++q) s += red[32 * q + l];
+    out[p] = (float)s;
+  }
 }
 
 __global__ void sg_adam_kernel(float* __restrict__ w, const float* __restrict__ g, float* __restrict__ m,
@@ -936,7 +1049,7 @@ struct rwpsf_sg {
   std::vector<void*> allocations;
   float *w = nullptr, *g = nullptr, *m = nullptr, *v = nullptr;   // [L.total]
   float *x = nullptr, *h1 = nullptr, *h2 = nullptr, *h3 = nullptr, *d1 = nullptr, *d2 = nullptr, *y = nullptr;
-  float *gx = nullptr, *g1 = nullptr, *g2 = nullptr, *g3 = nullptr, *gd1 = nullptr, *gd2 = nullptr, *gy = nullptr;
+  float *gx = nullptr, *g1 = nullptr, *g2 = nullptr, *g3 = nullptr, *gy = nullptr;
   float *a = nullptr, *ga = nullptr;   // basis coefficients [B][kBasis] and their gradient
   float* partial = nullptr;   // conv weight partials
   __bf16* decw = nullptr;     // B fragments of the decoder's matrix-core layers (hi / lo)
@@ -1027,20 +1140,17 @@ static int sg_forward_impl(rwpsf_sg* s, int B, const float* coef, const float* z
 static int sg_backward_impl(rwpsf_sg* s, int B, const float* target, float* loss, hipStream_t st) {
   const Layout& L = s->L;
   int rc;
-  const size_t ny = (size_t)B * 4096;
-  const int lb = 256;
-  hipLaunchKernelGGL(sg_mse_kernel, dim3(lb), dim3(256), 0, st, s->y, target, ny, s->gy, s->loss_partial);
-  if ((rc = hip_check(hipGetLastError()))) return rc;
-  if (loss) {
-    hipLaunchKernelGGL(sg_sum_kernel, dim3(1), dim3(64), 0, st, s->loss_partial, lb, 1.0 / (double)ny, loss);
-    if ((rc = hip_check(hipGetLastError()))) return rc;
-  }
+  // loss gradient and the convolution branch
   const int chunk = (B + kMaxChunks - 1) / kMaxChunks;   // samples per partial sum
   const int chunks = (B + chunk - 1) / chunk;
-  struct Conv { float *in, *gin, *gout; int Ci, Co, H; size_t K, c; bool relu_in; };
-  const Conv convs[3] = {{s->d2, s->gd2, s->gy, 8, 1, 32, L.K3, L.c3, true},
-                         {s->d1, s->gd1, s->gd2, 16, 8, 16, L.K2, L.c2, true},
-                         {s->h3, s->g3, s->gd1, 16, 16, 8, L.K1, L.c1, true}};
+  hipLaunchKernelGGL(sg_decoder_bwd_kernel, dim3(chunks), dim3(kBwdThreads), kBwdLdsFloats * sizeof(float), st, s->y,
+                     target, s->h3, s->d1, s->d2, s->w + L.K1, s->w + L.K2, s->w + L.K3, B, chunk, s->gy, s->g3,
+                     s->partial, s->loss_partial);
+  if ((rc = hip_check(hipGetLastError()))) return rc;
+  // (the convolution parameters K1 c1 K2 c2 K3 c3 are adjacent in the layout)
+  hipLaunchKernelGGL(sg_reduce_partials_kernel, dim3((kConvParams + 31) / 32 + 1), dim3(256), 0, st, s->partial, chunks,
+                     kConvParams, s->g + L.K1, s->loss_partial, 1.0 / ((double)B * 4096.0), loss);
+  if ((rc = hip_check(hipGetLastError()))) return rc;
   // weights split to BF16 in their own order: B operands of the products g W^T
   __bf16* w3h = s->wsplit_t;
   __bf16* w3l = w3h + 1024 * 1024;
@@ -1069,27 +1179,12 @@ static int sg_backward_impl(rwpsf_sg* s, int B, const float* target, float* loss
   if ((rc = hip_check(sg_gemm<true, false>(s->h3, 1024, s->ga, kBasis, s->g + L.Wa, kBasis, 1024, kBasis, B, nullptr,
                                            0, 3, st)))) return rc;
   if ((rc = hip_check(sg_colsum(s->ga, B, kBasis, s->g + L.ba, s->colpart, st)))) return rc;
-  for (const Conv& c : convs) {
-    const int np = c.Ci * c.Co * 16;
-    const int lds = (c.Ci * c.H * c.H + c.Co * 4 * c.H * c.H + np + c.Co) * 4;
-    hipLaunchKernelGGL(sg_deconv_bwd_weight_kernel, dim3(chunks), dim3(256), lds, st, c.in, c.gout, B, chunk, c.Ci,
-                       c.Co, c.H, s->partial);
-    if ((rc = hip_check(hipGetLastError()))) return rc;
-    hipLaunchKernelGGL(sg_reduce_partials_kernel, dim3((np + c.Co + 255) / 256), dim3(256), 0, st, s->partial, chunks,
-                       np + c.Co, s->g + c.K);   // K and its bias are adjacent in the layout
-    if ((rc = hip_check(hipGetLastError()))) return rc;
-    const int HO = 2 * c.H;
-    hipLaunchKernelGGL(sg_deconv_bwd_data_kernel, dim3(B), dim3(256), (c.Co * HO * HO + c.Ci * c.Co * 16) * 4, st,
-                       c.gout, s->w + c.K, c.Ci, c.Co, c.H, c.gin);
-    if ((rc = hip_check(hipGetLastError()))) return rc;
-    // h3 also feeds the basis branch: g3 += ga Wa^T before the relu mask
-    if (c.gin == s->g3 &&
-        (rc = hip_check(sg_gemm_fast(s->ga, wah, wal, s->g3, B, 1024, kBasis, nullptr, 0, 3, st, 1, s->ws,
-                                     kSplitKFloats, twg)))) return rc;
-    const size_t n = (size_t)B * c.Ci * c.H * c.H;
-    hipLaunchKernelGGL(sg_relu_mask_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, c.gin, c.in, n);
-    if ((rc = hip_check(hipGetLastError()))) return rc;
-  }
+  // h3 feeds both branches: g3 += ga Wa^T, then the relu mask
+  if ((rc = hip_check(sg_gemm_fast(s->ga, wah, wal, s->g3, B, 1024, kBasis, nullptr, 0, 3, st, 1, s->ws, kSplitKFloats,
+                                   twg)))) return rc;
+  hipLaunchKernelGGL(sg_relu_mask_kernel, dim3((unsigned)(((size_t)B * 1024 + 255) / 256)), dim3(256), 0, st, s->g3,
+                     s->h3, (size_t)B * 1024);
+  if ((rc = hip_check(hipGetLastError()))) return rc;
   // dense layers: g3 = dL/d(pre3) already masked
   struct Dense { float *hin, *gin, *gout; int in, out; size_t W, b; const float* hmask; const __bf16 *th, *tl; };
   const Dense dense[3] = {{s->h2, s->g2, s->g3, 1024, 1024, L.W3, L.b3, s->h2, w3h, w3l},
@@ -1139,9 +1234,8 @@ int rwpsf_sg_create(int max_batch, rwpsf_sg** out) {
       (rc = sg_alloc(s, &s->d1, B * 4096)) || (rc = sg_alloc(s, &s->d2, B * 8192)) ||
       (rc = sg_alloc(s, &s->y, B * 4096)) || (rc = sg_alloc(s, &s->gx, B * 22)) ||
       (rc = sg_alloc(s, &s->g1, B * 1024)) || (rc = sg_alloc(s, &s->g2, B * 1024)) ||
-      (rc = sg_alloc(s, &s->g3, B * 1024)) || (rc = sg_alloc(s, &s->gd1, B * 4096)) ||
-      (rc = sg_alloc(s, &s->gd2, B * 8192)) || (rc = sg_alloc(s, &s->gy, B * 4096)) ||
-      (rc = sg_alloc(s, &s->partial, (size_t)chunks * (16 * 16 * 16 + 16))) ||
+      (rc = sg_alloc(s, &s->g3, B * 1024)) || (rc = sg_alloc(s, &s->gy, B * 4096)) ||
+      (rc = sg_alloc(s, &s->partial, (size_t)chunks * kConvParams)) ||
       (rc = sg_alloc(s, &s->loss_partial, 256)) || (rc = sg_alloc(s, &s->decw, 2 * (4 * DK1 + 2 * DK2) * 64 * 8)) ||
       (rc = sg_alloc(s, &s->a, B * kBasis)) || (rc = sg_alloc(s, &s->ga, B * kBasis)) ||
       (rc = sg_alloc(s, &s->wsplit, 2 * (1024 * 1024 + 1024 * 1024 + 1024 * kBasis + kBasis * 4096))) ||
@@ -1160,6 +1254,8 @@ int rwpsf_sg_create(int max_batch, rwpsf_sg** out) {
                                           hipFuncAttributeMaxDynamicSharedMemorySize, fast_lds))) ||
       (rc = hip_check(hipFuncSetAttribute((const void*)sg_gemm_fast_kernel<3>,
                                           hipFuncAttributeMaxDynamicSharedMemorySize, fast_lds))) ||
+      (rc = hip_check(hipFuncSetAttribute((const void*)sg_decoder_bwd_kernel,
+                                          hipFuncAttributeMaxDynamicSharedMemorySize, kBwdLdsFloats * 4))) ||
       (rc = hip_check(hipFuncSetAttribute((const void*)sg_decoder_kernel<1>,
                                           hipFuncAttributeMaxDynamicSharedMemorySize, kDecLdsBytes))) ||
       (rc = hip_check(hipFuncSetAttribute((const void*)sg_decoder_kernel<3>,
