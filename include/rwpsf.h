@@ -277,7 +277,7 @@ int rwpsf_batch_offsets(int n, const rwpsf_emitter* emitters, int64_t* offsets);
    device float [total voxels] or NULL; E_out: device complex64 [3 total voxels] or
    NULL (not both NULL).  The emitters are staged in a pinned host area and copied to the
    device at the start of the call's work on `stream`; with graphs enabled the kernels
-   (queue reset, phase GEMM, fold, persistent plane kernels) are captured once per (n,
+   (fold, persistent plane kernels) are captured once per (n,
    outputs, configuration, launched tile classes, stream) and replayed after the copy;
    graph mode needs a created stream (not NULL).  Before the staging area is rewritten
    the call waits for the previous call's copy (not for its kernels). */
@@ -287,12 +287,11 @@ int rwpsf_batch_set_graph(rwpsf_batch* batch, int enable);
 
 /* Launch configuration.  Crops fall into four buckets by size (1-16, 17-32, 33-48 and
    49-64 pixels); the crops of bucket q are evaluated on tiles of tile_rows[q] rows (16,
-   32, 48 or 64, at least 16 (q + 1)); the tile class of r rows stages its pupil GEMM in
-   k-stages of k_stage[r / 16 - 1] folded pupil rows (8 or 16); the persistent grid of
-   each class has wg_per_cu workgroups per CU (1..4).  The 32- and 64-row classes run
-   32 x 32 x 2 matrix-core tiles, the 16- and 48-row classes 16 x 16 x 4 ones.  The
-   default puts each bucket on its own class with k-stages of 16 and two workgroups per
-   CU. */
+   32, 48 or 64, at least 16 (q + 1)).  There are two tile classes, of 32 and of 64 rows:
+   16 runs as 32, 48 as 64.  k_stage[q] (8 or 16) is kept for saved configurations: the
+   matrix instruction takes 16 pupil rows at once, and both values run the same kernel.
+   The persistent grid of each class has wg_per_cu workgroups per CU (1..4).  The default
+   is tile_rows 16, 32, 48, 64, k_stage 16 and two workgroups per CU. */
 typedef struct rwpsf_batch_config {
   int wg_per_cu;
   int tile_rows[4];

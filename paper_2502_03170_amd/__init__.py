@@ -103,7 +103,8 @@ class BatchConfig(ctypes.Structure):
 
 def batch_config(wg_per_cu: int = 2, tile_rows=(16, 32, 48, 64), k_stage=(16, 16, 16, 16)) -> BatchConfig:
     """Launch configuration of the batched form: crops of 1-16, 17-32, 33-48, 49-64 pixels on
-    row tiles tile_rows[q]; the class of r-row tiles stages k_stage[r / 16 - 1] pupil rows."""
+    row tiles tile_rows[q] (16 runs as 32, 48 as 64); k_stage (8 or 16) is kept for saved
+    configurations, both values run the same kernel."""
     c = BatchConfig()
     c.wg_per_cu = wg_per_cu
     for q in range(4):

@@ -354,7 +354,7 @@ static int adjoint_zgroups(const rwpsf_plan* p) {
 }
 
 // Lazily built adjoint tables and workspace of a Fourier plan: the folded DFT tables with
-// the pixel index contiguous, CxT[2jf + p][m] = pref {cos, sin}(k s_jf x_m) and
+// the pixel index contiguous, CxT[2jf + p][m] = 2^e {cos, sin}(k s_jf x_m) and
 // CyT[2lf + p][n] = {cos, sin}(k s_lf y_n) (zero past nx, ny and for jf, lf >= N/2).
 // exp(i k s_z z) of every plan plane on the padded pupil cells (FP64 phase reduced
 // mod 2 pi before the FP32 sincos); 0 outside the disk where k s_z is 0 -> factor 1.
@@ -374,7 +374,11 @@ static int adjoint_prepare(rwpsf_plan* p, int n_stacks) {
   int st;
   if (!p->d_CxT) {
     const double s_max = p->s_max, k = p->k;
-    const double pref = std::ldexp(p->opt.focal_length * k / kTwoPi, -p->pf_exp);   // the pupils carry 2^pf_exp
+    // G conj(P~) needs the prefactor f k / 2 pi once: the folded pupils carry its mantissa and
+    // 2^pf_exp, the table the powers of two
+    int pref_exp = 0;
+    std::frexp(p->opt.focal_length * k / kTwoPi, &pref_exp);
+    const double pref = std::ldexp(1.0, pref_exp - p->pf_exp);
     std::vector<float> CxT((size_t)w * nxp, 0.f), CyT((size_t)w * nyp, 0.f);
     for (int f = 0; f < nh; ++f) {
       const double sv = (2.0 * f + 1.0 - N) * s_max / N;

@@ -5,18 +5,16 @@
 //
 // Per emitter b the pupil phase is
 //   Phi_b[j,l] = 2 pi sum_q c_bq Z_q(s) - k (s_x x0_b + s_y y0_b)
-// formed for all emitters at once by one real GEMM on the matrix cores,
-//   Phi[b][cell] = sum_k coef[k][b] basis[k][cell],  basis = (2 pi Z_1..Z_21, s_x, s_y).
-// The cell-centred grids are mirror-symmetric, so each emitter's pupil is folded once
-// (four parities per folded cell, written to the emitter's HBM slot) and each plane d of
-// each field component c is two real-coefficient GEMMs on the matrix cores,
-//   U  = A2_S (D o Pf_c)    (S x N; D = exp(i k s_z z) of each folded cell, formed as the
-//                            operand is staged: FP64 phase in revolutions, hardware sin/cos)
-//   E' = U B1_S             (S x S, U staged in LDS as the A operand),  E = -i E'
+// a sum over 23 tables, basis = (2 pi Z_1..Z_21, s_x, s_y), which a thread keeps in registers
+// for its pupil cells and applies to several emitters.  The cell-centred grids are
+// mirror-symmetric, so each emitter's pupil is folded in the same pass (four parities per
+// folded cell, written to the emitter's HBM slot) and each plane d of each field component c
+// are two real-coefficient GEMMs on the matrix cores,
+//   T  = (D o Pf_c) B1_S    (N x S; D = exp(i k s_z z) of each folded cell)
+//   E' = A2_S T             (S x S, T kept in LDS),  E = -i E'
 // and I = sum_c |E_c|^2.  A2_S / B1_S are the rows of one 96-row table that cover the
 // crop (pixel i of an S-crop is table row i - S/2 + 32).  Crops are evaluated on 32- or
-// 64-wide tiles (the two tile classes); the (emitter, plane) items of each class are
-// dealt, emitter by emitter and longest first, to eight queues, one per XCD, and the
+// 64-wide tiles, the two tile classes; the (emitter, plane) items of each class are dealt, emitter by emitter and longest first, to eight queues, one per XCD, and the
 // class's persistent kernel takes items from the queues' atomic counters until they are
 // exhausted.
 #include <algorithm>
@@ -31,20 +29,18 @@
 #include <numeric>
 #include <vector>
 
+#include "hfold.h"
 #include "rw_common.h"
+#include "rw_fourier.h"
 #include "rw_plan.h"
 
 namespace rw {
 
-hipError_t launch_rgemm(const float* A, int lda, const float* B, int ldb, float* C, int ldc, int M,
-                        int N, int K, hipStream_t st);
-
-typedef float f16v_t __attribute__((ext_vector_type(16)));
-
 constexpr int kTabRows = 96;    // DFT table rows: x_r = (r - 32) * pixel
-constexpr int kBasisRows = 32;  // 21 Zernike + s_x + s_y, zero-padded
+constexpr int kBasisRows = 23;  // 21 Zernike + s_x + s_y
 constexpr int kMaxWgPerCu = 4;  // workgroups per CU of the persistent launch (configuration bound)
-constexpr int kQueues = 32;     // 8 XCD queues for each of the four tile classes (16 .. 64 rows)
+constexpr int kTileClasses = 2;  // crops on 32- and on 64-row tiles
+constexpr int kQueues = 8 * kTileClasses;   // one queue per XCD for each class
 
 struct BatchParam {
   double zoff;      // -z_e
@@ -57,11 +53,12 @@ struct BatchArgs {
   const BatchParam* params;  // [n] cost-sorted (slot order)
   const float2* Q;           // [3][N][N]
   const double* ksz;         // [N][N]
-  const float* phi;          // [n][N*N], slot order
+  const float* coef;         // [n][23] coefficients of the phase, slot order
+  const float* basis;        // [23][N*N]
   const double4* gl;         // [N*N] Gibson-Lanni phase W = t_s (g1.x + i g1.y) + (g0.x + i g0.y) as
                              // (g0.x, g0.y, g1.x, g1.y), or null without the layer
-  const float* A2T;          // [N][96] rows 2jf + pj: pref cos / sin (k s_x[jf] x_r)
-  const float* B1T;          // [N][96] rows 2lf + pl: cos / sin (k s_y[lf] y_r)
+  const uint4* tab;          // split-f16 panel of 96 rows r, k = 2f + p: 2^kTabExp cos / sin (k s[f] x_r)
+  float tscale, escale;      // powers of two: on T, and fields per unit of the image product
   float2* Pf;                // [n][3][N][N] folded pupils, slot order
   const int* list;           // [n] slots grouped by XCD queue
   const long long* pre;      // [n + 1] plane prefix sums over list
@@ -70,568 +67,323 @@ struct BatchArgs {
   float* I;
   float2* E;
   int n, N;
+  int group;                 // emitters per workgroup of the fold kernel
   double pitch;
 };
 
-// Each queue's counter starts at its first item (a kernel, not a memset, so that the
-// launch sequence can be captured in a graph).
-__global__ void batch_reset_kernel(unsigned long long* counter, const long long* pre, const int* qoff) {
-  const int x = threadIdx.x;
-  if (x < kQueues) counter[x] = (unsigned long long)pre[qoff[x]];
+// A phase reduced to half turns in [-1, 1].
+__device__ __forceinline__ float turns(double phase) {
+  const double t = phase * (1.0 / kTwoPi);
+  return (float)(2.0 * (t - rint(t)));
 }
 
-// Folded pupil of every emitter (one workgroup per emitter).  The pupil and pixel grids
-// are mirror-symmetric (s[N-1-j] = -s[j]); with P = Q_c exp(i Phi) at the four mirror
-// cells of (jf, lf),
+// Folded pupil of every emitter.  The pupil and pixel grids are mirror-symmetric
+// (s[N-1-j] = -s[j]); with P = Q_c exp(i Phi) at the four mirror cells of (jf, lf),
 //   Pf_{pj,pl}[jf][lf] = i^(pj+pl) sum_{a,b} (-1)^(a pj + b pl) P[mir_a(jf)][mir_b(lf)],
-// stored at Pf[c][2jf + pj][2lf + pl].
+// stored at Pf[c][2jf + pj][2lf + pl].  A thread owns one folded cell: the 23 basis values and
+// the base pupil of its four mirror cells stay in registers while it goes through `group`
+// emitters, whose coefficients come over the scalar path.  The phase is reduced in FP64 and
+// goes through sincospif, which has no path for large arguments (the hardware sine and cosine
+// left the intensities at 1.5e-7 of their norm in place of 1.0e-7 and saved 20 us of 289).
+// Bound by the writes (393 KB an emitter at N = 128).  4096 emitters: 289 us; the phases as a
+// matrix product of their own (80 us), written and read back by a workgroup per emitter (531
+// us), took 611.
+// Workgroup 0 also sets each queue's counter to its first item (a kernel, not a memset, so
+// that the launch sequence can be captured in a graph; one launch less than a kernel of its
+// own).
 __global__ void __launch_bounds__(256) batch_fold_kernel(BatchArgs a) {
-  const int slot = blockIdx.x;
-  const int N = a.N, NN = N * N, nh = N / 2;
-  const float* phi = a.phi + (size_t)slot * NN;
-  float2* Pf = a.Pf + (size_t)slot * 3 * NN;
-  const double ts = a.params[slot].ts;
-  for (int cell = threadIdx.x; cell < nh * nh; cell += 256) {
-    const int jf = cell / nh, lf = cell % nh, j1 = N - 1 - jf, l1 = N - 1 - lf;
-    const int idx[4] = {jf * N + lf, jf * N + l1, j1 * N + lf, j1 * N + l1};
+  const int N = a.N, nh = N / 2;
+  const size_t NN = (size_t)N * N;
+  const int tid = threadIdx.x;
+  if (blockIdx.x == 0 && tid < kQueues) a.counter[tid] = (unsigned long long)a.pre[a.qoff[tid]];
+  const int cells = nh * nh / 256;   // whole workgroups at every pupil size
+  const int cell = blockIdx.x % cells * 256 + tid;
+  const int jf = cell / nh, lf = cell % nh, j1 = N - 1 - jf, l1 = N - 1 - lf;
+  const int idx[4] = {jf * N + lf, jf * N + l1, j1 * N + lf, j1 * N + l1};
+  float basis[4][kBasisRows];
+  float2 Q[3][4];
+  double4 g[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+#pragma unroll
+    for (int k = 0; k < kBasisRows; ++k) basis[q][k] = a.basis[(size_t)k * NN + idx[q]];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) Q[c][q] = a.Q[(size_t)c * NN + idx[q]];
+    g[q] = a.gl ? a.gl[idx[q]] : make_double4(0.0, 0.0, 0.0, 0.0);
+  }
+  const int s0 = blockIdx.x / cells * a.group, s1 = min(s0 + a.group, a.n);
+#pragma unroll 1
+  for (int slot = s0; slot < s1; ++slot) {
+    const float* cf = a.coef + (size_t)slot * kBasisRows;
+    float phi[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < kBasisRows; ++k)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) phi[q] = fmaf(cf[k], basis[q][k], phi[q]);
     float er[4], ei[4];
     if (a.gl) {
-      // the layer's phase is formed in FP64 and reduced mod 2 pi before it joins phi;
-      // its imaginary part is the evanescent decay
+      // the layer's phase is formed in FP64 and joins phi before the reduction; its imaginary
+      // part is the evanescent decay
+      const double ts = a.params[slot].ts;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const double4 g = a.gl[idx[q]];
-        const double wr = ts * g.z + g.x, wi = ts * g.w + g.y;
+        const double wr = ts * g[q].z + g[q].x, wi = ts * g[q].w + g[q].y;
         const float amp = (float)exp(-wi);
         float sn, cs;
-        sincosf((float)reduce_2pi(wr + (double)phi[idx[q]]), &sn, &cs);
+        sincospif(turns(wr + (double)phi[q]), &sn, &cs);
         er[q] = amp * cs;
         ei[q] = amp * sn;
       }
     } else {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) sincosf(phi[idx[q]], &ei[q], &er[q]);
+      for (int q = 0; q < 4; ++q) sincospif(turns((double)phi[q]), &ei[q], &er[q]);
     }
+    float2* Pf = a.Pf + (size_t)slot * 3 * NN;
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
       float pr[4], pi[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const float2 v = a.Q[(size_t)c * NN + idx[q]];
+        const float2 v = Q[c][q];
         pr[q] = v.x * er[q] - v.y * ei[q];
         pi[q] = v.x * ei[q] + v.y * er[q];
       }
-      float2* o = Pf + (size_t)c * NN + (size_t)(2 * jf) * N + 2 * lf;
+      float4* o = reinterpret_cast<float4*>(Pf + (size_t)c * NN + (size_t)(2 * jf) * N + 2 * lf);
       // (pj, pl) = (0,0): +,+,+,+   (0,1): i(+,-,+,-)   (1,0): i(+,+,-,-)   (1,1): -(+,-,-,+)
-      o[0] = make_float2(pr[0] + pr[1] + pr[2] + pr[3], pi[0] + pi[1] + pi[2] + pi[3]);
-      o[1] = make_float2(-(pi[0] - pi[1] + pi[2] - pi[3]), pr[0] - pr[1] + pr[2] - pr[3]);
-      o[N] = make_float2(-(pi[0] + pi[1] - pi[2] - pi[3]), pr[0] + pr[1] - pr[2] - pr[3]);
-      o[N + 1] = make_float2(-(pr[0] - pr[1] - pr[2] + pr[3]), -(pi[0] - pi[1] - pi[2] + pi[3]));
+      o[0] = make_float4(pr[0] + pr[1] + pr[2] + pr[3], pi[0] + pi[1] + pi[2] + pi[3],
+                         -(pi[0] - pi[1] + pi[2] - pi[3]), pr[0] - pr[1] + pr[2] - pr[3]);
+      o[N / 2] = make_float4(-(pi[0] + pi[1] - pi[2] - pi[3]), pr[0] + pr[1] - pr[2] - pr[3],
+                             -(pr[0] - pr[1] - pr[2] + pr[3]), -(pi[0] - pi[1] - pi[2] + pi[3]));
     }
   }
 }
 
-// MFMA 32x32x2 f32: A lane l -> A[l%32][l/32], B lane l -> B[l/32][l%32],
-// C register r of lane l -> C[8(r/4) + 4(l/32) + r%4][l%32].
-//
-// Plane d of emitter `slot`:  U = A2 (D o Pf_c)  (real x complex),  E' = U B1
-// (complex x real),  E = -i E',  I = sum_c |E_c|^2, with the defocus D[jf][lf] =
-// exp(i k s_z z) of the folded cell, the same for its four mirror cells.
-template <int SP, int BK>
-__device__ __forceinline__ void batch_plane32(const BatchArgs& a, const BatchParam& bp, int slot, int d,
-                                            float* lds, int tid) {
-  constexpr int TI = SP / 32;
-  constexpr int LDU = SP + 1;
-  constexpr int kLdaU = 64 + 4, kLdbU = 128 + 4;   // LDS row strides of the staged A (crop rows) and B (columns)
-  constexpr int kStage32 = BK * (kLdaU + 2 * kLdbU);
+// Plane kernel.  Plane d of emitter `slot`, per field component c, with the operands split in
+// f16 halves (hgemm.h):
+//   T[q][n]  = sum_kk (D o Pf_c)[q][kk] B1[kk][n]     2N x SP, K = N: the defocused pupil staged
+//              as in the plain form (D = exp(i k s_z z) of each folded cell, FP64 phase in
+//              revolutions, hardware sine and cosine), all rows (q, re / im) in one workgroup
+//   E'[m][n] = sum_q A2[m][q] T[q][n]                 SP x SP, K = N, real and imaginary part
+//   E = -i E',  I = sum_c |E_c|^2
+// T never leaves the CU: it is written to LDS as a split panel (rows ri SP + n, k = q) in the
+// place of the stage buffers and is the second product's operand as it lies there; the table
+// rows of the other operand come from global memory (one table serves both products).  SP =
+// 64: a wave per 32 x 32 block of the image; SP = 32: K split over the waves, the partial sums
+// joined through LDS.  Waves own 64 pupil rows (N = 128) or 32.
+// Bound by the matrix cores and by what stands between their products (staging, the split of
+// T).  Measured on 4096 emitters (crops 24-64, 1-41 planes, N = 128), a whole call: 16.7 ms with
+// FP32 MFMA tiles (planes 16.1), 6.5 ms so (planes 5.4 + 1.1); a frame of 100 emitters of one
+// plane 87 -> 30 us.  Waves of 32 pupil rows (eight of them) took 7.0 + 1.55 ms; table rows
+// of the second product requested ahead of the split of T gave 2.75 -> 3.09 ms on the 64-row
+// tile (they spill) and 1.20 -> 1.12 ms on the 32-row tile, where they are.
+template <int N, int SP>
+struct PlaneTile {
+  static constexpr int WM = N >= 128 ? 64 : 32;
+  using Cfg = HgCfg<2 * N, SP, 16, WM, SP>;
+  static constexpr int NW = Cfg::NT / 64;
+  static constexpr int COMBOS = SP == 64 ? (4 + NW - 1) / NW : 1;   // 32 x 32 image blocks per wave
+  static constexpr int KPW = SP == 64 ? N / 16 : N / 16 / NW;       // k-steps per wave
+  static_assert(SP == 64 || N / 16 % NW == 0, "whole k-steps per wave");
+  static constexpr int PART = SP == 64 ? 0 : NW * 2 * 32 * 33 * 4;  // partial sums of a 32 x 32 image
+  static constexpr int T_BYTES = (int)hg_panel_bytes(N, 2 * SP);
+  static constexpr int LDS_BYTES =
+      Cfg::LDS_BYTES > T_BYTES ? (Cfg::LDS_BYTES > PART ? Cfg::LDS_BYTES : PART) : (T_BYTES > PART ? T_BYTES : PART);
+  static constexpr int PIX = SP == 64 ? 16 * COMBOS : (1024 + Cfg::NT - 1) / Cfg::NT;   // intensities per lane
+};
+
+template <int N, int SP>
+__device__ __forceinline__ void batch_plane(const BatchArgs& a, const BatchParam& bp, int slot, int d, char* lds,
+                                            int tid) {
+  using P = PlaneTile<N, SP>;
+  using Cfg = typename P::Cfg;
   const int lane = tid & 63, w = tid >> 6, h = lane >> 5, l32 = lane & 31;
-  const int N = a.N, NN = N * N, S = bp.S;
-  const int r0 = 32 - S / 2;
-  const float2* Pf = a.Pf + (size_t)slot * 3 * NN;
-  float* Ure = lds;
-  float* Uim = lds + N * LDU;
+  const int S = bp.S, r0 = 32 - S / 2;
   const double zrev = ((d - 0.5 * (bp.D - 1)) * a.pitch + bp.zoff) * (1.0 / kTwoPi);
-  float isum64[16];   // SP = 64: this wave's 32x32 block of E, MFMA C layout
-  float isum32[4];    // SP = 32: elements tid + 256 q of the 32x32 image
+  float isum[P::PIX];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) isum64[r] = 0.f;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) isum32[q] = 0.f;
+  for (int r = 0; r < P::PIX; ++r) isum[r] = 0.f;
+  FoldDefocusLoader<Cfg, 1> la;
+  const float2* pf = a.Pf + (size_t)slot * 3 * N * N;
+  la.Pf = pf;
+  la.kszf = a.ksz;
+  la.zrev[0] = zrev;
+  la.w = N;
+  la.nhp = N;   // row stride of ksz
+  HgPanelLoader<Cfg, SP> lb;
+  lb.src = a.tab + r0;
+  lb.ld = kTabRows;
+  typename FoldDefocusLoader<Cfg, 1>::Regs ra;
+  typename HgPanelLoader<Cfg, SP>::Regs rb;
+  if constexpr (SP == 32) {
+    ra = la.load(0, tid);
+    rb = lb.load(0, tid);
+  }
+#pragma unroll 1
   for (int c = 0; c < 3; ++c) {
-    const float2* Pc = Pf + (size_t)c * NN;
-    // ---- U[m][col] = sum_k A2[r0 + m][k] (D o Pf)[k][col]: k-stages of A2 rows and of the
-    // defocused folded pupil (re / im planes) staged in LDS, double-buffered; wave w owns
-    // columns 32 w .. 32 w + 31
+    if constexpr (SP == 64) {
+      la.Pf = pf + (size_t)c * N * N;
+      ra = la.load(0, tid);
+      rb = lb.load(0, tid);
+    }
+    hg8 fh[P::KPW], fl[P::KPW];   // table rows of this wave's image block, over its k-steps
+    auto fetch = [&](int mb, int ks0) {
+      const hg8* ap = reinterpret_cast<const hg8*>(a.tab) + r0 + 32 * mb + l32;
+#pragma unroll
+      for (int u = 0; u < P::KPW; ++u) {
+        fh[u] = ap[(4 * (ks0 + u) + h) * kTabRows];
+        fl[u] = ap[(4 * (ks0 + u) + 2 + h) * kTabRows];
+      }
+    };
     {
-      float ra[4];      // A prefetch: BK x SP floats, up to 4 per thread
-      float4 rp[4];     // B prefetch: BK x N/2 float4, up to 4 per thread
-      double rd[4];     // k s_z of the staged folded cell
-      const int na = BK * SP, nb = BK * (N / 2);   // A floats and B float4 of one stage, up to 4 per thread
-      auto load = [&](int k0) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int idx = tid + 256 * i;
-          if (idx < na) {
-            const int kk = idx / SP, m = idx % SP;
-            ra[i] = a.A2T[(k0 + kk) * kTabRows + r0 + m];
-          }
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int idx = tid + 256 * i;
-          if (idx < nb) {
-            const int kk = idx / (N / 2), c2 = idx % (N / 2);
-            rp[i] = *reinterpret_cast<const float4*>(Pc + (size_t)(k0 + kk) * N + 2 * c2);
-            rd[i] = a.ksz[((k0 + kk) >> 1) * N + c2];
-          }
-        }
-      };
-      auto store = [&](float* st) {
-        float* sa = st;
-        float* sr = st + BK * kLdaU;
-        float* si = sr + BK * kLdbU;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int idx = tid + 256 * i;
-          if (idx < na) {
-            const int kk = idx / SP, m = idx % SP;
-            sa[kk * kLdaU + m] = ra[i];
-          }
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int idx = tid + 256 * i;
-          if (idx < nb) {
-            const int kk = idx / (N / 2), c2 = idx % (N / 2);
-            float2 dz;   // exp(i k s_z z): FP64 phase in revolutions, hardware sine and cosine
-            sincos_rev(rd[i] * zrev, &dz.y, &dz.x);
-            *reinterpret_cast<float2*>(sr + kk * kLdbU + 2 * c2) =
-                make_float2(rp[i].x * dz.x - rp[i].y * dz.y, rp[i].z * dz.x - rp[i].w * dz.y);
-            *reinterpret_cast<float2*>(si + kk * kLdbU + 2 * c2) =
-                make_float2(rp[i].x * dz.y + rp[i].y * dz.x, rp[i].z * dz.y + rp[i].w * dz.x);
-          }
-        }
-      };
-      f16v_t ur[TI], ui[TI];
-#pragma unroll
-      for (int i = 0; i < TI; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          ur[i][r] = 0.f;
-          ui[i][r] = 0.f;
-        }
-      const bool has_cols = 32 * w < N;
-      const int KT = N / BK;
-      load(0);
-      store(lds);
-      __syncthreads();
-      for (int kt = 0; kt < KT; ++kt) {
-        float* cur = lds + (kt & 1) * kStage32;
-        float* nxt = lds + ((kt + 1) & 1) * kStage32;
-        const bool more = kt + 1 < KT;
-        if (more) load((kt + 1) * BK);
-        if (has_cols) {
-          const float* sa = cur;
-          const float* sr = cur + BK * kLdaU;
-          const float* si = sr + BK * kLdbU;
-#pragma unroll
-          for (int kp = 0; kp < BK / 2; ++kp) {
-            const int kk = 2 * kp + h;
-            const float br = sr[kk * kLdbU + 32 * w + l32], bi = si[kk * kLdbU + 32 * w + l32];
-#pragma unroll
-            for (int i = 0; i < TI; ++i) {
-              const float av = sa[kk * kLdaU + 32 * i + l32];
-              ur[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, br, ur[i], 0, 0, 0);
-              ui[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bi, ui[i], 0, 0, 0);
-            }
-          }
-        }
-        if (more) store(nxt);
-        __syncthreads();
+      HgAcc<Cfg> acc;
+      acc.zero();
+      hg_mainloop_pre<Cfg>(acc, la, lb, ra, rb, 0, N, lds, tid, w * P::WM, 0, lane);
+      // every wave has left the stage buffers
+      if constexpr (SP == 32) {
+        // the table rows of the second product and the next component's first stage (the last
+        // component reloads its own, unused) arrive while T is split and written; at SP = 64
+        // the registers are taken
+        la.Pf = pf + (size_t)min(c + 1, 2) * N * N;
+        ra = la.load(0, tid);
+        rb = lb.load(0, tid);
+        fetch(0, w * P::KPW);
+        __builtin_amdgcn_sched_barrier(0);
       }
-      // U overwrites the stage buffers: every wave has passed the last barrier above
-      if (has_cols) {
-        const int col = 32 * w + l32;
 #pragma unroll
-        for (int i = 0; i < TI; ++i)
+      for (int i = 0; i < Cfg::TM; ++i)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int m = 32 * i + 8 * (r >> 2) + 4 * h + (r & 3);
-            Ure[col * LDU + m] = ur[i][r];
-            Uim[col * LDU + m] = ui[i][r];
-          }
-      }
+        for (int j = 0; j < Cfg::TN; ++j) {
+          float v[16];
+#pragma unroll
+          for (int r = 0; r < 16; ++r) v[r] = acc.c[i][j][r] * a.tscale;
+          uint4 piece[4];
+          hg_split16(v, piece);
+          uint4* o = reinterpret_cast<uint4*>(lds) + (size_t)(4 * (w * P::WM / 32 + i)) * (2 * SP) + h * SP + 32 * j + l32;
+#pragma unroll
+          for (int p = 0; p < 4; ++p) o[p * 2 * SP] = piece[p];
+        }
     }
     __syncthreads();
-    // ---- E'[m][n] = sum_col U[m][col] B1[col][r0 + n]
-    f16v_t er, ei;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      er[r] = 0.f;
-      ei[r] = 0.f;
-    }
-    const int mi = (SP == 64) ? (w >> 1) : 0, ni = (SP == 64) ? (w & 1) : 0;
-    const int kp1a = (SP == 64) ? 0 : w * (N / 8);               // SP = 32: K split over the waves
-    const int kp1b = (SP == 64) ? N / 2 : (w + 1) * (N / 8);     // (kp1b - kp1a) is a multiple of 4
-    {
-      // the y-table operand comes from global memory: chunks of 4 k-steps are loaded one
-      // chunk ahead of the MFMAs that use them
-      const float* bsrc = a.B1T + h * kTabRows + r0 + 32 * ni + l32;
-      float bc[4], bn[4];
-#pragma unroll
-      for (int t = 0; t < 4; ++t) bc[t] = bsrc[(2 * (kp1a + t)) * kTabRows];
-      for (int kp = kp1a; kp < kp1b; kp += 4) {
-        const bool more = kp + 4 < kp1b;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) bn[t] = more ? bsrc[(2 * (kp + 4 + t)) * kTabRows] : 0.f;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const int kk = 2 * (kp + t) + h;
-          const float ar = Ure[kk * LDU + 32 * mi + l32], ai = Uim[kk * LDU + 32 * mi + l32];
-          er = __builtin_amdgcn_mfma_f32_32x32x2f32(ar, bc[t], er, 0, 0, 0);
-          ei = __builtin_amdgcn_mfma_f32_32x32x2f32(ai, bc[t], ei, 0, 0, 0);
-        }
-#pragma unroll
-        for (int t = 0; t < 4; ++t) bc[t] = bn[t];
-      }
-    }
-    __syncthreads();   // U is consumed
-    // E = -i E' = (Im E', -Re E')
-    if (SP == 64) {
-      float2* Ec = a.E ? a.E + 3 * bp.off + ((size_t)(d * 3 + c) * S) * S : nullptr;
+    float2* Ec = a.E ? a.E + 3 * bp.off + ((size_t)(d * 3 + c) * S) * S : nullptr;
+    // E' block of columns nb over k-steps [ks0, ks0 + KPW).  The cross products of all k go
+    // first: the accumulators are then 2^-11 of their final size and their roundings do not
+    // count.
+    auto product = [&](int nb, int ks0, hg16& er, hg16& ei) {
+      const hg8* bt = reinterpret_cast<const hg8*>(lds) + 32 * nb + l32;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int m = 32 * mi + 8 * (r >> 2) + 4 * h + (r & 3), n = 32 * ni + l32;
-        isum64[r] += er[r] * er[r] + ei[r] * ei[r];
-        if (Ec && m < S && n < S) Ec[m * S + n] = make_float2(ei[r], -er[r]);
+        er[r] = 0.f;
+        ei[r] = 0.f;
       }
+#pragma unroll
+      for (int u = 0; u < P::KPW; ++u) {
+        const hg8* t = bt + (4 * (ks0 + u) + h) * 2 * SP;
+        er = __builtin_amdgcn_mfma_f32_32x32x16_f16(fh[u], t[4 * SP], er, 0, 0, 0);
+        ei = __builtin_amdgcn_mfma_f32_32x32x16_f16(fh[u], t[5 * SP], ei, 0, 0, 0);
+        er = __builtin_amdgcn_mfma_f32_32x32x16_f16(fl[u], t[0], er, 0, 0, 0);
+        ei = __builtin_amdgcn_mfma_f32_32x32x16_f16(fl[u], t[SP], ei, 0, 0, 0);
+      }
+#pragma unroll
+      for (int u = 0; u < P::KPW; ++u) {
+        const hg8* t = bt + (4 * (ks0 + u) + h) * 2 * SP;
+        er = __builtin_amdgcn_mfma_f32_32x32x16_f16(fh[u], t[0], er, 0, 0, 0);
+        ei = __builtin_amdgcn_mfma_f32_32x32x16_f16(fh[u], t[SP], ei, 0, 0, 0);
+      }
+    };
+    // E = -i E' = (Im E', -Re E')
+    if constexpr (SP == 64) {
+#pragma unroll
+      for (int q = 0; q < P::COMBOS; ++q) {
+        const int blk = w + q * P::NW;
+        if (blk >= 4) break;
+        hg16 er, ei;
+        fetch(blk >> 1, 0);
+        product(blk & 1, 0, er, ei);
+        const int n = 32 * (blk & 1) + l32;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int m = 32 * (blk >> 1) + 8 * (r >> 2) + 4 * h + (r & 3);
+          const float x = ei[r] * a.escale, y = -er[r] * a.escale;
+          isum[16 * q + r] += x * x + y * y;
+          if (Ec && m < S && n < S) Ec[m * S + n] = make_float2(x, y);
+        }
+      }
+      __syncthreads();   // T is consumed
     } else {
-      // reduce the four K-partials through LDS (the U area is free now)
-      float* pre = lds + w * 2 * 32 * 33;
-      float* pim = pre + 32 * 33;
+      hg16 er, ei;
+      product(0, w * P::KPW, er, ei);
+      __syncthreads();   // T is consumed: the partial sums take its place
+      float* part = reinterpret_cast<float*>(lds);
+      float* pre = part + w * 2 * 32 * 33;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int m = 8 * (r >> 2) + 4 * h + (r & 3);
         pre[m * 33 + l32] = er[r];
-        pim[m * 33 + l32] = ei[r];
+        pre[32 * 33 + m * 33 + l32] = ei[r];
       }
       __syncthreads();
-      float2* Ec = a.E ? a.E + 3 * bp.off + ((size_t)(d * 3 + c) * S) * S : nullptr;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int e = tid + 256 * q, m = e >> 5, n = e & 31;
+      for (int q = 0; q < P::PIX; ++q) {
+        const int e = tid + Cfg::NT * q, m = e >> 5, n = e & 31;
+        if (1024 % Cfg::NT != 0 && e >= 1024) break;
         float sr = 0.f, si = 0.f;
 #pragma unroll
-        for (int ww = 0; ww < 4; ++ww) {
-          sr += lds[ww * 2 * 32 * 33 + m * 33 + n];
-          si += lds[ww * 2 * 32 * 33 + 32 * 33 + m * 33 + n];
+        for (int ww = 0; ww < P::NW; ++ww) {
+          sr += part[ww * 2 * 32 * 33 + m * 33 + n];
+          si += part[ww * 2 * 32 * 33 + 32 * 33 + m * 33 + n];
         }
-        isum32[q] += sr * sr + si * si;
-        if (Ec && m < S && n < S) Ec[m * S + n] = make_float2(si, -sr);
+        const float x = si * a.escale, y = -sr * a.escale;
+        isum[q] += x * x + y * y;
+        if (Ec && m < S && n < S) Ec[m * S + n] = make_float2(x, y);
       }
       __syncthreads();
     }
   }
   if (a.I) {
     float* Ip = a.I + bp.off + (size_t)d * S * S;
-    if (SP == 64) {
-      const int mi = w >> 1, ni = w & 1;
+    if constexpr (SP == 64) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = 32 * mi + 8 * (r >> 2) + 4 * h + (r & 3), n = 32 * ni + l32;
-        if (m < S && n < S) Ip[m * S + n] = isum64[r];
+      for (int q = 0; q < P::COMBOS; ++q) {
+        const int blk = w + q * P::NW;
+        if (blk >= 4) break;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int m = 32 * (blk >> 1) + 8 * (r >> 2) + 4 * h + (r & 3), n = 32 * (blk & 1) + l32;
+          if (m < S && n < S) Ip[m * S + n] = isum[16 * q + r];
+        }
       }
     } else {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int e = tid + 256 * q, m = e >> 5, n = e & 31;
-        if (m < S && n < S) Ip[m * S + n] = isum32[q];
+      for (int q = 0; q < P::PIX; ++q) {
+        const int e = tid + Cfg::NT * q, m = e >> 5, n = e & 31;
+        if (m < S && n < S) Ip[m * S + n] = isum[q];
       }
     }
   }
-  __syncthreads();   // every wave is done with the LDS before the next item
 }
 
-// MFMA 16x16x4 f32: A lane l -> A[l%16][l/16], B lane l -> B[l/16][l%16],
-// C register r of lane l -> C[4(l/16) + r][l%16].
-//
-// Plane d of emitter `slot` on a tile of SP rows (SP = 16, 32, 48 or 64 >= S):
-//   U = A2 (D o Pf_c)  (real x complex, SP x N),  E' = U B1  (complex x real, SP x SP),
-//   E = -i E',  I = sum_c |E_c|^2,
-// with the defocus D[jf][lf] = exp(i k s_z z) of the folded cell, the same for its four
-// mirror cells.  U: wave w owns columns 32 w .. 32 w + 31 (two 16-wide column tiles) and
-// all SP / 16 row tiles; k-stages of BK folded rows are staged in LDS, double-buffered.
-// E': the (SP / 16)^2 output tiles are dealt round-robin to the four waves, each over the
-// whole K = N; a single tile (SP = 16) is split over K between the waves and the four
-// partial sums are added through LDS.
-typedef float f4_t __attribute__((ext_vector_type(4)));
-
-template <int SP, int BK>
-struct PlaneTile {
-  static constexpr int MT = SP / 16;                 // row tiles
-  static constexpr int T2 = MT * MT;                 // output tiles of E'
-  static constexpr bool KSPLIT = T2 < 4;             // SP = 16: one tile, K split four ways
-  static constexpr int TPW = KSPLIT ? 1 : (T2 + 3) / 4;   // output tiles per wave
-  static constexpr int LDA = SP + 4;                 // LDS row strides of the staged operands
-  static constexpr int LDB = 128 + 4;
-  static constexpr int STAGE = BK * (LDA + 2 * LDB);
-  static constexpr int LDU = SP + 1;                 // U: [col][m]
-  static constexpr int LDS_FLOATS = (2 * STAGE > 2 * 128 * LDU) ? 2 * STAGE : 2 * 128 * LDU;
-};
-
-template <int SP, int BK>
-__device__ __forceinline__ void batch_plane16(const BatchArgs& a, const BatchParam& bp, int slot, int d,
-                                              float* lds, int tid) {
-  using P = PlaneTile<SP, BK>;
-  constexpr int MT = P::MT, TPW = P::TPW;
-  const int lane = tid & 63, w = tid >> 6, g = lane >> 4, l16 = lane & 15;
-  const int N = a.N, NN = N * N, S = bp.S;
-  const int r0 = 32 - S / 2;
-  const float2* Pf = a.Pf + (size_t)slot * 3 * NN;
-  float* Ure = lds;
-  float* Uim = lds + 128 * P::LDU;
-  const double zrev = ((d - 0.5 * (bp.D - 1)) * a.pitch + bp.zoff) * (1.0 / kTwoPi);
-  f4_t isum[TPW];
-#pragma unroll
-  for (int t = 0; t < TPW; ++t) isum[t] = f4_t{0.f, 0.f, 0.f, 0.f};
-  for (int c = 0; c < 3; ++c) {
-    const float2* Pc = Pf + (size_t)c * NN;
-    // ---- U[m][col] = sum_k A2[r0 + m][k] (D o Pf)[k][col]
-    {
-      constexpr int NA = (BK * SP + 255) / 256;       // A loads per thread (the last may be partial)
-      constexpr int NB = (BK * 64 + 255) / 256;       // B loads (float4 = two complex) per thread, N <= 128
-      float ra[NA];
-      float4 rp[NB];
-      double rd[NB];
-      const int nbv = BK * (N / 2);                   // float4 of B per stage
-      auto load = [&](int k0) {
-#pragma unroll
-        for (int i = 0; i < NA; ++i) {
-          const int idx = tid + 256 * i;
-          if (idx < BK * SP) {
-            const int kk = idx / SP, m = idx % SP;
-            ra[i] = a.A2T[(k0 + kk) * kTabRows + r0 + m];
-          }
-        }
-#pragma unroll
-        for (int i = 0; i < NB; ++i) {
-          const int idx = tid + 256 * i;
-          if (idx < nbv) {
-            const int kk = idx / (N / 2), c2 = idx % (N / 2);
-            rp[i] = *reinterpret_cast<const float4*>(Pc + (size_t)(k0 + kk) * N + 2 * c2);
-            rd[i] = a.ksz[((k0 + kk) >> 1) * N + c2];
-          }
-        }
-      };
-      auto store = [&](float* st) {
-        float* sa = st;
-        float* sr = st + BK * P::LDA;
-        float* si = sr + BK * P::LDB;
-#pragma unroll
-        for (int i = 0; i < NA; ++i) {
-          const int idx = tid + 256 * i;
-          if (idx < BK * SP) {
-            const int kk = idx / SP, m = idx % SP;
-            sa[kk * P::LDA + m] = ra[i];
-          }
-        }
-#pragma unroll
-        for (int i = 0; i < NB; ++i) {
-          const int idx = tid + 256 * i;
-          if (idx < nbv) {
-            const int kk = idx / (N / 2), c2 = idx % (N / 2);
-            float2 dz;   // exp(i k s_z z): FP64 phase in revolutions, hardware sine and cosine
-            sincos_rev(rd[i] * zrev, &dz.y, &dz.x);
-            *reinterpret_cast<float2*>(sr + kk * P::LDB + 2 * c2) =
-                make_float2(rp[i].x * dz.x - rp[i].y * dz.y, rp[i].z * dz.x - rp[i].w * dz.y);
-            *reinterpret_cast<float2*>(si + kk * P::LDB + 2 * c2) =
-                make_float2(rp[i].x * dz.y + rp[i].y * dz.x, rp[i].z * dz.y + rp[i].w * dz.x);
-          }
-        }
-      };
-      f4_t ur[MT][2], ui[MT][2];
-#pragma unroll
-      for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          ur[i][j] = f4_t{0.f, 0.f, 0.f, 0.f};
-          ui[i][j] = f4_t{0.f, 0.f, 0.f, 0.f};
-        }
-      const bool has_cols = 32 * w < N;
-      const int KT = N / BK;
-      load(0);
-      store(lds);
-      __syncthreads();
-      for (int kt = 0; kt < KT; ++kt) {
-        float* cur = lds + (kt & 1) * P::STAGE;
-        float* nxt = lds + ((kt + 1) & 1) * P::STAGE;
-        const bool more = kt + 1 < KT;
-        if (more) load((kt + 1) * BK);
-        if (has_cols) {
-          const float* sa = cur;
-          const float* sr = cur + BK * P::LDA;
-          const float* si = sr + BK * P::LDB;
-#pragma unroll
-          for (int kq = 0; kq < BK / 4; ++kq) {
-            const int kk = 4 * kq + g;
-            float br[2], bi[2];
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-              br[j] = sr[kk * P::LDB + 32 * w + 16 * j + l16];
-              bi[j] = si[kk * P::LDB + 32 * w + 16 * j + l16];
-            }
-#pragma unroll
-            for (int i = 0; i < MT; ++i) {
-              const float av = sa[kk * P::LDA + 16 * i + l16];
-#pragma unroll
-              for (int j = 0; j < 2; ++j) {
-                ur[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, br[j], ur[i][j], 0, 0, 0);
-                ui[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bi[j], ui[i][j], 0, 0, 0);
-              }
-            }
-          }
-        }
-        if (more) store(nxt);
-        __syncthreads();
-      }
-      // U overwrites the stage buffers: every wave has passed the last barrier above
-      if (has_cols) {
-#pragma unroll
-        for (int i = 0; i < MT; ++i)
-#pragma unroll
-          for (int j = 0; j < 2; ++j) {
-            const int col = 32 * w + 16 * j + l16;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const int m = 16 * i + 4 * g + r;
-              Ure[col * P::LDU + m] = ur[i][j][r];
-              Uim[col * P::LDU + m] = ui[i][j][r];
-            }
-          }
-      }
-    }
-    __syncthreads();
-    // ---- E'[m][n] = sum_col U[m][col] B1[col][r0 + n]
-    float2* Ec = a.E ? a.E + 3 * bp.off + ((size_t)(d * 3 + c) * S) * S : nullptr;
-    if (!P::KSPLIT) {
-#pragma unroll
-      for (int t = 0; t < TPW; ++t) {
-        const int tile = w + 4 * t;
-        if (tile < P::T2) {
-          const int mi = tile / MT, ni = tile % MT;
-          f4_t er = {0.f, 0.f, 0.f, 0.f}, ei = {0.f, 0.f, 0.f, 0.f};
-          // the y-table operand comes from global memory: chunks of four k-steps (16
-          // columns) are loaded one chunk ahead of the MFMAs that use them (N % 16 == 0)
-          const float* bsrc = a.B1T + r0 + 16 * ni + l16 + g * kTabRows;
-          float bc[4], bn[4];
-#pragma unroll
-          for (int q = 0; q < 4; ++q) bc[q] = bsrc[(4 * q) * kTabRows];
-          for (int k0 = 0; k0 < N; k0 += 16) {
-            const bool more = k0 + 16 < N;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) bn[q] = more ? bsrc[(k0 + 16 + 4 * q) * kTabRows] : 0.f;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              const int col = k0 + 4 * q + g;
-              const float ar = Ure[col * P::LDU + 16 * mi + l16], ai = Uim[col * P::LDU + 16 * mi + l16];
-              er = __builtin_amdgcn_mfma_f32_16x16x4f32(ar, bc[q], er, 0, 0, 0);
-              ei = __builtin_amdgcn_mfma_f32_16x16x4f32(ai, bc[q], ei, 0, 0, 0);
-            }
-#pragma unroll
-            for (int q = 0; q < 4; ++q) bc[q] = bn[q];
-          }
-          // E = -i E' = (Im E', -Re E')
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int m = 16 * mi + 4 * g + r, n = 16 * ni + l16;
-            isum[t][r] += er[r] * er[r] + ei[r] * ei[r];
-            if (Ec && m < S && n < S) Ec[m * S + n] = make_float2(ei[r], -er[r]);
-          }
-        }
-      }
-      __syncthreads();   // U is consumed
-    } else {
-      // one 16 x 16 tile: wave w sums columns [w N / 4, (w + 1) N / 4), partials through LDS
-      f4_t er = {0.f, 0.f, 0.f, 0.f}, ei = {0.f, 0.f, 0.f, 0.f};
-      const float* bsrc = a.B1T + r0 + l16;
-      const int ka = w * (N / 4), kb = (w + 1) * (N / 4);
-      for (int k0 = ka; k0 < kb; k0 += 4) {
-        const int col = k0 + g;
-        const float bv = bsrc[col * kTabRows];
-        er = __builtin_amdgcn_mfma_f32_16x16x4f32(Ure[col * P::LDU + l16], bv, er, 0, 0, 0);
-        ei = __builtin_amdgcn_mfma_f32_16x16x4f32(Uim[col * P::LDU + l16], bv, ei, 0, 0, 0);
-      }
-      __syncthreads();   // U is consumed; the partials reuse its space
-      float* part = lds + w * 2 * 256;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int m = 4 * g + r;
-        part[m * 16 + l16] = er[r];
-        part[256 + m * 16 + l16] = ei[r];
-      }
-      __syncthreads();
-      if (tid < 256) {
-        const int m = tid >> 4, n = tid & 15;
-        float sr = 0.f, si = 0.f;
-#pragma unroll
-        for (int ww = 0; ww < 4; ++ww) {
-          sr += lds[ww * 512 + m * 16 + n];
-          si += lds[ww * 512 + 256 + m * 16 + n];
-        }
-        // thread tid keeps element (m, n) = (tid / 16, tid % 16) of the single tile
-        isum[0][0] += sr * sr + si * si;
-        if (Ec && m < S && n < S) Ec[m * S + n] = make_float2(si, -sr);
-      }
-      __syncthreads();
-    }
-  }
-  if (a.I) {
-    float* Ip = a.I + bp.off + (size_t)d * S * S;
-    if (!P::KSPLIT) {
-#pragma unroll
-      for (int t = 0; t < TPW; ++t) {
-        const int tile = w + 4 * t;
-        if (tile < P::T2) {
-          const int mi = tile / MT, ni = tile % MT;
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int m = 16 * mi + 4 * g + r, n = 16 * ni + l16;
-            if (m < S && n < S) Ip[m * S + n] = isum[t][r];
-          }
-        }
-      }
-    } else {
-      const int m = tid >> 4, n = tid & 15;
-      if (m < S && n < S) Ip[m * S + n] = isum[0][0];
-    }
-  }
-  __syncthreads();   // every wave is done with the LDS before the next item
-}
-
-// Tile classes: row tiles of 16, 32, 48, 64; class t serves queues 8 t .. 8 t + 7.
-constexpr int kTileClasses = 4;
-__host__ __device__ constexpr int class_rows(int t) { return 16 * (t + 1); }
-
-// Persistent plane kernel of one tile class (one launch per class, so that each has the
-// registers of its own tile shape).  Workgroup ids are dealt round-robin over the 8 XCDs,
-// so workgroup b serves queue b % 8 of the class: the (emitter, plane) items of the
-// emitters assigned to that queue, in order, so that the planes of one emitter run at the
-// same time on one XCD and its folded pupil is read from that XCD's L2.  A workgroup exits
-// when its queue is exhausted; the grid has at least 8 workgroups, one per queue.
-template <int SP, int BK>
-__global__ void __launch_bounds__(256, 2) batch_planes_kernel(BatchArgs a) {
-  extern __shared__ float lds[];
-  __shared__ long long item;
+// Persistent plane kernel of tile class cls (one launch per class), which serves queues 8 cls
+// .. 8 cls + 7.  Workgroup ids are dealt
+// round-robin over the 8 XCDs, so workgroup b serves queue b % 8 of the class: the (emitter,
+// plane) items of the emitters assigned to that queue, in order, so that the planes of one
+// emitter run at the same time on one XCD and its folded pupil is read from that XCD's L2.
+// The next item is drawn while the current one is computed.  A workgroup exits when its
+// queue is exhausted; the grid has at least 8 workgroups, one per queue.
+template <int N, int SP>
+__global__ void __launch_bounds__((PlaneTile<N, SP>::Cfg::NT), 2) batch_planes_kernel(BatchArgs a, int cls) {
+  extern __shared__ __align__(16) char blds[];
+  __shared__ long long item[2];
   const int tid = threadIdx.x;
-  const int x = 8 * (SP / 16 - 1) + (blockIdx.x & 7);
+  const int x = 8 * cls + (blockIdx.x & 7);
   const int lo = a.qoff[x], hi = a.qoff[x + 1];
   const long long end = a.pre[hi];
-  for (;;) {
-    if (tid == 0) item = (long long)atomicAdd(&a.counter[x], 1ull);
-    __syncthreads();
-    const long long it = item;
-    __syncthreads();
+  if (tid == 0) item[0] = (long long)atomicAdd(&a.counter[x], 1ull);
+  __syncthreads();
+  for (int turn = 0;; turn ^= 1) {
+    const long long it = item[turn];
     if (it >= end) break;
+    long long next = 0;
+    if (tid == 0) next = (long long)atomicAdd(&a.counter[x], 1ull);
     // emitter e of the queue with pre[e] <= it < pre[e + 1]
     int e0 = lo, e1 = hi - 1;
     while (e0 < e1) {
@@ -641,32 +393,26 @@ __global__ void __launch_bounds__(256, 2) batch_planes_kernel(BatchArgs a) {
     const int slot = a.list[e0];
     const int d = (int)(it - a.pre[e0]);
     const BatchParam bp = a.params[slot];
-    if constexpr (SP == 32 || SP == 64)
-      batch_plane32<SP, BK>(a, bp, slot, d, lds, tid);
-    else
-      batch_plane16<SP, BK>(a, bp, slot, d, lds, tid);
+    batch_plane<N, SP>(a, bp, slot, d, blds, tid);
+    if (tid == 0) item[turn ^ 1] = next;   // read after the barriers of the next plane, or below
+    __syncthreads();
   }
 }
 
-// LDS of a class: the 32 x 32 tiles (SP = 32, 64) hold U of a 64-row tile (or the two
-// stage buffers, if larger); the 16 x 16 tiles size it for their own rows
-template <int SP, int BK>
-constexpr int plane_lds_bytes() {
-  return (SP == 32 || SP == 64) ? ((2 * 128 * 65 > 2 * BK * (68 + 2 * 132)) ? 2 * 128 * 65 : 2 * BK * (68 + 2 * 132)) * 4
-                                : PlaneTile<SP, BK>::LDS_FLOATS * 4;
+// Every pupil size and tile class its own instantiation, indexed [N / 32 - 1][class].
+typedef void (*PlaneKernel)(BatchArgs, int);
+struct PlaneLaunch {
+  PlaneKernel k;
+  int threads, lds;
+};
+template <int N, int SP>
+static PlaneLaunch plane_launch() {
+  return PlaneLaunch{batch_planes_kernel<N, SP>, PlaneTile<N, SP>::Cfg::NT, PlaneTile<N, SP>::LDS_BYTES};
 }
-
-// every (tile class, k-stage) instantiation, indexed [class][k-stage index] (BK = 8, 16)
-typedef void (*PlaneKernel)(BatchArgs);
-static const PlaneKernel kPlaneKernels[kTileClasses][2] = {
-    {batch_planes_kernel<16, 8>, batch_planes_kernel<16, 16>},
-    {batch_planes_kernel<32, 8>, batch_planes_kernel<32, 16>},
-    {batch_planes_kernel<48, 8>, batch_planes_kernel<48, 16>},
-    {batch_planes_kernel<64, 8>, batch_planes_kernel<64, 16>}};
-static const int kPlaneLds[kTileClasses][2] = {{plane_lds_bytes<16, 8>(), plane_lds_bytes<16, 16>()},
-                                               {plane_lds_bytes<32, 8>(), plane_lds_bytes<32, 16>()},
-                                               {plane_lds_bytes<48, 8>(), plane_lds_bytes<48, 16>()},
-                                               {plane_lds_bytes<64, 8>(), plane_lds_bytes<64, 16>()}};
+static const PlaneLaunch kPlanes[4][2] = {{plane_launch<32, 32>(), plane_launch<32, 64>()},
+                                          {plane_launch<64, 32>(), plane_launch<64, 64>()},
+                                          {plane_launch<96, 32>(), plane_launch<96, 64>()},
+                                          {plane_launch<128, 32>(), plane_launch<128, 64>()}};
 
 }  // namespace rw
 
@@ -674,7 +420,9 @@ static const int kPlaneLds[kTileClasses][2] = {{plane_lds_bytes<16, 8>(), plane_
 // Host side
 // ---------------------------------------------------------------------------
 namespace rw {
-// each crop bucket on its own tile class, k-stages of 16, two workgroups per CU
+// each crop bucket on its own tile class, two workgroups per CU.  k_stage (8 or 16) is part of
+// the configuration and of saved plans; the matrix instruction takes 16 pupil rows at once, so
+// both run the same kernel.
 static rwpsf_batch_config default_config() {
   rwpsf_batch_config c{};
   c.wg_per_cu = 2;
@@ -707,19 +455,17 @@ struct rwpsf_batch {
   float2* d_Q = nullptr;
   double* d_ksz = nullptr;
   double4* d_gl = nullptr;      // [N*N] Gibson-Lanni phase tables, or null
-  float* d_A2T = nullptr;       // [N][96] folded x table (prefactor included)
-  float* d_B1T = nullptr;       // [N][96] folded y table
+  uint4* d_tab = nullptr;       // folded DFT table of both axes, a split-f16 panel of 96 rows
+  float tscale = 1.f, escale = 1.f;
   float2* d_pf = nullptr;       // [max][3][N][N] folded pupils
   long long items = 0;          // (emitter, plane) items of the staged call
-  long long class_items[4] = {0, 0, 0, 0};   // of them, in the 16-, 32-, 48- and 64-row tile classes
-  int class_grid[4] = {0, 0, 0, 0};          // persistent grid of each class (0 = class not launched)
+  long long class_items[rw::kTileClasses] = {};   // of them, in the 32- and 64-row tile classes
+  int class_grid[rw::kTileClasses] = {};          // persistent grid of each class (0 = class not launched)
   float* d_basis = nullptr;
-  float* d_phi = nullptr;
-  char* d_upload = nullptr;     // params [max] then coefT [32][max_pad]
+  char* d_upload = nullptr;     // see off_coef() and the others
   unsigned long long* d_counter = nullptr;   // [8] queue counters
   char* h_staging = nullptr;    // pinned mirror of d_upload
   size_t upload_bytes = 0;
-  int max_pad = 0;
   hipEvent_t upload_done = nullptr;
   bool upload_pending = false;
   rwpsf_batch_config cfg = rw::default_config();
@@ -730,7 +476,7 @@ struct rwpsf_batch {
     void* I = nullptr;
     void* E = nullptr;
     rwpsf_batch_config cfg{};
-    int grid[4] = {0, 0, 0, 0};   // the captured launches: a replay must launch the same classes
+    int grid[rw::kTileClasses] = {};   // the captured launches: a replay must launch the same classes
     hipStream_t st = nullptr;
   } gkey;
   ~rwpsf_batch() {   // teardown: failures cannot be reported and are ignored
@@ -772,9 +518,9 @@ static int balloc(rwpsf_batch* b, T** p, size_t count) {
   return RWPSF_OK;
 }
 
-// Upload block: params [max] | coefT [32][max_pad] | list [max] | pre [max + 1] | qoff [17]
+// Upload block: params [max] | coef [max][23] | list [max] | pre [max + 1] | qoff [17]
 static size_t off_coef(const rwpsf_batch* b) { return sizeof(BatchParam) * b->max_emitters; }
-static size_t off_list(const rwpsf_batch* b) { return off_coef(b) + sizeof(float) * kBasisRows * b->max_pad; }
+static size_t off_list(const rwpsf_batch* b) { return off_coef(b) + sizeof(float) * kBasisRows * b->max_emitters; }
 static size_t off_pre(const rwpsf_batch* b) {
   return (off_list(b) + sizeof(int) * b->max_emitters + 7) / 8 * 8;
 }
@@ -789,11 +535,12 @@ static void batch_stage(rwpsf_batch* b, int n, const rwpsf_emitter* e) {
   for (int i = 0; i < n; ++i) off[i + 1] = off[i] + (long long)e[i].planes * e[i].crop * e[i].crop;
   std::vector<int> order(n);
   std::iota(order.begin(), order.end(), 0);
-  auto sp_of = [&](int i) { return b->cfg.tile_rows[(e[i].crop - 1) / 16]; };
+  // tile rows of 16 and 48 run on the next larger tile
+  auto sp_of = [&](int i) { return b->cfg.tile_rows[(e[i].crop - 1) / 16] > 32 ? 64 : 32; };
   auto cost = [&](int i) { return (double)e[i].planes * sp_of(i) * (b->N + sp_of(i)); };
   std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return cost(x) > cost(y); });
   BatchParam* prm = (BatchParam*)b->h_staging;
-  float* coefT = (float*)(b->h_staging + off_coef(b));
+  float* coef = (float*)(b->h_staging + off_coef(b));
   for (int slot = 0; slot < n; ++slot) {
     const int i = order[slot];
     prm[slot].zoff = -e[i].z_nm;
@@ -803,20 +550,17 @@ static void batch_stage(rwpsf_batch* b, int n, const rwpsf_emitter* e) {
     prm[slot].D = e[i].planes;
     prm[slot].SP = sp_of(i);
     prm[slot].pad = 0;
-    for (int q = 0; q < kBasisRows; ++q) {
-      double v = 0.0;
-      if (q < RWPSF_BATCH_MAX_ZERNIKE) v = e[i].zernike_waves[q];
-      else if (q == RWPSF_BATCH_MAX_ZERNIKE) v = -b->k * e[i].x0_nm;
-      else if (q == RWPSF_BATCH_MAX_ZERNIKE + 1) v = -b->k * e[i].y0_nm;
-      coefT[(size_t)q * b->max_pad + slot] = (float)v;
-    }
+    float* cf = coef + (size_t)slot * kBasisRows;
+    for (int q = 0; q < RWPSF_BATCH_MAX_ZERNIKE; ++q) cf[q] = (float)e[i].zernike_waves[q];
+    cf[RWPSF_BATCH_MAX_ZERNIKE] = (float)(-b->k * e[i].x0_nm);
+    cf[RWPSF_BATCH_MAX_ZERNIKE + 1] = (float)(-b->k * e[i].y0_nm);
   }
   std::vector<int> queue(n);
   double load[kQueues] = {};
   int count[kQueues] = {};
   for (int t = 0; t < kTileClasses; ++t) b->class_items[t] = 0;
   for (int slot = 0; slot < n; ++slot) {
-    const int t = prm[slot].SP / 16 - 1;
+    const int t = prm[slot].SP > 32;
     const int x = 8 * t + (int)(std::min_element(load + 8 * t, load + 8 * t + 8) - (load + 8 * t));
     queue[slot] = x;
     load[x] += cost(order[slot]);
@@ -855,45 +599,43 @@ static int batch_upload(rwpsf_batch* b, hipStream_t st) {
   return RWPSF_OK;
 }
 
-// The kernels of one call (they read the uploaded block in stream order): queue reset,
-// phase GEMM, fold, one persistent launch per tile class.  This is what a graph captures.
+// The kernels of one call (they read the uploaded block in stream order): the fold, which also
+// resets the queues, and one persistent launch per tile class.  This is what a graph captures.
 static int batch_kernels(rwpsf_batch* b, int n, float* I, float2* E, hipStream_t st) {
   int rc;
-  const long long* d_pre = (const long long*)(b->d_upload + off_pre(b));
-  const int* d_qoff = (const int*)(b->d_upload + off_qoff(b));
-  hipLaunchKernelGGL(batch_reset_kernel, dim3(1), dim3(64), 0, st, b->d_counter, d_pre, d_qoff);
-  if ((rc = hip_check(hipGetLastError()))) return rc;
-  const float* coefT = (const float*)(b->d_upload + off_coef(b));
-  const int NN = b->N * b->N;
-  if ((rc = hip_check(launch_rgemm(coefT, b->max_pad, b->d_basis, NN, b->d_phi, NN, n, NN, kBasisRows, st))))
-    return rc;
   BatchArgs a{};
   a.params = (const BatchParam*)b->d_upload;
   a.Q = b->d_Q;
   a.ksz = b->d_ksz;
-  a.phi = b->d_phi;
+  a.coef = (const float*)(b->d_upload + off_coef(b));
+  a.basis = b->d_basis;
   a.gl = b->d_gl;
-  a.A2T = b->d_A2T;
-  a.B1T = b->d_B1T;
+  a.tab = b->d_tab;
+  a.tscale = b->tscale;
+  a.escale = b->escale;
   a.Pf = b->d_pf;
   a.list = (const int*)(b->d_upload + off_list(b));
-  a.pre = d_pre;
-  a.qoff = d_qoff;
+  a.pre = (const long long*)(b->d_upload + off_pre(b));
+  a.qoff = (const int*)(b->d_upload + off_qoff(b));
   a.I = I;
   a.E = E;
   a.counter = b->d_counter;
   a.n = n;
   a.N = b->N;
   a.pitch = b->pitch;
-  hipLaunchKernelGGL(batch_fold_kernel, dim3(n), dim3(256), 0, st, a);
+  // as many emitters per workgroup as leave four workgroups for each CU: the tables of a cell
+  // (116 floats) are read once per group
+  const int cells = b->N * b->N / 4 / 256;
+  a.group = (int)std::min<long long>(16, std::max<long long>(1, (long long)n * cells / (4 * b->num_cus)));
+  hipLaunchKernelGGL(batch_fold_kernel, dim3(cells * ((n + a.group - 1) / a.group)), dim3(256), 0, st, a);
   if ((rc = hip_check(hipGetLastError()))) return rc;
   // one launch per tile class, the tall tiles first; at least one workgroup per queue and
   // no more than the configured residency
   for (int t = kTileClasses - 1; t >= 0; --t) {
     const int grid = b->class_grid[t];
     if (grid == 0) continue;
-    const int ki = b->cfg.k_stage[t] == 8 ? 0 : 1;
-    hipLaunchKernelGGL(kPlaneKernels[t][ki], dim3(grid), dim3(256), kPlaneLds[t][ki], st, a);
+    const PlaneLaunch& pl = kPlanes[b->N / 32 - 1][t];
+    hipLaunchKernelGGL(pl.k, dim3(grid), dim3(pl.threads), pl.lds, st, a, t);
     if ((rc = hip_check(hipGetLastError()))) return rc;
   }
   return RWPSF_OK;
@@ -954,6 +696,7 @@ int rwpsf_batch_create(const rwpsf_optics* o, int n_pupil, double pixel_nm, doub
   std::vector<float2> Q(3 * NN, make_float2(0.f, 0.f));
   std::vector<double> ksz(NN, 0.0);
   std::vector<double4> gl(o->gibson_lanni ? NN : 0, make_double4(0.0, 0.0, 0.0, 0.0));
+  std::vector<double> bound(o->gibson_lanni ? NN : 0, 1.0);   // largest amplitude of the layer's factor per cell
   GLParams glp{};
   glp.k0 = kTwoPi / o->wavelength_nm;
   glp.n_i = o->n_i;
@@ -966,6 +709,8 @@ int rwpsf_batch_create(const rwpsf_optics* o, int n_pupil, double pixel_nm, doub
   glp.t_i_d = o->t_i_design_nm;
   std::vector<float> basis((size_t)kBasisRows * NN, 0.f);
   const double ds = 2.0 * b->s_max / N;
+  int pref_exp = 0;   // Q carries the mantissa of the prefactor, escale its power of two
+  const double pref = std::frexp(o->focal_length * b->k / kTwoPi, &pref_exp);
   for (int j = 0; j < N; ++j)
     for (int l = 0; l < N; ++l) {
       const long u = 2L * j + 1 - N, v = 2L * l + 1 - N;
@@ -980,7 +725,7 @@ int rwpsf_batch_create(const rwpsf_optics* o, int n_pupil, double pixel_nm, doub
       if (u * u + v * v > (long)N * N) continue;
       std::complex<double> e[3];
       base_pupil_cell(*o, 3, ds, sx, sy, e);
-      for (int c = 0; c < 3; ++c) Q[c * NN + cell] = make_float2((float)e[c].real(), (float)e[c].imag());
+      for (int c = 0; c < 3; ++c) Q[c * NN + cell] = make_float2((float)(pref * e[c].real()), (float)(pref * e[c].imag()));
       ksz[cell] = b->k * std::sqrt(1.0 - (sx * sx + sy * sy));
       if (o->gibson_lanni) {
         // the phase is affine in t_s (t_i is affine in it and each layer's term is linear
@@ -990,30 +735,21 @@ int rwpsf_batch_create(const rwpsf_optics* o, int n_pupil, double pixel_nm, doub
         gl_opd(glp, 0.0, sin_t, &r0, &i0);
         gl_opd(glp, T, sin_t, &r1, &i1);
         gl[cell] = make_double4(r0, i0, (r1 - r0) / T, (i1 - i0) / T);
+        // the decay exp(-(i0 + t_s slope)) is largest at t_s = 0 (the slope is not negative)
+        bound[cell] = std::exp(std::min(std::max(0.0, -i0), 600.0));
       }
     }
-  // folded DFT tables: row 2jf + p holds cos (p = 0) or sin (p = 1) of k s[jf] x_r,
-  // x_r = (r - 32) pixel; the x table carries the prefactor f k / 2 pi (E = -i E')
-  std::vector<float> A2T((size_t)N * kTabRows), B1T((size_t)N * kTabRows);
-  const double pref = o->focal_length * b->k / kTwoPi;
-  for (int jf = 0; jf < N / 2; ++jf) {
-    const double s = (2.0 * jf + 1.0 - N) * b->s_max / N;
-    for (int r = 0; r < kTabRows; ++r) {
-      const double ph = b->k * s * (r - 32) * pixel_nm;
-      A2T[(size_t)(2 * jf) * kTabRows + r] = (float)(pref * std::cos(ph));
-      A2T[(size_t)(2 * jf + 1) * kTabRows + r] = (float)(pref * std::sin(ph));
-      B1T[(size_t)(2 * jf) * kTabRows + r] = (float)std::cos(ph);
-      B1T[(size_t)(2 * jf + 1) * kTabRows + r] = (float)std::sin(ph);
-    }
-  }
-  b->max_pad = (max_emitters + 63) / 64 * 64;
+  const PupilScales ps = pupil_scales(Q, 3, N, N, bound.empty() ? nullptr : bound.data(), pref_exp);
+  b->tscale = ps.tscale;
+  b->escale = ps.escale;
+  for (float2& q : Q) q = make_float2(std::ldexp(q.x, ps.pf_exp), std::ldexp(q.y, ps.pf_exp));
   b->upload_bytes = upload_size(b);
   int rc;
   if ((rc = balloc(b, &b->d_Q, 3 * NN)) || (rc = balloc(b, &b->d_ksz, NN)) ||
-      (rc = balloc(b, &b->d_A2T, (size_t)N * kTabRows)) || (rc = balloc(b, &b->d_B1T, (size_t)N * kTabRows)) ||
+      (rc = balloc(b, &b->d_tab, hg_panel_bytes(N, kTabRows) / sizeof(uint4))) ||
       (rc = balloc(b, &b->d_pf, (size_t)max_emitters * 3 * NN)) ||
       (rc = balloc(b, &b->d_basis, (size_t)kBasisRows * NN)) ||
-      (rc = balloc(b, &b->d_phi, (size_t)max_emitters * NN)) || (rc = balloc(b, &b->d_upload, b->upload_bytes)) ||
+      (rc = balloc(b, &b->d_upload, b->upload_bytes)) ||
       (rc = balloc(b, &b->d_counter, kQueues)) || (o->gibson_lanni && (rc = balloc(b, &b->d_gl, NN)))) {
     delete b;
     return rc;
@@ -1027,8 +763,8 @@ int rwpsf_batch_create(const rwpsf_optics* o, int n_pupil, double pixel_nm, doub
   if ((rc = hip_check(hipEventCreateWithFlags(&b->upload_done, hipEventDisableTiming))) ||
       (rc = hip_check(hipMemcpy(b->d_Q, Q.data(), Q.size() * sizeof(float2), hipMemcpyHostToDevice))) ||
       (rc = hip_check(hipMemcpy(b->d_ksz, ksz.data(), ksz.size() * sizeof(double), hipMemcpyHostToDevice))) ||
-      (rc = hip_check(hipMemcpy(b->d_A2T, A2T.data(), A2T.size() * sizeof(float), hipMemcpyHostToDevice))) ||
-      (rc = hip_check(hipMemcpy(b->d_B1T, B1T.data(), B1T.size() * sizeof(float), hipMemcpyHostToDevice))) ||
+      // (pixel r of the table at (r - 32) pixel: 64 "pixels" centred on row 32, and 32 more)
+      (rc = hip_check(launch_dft_panel(b->d_tab, kTabRows, kTabRows, 32, N, N, b->k, b->s_max, pixel_nm, nullptr))) ||
       (o->gibson_lanni &&
        (rc = hip_check(hipMemcpy(b->d_gl, gl.data(), gl.size() * sizeof(double4), hipMemcpyHostToDevice)))) ||
       (rc = hip_check(hipMemcpy(b->d_basis, basis.data(), basis.size() * sizeof(float), hipMemcpyHostToDevice))) ||
@@ -1037,13 +773,13 @@ int rwpsf_batch_create(const rwpsf_optics* o, int n_pupil, double pixel_nm, doub
     delete b;
     return rc;
   }
-  for (int t = 0; t < kTileClasses; ++t)
-    for (int k = 0; k < 2; ++k)
-      if ((rc = hip_check(hipFuncSetAttribute((const void*)kPlaneKernels[t][k],
-                                              hipFuncAttributeMaxDynamicSharedMemorySize, kPlaneLds[t][k])))) {
-        delete b;
-        return rc;
-      }
+  for (int t = 0; t < 2; ++t) {
+    const PlaneLaunch& pl = kPlanes[N / 32 - 1][t];
+    if ((rc = hip_check(hipFuncSetAttribute((const void*)pl.k, hipFuncAttributeMaxDynamicSharedMemorySize, pl.lds)))) {
+      delete b;
+      return rc;
+    }
+  }
   *out = b;
   return RWPSF_OK;
 }
@@ -1251,8 +987,7 @@ int rwpsf_batch_autotune(rwpsf_batch* b, int n, const rwpsf_emitter* e, float* I
     return rc;
   }
   // coordinate search from the default: workgroups per CU, then for each crop bucket the
-  // taller tile classes it could share (fewer, fuller launches against more padding),
-  // then the k-stage of each class in use
+  // taller tile classes it could share (fewer, fuller launches against more padding)
   rwpsf_batch_config best = default_config();
   float best_t = 1e30f;
   auto consider = [&](const rwpsf_batch_config& c) {
@@ -1281,14 +1016,6 @@ int rwpsf_batch_autotune(rwpsf_batch* b, int n, const rwpsf_emitter* e, float* I
       c.tile_rows[q] = rows;
       rc = consider(c);
     }
-  }
-  for (int t = 0; t < kTileClasses && !rc; ++t) {
-    bool in_use = false;
-    for (int q = 0; q < 4; ++q) in_use = in_use || (used[q] && best.tile_rows[q] == class_rows(t));
-    if (!in_use) continue;
-    rwpsf_batch_config c = best;
-    c.k_stage[t] = best.k_stage[t] == 16 ? 8 : 16;
-    rc = consider(c);
   }
   (void)hipEventDestroy(t0);
   (void)hipEventDestroy(t1);

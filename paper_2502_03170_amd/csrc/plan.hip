@@ -4,13 +4,14 @@
 //   s_x[j] = (2j + 1 - N) s_max / N,  s_y[l] likewise,  cell area ds^2 = (2 s_max / N)^2,
 // disk mask (2j+1-N)^2 + (2l+1-N)^2 <= N^2 decided in integers:
 //   Q_c[j,l]  = ds^2 a(s) e_inf,c(s) / s_z          (complex64, 0 outside the disk;
-//               one channel ds^2 a(s) / s_z for the scalar model, Sec. 3.2)
+//               one channel ds^2 a(s) / s_z for the scalar model, Sec. 3.2; in the Fourier
+//               form times the mantissa of the prefactor f k / 2 pi and a power of two)
 //   ksz[j,l]  = k s_z                                (FP64, for the defocus phase)
 // and of the folded transforms (jf, lf < nh = ceil(N/2), the mirror-symmetric half):
 //   kszf[jf,lf]   = k s_z                            (FP64)
 //   B1[n][2lf]    = cos(k s_y[lf] y_n),  B1[n][2lf+1] = sin(k s_y[lf] y_n)
 //   A2[m][2jf]    = cos(k s_x[jf] x_m),  A2[m][2jf+1] = sin(k s_x[jf] x_m)
-// (split-f16 panels; the prefactor f k / 2 pi is applied with the operand scales)
+// (split-f16 panels)
 // with x_m = (m - nx/2) dx, y_n = (n - ny/2) dy.
 #include <algorithm>
 #include <cmath>
@@ -26,24 +27,21 @@ namespace rw {
 
 int bessel_plan_init(rwpsf_plan* p);
 
-// Power-of-two scales of the Fourier GEMMs' operands.  Q is scaled in place so that no
-// folded pupil value (a sum over up to four mirrors, each of unit phase factor) exceeds
-// 2^10, and T = Pf B1, bounded by the largest row sum of |Pf|, is brought under 2^15: f16
-// halves then neither overflow nor, down to 2^-13 (Pf) or 2^-18 (T) of the bounds, lose
-// bits to subnormal halves.
-static void fourier_scales(rwpsf_plan* p, std::vector<float2>& Q) {
-  const int N = p->num.n_pupil, np = p->np, nh = (N + 1) / 2;
+// Power-of-two scales of the split-f16 GEMMs' operands (rw_fourier.h).
+PupilScales pupil_scales(const std::vector<float2>& Q, int nc, int N, int np, const double* amplitude, int pref_exp) {
+  const int nh = (N + 1) / 2;
   const size_t npp = (size_t)np * np;
   double cell_max = 0.0, row_max = 0.0;
-  for (int c = 0; c < p->nc; ++c)
+  for (int c = 0; c < nc; ++c)
     for (int jf = 0; jf < nh; ++jf) {
       double row = 0.0;
       for (int lf = 0; lf < nh; ++lf) {
         double m = 0.0;
         for (int j : {jf, N - 1 - jf})
           for (int l : {lf, N - 1 - lf}) {
-            const float2 q = Q[c * npp + (size_t)j * np + l];
-            m += std::fabs((double)q.x) + std::fabs((double)q.y);
+            const size_t cell = (size_t)j * np + l;
+            const float2 q = Q[c * npp + cell];
+            m += (std::fabs((double)q.x) + std::fabs((double)q.y)) * (amplitude ? amplitude[cell] : 1.0);
           }
         cell_max = std::max(cell_max, m);
         row += 2.0 * m;
@@ -53,11 +51,12 @@ static void fourier_scales(rwpsf_plan* p, std::vector<float2>& Q) {
   int ec = 0, er = 0;   // cell_max < 2^ec, row_max < 2^er
   std::frexp(cell_max, &ec);
   std::frexp(row_max, &er);
-  p->pf_exp = cell_max > 0.0 ? 10 - ec : 0;
-  const int t_exp = row_max > 0.0 ? 15 - (er + p->pf_exp + kTabExp) : 0;
-  p->tscale = (float)std::ldexp(1.0, t_exp);
-  p->escale = (float)std::ldexp(p->opt.focal_length * p->k / kTwoPi, -(p->pf_exp + 2 * kTabExp + t_exp));
-  for (float2& q : Q) q = make_float2(std::ldexp(q.x, p->pf_exp), std::ldexp(q.y, p->pf_exp));
+  PupilScales s;
+  s.pf_exp = cell_max > 0.0 ? 10 - ec : 0;
+  const int t_exp = row_max > 0.0 ? 15 - (er + s.pf_exp + kTabExp) : 0;
+  s.tscale = (float)std::ldexp(1.0, t_exp);
+  s.escale = (float)std::ldexp(1.0, pref_exp - (s.pf_exp + 2 * kTabExp + t_exp));
+  return s;
 }
 
 static int fourier_plan_init(rwpsf_plan* p) {
@@ -71,6 +70,12 @@ static int fourier_plan_init(rwpsf_plan* p) {
   std::vector<float2> Q(3 * npp, make_float2(0.f, 0.f));
   std::vector<double> ksz(npp, 0.0);
   const double ds = 2.0 * s_max / N;
+  // The Fourier form's Q carries the mantissa of the prefactor f k / 2 pi (its power of two is
+  // applied with the operand scales): a factor on the fields, rounded to FP32 by itself, would
+  // put one common relative error on all of them.
+  int pref_exp = 0;
+  const bool folded = p->num.form == RWPSF_FORM_FOURIER;
+  const double pref = folded ? std::frexp(p->opt.focal_length * k / kTwoPi, &pref_exp) : 1.0;
   for (int j = 0; j < N; ++j)
     for (int l = 0; l < N; ++l) {
       const long u = 2L * j + 1 - N, v = 2L * l + 1 - N;
@@ -79,7 +84,7 @@ static int fourier_plan_init(rwpsf_plan* p) {
       const double sx = u * s_max / N, sy = v * s_max / N;
       std::complex<double> e[3];
       base_pupil_cell(p->opt, p->nc, ds, sx, sy, e);
-      for (int c = 0; c < p->nc; ++c) Q[c * npp + cell] = make_float2((float)e[c].real(), (float)e[c].imag());
+      for (int c = 0; c < p->nc; ++c) Q[c * npp + cell] = make_float2((float)(pref * e[c].real()), (float)(pref * e[c].imag()));
       ksz[cell] = k * std::sqrt(1.0 - (sx * sx + sy * sy));
     }
   const int nh = (N + 1) / 2, nhp = round_up(nh, kFoldPad), w = 2 * nhp;
@@ -87,7 +92,13 @@ static int fourier_plan_init(rwpsf_plan* p) {
   std::vector<double> kszf((size_t)nhp * nhp, 0.0);
   for (int jf = 0; jf < nh; ++jf)
     for (int lf = 0; lf < nh; ++lf) kszf[(size_t)jf * nhp + lf] = ksz[(size_t)jf * np + lf];
-  if (p->num.form == RWPSF_FORM_FOURIER) fourier_scales(p, Q);
+  if (folded) {
+    const PupilScales ps = pupil_scales(Q, p->nc, N, np, nullptr, pref_exp);
+    p->pf_exp = ps.pf_exp;
+    p->tscale = ps.tscale;
+    p->escale = ps.escale;
+    for (float2& q : Q) q = make_float2(std::ldexp(q.x, ps.pf_exp), std::ldexp(q.y, ps.pf_exp));
+  }
   int st;
   if ((st = dev_alloc(p, &p->d_Q, 3 * npp))) return st;
   if ((st = dev_alloc(p, &p->d_ksz, npp))) return st;
@@ -109,8 +120,8 @@ static int fourier_plan_init(rwpsf_plan* p) {
   if ((st = hip_check(hipMemcpy(p->d_Q, Q.data(), Q.size() * sizeof(float2), hipMemcpyHostToDevice)))) return st;
   if ((st = hip_check(hipMemcpy(p->d_ksz, ksz.data(), ksz.size() * sizeof(double), hipMemcpyHostToDevice)))) return st;
   if ((st = hip_check(hipMemcpy(p->d_kszf, kszf.data(), kszf.size() * sizeof(double), hipMemcpyHostToDevice)))) return st;
-  if ((st = hip_check(launch_dft_panel(p->d_B1, nyp, ny, N, w, k, s_max, p->grid.dy_nm, 0)))) return st;
-  if ((st = hip_check(launch_dft_panel(p->d_A2, nxp, nx, N, w, k, s_max, p->grid.dx_nm, 0)))) return st;
+  if ((st = hip_check(launch_dft_panel(p->d_B1, nyp, ny, ny / 2, N, w, k, s_max, p->grid.dy_nm, 0)))) return st;
+  if ((st = hip_check(launch_dft_panel(p->d_A2, nxp, nx, nx / 2, N, w, k, s_max, p->grid.dx_nm, 0)))) return st;
   if ((st = hip_check(hipMemcpy(p->d_z, p->z.data(), p->z.size() * sizeof(double), hipMemcpyHostToDevice)))) return st;
   if ((st = hip_check(launch_zernike_table(p->d_ztab, N, RWPSF_MAX_ZERNIKE, 0)))) return st;
   if ((st = hip_check(fourier_kernel_attributes()))) return st;

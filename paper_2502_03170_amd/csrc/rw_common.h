@@ -169,7 +169,7 @@ struct rwpsf_plan {
   uint4* d_A2 = nullptr;        // split-f16 panel of nxp rows m, k = 2jf + p: cos / sin (k s_x[jf] x_m)
   int pf_exp = 0;               // Q and the folded pupils carry 2^pf_exp (Fourier form)
   float tscale = 1.f;           // power of two that T is multiplied by when it is written
-  float escale = 1.f;           // fields per unit of the image GEMM's accumulators
+  float escale = 1.f;           // power of two: fields per unit of the image GEMM's accumulators
   float* d_ztab = nullptr;      // [RWPSF_MAX_ZERNIKE][N][N] Noll basis on the pupil cells
   float2* d_P = nullptr;        // workspace [chunk][3][np][np]
   float2* d_Pf = nullptr;       // workspace [chunk][3][2 nhp][2 nhp] folded pupils

@@ -32,10 +32,21 @@ static_assert(sizeof(PupilArgs) <= 4000, "kernel arguments are passed by value (
 // to 128, nyp = ny rounded up to 128 (64 for axes of at most 64 pixels), and the folded pupil axis nh = ceil(n/2) to
 // nhp = nh rounded up to 32 (so 2 nhp = np).
 
-// Operands of the two GEMMs are split-f16 panels (hgemm.h).  Their power-of-two scales
-// (fourier_scales) keep the halves in range: Pf carries 2^pf_exp (through Q), the tables
-// 2^kTabExp, and T is rescaled by tscale when it is written.
+// Operands of the two GEMMs are split in f16 halves (hgemm.h).  Their power-of-two scales
+// keep the halves in range: Q, and with it the folded pupils, carries 2^pf_exp, so that no
+// folded value (a sum over up to four mirrors, each of unit phase factor times the given
+// largest amplitude of the cell) exceeds 2^10; the DFT tables carry 2^kTabExp; T = Pf B1,
+// bounded by the largest row sum of |Pf|, is multiplied by tscale to stay under 2^15 when it
+// is split.  The halves then neither overflow nor, down to 2^-13 (Pf) or 2^-18 (T) of the
+// bounds, lose bits to subnormal halves.  escale, a power of two, turns the image GEMM's sums
+// into fields.
 constexpr int kTabExp = 6;
+struct PupilScales {
+  int pf_exp;
+  float tscale, escale;
+};
+// Q [nc][np][np] on the N x N cells, with the prefactor's mantissa; amplitude [np][np] or null
+PupilScales pupil_scales(const std::vector<float2>& Q, int nc, int N, int np, const double* amplitude, int pref_exp);
 
 struct Gemm1Args {
   const float2* Pf;    // [nstk][nc][2 nhp][2 nhp]
@@ -53,7 +64,7 @@ struct Gemm2Args {
   const uint4* T;      // [nstk][nzs][nc] panels of 2 nyp rows 2n + ri, k = q
   float2* E;           // [stacks][nz][nc][nx][ny] or null
   float* I;            // [stacks][nz][nx][ny] or null
-  float escale;        // prefactor f k / 2 pi over the operand scales
+  float escale;        // power of two: the prefactor's over the operand scales
   int vec;             // E and I rows allow 16- and 8-byte stores (ny even, aligned outputs)
   int nhp, nxp, nyp, nx, ny, nz, nstk, s_base, z0, nzs, nc;
 };
@@ -64,10 +75,10 @@ constexpr int kPadPupil = 64, kPadX = 128, kPadY = 128, kFoldPad = 32, kPadSmall
 inline int pad_axis(int n) { return n <= kPadSmall ? kPadSmall : round_up(n, kPadX); }
 
 hipError_t launch_zernike_table(float* out, int n, int nj, hipStream_t st);
-// DFT table of `count` output pixels (pixel r at (r - count / 2) pitch) as a split-f16 panel
+// DFT table of `count` output pixels (pixel r at (r - centre) pitch) as a split-f16 panel
 // of `rows` rows, k = 2f + p: 2^kTabExp {cos, sin}(wavenumber s_f x_r), zero past count and n
-hipError_t launch_dft_panel(uint4* panel, int rows, int count, int n, int w, double wavenumber, double s_max,
-                            double pitch, hipStream_t st);
+hipError_t launch_dft_panel(uint4* panel, int rows, int count, int centre, int n, int w, double wavenumber,
+                            double s_max, double pitch, hipStream_t st);
 hipError_t launch_pupil_build(const PupilArgs& a, const float2* Q, const float* ztab, float2* P,
                               hipStream_t st);
 // Pf [nstk][nc][2 nhp][2 nhp] of the stacks of a (its np field is the stride of Q)
