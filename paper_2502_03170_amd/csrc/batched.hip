@@ -71,12 +71,6 @@ struct BatchArgs {
   double pitch;
 };
 
-// A phase reduced to half turns in [-1, 1].
-__device__ __forceinline__ float turns(double phase) {
-  const double t = phase * (1.0 / kTwoPi);
-  return (float)(2.0 * (t - rint(t)));
-}
-
 // Folded pupil of every emitter.  The pupil and pixel grids are mirror-symmetric
 // (s[N-1-j] = -s[j]); with P = Q_c exp(i Phi) at the four mirror cells of (jf, lf),
 //   Pf_{pj,pl}[jf][lf] = i^(pj+pl) sum_{a,b} (-1)^(a pj + b pl) P[mir_a(jf)][mir_b(lf)],
@@ -130,13 +124,13 @@ __global__ void __launch_bounds__(256) batch_fold_kernel(BatchArgs a) {
         const double wr = ts * g[q].z + g[q].x, wi = ts * g[q].w + g[q].y;
         const float amp = (float)exp(-wi);
         float sn, cs;
-        sincospif(turns(wr + (double)phi[q]), &sn, &cs);
+        sincospif(half_turns(wr + (double)phi[q]), &sn, &cs);
         er[q] = amp * cs;
         ei[q] = amp * sn;
       }
     } else {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) sincospif(turns((double)phi[q]), &ei[q], &er[q]);
+      for (int q = 0; q < 4; ++q) sincospif(half_turns((double)phi[q]), &ei[q], &er[q]);
     }
     float2* Pf = a.Pf + (size_t)slot * 3 * NN;
 #pragma unroll

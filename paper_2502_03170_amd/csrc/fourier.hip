@@ -9,7 +9,7 @@
 // separable transform becomes two real GEMMs with half the flops of the complex matrix DFT,
 // run on the F16 matrix cores with split operands at FP32-level accuracy (hgemm.h):
 //   K1  pupil_build_folded   mirror-folded pupils Pf (four parities per folded cell)
-//                     of up to 8 stacks, each cell's P_c formed on the way (FP64
+//                     of up to 16 stacks, each cell's P_c formed on the way (FP64
 //                     phase: Gibson-Lanni, Zernike, free phase map, lateral emitter
 //                     shift); the chirp-z and adjoint paths take the unfolded P_c of
 //                     pupil_build
@@ -17,6 +17,8 @@
 //                     pupil tile is staged (FP64 phase, reduced mod 2 pi, FP32 sincos)
 //   K3  gemm_image    E'_c = A2 T_c (fold along x) for c = x, y, z in one workgroup,
 //                     writing E = -i E' and I = sum_c |E_c|^2 from registers.
+#include <algorithm>
+
 #include "hfold.h"
 #include "hgemm.h"
 #include "rw_common.h"
@@ -63,31 +65,45 @@ __global__ void dft_panel_kernel(_Float16* __restrict__ panel, int rows, int cou
 // --------------------------------------------------------------------------
 // K1: base pupil of each stack.
 // --------------------------------------------------------------------------
-// exp(i W) (times the evanescent decay of a Gibson-Lanni layer) at cell (j, l) of stack
-// st.  The Zernike loads are unrolled to the maximum term count, so that a thread has
-// them all in flight at once instead of waiting for each in turn.
-template <class Args>
-__device__ __forceinline__ float2 pupil_phase_factor(const Args& a, const PupilStack& st,
-                                                     const float* __restrict__ ztab, int j, int l) {
+// What a pupil cell's phase needs of the cell alone, with room for NZ Zernike terms.  Their
+// loads are unrolled, so that a thread has them all in flight at once instead of waiting for
+// each in turn.
+template <int NZ>
+struct PupilCell {
+  int cell;   // unpadded index: Zernike table and user phase map
+  double sx, sy, sin_t;
+  float zv[NZ > 0 ? NZ : 1];
+};
+template <int NZ>
+__device__ __forceinline__ PupilCell<NZ> pupil_cell(const PupilGeom& a, const float* __restrict__ ztab, int j, int l) {
+  PupilCell<NZ> p;
   const int n = a.n;
-  const int cell = j * n + l;   // unpadded index: Zernike table and user phase map
-  const double sx = (2.0 * j + 1.0 - n) * a.s_max / n;
-  const double sy = (2.0 * l + 1.0 - n) * a.s_max / n;
-  const double sin_t = sqrt(sx * sx + sy * sy);
-  float zv[RWPSF_MAX_ZERNIKE];
+  p.cell = j * n + l;
+  p.sx = (2.0 * j + 1.0 - n) * a.s_max / n;
+  p.sy = (2.0 * l + 1.0 - n) * a.s_max / n;
+  p.sin_t = sqrt(p.sx * p.sx + p.sy * p.sy);
 #pragma unroll
-  for (int k = 0; k < RWPSF_MAX_ZERNIKE; ++k) zv[k] = k < a.max_zernike ? ztab[(size_t)k * n * n + cell] : 0.f;
+  for (int k = 0; k < NZ; ++k) p.zv[k] = k < a.max_zernike ? ztab[(size_t)k * n * n + p.cell] : 0.f;
+  return p;
+}
+
+// exp(i W) (times the evanescent decay of a Gibson-Lanni layer) at a cell, for stack st with the
+// coefficients 2 pi c in coef and the value w0 of its phase map (the table values of terms past
+// max_zernike are 0).
+template <int NZ, class Stack>
+__device__ __forceinline__ float2 pupil_phase_factor(const PupilGeom& a, const Stack& st, const double* coef, float w0,
+                                                     const PupilCell<NZ>& p) {
   double w_re = 0.0, w_im = 0.0;
-  if (a.gibson_lanni) gl_opd(a.gl, st.t_s, sin_t, &w_re, &w_im);
-  w_re -= a.k * (sx * st.x0 + sy * st.y0);
-  if (st.w0) w_re += (double)st.w0[cell];
+  if (a.gibson_lanni) gl_opd(a.gl, st.t_s, p.sin_t, &w_re, &w_im);
+  w_re -= a.k * (p.sx * st.x0 + p.sy * st.y0);
+  w_re += (double)w0;
 #pragma unroll
-  for (int k = 0; k < RWPSF_MAX_ZERNIKE; ++k) w_re += kTwoPi * st.coef[k] * (double)zv[k];
-  // the evanescent decay in FP32 (relative error ~1e-7, far below the tolerance), the
-  // phase reduced in FP64 in revolutions before the hardware sine and cosine
+  for (int k = 0; k < NZ; ++k) w_re += coef[k] * (double)p.zv[k];
+  // the evanescent decay in FP32 (relative error ~1e-7, far below the tolerance); the phase
+  // reduced in FP64
   const float amp = w_im > 0.0 ? expf((float)-w_im) : 1.f;
   float sn, cs;
-  sincos_rev(w_re * (1.0 / kTwoPi), &sn, &cs);
+  sincospif(half_turns(w_re), &sn, &cs);
   return make_float2(amp * cs, amp * sn);
 }
 
@@ -114,7 +130,8 @@ __global__ void __launch_bounds__(256) pupil_build_kernel(PupilArgs a, const flo
     for (int c = 0; c < nc; ++c) out[c * npp] = make_float2(0.f, 0.f);
     return;
   }
-  const float2 e = pupil_phase_factor(a, a.s[s], ztab, j, l);
+  const PupilCell<RWPSF_MAX_ZERNIKE> pc = pupil_cell<RWPSF_MAX_ZERNIKE>(a, ztab, j, l);
+  const float2 e = pupil_phase_factor(a, a.s[s], a.s[s].coef, a.s[s].w0 ? a.s[s].w0[pc.cell] : 0.f, pc);
   for (int c = 0; c < nc; ++c) out[c * npp] = make_float2(q[c].x * e.x - q[c].y * e.y, q[c].x * e.y + q[c].y * e.x);
 }
 
@@ -142,34 +159,35 @@ __device__ __forceinline__ float4 quad_values(float v) {
                      __int_as_float(__builtin_amdgcn_update_dpp(0, b, 0xFF, 0xF, 0xF, false)));
 }
 
-// Four lanes per (folded cell, stack), grid.y the stack: lane m of a quad forms the pupil
-// of mirror m = 2 a + b, i.e. of cell (mir_a(jf), mir_b(lf)), broadcasts it to the quad
-// (DPP quad permutes) and writes parity (pj, pl) = (m / 2, m % 2) of every channel.
-__global__ void __launch_bounds__(256) pupil_build_folded_kernel(PupilArgs a, const float2* __restrict__ Q,
+// Four lanes per folded cell, which go through a group of stacks (grid.y): lane m of a quad
+// forms the pupil of mirror m = 2 a + b, i.e. of cell (mir_a(jf), mir_b(lf)), broadcasts it to
+// the quad (DPP quad permutes) and writes parity (pj, pl) = (m / 2, m % 2) of every channel.
+// A lane keeps its base pupil and its table values for the whole group, and the coefficients
+// of 16 stacks fit one launch.  64 stacks of 256 x 256 cells: 8 launches of 15.4 us with a lane
+// per cell and stack, 4 of 15.2 us so (groups of 8 or 16 and unrolling by two change nothing: 25
+// MB leave each launch); one stack of 64 x 64 cells without aberrations 19 -> 5.3 us with room
+// for the terms in use only.
+constexpr int kFoldGroup = 4;
+template <int NZ>
+__global__ void __launch_bounds__(256) pupil_build_folded_kernel(FoldArgs a, const float2* __restrict__ Q,
                                                                  const float* __restrict__ ztab,
-                                                                 float2* __restrict__ Pf, int nhp) {
+                                                                 float2* __restrict__ Pf, int nhp, int group) {
   const int n = a.n, np = a.np, nh = (a.n + 1) / 2;
   const int gid = blockIdx.x * blockDim.x + threadIdx.x;
   const int cell = gid >> 2, m = gid & 3;
-  const int s = blockIdx.y;
   if (cell >= nhp * nhp) return;   // whole quads
   const int jf = cell / nhp, lf = cell % nhp;
   const int pj = m >> 1, pl = m & 1;
   const size_t npp = (size_t)np * np, fpp = (size_t)4 * nhp * nhp;
   const int w = 2 * nhp, nc = a.nc;
-  float2* out = Pf + (size_t)s * nc * fpp + (size_t)(2 * jf + pj) * w + 2 * lf + pl;
+  const int s0 = blockIdx.y * group, s1 = min(s0 + group, a.nstk);
   const float2 zero = make_float2(0.f, 0.f);
-  if (jf >= nh || lf >= nh) {   // whole quads
-#pragma unroll
-    for (int c = 0; c < 3; ++c)
-      if (c < nc) out[c * fpp] = make_float2(0.f, 0.f);
-    return;
-  }
+  const bool cells = jf < nh && lf < nh;   // whole quads
   const int j1 = n - 1 - jf, l1 = n - 1 - lf;
   const bool dj = j1 != jf, dl = l1 != lf;
   // this lane's mirror; a mirror equal to the cell itself is absent (zero)
   const int j = pj ? j1 : jf, l = pl ? l1 : lf;
-  const bool present = (pj ? dj : true) && (pl ? dl : true);
+  const bool present = cells && (pj ? dj : true) && (pl ? dl : true);
   float2 q[3];
   bool inside = false;
 #pragma unroll
@@ -177,28 +195,43 @@ __global__ void __launch_bounds__(256) pupil_build_folded_kernel(PupilArgs a, co
     q[c] = present && c < nc ? Q[c * npp + (size_t)j * np + l] : zero;
     inside = inside || q[c].x != 0.f || q[c].y != 0.f;
   }
+  PupilCell<NZ> pc{};
   if (inside) {
-    const float2 e = pupil_phase_factor(a, a.s[s], ztab, j, l);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) q[c] = make_float2(q[c].x * e.x - q[c].y * e.y, q[c].x * e.y + q[c].y * e.x);
+    pc = pupil_cell<NZ>(a, ztab, j, l);
   }
   // the mirror's sign in this lane's parity: (-1)^(a pj + b pl) for mirror (a, b)
   const float s01 = pl ? -1.f : 1.f, s10 = pj ? -1.f : 1.f;
   const bool odd_ok = (!pj || dj) && (!pl || dl);   // odd parts of a self-mirrored row vanish
+  const float* map = nullptr;
+  float w0 = 0.f;
+#pragma unroll 1
+  for (int s = s0; s < s1; ++s) {
+    if (a.s[s].w0 != map) {   // the map of the stack before is the usual one
+      map = a.s[s].w0;
+      w0 = map && inside ? map[pc.cell] : 0.f;
+    }
+    float2* out = Pf + (size_t)s * nc * fpp + (size_t)(2 * jf + pj) * w + 2 * lf + pl;
+    float2 p[3] = {zero, zero, zero};
+    if (inside) {
+      const float2 e = pupil_phase_factor(a, a.s[s], a.coef + s * a.max_zernike, w0, pc);
 #pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    if (c >= nc) break;
-    const float4 vr = quad_values(q[c].x), vi = quad_values(q[c].y);
-    // mirrors (0,0) + s01 (0,1) + s10 [(1,0) + s01 (1,1)]
-    float re = (vr.x + s01 * vr.y) + s10 * (vr.z + s01 * vr.w);
-    float im = (vi.x + s01 * vi.y) + s10 * (vi.z + s01 * vi.w);
-    if (!odd_ok) re = im = 0.f;
-    // times i^(pj + pl)
-    float2 v;
-    if (pj + pl == 0) v = make_float2(re, im);
-    else if (pj + pl == 1) v = make_float2(-im, re);
-    else v = make_float2(-re, -im);
-    out[c * fpp] = v;
+      for (int c = 0; c < 3; ++c) p[c] = make_float2(q[c].x * e.x - q[c].y * e.y, q[c].x * e.y + q[c].y * e.x);
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      if (c >= nc) break;
+      const float4 vr = quad_values(p[c].x), vi = quad_values(p[c].y);
+      // mirrors (0,0) + s01 (0,1) + s10 [(1,0) + s01 (1,1)]
+      float re = (vr.x + s01 * vr.y) + s10 * (vr.z + s01 * vr.w);
+      float im = (vi.x + s01 * vi.y) + s10 * (vi.z + s01 * vi.w);
+      if (!odd_ok) re = im = 0.f;
+      // times i^(pj + pl)
+      float2 v;
+      if (pj + pl == 0) v = make_float2(re, im);
+      else if (pj + pl == 1) v = make_float2(-im, re);
+      else v = make_float2(-re, -im);
+      out[c * fpp] = v;
+    }
   }
 }
 
@@ -460,11 +493,17 @@ hipError_t launch_pupil_build(const PupilArgs& a, const float2* Q, const float* 
   return hipGetLastError();
 }
 
-hipError_t launch_pupil_build_folded(const PupilArgs& a, const float2* Q, const float* ztab, float2* Pf, int nhp,
+hipError_t launch_pupil_build_folded(const FoldArgs& a, const float2* Q, const float* ztab, float2* Pf, int nhp,
                                      hipStream_t st) {
-  const int lanes = 4 * nhp * nhp;
-  hipLaunchKernelGGL(pupil_build_folded_kernel, dim3((lanes + 255) / 256, a.nstk), dim3(256), 0, st, a, Q, ztab, Pf,
-                     nhp);
+  const int blocks = (4 * nhp * nhp + 255) / 256;
+  // stacks per thread: as many as leave four workgroups for each of 256 CUs
+  const int group = std::min(kFoldGroup, std::max(1, a.nstk * blocks / 1024));
+  // (room for 24 terms keeps two more waves on a SIMD than room for all 36)
+  const auto kernel = a.max_zernike == 0    ? pupil_build_folded_kernel<0>
+                      : a.max_zernike <= 24 ? pupil_build_folded_kernel<24>
+                                            : pupil_build_folded_kernel<RWPSF_MAX_ZERNIKE>;
+  hipLaunchKernelGGL(kernel, dim3(blocks, (a.nstk + group - 1) / group), dim3(256), 0, st, a, Q,
+                     ztab, Pf, nhp, group);
   return hipGetLastError();
 }
 

@@ -159,9 +159,8 @@ int plan_init(rwpsf_plan* p, const rwpsf_optics& o, const rwpsf_grid& g, const r
   return bessel_plan_init(p);
 }
 
-// Pupil arguments of nb <= NS stacks.
-template <int NS>
-static void fill_pupil_args(const rwpsf_plan* p, const rwpsf_stack* s, int nb, PupilArgsT<NS>& pa) {
+// Pupil arguments of nb stacks, but for the stacks themselves.
+static void fill_pupil_geom(const rwpsf_plan* p, const rwpsf_stack* s, int nb, PupilGeom& pa) {
   pa.n = p->num.n_pupil;
   pa.np = p->np;
   pa.nstk = nb;
@@ -171,41 +170,57 @@ static void fill_pupil_args(const rwpsf_plan* p, const rwpsf_stack* s, int nb, P
   pa.k = p->k;
   pa.gl = p->gl;
   int maxz = 0;
-  for (int i = 0; i < nb; ++i) {
-    const rwpsf_stack& x = s[i];
-    PupilStack& d = pa.s[i];
-    d.t_s = x.t_s_nm;
-    d.x0 = x.x0_nm;
-    d.y0 = x.y0_nm;
-    for (int q = 0; q < RWPSF_MAX_ZERNIKE; ++q) d.coef[q] = q < x.n_zernike ? x.zernike_waves[q] : 0.0;
-    d.w0 = x.phase_map;
-    maxz = std::max(maxz, x.n_zernike);
-  }
+  for (int i = 0; i < nb; ++i) maxz = std::max(maxz, s[i].n_zernike);
   pa.max_zernike = maxz;
+}
+static double pupil_coef(const rwpsf_stack& x, int q) { return q < x.n_zernike ? kTwoPi * x.zernike_waves[q] : 0.0; }
+template <class Stack>
+static void fill_pupil_stack(const rwpsf_stack& x, Stack& d) {
+  d.t_s = x.t_s_nm;
+  d.x0 = x.x0_nm;
+  d.y0 = x.y0_nm;
+  d.w0 = x.phase_map;
 }
 
 // Base pupils P_{b,c} of up to 8 stacks into the plan's pupil workspace.
 int fourier_build_pupils(rwpsf_plan* p, const rwpsf_stack* s, int nb, hipStream_t st) {
   PupilArgs pa{};
-  fill_pupil_args(p, s, nb, pa);
+  fill_pupil_geom(p, s, nb, pa);
+  for (int i = 0; i < nb; ++i) {
+    fill_pupil_stack(s[i], pa.s[i]);
+    for (int q = 0; q < RWPSF_MAX_ZERNIKE; ++q) pa.s[i].coef[q] = pupil_coef(s[i], q);
+  }
   const int tr = p->time_begin(RWPSF_KERNEL_PUPIL_BUILD, st);
   const int rc = hip_check(launch_pupil_build(pa, p->d_Q, p->d_ztab, p->d_P, st));
   p->time_end(tr, st);
   return rc;
 }
 
-// Mirror-folded pupils of up to 8 stacks into Pf ([nb][nc][2 nhp][2 nhp]).
-int fourier_build_folded(rwpsf_plan* p, const rwpsf_stack* s, int nb, float2* Pf, hipStream_t st) {
-  PupilArgs pa{};
-  fill_pupil_args(p, s, nb, pa);
-  const int tr = p->time_begin(RWPSF_KERNEL_PUPIL_BUILD, st);
-  const int rc = hip_check(launch_pupil_build_folded(pa, p->d_Q, p->d_ztab, Pf, p->nhp, st));
-  p->time_end(tr, st);
-  return rc;
+// Mirror-folded pupils of n stacks into Pf ([n][nc][2 nhp][2 nhp]), in launches of up to
+// kFoldStacks.
+int fourier_build_folded(rwpsf_plan* p, const rwpsf_stack* s, int n, float2* Pf, hipStream_t st) {
+  int maxz = 1;
+  for (int i = 0; i < n; ++i) maxz = std::max(maxz, s[i].n_zernike);
+  const int per = std::min(kFoldStacks, 1 + (kFoldTerms - RWPSF_MAX_ZERNIKE) / maxz);
+  for (int c0 = 0; c0 < n; c0 += per) {
+    const int nb = std::min(per, n - c0);
+    FoldArgs pa{};
+    fill_pupil_geom(p, s + c0, nb, pa);
+    for (int i = 0; i < nb; ++i) {
+      fill_pupil_stack(s[c0 + i], pa.s[i]);
+      for (int q = 0; q < pa.max_zernike; ++q) pa.coef[i * pa.max_zernike + q] = pupil_coef(s[c0 + i], q);
+    }
+    const int tr = p->time_begin(RWPSF_KERNEL_PUPIL_BUILD, st);
+    const int rc = hip_check(launch_pupil_build_folded(pa, p->d_Q, p->d_ztab,
+                                                       Pf + (size_t)c0 * p->nc * 4 * p->nhp * p->nhp, p->nhp, st));
+    p->time_end(tr, st);
+    if (rc) return rc;
+  }
+  return RWPSF_OK;
 }
 
 // --------------------------------------------------------------------------
-// Fourier dispatch: chunks of up to 64 stacks (folded pupils in launches of 8), then
+// Fourier dispatch: chunks of up to 64 stacks (their folded pupils first), then
 // slabs of stack-planes through the two GEMM kernels.
 // --------------------------------------------------------------------------
 static int fourier_gemms(rwpsf_plan* p, int s_local, int ns, const double* zoff, int s_global, int z0, int nzs,
@@ -261,11 +276,7 @@ int fourier_compute(rwpsf_plan* p, int n, const rwpsf_stack* s, float2* E, float
   for (int b0 = 0; b0 < n; b0 += kGemmStacks) {
     const int nb = std::min(kGemmStacks, n - b0);
     int rc;
-    // folded pupils of the group in launches of up to kPupilStacks, side by side
-    for (int c0 = 0; c0 < nb; c0 += kPupilStacks)
-      if ((rc = fourier_build_folded(p, s + b0 + c0, std::min(kPupilStacks, nb - c0),
-                                     p->d_Pf + (size_t)c0 * p->nc * 4 * p->nhp * p->nhp, st)))
-        return rc;
+    if ((rc = fourier_build_folded(p, s + b0, nb, p->d_Pf, st))) return rc;
     double zoff[kGemmStacks];
     for (int i = 0; i < nb; ++i) zoff[i] = s[b0 + i].z_offset_nm;
     // slabs over (stack, plane): a slab is a run of planes of one or more stacks

@@ -5,28 +5,42 @@
 
 namespace rw {
 
-constexpr int kPupilStacks = 8;  // stacks per pupil launch (by-value arguments stay < 4 KB)
-constexpr int kGemmStacks = 64;  // stacks per GEMM launch (folded pupils of up to 8 pupil launches): fewer
+constexpr int kPupilStacks = 8;  // stacks per launch of unfolded pupils (the size of their workspace)
+constexpr int kFoldStacks = 16;  // stacks per launch of folded pupils, fewer if each has more than
+constexpr int kFoldTerms = 384;  // 23 Zernike terms: they share this room (by-value arguments stay < 4 KB)
+constexpr int kGemmStacks = 64;  // stacks per GEMM launch (folded pupils of several launches): fewer
                                  // kernel prologues and tails, and small outputs need many stacks per
                                  // launch to fill the GPU
 
 struct PupilStack {
   double t_s, x0, y0;
-  double coef[RWPSF_MAX_ZERNIKE];
+  double coef[RWPSF_MAX_ZERNIKE];   // 2 pi c
   const float* w0;
 };
 
 // Channels: nc = 3 (vectorial model, x, y, z) or 1 (scalar model); every per-channel
 // array below holds nc channels.
-template <int NS>
-struct PupilArgsT {
+struct PupilGeom {
   int n, np, nstk, max_zernike, gibson_lanni, nc;   // n: pupil cells per axis, np: padded stride
   double s_max, k;
   GLParams gl;
-  PupilStack s[NS];
 };
-using PupilArgs = PupilArgsT<kPupilStacks>;
+struct PupilArgs : PupilGeom {
+  PupilStack s[kPupilStacks];
+};
 static_assert(sizeof(PupilArgs) <= 4000, "kernel arguments are passed by value (4 KB limit)");
+
+// Arguments of the folded pupils: the coefficients are packed, max_zernike a stack (a read of
+// RWPSF_MAX_ZERNIKE from any stack's first stays inside).
+struct FoldStack {
+  double t_s, x0, y0;
+  const float* w0;
+};
+struct FoldArgs : PupilGeom {
+  FoldStack s[kFoldStacks];
+  double coef[kFoldTerms];          // 2 pi c
+};
+static_assert(sizeof(FoldArgs) <= 4000, "kernel arguments are passed by value (4 KB limit)");
 
 // Device operands are zero-padded: np = n rounded up to 64, nxp = nx rounded up
 // to 128, nyp = ny rounded up to 128 (64 for axes of at most 64 pixels), and the folded pupil axis nh = ceil(n/2) to
@@ -82,7 +96,7 @@ hipError_t launch_dft_panel(uint4* panel, int rows, int count, int centre, int n
 hipError_t launch_pupil_build(const PupilArgs& a, const float2* Q, const float* ztab, float2* P,
                               hipStream_t st);
 // Pf [nstk][nc][2 nhp][2 nhp] of the stacks of a (its np field is the stride of Q)
-hipError_t launch_pupil_build_folded(const PupilArgs& a, const float2* Q, const float* ztab, float2* Pf, int nhp,
+hipError_t launch_pupil_build_folded(const FoldArgs& a, const float2* Q, const float* ztab, float2* Pf, int nhp,
                                      hipStream_t st);
 hipError_t launch_gemm_pupil(const Gemm1Args& a, hipStream_t st);
 hipError_t launch_gemm_image(const Gemm2Args& a, hipStream_t st);
