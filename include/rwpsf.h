@@ -372,8 +372,8 @@ enum rwpsf_kernel_id {
   RWPSF_KERNEL_BESSEL_PHI = 3,        /* Bessel: pupil x defocus on the theta nodes */
   RWPSF_KERNEL_BESSEL_CONTRACT = 4,   /* Bessel: theta contraction on the matrix cores */
   RWPSF_KERNEL_BESSEL_EPILOGUE = 5,   /* Bessel: radial interpolation, fields and |E|^2 */
-  RWPSF_KERNEL_ADJ_H = 6,             /* adjoint: (2 dL/dI E) conj(Ay) */
-  RWPSF_KERNEL_ADJ_G = 7,             /* adjoint: Ax'^H H with Im(G conj(P~)) accumulation */
+  RWPSF_KERNEL_ADJ_H = 6,             /* adjoint: power-of-two scales of 2 dL/dI E */
+  RWPSF_KERNEL_ADJ_G = 7,             /* adjoint: both transforms of 2 dL/dI E, pupil and defocus */
   RWPSF_KERNEL_ADJ_REDUCE = 8,        /* adjoint: fixed-order reductions to dL/dW0, dL/dc */
   RWPSF_KERNEL_CZT_ROWS = 9,          /* chirp-z: pupil rows (defocus, FFT convolution along y) */
   RWPSF_KERNEL_CZT_COLS = 10,         /* chirp-z: output columns (FFT convolution along x), |E|^2 */

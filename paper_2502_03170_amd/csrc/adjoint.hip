@@ -13,14 +13,13 @@
 //   SC = sum_m sin theta Hc, SS = sum_m sin theta Hs (pref = f k / 2 pi), i.e.
 //   G[jf,lf] = i pref (CC - iCS - iSC - SS)    G[jf,l'] = i pref (CC + iCS - iSC + SS)
 //   G[j',lf] = i pref (CC - iCS + iSC + SS)    G[j',l'] = i pref (CC + iCS + iSC - SS)
-// Kernels (real-coefficient GEMMs on the FP32 matrix cores, FP32 accumulate):
-//   adj_h_kernel   H'[b,z,c][m][2lf + p] = {Hc, Hs}: rows 2m + re/im of 2 g E (the scaling
-//                  applied while E is staged) times the folded y table
-//   adj_g_kernel   for each (stack, component, plane group) and folded pupil tile, over
-//                  the planes in order: Q = {cos, sin}(theta) H', then the four mirror
-//                  values of G from each lane quad, acc += Im(G conj(P~)) -- one partial
-//                  per (stack, component, plane group), no atomics
-//   adj_reduce_*   dL/dPhi = sum of the partials in a fixed order (FP64), dL/dW0
+// Kernels:
+//   adj_scale_kernel  the power of two of each plane of 2 g E (its operand halves are f16)
+//   adj_kernel        both contractions as real GEMMs on the F16 matrix cores with split
+//                     operands (hgemm.h), H in LDS; sums CC .. SS conj(exp(i k s_z z)) over a run
+//                     of planes, then takes mirrors and pupil: one partial of dL/dPhi per
+//                     (stack, component, run), no atomics
+//   adj_reduce_*      dL/dPhi = sum of the partials in a fixed order (FP64), dL/dW0
 //   adj_zernike_kernel dL/dc_q by a fixed-shape tree reduction (FP64)
 // The result does not depend on scheduling: every sum runs in a fixed order.
 #include <algorithm>
@@ -29,266 +28,385 @@
 #include <vector>
 
 #include "hgemm.h"
-#include "rgemm.h"
 #include "rw_common.h"
 #include "rw_fourier.h"
 #include "rw_plan.h"
 
 namespace rw {
 
-constexpr int kAdjStacks = 32;   // stacks per adj_h / adj_g launch (fewer kernel prologues and tails)
-using CfgAdjH = RgCfg<128, 64, 16, 64, 32>;   // rows 2m + re/im, columns 2lf + p, k = n
-using CfgAdjG = RgCfg<64, 128, 16, 32, 64>;   // rows 2jf + p, columns 2(2lf + p) + re/im, k = m
+constexpr int kAdjStacks = 64;    // stacks per launch (their z offsets are passed by value)
+constexpr int kAdjThreads = 512;  // eight waves
+constexpr int kAdjCols = 32;      // folded y cells per workgroup
+constexpr int kAdjChunk = 64;     // pixels per chunk, along x and along y
+constexpr int kAdjPanel = kAdjChunk * 128 * 4;   // bytes of the field and of the H panel
+constexpr int kAdjTab = kAdjChunk * 2 * kAdjCols * 4;
+constexpr int kAdjRows = 256;     // folded x rows 2jf + p per workgroup, 32 a wave
+constexpr int kAdjLds = 2 * kAdjPanel + kAdjTab + kAdjChunk * kAdjRows * 4;
 
-// A operand of adj_h: rows 2m + ri of 2 g E ([nx][ny] complex, k = n contiguous); rows
-// past nx read row nx - 1 with a zero factor (no branches in the load path).
-template <class Cfg>
-struct ScaledFieldLoader {
-  static constexpr int ROWS = Cfg::BM / 2, PAIRS = Cfg::BK / 2;
-  static constexpr int PER_THREAD = ROWS * PAIRS / Cfg::NT;
-  static_assert(ROWS * PAIRS % Cfg::NT == 0, "loader shape");
-  const float2* E;
-  const float* g;
-  int ld, nrows, row0;
-  struct Regs {
-    float4 v[PER_THREAD];
-    float2 f[PER_THREAD];
-  };
-
-  __device__ Regs load(int k0, int tid) const {
-    Regs r;
-    float4* v = r.v;
-    float2* f = r.f;
-#pragma unroll
-    for (int i = 0; i < PER_THREAD; ++i) {
-      const int idx = tid + i * Cfg::NT;
-      const int row = idx / PAIRS, kk = 2 * (idx % PAIRS);
-      const int gr = min(row0 + row, nrows - 1);
-      const size_t off = (size_t)gr * ld + k0 + kk;
-      v[i] = *reinterpret_cast<const float4*>(E + off);
-      const float2 gg = *reinterpret_cast<const float2*>(g + off);
-      const float keep = (row0 + row < nrows) ? 2.f : 0.f;
-      f[i] = make_float2(keep * gg.x, keep * gg.y);
-    }
-    return r;
+// Split-f16 panel of one axis' folded table for contractions over its pixels, [pixel / 16]
+// [piece][col][8 halves], 2^kTabExp {cos, sin}(k s_f x): columns 2f + p, or with `blocks` runs of
+// 32 cells of one p, 64 (f / 32) + 32 p + f % 32.  Zero for f >= ceil(N / 2).
+__global__ void adj_panel_kernel(_Float16* __restrict__ panel, int pixels, int n, int w, double k, double s_max,
+                                 double pitch, int blocks) {
+  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx >= pixels * (w / 2)) return;
+  const int x = idx % pixels, f = idx / pixels;
+  double v[2] = {0.0, 0.0};
+  if (f < (n + 1) / 2) {
+    const double ph = k * ((2.0 * f + 1.0 - n) * s_max / n) * ((double)(x - pixels / 2) * pitch);
+    sincos(ph, &v[1], &v[0]);
   }
-  __device__ void store(float* dst, int tid, const Regs& r) const {
-    const float4* v = r.v;
-    const float2* f = r.f;
 #pragma unroll
-    for (int i = 0; i < PER_THREAD; ++i) {
-      const int idx = tid + i * Cfg::NT;
-      const int row = idx / PAIRS, kk = 2 * (idx % PAIRS);
-      float* d = dst + (2 * row) * Cfg::LDK + kk;
-      *reinterpret_cast<float2*>(d) = make_float2(f[i].x * v[i].x, f[i].y * v[i].z);
-      *reinterpret_cast<float2*>(d + Cfg::LDK) = make_float2(f[i].x * v[i].y, f[i].y * v[i].w);
+  for (int p = 0; p < 2; ++p) {
+    const double y = ldexp(v[p], kTabExp);
+    const int col = blocks ? 64 * (f / 32) + 32 * p + f % 32 : 2 * f + p;
+    _Float16* o = panel + ((size_t)(x / 16 * 4 + x % 16 / 8) * w + col) * 8 + x % 8;
+    const _Float16 hi = (_Float16)(float)y;
+    o[0] = hi;
+    o[(size_t)2 * w * 8] = (_Float16)(float)(y - (double)(float)hi);
+  }
+}
+
+// exp(i k s_z z) of every plan plane on the folded cells (FP64 phase reduced mod 2 pi before the
+// FP32 sincos); 1 where k s_z is 0.
+__global__ void adj_defocus_kernel(const double* __restrict__ kszf, const double* __restrict__ z, int nz, int cells,
+                                   float2* __restrict__ D) {
+  const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx >= (size_t)nz * cells) return;
+  const int zi = (int)(idx / cells), cell = (int)(idx % cells);
+  float sn, cs;
+  sincosf((float)reduce_2pi(kszf[cell] * z[zi]), &sn, &cs);
+  D[idx] = make_float2(cs, sn);
+}
+
+// Scale of every (stack, plane, component): the exponent e that puts the largest part of
+// 2 g E 2^e in [2^13, 2^14), 0 for an empty or not finite plane.  One workgroup per
+// (stack, plane); pixels a multiple of 4.
+__global__ void __launch_bounds__(256) adj_scale_kernel(const float2* __restrict__ E, const float* __restrict__ g,
+                                                        int pixels, int* __restrict__ ex) {
+  const size_t item = blockIdx.x;
+  const float4* e4 = reinterpret_cast<const float4*>(E + item * 3 * pixels);
+  const float2* g2 = reinterpret_cast<const float2*>(g + item * pixels);
+  const int pairs = pixels / 2;
+  float m[3] = {0.f, 0.f, 0.f};
+  for (int i = threadIdx.x; i < pairs; i += 256) {
+    const float2 f = g2[i];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const float4 v = e4[(size_t)c * pairs + i];
+      m[c] = fmaxf(m[c], fmaxf(fmaxf(fabsf(2.f * f.x * v.x), fabsf(2.f * f.x * v.y)),
+                               fmaxf(fabsf(2.f * f.y * v.z), fabsf(2.f * f.y * v.w))));
     }
   }
-};
+  __shared__ float red[3][4];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) m[c] = fmaxf(m[c], __shfl_xor(m[c], d));
+    if ((threadIdx.x & 63) == 0) red[c][threadIdx.x >> 6] = m[c];
+  }
+  __syncthreads();
+  if (threadIdx.x < 3) {
+    const float* r = red[threadIdx.x];
+    const float x = fmaxf(fmaxf(r[0], r[1]), fmaxf(r[2], r[3]));
+    int b = 0;
+    if (x > 0.f && x < INFINITY) frexpf(x, &b);   // x in [2^(b-1), 2^b)
+    ex[item * 3 + threadIdx.x] = x > 0.f && x < INFINITY ? 14 - b : 0;
+  }
+}
 
-struct AdjHArgs {
+struct AdjArgs {
   const float2* E;     // [stacks][nz][3][nx][ny] (the caller's fields)
   const float* g;      // [stacks][nz][nx][ny]
-  const float* CyT;    // [w][nyp] rows 2lf + p: {cos, sin}(k s_lf y_n)
-  float2* H;           // [chunk][nz][3][nxp][w]
-  int s0, nstk, nz, nx, ny, nyp, nxp, w;
+  const int* ex;       // [stacks][nz][3] scales
+  const uint4* X;      // panel of w columns 2jf + p, k = m
+  const uint4* Y;      // panel of w columns 64 (lf / 32) + 32 p + lf % 32, k = n
+  const float2* D;     // [nz][nhp][nhp] exp(i k s_z z) of the plan's planes
+  const float2* Pf;    // [launch's stacks][3][w][w] mirror-folded pupils (the forward's fold)
+  const double* kszf;  // [nhp][nhp]
+  float* partial;      // [stacks * 3 * zgroups * MC][np][np], MC chunks along x
+  double zoff[kAdjStacks];
+  int s0, nstk, nz, nx, ny, w, n, row_groups;
+  int zgroups, zper;   // planes are split into zgroups runs of zper (the last may be shorter)
+  int hshift;          // H is stored with 2^-hshift
+  float gexp;          // power of two of the result
 };
 
-__global__ void __launch_bounds__(CfgAdjH::NT, 2) adj_h_kernel(AdjHArgs a) {
-  using Cfg = CfgAdjH;
-  extern __shared__ float lds[];
-  const int tiles_m = 2 * a.nxp / Cfg::BM, tiles_n = a.w / Cfg::BN;
-  const int nblocks = a.nstk * a.nz * 3 * tiles_m * tiles_n;
+// One (stack, component, run of planes, 64 pixel rows, 32 folded y cells, 256 folded x rows) per
+// workgroup of eight waves (waves past a smaller pupil's rows only take part in H: giving them a
+// share of the contraction over x was no faster, and its partial sums cancel less exactly).  A
+// step is a chunk of 64 x 64 pixels of one plane:
+//   H[m][p, lf]      = sum_n (2 g E)[m][n] {cos, sin} phi    128 rows (m, re / im) x 64 columns
+//   G[2jf + p][p, ri, lf] += sum_m {cos, sin} theta H        a wave: 32 rows x four blocks of 32
+//                                                            columns, one per (p, re / im)
+// H stays in LDS as a split panel.  A lane ends up with CC, CS, SC, SS of the same eight cells.
+// The defocus and the pupil are the same function of z for all four mirrors and no function of z,
+// so that per plane only  Z += {CC, CS, SC, SS} conj(D_z)  is summed (16 FMAs a folded cell); the
+// mirrors and the pupil are taken once per run.
+// While a step is multiplied the next one is split into LDS and the one after it is on its way
+// from memory.  The field chunk, 2 g E 2^e split in halves, is 32-row blocks of 16 pixel rows m as
+// rows 8 (m / 4) + 4 ri + m % 4, so that an accumulator lane holds 16 consecutive m of one part.
+// Bound by latency: eight waves of 253 registers fill a CU, and its steps run one after the
+// other between barriers (matrix cores busy a third of the time, vector units another, LDS a
+// fifth).  64 stacks of 64 x 64 x 21 on a 256 x 256 pupil, the whole of 2 g E to the partial
+// sums: 1140 us as two FP32 MFMA kernels with H in memory (2 x 120 + 2 x 450), 310 so and 27 for
+// the scales.  Without the sum over planes 268, without G 190, without H 232.  The x table in
+// registers spilled (406 us: a spill's reload waits for the loads in flight); the two waves of a
+// SIMD in opposite order 370 against 328; all LDS reads of H first, or three chains, 305-307.
+// MULTI: more than one chunk along y, so that H and the y table pass from step to step.
+template <bool MULTI>
+__global__ void __launch_bounds__(kAdjThreads, 2) adj_kernel(AdjArgs a) {
+  extern __shared__ __align__(16) char alds[];
+  uint4* As = reinterpret_cast<uint4*>(alds);
+  uint4* Hs = reinterpret_cast<uint4*>(alds + kAdjPanel);
+  uint4* Ts = reinterpret_cast<uint4*>(alds + 2 * kAdjPanel);
+  uint4* Xs = reinterpret_cast<uint4*>(alds + 2 * kAdjPanel + kAdjTab);
+  const int tiles_n = a.w / (2 * kAdjCols);
+  const int MC = (a.nx + kAdjChunk - 1) / kAdjChunk, NC = MULTI ? (a.ny + kAdjChunk - 1) / kAdjChunk : 1;
+  const int nblocks = a.nstk * 3 * a.zgroups * MC * a.row_groups * tiles_n;
   int id = xcd_remap(blockIdx.x, nblocks);
   const int tn = id % tiles_n; id /= tiles_n;
-  const int tm = id % tiles_m; id /= tiles_m;
-  const int item = id;   // (s, z, c) within the chunk
-  const int c = item % 3, z = (item / 3) % a.nz, s = item / (3 * a.nz);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wrow = (wave / Cfg::WAVES_N) * Cfg::WM, wcol = (wave % Cfg::WAVES_N) * Cfg::WN;
+  const int rg = id % a.row_groups; id /= a.row_groups;
+  const int c = id % 3; id /= 3;
+  const int mc = id % MC; id /= MC;
+  const int zg = id % a.zgroups, s = id / a.zgroups;
+  const int z_begin = zg * a.zper, z_end = min(a.nz, z_begin + a.zper);
+  const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, l32 = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int row0 = rg * kAdjRows + wave * 32;   // folded x rows 2jf + p of this wave
+  const bool active = row0 < a.w;
+  const int nhp = a.w / 2, lf = kAdjCols * tn + l32, jf0 = row0 / 2;
   const size_t plane = (size_t)a.nx * a.ny;
   const size_t gs = (size_t)(a.s0 + s);
-  const int row0 = tm * Cfg::BM, col0 = tn * Cfg::BN;
-  ScaledFieldLoader<Cfg> la;
-  la.E = a.E + ((gs * a.nz + z) * 3 + c) * plane;
-  la.g = a.g + (gs * a.nz + z) * plane;
-  la.ld = a.ny;
-  la.nrows = a.nx;
-  la.row0 = row0 / 2;
-  RRowLoader<Cfg, Cfg::BN> lb;
-  lb.src = a.CyT + (size_t)col0 * a.nyp;
-  lb.ld = a.nyp;
-  RgAcc<Cfg> acc;
-  acc.zero();
-  rg_mainloop<Cfg, kOrderFull>(acc, la, lb, 0, a.ny, lds, tid, wrow, wcol, lane);
-  // rows 2m + ri: registers r and r + 1 (r even) are the re/im parts of one H'[m][col]
-  float2* H = a.H + (size_t)item * a.nxp * a.w;
+
+  // this thread's share of a chunk: eight pixels of row ml from nl
+  const int ml = (lane & 7) + 8 * wave, nl = lane & ~7;
+  struct Regs {
+    float4 v[4], f[2];
+    uint4 t[MULTI ? 2 : 1];   // of the y table
+    int e;
+    float two;   // 0 past the edges (such pixels are loaded from pixel 0)
+  };
+  const int m = kAdjChunk * mc + ml;
+  auto load = [&](int zi, int nc) {
+    Regs r;
+    const int n = kAdjChunk * nc + nl;
+    const size_t pl = gs * a.nz + zi;
+    const bool ok = m < a.nx && n < a.ny;
+    const size_t off = ok ? (size_t)m * a.ny + n : 0;
+    const float4* ep = reinterpret_cast<const float4*>(a.E + (pl * 3 + c) * plane + off);
+    const float4* gp = reinterpret_cast<const float4*>(a.g + pl * plane + off);
 #pragma unroll
-  for (int i = 0; i < Cfg::TM; ++i)
+    for (int i = 0; i < 4; ++i) r.v[i] = ep[i];
 #pragma unroll
-    for (int jj = 0; jj < Cfg::TN; ++jj) {
-      const int col = col0 + rg_col(wcol, jj, lane);
+    for (int i = 0; i < 2; ++i) r.f[i] = gp[i];
+    r.two = ok ? 2.f : 0.f;
+    r.e = a.ex[pl * 3 + c];
+    if constexpr (MULTI) {
 #pragma unroll
-      for (int r = 0; r < 16; r += 2) {
-        const int m = (row0 + rg_row(wrow, i, r, lane)) >> 1;
-        H[(size_t)m * a.w + col] = make_float2(acc.c[i][jj][r], acc.c[i][jj][r + 1]);
+      for (int i = 0; i < 2; ++i) {
+        const int idx = tid + i * kAdjThreads, q = min(16 * nc + idx / 64, a.ny / 4 - 1);
+        r.t[i] = a.Y[(size_t)q * a.w + 2 * kAdjCols * tn + idx % 64];
       }
     }
-}
-
-struct AdjGArgs {
-  const float* CxT;    // [w][nxp] rows 2jf + p: pref {cos, sin}(k s_jf x_m)
-  const float2* H;     // [chunk][nz][3][nxp][w]
-  const float2* Pf;    // [chunk][3][w][w] mirror-folded pupils (the forward's fold)
-  const double* ksz;   // [np][np]
-  const float2* D;     // [nz][np][np] exp(i k s_z z) of the plan's planes
-  float* partial;      // [stacks * 3 * zgroups][np][np]
-  double zoff[kAdjStacks];
-  int s0, nstk, nz, nxp, w, n;
-  int zgroups, zper;   // planes are split into zgroups runs of zper (the last may be shorter)
-};
-
-// quad_perm DPP: lane 4t + q reads lane 4t + sel[q]
-template <int CTRL>
-__device__ __forceinline__ float dpp(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
-}
-
-// at most 168 VGPRs, so that three 4-wave workgroups share a CU
-__global__ void __launch_bounds__(CfgAdjG::NT, 3) adj_g_kernel(AdjGArgs a) {
-  using Cfg = CfgAdjG;
-  extern __shared__ float lds[];
-  const int tiles_m = a.w / Cfg::BM, tiles_n = 2 * a.w / Cfg::BN;
-  const int nblocks = a.nstk * 3 * a.zgroups * tiles_m * tiles_n;
-  int id = xcd_remap(blockIdx.x, nblocks);
-  const int tn = id % tiles_n; id /= tiles_n;
-  const int tm = id % tiles_m; id /= tiles_m;
-  const int g = id % a.zgroups; id /= a.zgroups;
-  const int c = id % 3, s = id / 3;
-  const int z_begin = g * a.zper, z_end = min(a.nz, z_begin + a.zper);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wrow = (wave / Cfg::WAVES_N) * Cfg::WM, wcol = (wave % Cfg::WAVES_N) * Cfg::WN;
-  const int row0 = tm * Cfg::BM, col0 = tn * Cfg::BN;
-  const int n = a.n, nh = (n + 1) / 2;
-  const size_t npp = (size_t)a.w * a.w;
-  const float2* Pf = a.Pf + ((size_t)s * 3 + c) * npp;
-  // lane quad q = lane & 3 of columns 2(2lf + p) + ri: q = 2p + ri.  After the exchange the
-  // lane owns mirror cell q: (jf, lf), (jf, l'), (j', lf), (j', l').
-  const int q = lane & 3;
-  // The defocus of plane z for stack s is exp(i k s_z z) exp(i k s_z zoff_s): the second
-  // factor is applied to the lane's pupil cells once, the first comes from the plan's table.
-  float2 p0[Cfg::TM][Cfg::TN][8];
+    return r;
+  };
+  auto store = [&](const Regs& r) {
+    float x[8], y[8];
+    const float* v = reinterpret_cast<const float*>(r.v);
+    const float* f = reinterpret_cast<const float*>(r.f);
 #pragma unroll
-  for (int i = 0; i < Cfg::TM; ++i)
+    for (int i = 0; i < 8; ++i) {
+      const float ff = r.two * f[i];
+      x[i] = ldexpf(ff * v[2 * i], r.e);
+      y[i] = ldexpf(ff * v[2 * i + 1], r.e);
+    }
+    const int row = 32 * (ml >> 4) + 8 * ((ml >> 2) & 3) + (ml & 3);
+    uint4* o = As + (size_t)(4 * (nl >> 4) + ((nl >> 3) & 1)) * 128 + row;
+    unsigned hi[4], lo[4];
 #pragma unroll
-    for (int jj = 0; jj < Cfg::TN; ++jj) {
-      const int lf = (col0 + rg_col(wcol, jj, lane)) >> 2;
+    for (int i = 0; i < 4; ++i) hg_split2(x[2 * i], x[2 * i + 1], &hi[i], &lo[i]);
+    o[0] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+    o[256] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
 #pragma unroll
-      for (int r = 0; r < 16; r += 2) {
-        const int jf = (row0 + rg_row(wrow, i, r, lane)) >> 1;
-        const int jc = (q & 2) ? n - 1 - jf : jf, lc = (q & 1) ? n - 1 - lf : lf;
-        const bool own = jf < nh && lf < nh && !((q & 2) && jc == jf) && !((q & 1) && lc == lf);
-        float2 v = make_float2(0.f, 0.f);
-        if (own) {
-          // the pupil at mirror (a, b) = (q / 2, q % 2) from the four parities of the
-          // folded cell: P_ab = sum_{pj, pl} (-1)^(a pj + b pl) (-i)^(pj + pl) Pf_{pj, pl},
-          // over 2 per folded axis with two mirrors (a self-mirrored row has no odd part)
-          const float2* f = Pf + (size_t)(2 * jf) * a.w + 2 * lf;
-          const float2 f00 = f[0], f01 = f[1], f10 = f[a.w], f11 = f[a.w + 1];
-          const float sb = (q & 1) ? -1.f : 1.f, sa = (q & 2) ? -1.f : 1.f;
-          const float scale = (jf != n - 1 - jf ? 0.5f : 1.f) * (lf != n - 1 - lf ? 0.5f : 1.f);
-          // (-i) (x + i y) = y - i x
-          const float2 pp = make_float2(scale * (f00.x + sb * f01.y + sa * f10.y - sa * sb * f11.x),
-                                        scale * (f00.y - sb * f01.x - sa * f10.x - sa * sb * f11.y));
-          const size_t cell = (size_t)jc * a.w + lc;
-          float sn, cs;
-          sincosf((float)reduce_2pi(a.ksz[cell] * a.zoff[s]), &sn, &cs);
-          v = make_float2(pp.x * cs - pp.y * sn, pp.x * sn + pp.y * cs);
+    for (int i = 0; i < 4; ++i) hg_split2(y[2 * i], y[2 * i + 1], &hi[i], &lo[i]);
+    o[4] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+    o[260] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+    if constexpr (MULTI) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) Ts[tid + i * kAdjThreads] = r.t[i];
+    }
+  };
+  int zl = z_begin, nl_c = 0;   // chunk that is loaded next
+  auto advance = [&]() {
+    if (!MULTI || ++nl_c == NC) {
+      nl_c = 0;
+      zl = min(zl + 1, z_end - 1);
+    }
+  };
+  Regs cur = load(zl, nl_c);
+  advance();
+  if constexpr (!MULTI) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int idx = tid + i * kAdjThreads, q = min(idx / 64, a.ny / 4 - 1);
+      Ts[idx] = a.Y[(size_t)q * a.w + 2 * kAdjCols * tn + idx % 64];
+    }
+  }
+  // x rows past the table repeat its last row
+#pragma unroll
+  for (int idx = tid; idx < kAdjChunk / 4 * kAdjRows; idx += kAdjThreads) {
+    const int q = min(kAdjChunk / 4 * mc + idx / kAdjRows, a.nx / 4 - 1);
+    Xs[idx] = a.X[(size_t)q * a.w + min(rg * kAdjRows + idx % kAdjRows, a.w - 1)];
+  }
+  hg16 zero;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) zero[r] = 0.f;
+  hg16 zacc[4] = {zero, zero, zero, zero}, acc[4] = {zero, zero, zero, zero};
+  hg16 hx = zero, hm = zero;   // cross products and main product of this wave's block of H
+  float2 d[8];                 // defocus of the plane in acc
+#pragma unroll
+  for (int q = 0; q < 8; ++q) d[q] = make_float2(0.f, 0.f);
+  int e_acc = 0, e_cur = cur.e;
+  store(cur);
+  cur = load(zl, nl_c);
+  const float hscale = ldexpf(1.f, -a.hshift);
+  const int hb = wave >> 1, hp = wave & 1;   // 16 pixel rows and the parity of this wave's block of H
+  // Z += acc conj(D).  Blocks 0, 1 (2, 3) hold the parts of C* and S* at y parity 0 (1); even
+  // registers are x parity 0, odd ones 1.
+  auto add_plane = [&]() {
+    const int eu = a.hshift - e_acc - 2 * kTabExp;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const float cs = ldexpf(d[q].x, eu), sn = ldexpf(d[q].y, eu);
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+          const int r = 2 * q + p;
+          const float xr = acc[2 * b][r], xi = acc[2 * b + 1][r];
+          zacc[2 * b][r] = fmaf(xi, sn, fmaf(xr, cs, zacc[2 * b][r]));
+          zacc[2 * b + 1][r] = fmaf(-xr, sn, fmaf(xi, cs, zacc[2 * b + 1][r]));
         }
-        p0[i][jj][r >> 1] = v;
-      }
     }
-  float dphi[Cfg::TM][Cfg::TN][8];
+  };
+  auto transform_y = [&]() {
+    const hg8* ap = reinterpret_cast<const hg8*>(As) + 32 * hb + l32;
+    const hg8* bp = reinterpret_cast<const hg8*>(Ts) + 32 * hp + l32;
 #pragma unroll
-  for (int i = 0; i < Cfg::TM; ++i)
-#pragma unroll
-    for (int jj = 0; jj < Cfg::TN; ++jj)
-#pragma unroll
-      for (int r = 0; r < 8; ++r) dphi[i][jj][r] = 0.f;
-  RRowLoader<Cfg, Cfg::BM> la;
-  la.src = a.CxT + (size_t)row0 * a.nxp;
-  la.ld = a.nxp;
-  RColLoader<Cfg, Cfg::BN> lb;
-  const float* hsrc = reinterpret_cast<const float*>(a.H) + col0;
-  const size_t hplane = 2 * (size_t)a.nxp * a.w;   // floats per (stack, plane, channel) of H
-  lb.src = hsrc + ((size_t)(s * a.nz + z_begin) * 3 + c) * hplane;
-  lb.ld = 2 * a.w;
-  auto ra = la.load(0, tid);
-  auto rb = lb.load(0, tid);
+    for (int u = 0; u < kAdjChunk / 16; ++u) {
+      const hg8 ah = ap[(4 * u + h) * 128], al = ap[(4 * u + 2 + h) * 128];
+      const hg8 bh = bp[(4 * u + h) * 64], bl = bp[(4 * u + 2 + h) * 64];
+      hx = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bl, hx, 0, 0, 0);
+      hm = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bh, hm, 0, 0, 0);
+      hx = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, bh, hx, 0, 0, 0);
+    }
+  };
 #pragma unroll 1
   for (int zi = z_begin; zi < z_end; ++zi) {
-    RgAcc<Cfg> acc;
-    acc.zero();
-    rg_mainloop_pre<Cfg, kOrderFree>(acc, la, lb, ra, rb, 0, a.nxp, lds, tid, wrow, wcol, lane);
-    // the next plane's first stage (the last plane reloads its own, unused) is loaded
-    // before this plane's epilogue, which hides its latency
-    lb.src = hsrc + ((size_t)(s * a.nz + min(zi + 1, z_end - 1)) * 3 + c) * hplane;
-    ra = la.load(0, tid);
-    rb = lb.load(0, tid);
-    // Per column block: the table cells of its 8 accumulator pairs (the lane's mirror
-    // cell, or cell 0 where the lane owns none: its p0 is zero there, so the product
-    // adds nothing) are all loaded before any is used.
-    const float2* Dz = a.D + (size_t)zi * npp;
+    __syncthreads();   // the chunk is in LDS, H of the plane before is consumed
+    add_plane();       // of the plane before, a share of it behind every matrix instruction
+    hx = zero;
+    hm = zero;
+    transform_y();
 #pragma unroll
-    for (int i = 0; i < Cfg::TM; ++i)
-#pragma unroll
-      for (int jj = 0; jj < Cfg::TN; ++jj) {
-        const int lf = (col0 + rg_col(wcol, jj, lane)) >> 2;
-        float2 dz[8];
-#pragma unroll
-        for (int r = 0; r < 16; r += 2) {
-          const int jf = (row0 + rg_row(wrow, i, r, lane)) >> 1;
-          const int jc = (q & 2) ? n - 1 - jf : jf, lc = (q & 1) ? n - 1 - lf : lf;
-          const bool own = jf < nh && lf < nh && !((q & 2) && jc == jf) && !((q & 1) && lc == lf);
-          dz[r >> 1] = Dz[own ? jc * a.w + lc : 0];
-        }
-#pragma unroll
-        for (int r = 0; r < 16; r += 2) {
-          // this lane holds row (jf, p = 0) in register r and (jf, 1) in r + 1, column q
-          const float x0 = acc.c[i][jj][r], x1 = acc.c[i][jj][r + 1];
-          // quad values: [q'] of register r -> C* , of register r + 1 -> S*
-          const float c0 = dpp<0x00>(x0), c1 = dpp<0x55>(x0), c2 = dpp<0xAA>(x0), c3 = dpp<0xFF>(x0);
-          const float s0 = dpp<0x00>(x1), s1 = dpp<0x55>(x1), s2 = dpp<0xAA>(x1), s3 = dpp<0xFF>(x1);
-          // CC = c0 + i c1, CS = c2 + i c3, SC = s0 + i s1, SS = s2 + i s3
-          const float sl = (q & 1) ? 1.f : -1.f;   // sign of i CS: - for lf, + for l'
-          const float sj = (q & 2) ? 1.f : -1.f;   // sign of i SC: - for jf, + for j'
-          const float ss = (q == 0 || q == 3) ? -1.f : 1.f;
-          // T = CC + sl i CS + sj i SC + ss SS;  G = i pref T (pref is in the x table)
-          const float tr = c0 - sl * c3 - sj * s1 + ss * s2;
-          const float ti = c1 + sl * c2 + sj * s0 + ss * s3;
-          const float gr = -ti, gi = tr;
-          const float2 d = dz[r >> 1];
-          const float2 pv = p0[i][jj][r >> 1];
-          const float pr = pv.x * d.x - pv.y * d.y, pi = pv.x * d.y + pv.y * d.x;
-          // Im(G conj(P~)) = Gi Pr - Gr Pi
-          dphi[i][jj][r >> 1] += gi * pr - gr * pi;
-        }
-      }
-  }
-  float* out = a.partial + (((size_t)(a.s0 + s) * 3 + c) * a.zgroups + g) * npp;
-#pragma unroll
-  for (int i = 0; i < Cfg::TM; ++i)
-#pragma unroll
-    for (int jj = 0; jj < Cfg::TN; ++jj) {
-      const int lf = (col0 + rg_col(wcol, jj, lane)) >> 2;
-#pragma unroll
-      for (int r = 0; r < 16; r += 2) {
-        const int jf = (row0 + rg_row(wrow, i, r, lane)) >> 1;
-        const int jc = (q & 2) ? n - 1 - jf : jf, lc = (q & 1) ? n - 1 - lf : lf;
-        const bool own = jf < nh && lf < nh && !((q & 2) && jc == jf) && !((q & 1) && lc == lf);
-        if (own) out[(size_t)jc * a.w + lc] = dphi[i][jj][r >> 1];
+    for (int g = 0; g < 12; ++g) {
+      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);   // LDS reads
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // matrix
+      __builtin_amdgcn_sched_group_barrier(0x002, 12, 0);  // vector
+    }
+    if constexpr (MULTI) {
+#pragma unroll 1
+      for (int nc = 1; nc < NC; ++nc) {
+        __syncthreads();
+        store(cur);
+        advance();
+        cur = load(zl, nl_c);
+        __syncthreads();
+        transform_y();
       }
     }
+    {
+      // lane half h holds the part ri = h of 16 consecutive m at column (hp, l32)
+      float v[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) v[r] = (hm[r] + hx[r]) * hscale;
+      uint4 piece[4];
+      hg_split16(v, piece);
+      uint4* o = Hs + (size_t)(4 * hb) * 128 + 32 * (2 * hp + h) + l32;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) o[i * 128] = piece[i];
+    }
+    __syncthreads();   // H is in LDS, the chunk is consumed
+    // the defocus before the next chunk: loads return in order
+    const float2* Dz = a.D + ((size_t)zi * nhp + (active ? jf0 : 0)) * nhp + lf;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) d[q] = Dz[(size_t)(4 * (q >> 1) + 2 * h + (q & 1)) * nhp];
+    e_acc = e_cur;
+    __builtin_amdgcn_sched_barrier(0);
+    e_cur = cur.e;
+    store(cur);   // after the last plane once more, unused
+    advance();
+    cur = load(zl, nl_c);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[j] = zero;
+    const hg8* bp = reinterpret_cast<const hg8*>(Hs) + l32;
+    const hg8* xp = reinterpret_cast<const hg8*>(Xs) + 32 * wave + l32;
+#pragma unroll
+    for (int k16 = 0; k16 < kAdjChunk / 16; ++k16) {
+      const hg8 xh = xp[(4 * k16 + h) * kAdjRows], xl = xp[(4 * k16 + 2 + h) * kAdjRows];
+      hg8 bh[4], bl[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        bh[j] = bp[(4 * k16 + h) * 128 + 32 * j];
+        bl[j] = bp[(4 * k16 + 2 + h) * 128 + 32 * j];
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(xh, bl[j], acc[j], 0, 0, 0);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(xl, bh[j], acc[j], 0, 0, 0);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(xh, bh[j], acc[j], 0, 0, 0);
+    }
+  }
+  add_plane();
+  if (!active) return;
+  const int nh = (a.n + 1) / 2;
+  const size_t npp = (size_t)a.w * a.w;
+  const float2* Pf = a.Pf + ((size_t)s * 3 + c) * npp;
+  float* out = a.partial + (((gs * 3 + c) * a.zgroups + zg) * MC + mc) * npp;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    const int jf = jf0 + 4 * (q >> 1) + 2 * h + (q & 1);
+    if (jf >= nh || lf >= nh) continue;
+    const int j1 = a.n - 1 - jf, l1 = a.n - 1 - lf;
+    // the pupil at mirror (a, b) from the four parities of the folded cell:
+    //   P_ab = sum_{pj, pl} (-1)^(a pj + b pl) (-i)^(pj + pl) Pf_{pj, pl}
+    // over 2 per folded axis with two mirrors (a self-mirrored row has no odd part), times the
+    // stack's own defocus
+    const float4 f0 = *reinterpret_cast<const float4*>(Pf + (size_t)(2 * jf) * a.w + 2 * lf);
+    const float4 f1 = *reinterpret_cast<const float4*>(Pf + (size_t)(2 * jf + 1) * a.w + 2 * lf);
+    const float scale = (jf != j1 ? 0.5f : 1.f) * (lf != l1 ? 0.5f : 1.f) * a.gexp;
+    float sn, cs;
+    sincosf((float)reduce_2pi(a.kszf[(size_t)jf * nhp + lf] * a.zoff[s]), &sn, &cs);
+    const float ccr = zacc[0][2 * q], cci = zacc[1][2 * q], scr = zacc[0][2 * q + 1], sci = zacc[1][2 * q + 1];
+    const float csr = zacc[2][2 * q], csi = zacc[3][2 * q], ssr = zacc[2][2 * q + 1], ssi = zacc[3][2 * q + 1];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      const float sb = (m & 1) ? -1.f : 1.f, sa = (m & 2) ? -1.f : 1.f;
+      const int jc = (m & 2) ? j1 : jf, lc = (m & 1) ? l1 : lf;
+      if (((m & 2) && jc == jf) || ((m & 1) && lc == lf)) continue;
+      // (-i) (x + i y) = y - i x
+      const float ur = scale * ((f0.x + sb * f0.w) + sa * (f1.y - sb * f1.z));
+      const float ui = scale * ((f0.y - sb * f0.z) - sa * (f1.x + sb * f1.w));
+      const float pr = ur * cs - ui * sn, pi = ur * sn + ui * cs;
+      // G = i T, T = CC - sb i CS - sa i SC - sa sb SS; Im(G conj(P~)) = Re(T) Pr + Im(T) Pi
+      const float tr = (ccr + sb * csi) + sa * (sci - sb * ssr);
+      const float ti = (cci - sb * csr) - sa * (scr + sb * ssi);
+      out[(size_t)jc * a.w + lc] = tr * pr + ti * pi;
+    }
+  }
 }
 
 // dL/dPhi on the N x N cells: the partials are summed in group order (FP64) in two
@@ -308,117 +426,124 @@ __global__ void adj_reduce_runs_kernel(const float* __restrict__ partial, int gr
   runs[(size_t)blockIdx.y * n * n + cell] = s;
 }
 
-__global__ void adj_reduce_kernel(const double* __restrict__ runs, int nruns, int n, double* __restrict__ dphi,
-                                  float* __restrict__ dW0) {
-  const int cell = blockIdx.x * blockDim.x + threadIdx.x;
-  if (cell >= n * n) return;
+// Second level, dL/dW0, and each workgroup's share of dL/dc_q = 2 pi sum_cells dL/dPhi Z_q
+// (a tree over the lanes, then the four waves in order).
+constexpr int kReduceThreads = 256;
+__global__ void __launch_bounds__(kReduceThreads) adj_reduce_kernel(const double* __restrict__ runs, int nruns, int n,
+                                                                    float* __restrict__ dW0,
+                                                                    const float* __restrict__ ztab, int n_zernike,
+                                                                    double* __restrict__ shares) {
+  __shared__ double red[RWPSF_MAX_ZERNIKE][kReduceThreads / 64];
+  const int nn = n * n, cell = blockIdx.x * kReduceThreads + threadIdx.x;
+  const bool in = cell < nn;
   double s = 0.0;
-  for (int r = 0; r < nruns; ++r) s += runs[(size_t)r * n * n + cell];
-  dphi[cell] = s;
-  if (dW0) dW0[cell] = (float)s;
-}
-
-// dL/dc_q = 2 pi sum_cells dL/dPhi Z_q: one workgroup of 1024 threads per q, fixed-shape tree.
-constexpr int kZernThreads = 1024;
-__global__ void __launch_bounds__(kZernThreads) adj_zernike_kernel(const double* __restrict__ dphi,
-                                                                   const float* __restrict__ ztab, int nn,
-                                                                   float* __restrict__ dc) {
-  __shared__ double red[kZernThreads];
-  const int q = blockIdx.x;
-  double s = 0.0;
-  for (int cell = threadIdx.x; cell < nn; cell += kZernThreads)
-    s += dphi[cell] * (double)ztab[(size_t)q * nn + cell];
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int w = kZernThreads / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
+  if (in) {
+#pragma unroll 8
+    for (int r = 0; r < nruns; ++r) s += runs[(size_t)r * nn + cell];
+    if (dW0) dW0[cell] = (float)s;
   }
-  if (threadIdx.x == 0) dc[q] = (float)(kTwoPi * red[0]);
+  for (int q0 = 0; q0 < n_zernike; q0 += 6) {   // six terms' loads and trees in flight
+    double v[6];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) v[i] = in ? s * (double)ztab[(size_t)min(q0 + i, n_zernike - 1) * nn + cell] : 0.0;
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1)
+#pragma unroll
+      for (int i = 0; i < 6; ++i) v[i] += __shfl_xor(v[i], d);
+    if ((threadIdx.x & 63) == 0)
+#pragma unroll
+      for (int i = 0; i < 6; ++i)
+        if (q0 + i < n_zernike) red[q0 + i][threadIdx.x >> 6] = v[i];
+  }
+  __syncthreads();
+  if ((int)threadIdx.x < n_zernike) {
+    const double* r = red[threadIdx.x];
+    shares[(size_t)threadIdx.x * gridDim.x + blockIdx.x] = (r[0] + r[1]) + (r[2] + r[3]);
+  }
 }
 
-hipError_t adjoint_kernel_attributes() {
-  hipError_t e = hipFuncSetAttribute((const void*)adj_h_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     CfgAdjH::LDS_BYTES);
-  if (e != hipSuccess) return e;
-  return hipFuncSetAttribute((const void*)adj_g_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             CfgAdjG::LDS_BYTES);
+// dL/dc_q from the shares: one workgroup per q, fixed-shape tree.  (One workgroup of 1024 per q
+// over all cells instead took 30 us at 256 x 256 cells; shares and this 9 with the reduction.)
+__global__ void __launch_bounds__(kReduceThreads) adj_zernike_kernel(const double* __restrict__ shares, int count,
+                                                                     float* __restrict__ dc) {
+  __shared__ double red[kReduceThreads / 64];
+  double v = 0.0;
+  for (int i = threadIdx.x; i < count; i += kReduceThreads) v += shares[(size_t)blockIdx.x * count + i];
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+  __syncthreads();
+  if (threadIdx.x == 0) dc[blockIdx.x] = (float)(kTwoPi * ((red[0] + red[1]) + (red[2] + red[3])));
+}
+
+// How a call is spread over workgroups.
+struct AdjSplit {
+  void (*k)(AdjArgs);
+  int row_groups, zgroups, zper, chunks_x;
+};
+static AdjSplit adjoint_split(const rwpsf_plan* p, int n) {
+  const int w = 2 * p->nhp, nz = p->grid.nz;
+  const int mc = (p->grid.nx + kAdjChunk - 1) / kAdjChunk, nc = (p->grid.ny + kAdjChunk - 1) / kAdjChunk;
+  AdjSplit r{nc > 1 ? adj_kernel<true> : adj_kernel<false>, (w + kAdjRows - 1) / kAdjRows, 1, nz, mc};
+  // Runs of planes: one workgroup fits a CU (256 of them), a plane takes a step per chunk along y
+  // and the pupil at the end of a run costs about three.  The shortest runs (they are summed in
+  // FP32, the partial sums in FP64) within 15% of the least number of rounds times length.
+  const long long base = (long long)std::min(n, kAdjStacks) * 3 * mc * r.row_groups * (w / (2 * kAdjCols));
+  auto cost = [&](int zper) {
+    return ((base * ((nz + zper - 1) / zper) + 255) / 256) * ((long long)zper * nc + 3);
+  };
+  long long best = cost(nz);
+  for (int zper = 1; zper < nz; ++zper) best = std::min(best, cost(zper));
+  for (r.zper = 1; 20 * cost(r.zper) > 23 * best;) ++r.zper;
+  r.zgroups = (nz + r.zper - 1) / r.zper;
+  return r;
 }
 
 // Lazily built adjoint tables and workspace of a Fourier plan.
-// Plane groups of adj_g: enough workgroups to fill the chip (>= 4 per CU of 256).
-static int adjoint_zgroups(const rwpsf_plan* p) {
-  const int tiles = (p->np / CfgAdjG::BM) * (2 * p->np / CfgAdjG::BN);
-  const int per_group = kAdjStacks * 3 * tiles;
-  return std::max(1, std::min(p->grid.nz, (1024 + per_group - 1) / per_group));
-}
-
-// Lazily built adjoint tables and workspace of a Fourier plan: the folded DFT tables with
-// the pixel index contiguous, CxT[2jf + p][m] = 2^e {cos, sin}(k s_jf x_m) and
-// CyT[2lf + p][n] = {cos, sin}(k s_lf y_n) (zero past nx, ny and for jf, lf >= N/2).
-// exp(i k s_z z) of every plan plane on the padded pupil cells (FP64 phase reduced
-// mod 2 pi before the FP32 sincos); 0 outside the disk where k s_z is 0 -> factor 1.
-__global__ void adj_defocus_kernel(const double* __restrict__ ksz, const double* __restrict__ z, int nz,
-                                   int npp, float2* __restrict__ D) {
-  const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (size_t)nz * npp) return;
-  const int zi = (int)(idx / npp), cell = (int)(idx % npp);
-  float sn, cs;
-  sincosf((float)reduce_2pi(ksz[cell] * z[zi]), &sn, &cs);
-  D[idx] = make_float2(cs, sn);
-}
-
-static int adjoint_prepare(rwpsf_plan* p, int n_stacks) {
-  const int nx = p->grid.nx, ny = p->grid.ny, N = p->num.n_pupil, np = p->np;
-  const int nxp = p->nxp, nyp = p->nyp, w = 2 * p->nhp, nh = (N + 1) / 2;
+static int adjoint_prepare(rwpsf_plan* p, int n_stacks, const AdjSplit& sp) {
+  const int nx = p->grid.nx, ny = p->grid.ny, nz = p->grid.nz, N = p->num.n_pupil, np = p->np;
+  const int nhp = p->nhp, w = 2 * nhp;
   int st;
-  if (!p->d_CxT) {
+  if (!p->d_adjTx) {
     const double s_max = p->s_max, k = p->k;
-    // G conj(P~) needs the prefactor f k / 2 pi once: the folded pupils carry its mantissa and
-    // 2^pf_exp, the table the powers of two
-    int pref_exp = 0;
-    std::frexp(p->opt.focal_length * k / kTwoPi, &pref_exp);
-    const double pref = std::ldexp(1.0, pref_exp - p->pf_exp);
-    std::vector<float> CxT((size_t)w * nxp, 0.f), CyT((size_t)w * nyp, 0.f);
-    for (int f = 0; f < nh; ++f) {
-      const double sv = (2.0 * f + 1.0 - N) * s_max / N;
-      for (int m = 0; m < nx; ++m) {
-        const double ph = k * sv * (double)(m - nx / 2) * p->grid.dx_nm;
-        CxT[(size_t)(2 * f) * nxp + m] = (float)(pref * std::cos(ph));
-        CxT[(size_t)(2 * f + 1) * nxp + m] = (float)(pref * std::sin(ph));
-      }
-      for (int n = 0; n < ny; ++n) {
-        const double ph = k * sv * (double)(n - ny / 2) * p->grid.dy_nm;
-        CyT[(size_t)(2 * f) * nyp + n] = (float)std::cos(ph);
-        CyT[(size_t)(2 * f + 1) * nyp + n] = (float)std::sin(ph);
-      }
-    }
-    if ((st = dev_alloc(p, &p->d_CxT, CxT.size()))) return st;
-    if ((st = dev_alloc(p, &p->d_CyT, CyT.size()))) return st;
-    if ((st = dev_alloc(p, &p->d_dphi, (size_t)N * N))) return st;
-    if ((st = dev_alloc(p, &p->d_H, (size_t)kAdjStacks * p->grid.nz * 3 * nxp * w))) return st;
-    // folded pupils of a whole adjoint group
+    uint4 *tx = nullptr, *ty = nullptr;
+    if ((st = dev_alloc(p, &tx, hg_panel_bytes(nx, w) / sizeof(uint4)))) return st;
+    if ((st = dev_alloc(p, &ty, hg_panel_bytes(ny, w) / sizeof(uint4)))) return st;
+    if ((st = dev_alloc(p, &p->d_shares, (size_t)RWPSF_MAX_ZERNIKE * ((N * N + kReduceThreads - 1) / kReduceThreads))))
+      return st;
+    // folded pupils of a whole launch
     if ((st = dev_alloc(p, &p->d_adjPf, (size_t)kAdjStacks * 3 * w * w))) return st;
-    const size_t nzpp = (size_t)p->grid.nz * np * np;
-    if ((st = dev_alloc(p, &p->d_adjD, nzpp))) return st;
-    hipLaunchKernelGGL(adj_defocus_kernel, dim3((unsigned)((nzpp + 255) / 256)), dim3(256), 0, 0, p->d_ksz, p->d_z,
-                       p->grid.nz, np * np, p->d_adjD);
+    const size_t cells = (size_t)nhp * nhp;
+    if ((st = dev_alloc(p, &p->d_adjD, nz * cells))) return st;
+    hipLaunchKernelGGL(adj_panel_kernel, dim3((nx * nhp + 255) / 256), dim3(256), 0, 0, (_Float16*)tx, nx, N, w, k,
+                       s_max, p->grid.dx_nm, 0);
+    hipLaunchKernelGGL(adj_panel_kernel, dim3((ny * nhp + 255) / 256), dim3(256), 0, 0, (_Float16*)ty, ny, N, w, k,
+                       s_max, p->grid.dy_nm, 1);
+    hipLaunchKernelGGL(adj_defocus_kernel, dim3((unsigned)((nz * cells + 255) / 256)), dim3(256), 0, 0, p->d_kszf,
+                       p->d_z, nz, (int)cells, p->d_adjD);
     if ((st = hip_check(hipGetLastError()))) return st;
-    // the table is written on the null stream; the caller's stream may not order after it
+    // the tables are written on the null stream; the caller's stream may not order after it
     if ((st = hip_check(hipDeviceSynchronize()))) return st;
-    if ((st = hip_check(hipMemcpy(p->d_CxT, CxT.data(), CxT.size() * sizeof(float), hipMemcpyHostToDevice)))) return st;
-    if ((st = hip_check(hipMemcpy(p->d_CyT, CyT.data(), CyT.size() * sizeof(float), hipMemcpyHostToDevice)))) return st;
-    if ((st = hip_check(adjoint_kernel_attributes()))) return st;
+    if ((st = hip_check(hipFuncSetAttribute((const void*)sp.k, hipFuncAttributeMaxDynamicSharedMemorySize, kAdjLds))))
+      return st;
+    p->d_adjTy = ty;
+    p->d_adjTx = tx;
   }
-  const int groups = 3 * n_stacks * adjoint_zgroups(p);
+  if (p->adj_stacks < n_stacks) {
+    int* d = nullptr;
+    if ((st = dev_alloc(p, &d, (size_t)n_stacks * nz * 3))) return st;
+    p->d_adjEx = d;
+    p->adj_stacks = n_stacks;
+  }
+  const int groups = 3 * n_stacks * sp.zgroups * sp.chunks_x;
   if (p->partial_groups < groups) {
     float* d = nullptr;
     if ((st = dev_alloc(p, &d, (size_t)groups * np * np))) return st;
-    p->d_partial = d;
-    p->partial_groups = groups;
     double* r = nullptr;
     if ((st = dev_alloc(p, &r, (size_t)((groups + kReduceRun - 1) / kReduceRun) * N * N))) return st;
+    p->d_partial = d;
     p->d_runs = r;
+    p->partial_groups = groups;
   }
   return RWPSF_OK;
 }
@@ -426,56 +551,64 @@ static int adjoint_prepare(rwpsf_plan* p, int n_stacks) {
 int fourier_adjoint(rwpsf_plan* p, int n, const rwpsf_stack* s, const float2* E, const float* dLdI,
                     int n_zernike, float* dc, float* dW0, hipStream_t st) {
   const int nx = p->grid.nx, ny = p->grid.ny, nz = p->grid.nz, N = p->num.n_pupil, np = p->np;
-  if (nx % 16 || ny % 16) return RWPSF_ERR_UNSUPPORTED;   // whole MFMA k-stages along x and y
-  int rc = adjoint_prepare(p, n);
+  if (nx % 16 || ny % 16) return RWPSF_ERR_UNSUPPORTED;   // whole MFMA k-steps along x and y
+  const AdjSplit sp = adjoint_split(p, n);
+  int rc = adjoint_prepare(p, n, sp);
   if (rc) return rc;
-  const int nxp = p->nxp, w = 2 * p->nhp;
-  const int zg = adjoint_zgroups(p);
+  const int w = 2 * p->nhp;
+  int tr = p->time_begin(RWPSF_KERNEL_ADJ_H, st);
+  hipLaunchKernelGGL(adj_scale_kernel, dim3((unsigned)(n * nz)), dim3(256), 0, st, E, dLdI, nx * ny, p->d_adjEx);
+  if ((rc = hip_check(hipGetLastError()))) return rc;
+  p->time_end(tr, st);
   for (int b0 = 0; b0 < n; b0 += kAdjStacks) {
     const int nb = std::min(kAdjStacks, n - b0);
-    for (int c0 = 0; c0 < nb; c0 += kPupilStacks)
-      if ((rc = fourier_build_folded(p, s + b0 + c0, std::min(kPupilStacks, nb - c0),
-                                     p->d_adjPf + (size_t)c0 * 3 * w * w, st)))
-        return rc;
-    AdjHArgs ha{E, dLdI, p->d_CyT, p->d_H, b0, nb, nz, nx, ny, p->nyp, nxp, w};
-    const int hblocks = nb * nz * 3 * (2 * nxp / CfgAdjH::BM) * (w / CfgAdjH::BN);
-    int tr = p->time_begin(RWPSF_KERNEL_ADJ_H, st);
-    hipLaunchKernelGGL(adj_h_kernel, dim3(hblocks), dim3(CfgAdjH::NT), CfgAdjH::LDS_BYTES, st, ha);
-    if ((rc = hip_check(hipGetLastError()))) return rc;
-    p->time_end(tr, st);
-    AdjGArgs ga{};
-    ga.CxT = p->d_CxT;
-    ga.H = p->d_H;
-    ga.Pf = p->d_adjPf;
-    ga.ksz = p->d_ksz;
-    ga.D = p->d_adjD;
-    ga.partial = p->d_partial;
-    for (int i = 0; i < nb; ++i) ga.zoff[i] = s[b0 + i].z_offset_nm;
-    ga.s0 = b0;
-    ga.nstk = nb;
-    ga.nz = nz;
-    ga.nxp = nxp;
-    ga.w = w;
-    ga.n = N;
-    ga.zgroups = zg;
-    ga.zper = (nz + zg - 1) / zg;
-    const int gblocks = nb * 3 * zg * (w / CfgAdjG::BM) * (2 * w / CfgAdjG::BN);
+    if ((rc = fourier_build_folded(p, s + b0, nb, p->d_adjPf, st))) return rc;
+    AdjArgs a{};
+    a.E = E;
+    a.g = dLdI;
+    a.ex = p->d_adjEx;
+    a.X = p->d_adjTx;
+    a.Y = p->d_adjTy;
+    a.D = p->d_adjD;
+    a.Pf = p->d_adjPf;
+    a.kszf = p->d_kszf;
+    a.partial = p->d_partial;
+    for (int i = 0; i < nb; ++i) a.zoff[i] = s[b0 + i].z_offset_nm;
+    a.s0 = b0;
+    a.nstk = nb;
+    a.nz = nz;
+    a.nx = nx;
+    a.ny = ny;
+    a.w = w;
+    a.n = N;
+    a.row_groups = sp.row_groups;
+    a.zgroups = sp.zgroups;
+    a.zper = sp.zper;
+    // |H 2^(e + kTabExp)| <= ny 2^14 2^kTabExp is stored below 2^15
+    a.hshift = kTabExp - 1;
+    while ((1 << (a.hshift - kTabExp + 1)) < ny) ++a.hshift;
+    // G conj(P~) needs the prefactor f k / 2 pi once: the folded pupils carry its mantissa and
+    // 2^pf_exp
+    int pref_exp = 0;
+    std::frexp(p->opt.focal_length * p->k / kTwoPi, &pref_exp);
+    a.gexp = std::ldexp(1.f, pref_exp - p->pf_exp);
+    const int blocks = nb * 3 * sp.zgroups * sp.chunks_x * sp.row_groups * (w / (2 * kAdjCols));
     tr = p->time_begin(RWPSF_KERNEL_ADJ_G, st);
-    hipLaunchKernelGGL(adj_g_kernel, dim3(gblocks), dim3(CfgAdjG::NT), CfgAdjG::LDS_BYTES, st, ga);
+    hipLaunchKernelGGL(sp.k, dim3(blocks), dim3(kAdjThreads), kAdjLds, st, a);
     if ((rc = hip_check(hipGetLastError()))) return rc;
     p->time_end(tr, st);
   }
-  int tr = p->time_begin(RWPSF_KERNEL_ADJ_REDUCE, st);
-  const int groups = 3 * n * zg, nruns = (groups + kReduceRun - 1) / kReduceRun;
+  tr = p->time_begin(RWPSF_KERNEL_ADJ_REDUCE, st);
+  const int groups = 3 * n * sp.zgroups * sp.chunks_x, nruns = (groups + kReduceRun - 1) / kReduceRun;
   hipLaunchKernelGGL(adj_reduce_runs_kernel, dim3((N * N + 255) / 256, nruns), dim3(256), 0, st, p->d_partial,
                      groups, N, np, p->d_runs);
   if ((rc = hip_check(hipGetLastError()))) return rc;
-  hipLaunchKernelGGL(adj_reduce_kernel, dim3((N * N + 255) / 256), dim3(256), 0, st, p->d_runs, nruns, N,
-                     p->d_dphi, dW0);
+  const int rblocks = (N * N + kReduceThreads - 1) / kReduceThreads;
+  hipLaunchKernelGGL(adj_reduce_kernel, dim3(rblocks), dim3(kReduceThreads), 0, st, p->d_runs, nruns, N, dW0, p->d_ztab,
+                     n_zernike, p->d_shares);
   if ((rc = hip_check(hipGetLastError()))) return rc;
   if (n_zernike > 0) {
-    hipLaunchKernelGGL(adj_zernike_kernel, dim3(n_zernike), dim3(kZernThreads), 0, st, p->d_dphi, p->d_ztab, N * N,
-                       dc);
+    hipLaunchKernelGGL(adj_zernike_kernel, dim3(n_zernike), dim3(kReduceThreads), 0, st, p->d_shares, rblocks, dc);
     if ((rc = hip_check(hipGetLastError()))) return rc;
   }
   p->time_end(tr, st);

@@ -245,16 +245,6 @@ __global__ void __launch_bounds__(256) bessel_contract_kernel(const float* __res
   }
 }
 
-// C[M x N] (row stride ldc) = A^T B with A [K][lda], B [K][ldb]; also the batched
-// per-emitter phase GEMM.
-hipError_t launch_rgemm(const float* A, int lda, const float* B, int ldb, float* C, int ldc, int M,
-                        int N, int K, hipStream_t st) {
-  const int blocks = ((M + RBM - 1) / RBM) * ((N + RBN - 1) / RBN);
-  hipLaunchKernelGGL(bessel_contract_kernel, dim3(blocks), dim3(256), 0, st, A, lda, B, ldb, C, ldc, M,
-                     N, K);
-  return hipGetLastError();
-}
-
 // --------------------------------------------------------------------------
 // Radial epilogue: one workgroup per (stack, plane).  The GEMM rows of this plane,
 // (variant, re/im) x [G][R], are combined into I_n and staged in LDS as

@@ -183,14 +183,15 @@ struct rwpsf_plan {
   uint4* d_T = nullptr;         // workspace [planes][3] split-f16 panels of 2 nyp rows 2n + ri, k = q
   size_t T_planes = 0;          // capacity of d_T in stack-planes
   // adjoint (built on first use)
-  float* d_CxT = nullptr;       // [2 nhp][nxp] folded x table (prefactor included), pixels contiguous
-  float* d_CyT = nullptr;       // [2 nhp][nyp] folded y table, pixels contiguous
-  float2* d_H = nullptr;        // [32 stacks][nz][3][nxp][2 nhp] folded H
-  float2* d_adjPf = nullptr;    // [32 stacks][3][2 nhp][2 nhp] folded pupils of an adjoint group
-  float* d_partial = nullptr;   // [stacks * 3][np][np] per-(stack, component) dL/dPhi
+  uint4* d_adjTx = nullptr;     // split-f16 panel of 2 nhp columns 2jf + p, k = x pixel
+  uint4* d_adjTy = nullptr;     // split-f16 panel of 2 nhp columns 64 (lf / 32) + 32 p + lf % 32, k = y pixel
+  int* d_adjEx = nullptr;       // [adj_stacks][nz][3] power-of-two scales of 2 dL/dI E
+  int adj_stacks = 0;
+  float2* d_adjPf = nullptr;    // [64 stacks][3][2 nhp][2 nhp] folded pupils of an adjoint launch
+  float* d_partial = nullptr;   // [groups][np][np] per-(stack, component, run of planes, part) dL/dPhi
   int partial_groups = 0;
-  double* d_dphi = nullptr;     // [N][N]
-  float2* d_adjD = nullptr;     // [nz][np][np] exp(i k s_z z) of the plan's planes
+  double* d_shares = nullptr;   // [RWPSF_MAX_ZERNIKE][workgroups of the reduction] shares of dL/dc
+  float2* d_adjD = nullptr;     // [nz][nhp][nhp] exp(i k s_z z) of the plan's planes on the folded cells
   double* d_runs = nullptr;     // [partial runs][N][N] first level of the dL/dPhi reduction
   int P_stacks = 0;             // capacity of d_P in stacks
 
