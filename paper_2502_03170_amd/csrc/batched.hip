@@ -736,7 +736,8 @@ int rwpsf_batch_create(const rwpsf_optics* o, int n_pupil, double pixel_nm, doub
   const PupilScales ps = pupil_scales(Q, 3, N, N, bound.empty() ? nullptr : bound.data(), pref_exp);
   b->tscale = ps.tscale;
   b->escale = ps.escale;
-  for (float2& q : Q) q = make_float2(std::ldexp(q.x, ps.pf_exp), std::ldexp(q.y, ps.pf_exp));
+  const double sc = std::ldexp(1.0, ps.pf_exp);
+  for (float2& q : Q) q = make_float2((float)(sc * q.x), (float)(sc * q.y));
   b->upload_bytes = upload_size(b);
   int rc;
   if ((rc = balloc(b, &b->d_Q, 3 * NN)) || (rc = balloc(b, &b->d_ksz, NN)) ||

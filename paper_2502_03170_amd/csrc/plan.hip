@@ -32,19 +32,24 @@ PupilScales pupil_scales(const std::vector<float2>& Q, int nc, int N, int np, co
   const int nh = (N + 1) / 2;
   const size_t npp = (size_t)np * np;
   double cell_max = 0.0, row_max = 0.0;
+  std::vector<double> m(N);   // one row of bounds and its mirror, added (plain loops over rows)
   for (int c = 0; c < nc; ++c)
     for (int jf = 0; jf < nh; ++jf) {
+      const size_t r0 = (size_t)jf * np, r1 = (size_t)(N - 1 - jf) * np;
+      const float2 *q0 = Q.data() + c * npp + r0, *q1 = Q.data() + c * npp + r1;
+      if (amplitude) {
+        for (int l = 0; l < N; ++l)
+          m[l] = ((double)std::fabs(q0[l].x) + std::fabs(q0[l].y)) * amplitude[r0 + l] +
+                 ((double)std::fabs(q1[l].x) + std::fabs(q1[l].y)) * amplitude[r1 + l];
+      } else {
+        for (int l = 0; l < N; ++l)
+          m[l] = ((double)std::fabs(q0[l].x) + std::fabs(q0[l].y)) + ((double)std::fabs(q1[l].x) + std::fabs(q1[l].y));
+      }
       double row = 0.0;
       for (int lf = 0; lf < nh; ++lf) {
-        double m = 0.0;
-        for (int j : {jf, N - 1 - jf})
-          for (int l : {lf, N - 1 - lf}) {
-            const size_t cell = (size_t)j * np + l;
-            const float2 q = Q[c * npp + cell];
-            m += (std::fabs((double)q.x) + std::fabs((double)q.y)) * (amplitude ? amplitude[cell] : 1.0);
-          }
-        cell_max = std::max(cell_max, m);
-        row += 2.0 * m;
+        const double cell = m[lf] + m[N - 1 - lf];
+        cell_max = std::max(cell_max, cell);
+        row += 2.0 * cell;
       }
       row_max = std::max(row_max, row);
     }
@@ -97,7 +102,8 @@ static int fourier_plan_init(rwpsf_plan* p) {
     p->pf_exp = ps.pf_exp;
     p->tscale = ps.tscale;
     p->escale = ps.escale;
-    for (float2& q : Q) q = make_float2(std::ldexp(q.x, ps.pf_exp), std::ldexp(q.y, ps.pf_exp));
+    const double sc = std::ldexp(1.0, ps.pf_exp);
+    for (float2& q : Q) q = make_float2((float)(sc * q.x), (float)(sc * q.y));
   }
   int st;
   if ((st = dev_alloc(p, &p->d_Q, 3 * npp))) return st;
