@@ -27,6 +27,7 @@
 #include <complex>
 #include <vector>
 
+#include "hgemm.h"
 #include "rw_common.h"
 #include "rw_fourier.h"
 #include "rw_plan.h"
@@ -212,8 +213,7 @@ __device__ __forceinline__ void czt_fft_reg(float2* buf, float2 (&v)[L / 64], in
 }
 // v: in x (already multiplied by the pre-chirp), out conj(FFT(conj(FFT(x) chat)))
 template <int L>
-__device__ __forceinline__ void czt_pair_reg(float2* buf, float2 (&v)[L / 64], const float2* __restrict__ chat,
-                                             int lane) {
+__device__ __forceinline__ void czt_pair_reg(float2* buf, float2 (&v)[L / 64], const float2* __restrict__ chat, int lane) {
   // at L = 512 the lane's spectrum factors are requested before the first transform (16
   // registers); the longer transforms have no registers to spare and read them after it
   constexpr int CH = L == 512 ? L / 64 : 1;
@@ -324,76 +324,94 @@ struct CztColArgs {
   const float2* chat;    // [L]
   float2* E;             // [stacks][nz][nc][nx][ny] or null
   float* I;              // [stacks][nz][nx][ny] or null
-  int n, nx, ny, nz, cb, nstk, s_base, z0, nzs, nc;
+  int n, nx, ny, nz, cb, stride, nstk, s_base, z0, nzs, nc;   // stride: column stride in LDS
 };
 
+// Waves of the column kernel: eight where a transform of the wave fits 128 registers, so that
+// two workgroups give a SIMD four waves.
 template <int L>
-__global__ void __launch_bounds__(256) czt_cols_kernel(CztColArgs a) {
+constexpr int czt_col_waves() { return L <= 512 ? 8 : 4; }
+// Column stride in LDS, in complex entries: a column is read and written along itself, and the
+// block's rows across the CB columns, so a stride of 64 / CB modulo 32 puts the 64 lanes of a row
+// access in distinct banks.
+static int czt_col_stride(int cb, int N, int nx) {
+  const int n = std::max(N, nx), want = 64 / cb % 32;
+  return n + ((want - n) % 32 + 32) % 32;
+}
+
+// CB columns per workgroup, transformed in place.  Neighbouring blocks of columns share cache
+// lines of T and E, so they run on one XCD.  Bound by the vector units (104 of 160 us at their
+// full rate) and by the phases of a workgroup, which only the other one of its CU fills.  256 x
+// 128 inputs, 128 x 128 outputs, 256 planes of three components: 250 us with four waves, input and
+// output columns side by side and strides of N and nx (a row access met one bank in 16 lanes),
+// 169 us so.  The next channel's T in registers spilled (209); twiddles kept from pass to pass 166.
+template <int L>
+__global__ void __launch_bounds__(64 * czt_col_waves<L>(), L <= 512 ? 4 : (L == 1024 ? 2 : 1)) czt_cols_kernel(CztColArgs a) {
+  constexpr int NT = 64 * czt_col_waves<L>();
   extern __shared__ float2 cbuf[];
   const int CB = a.cb;
   const int cblocks = (a.ny + CB - 1) / CB;
-  int id = blockIdx.x;
+  int id = xcd_remap(blockIdx.x, gridDim.x);
   const int cbk = id % cblocks; id /= cblocks;
   const int zi = id % a.nzs;
   const int s = id / a.nzs;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int n0 = cbk * CB;
-  float2* stage = cbuf;                    // [CB][N]: the block's T columns
-  float2* outs = stage + CB * a.n;         // [CB][nx]: transformed columns
-  float2* buf = outs + CB * a.nx + wave * padded<L>();
-  float* isum = reinterpret_cast<float*>(outs + CB * a.nx + 4 * padded<L>());   // [nx * CB] sum_c |E_c|^2
+  const int S = a.stride;
+  float2* cols = cbuf;                     // [CB][S]: the block's T columns, then its output columns
+  float2* buf = cols + CB * S + wave * padded<L>();
+  float* isum = reinterpret_cast<float*>(cols + CB * S + czt_col_waves<L>() * padded<L>());   // [nx * CB] sum_c |E_c|^2
   const size_t gstk = (size_t)(a.s_base + s), gz = (size_t)(a.z0 + zi);
   const size_t plane = (size_t)a.nx * a.ny;
-  for (int idx = tid; idx < a.nx * CB; idx += 256) isum[idx] = 0.f;
+  const int lcb = __ffs(CB) - 1;   // CB is 4, 8 or 16
+  for (int idx = tid; idx < a.nx * CB; idx += NT) isum[idx] = 0.f;
   for (int c = 0; c < a.nc; ++c) {
     const float2* Tc = a.T + (((size_t)s * a.nzs + zi) * a.nc + c) * (size_t)a.n * a.ny;
-    for (int idx = tid; idx < a.n * CB; idx += 256) {
-      const int j = idx / CB, cc = idx % CB;
-      stage[cc * a.n + j] = (n0 + cc < a.ny) ? Tc[(size_t)j * a.ny + n0 + cc] : make_float2(0.f, 0.f);
+    for (int idx = tid; idx < a.n * CB; idx += NT) {
+      const int j = idx >> lcb, cc = idx & (CB - 1);
+      cols[cc * S + j] = (n0 + cc < a.ny) ? Tc[(size_t)j * a.ny + n0 + cc] : make_float2(0.f, 0.f);
     }
     __syncthreads();
-    if constexpr (czt_reg_ok<L>()) {
-      constexpr int U = L / 64;
-      for (int q = 0; q < CB / 4; ++q) {
-        const int cc = 4 * q + wave;
+    for (int cc = wave; cc < CB; cc += czt_col_waves<L>()) {
+      float2* col = cols + cc * S;
+      if constexpr (czt_reg_ok<L>()) {
+        constexpr int U = L / 64;
         float2 v[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           const int j = lane + 64 * u;
-          v[u] = j < a.n ? cmul(stage[cc * a.n + j], a.pre[j]) : make_float2(0.f, 0.f);
+          v[u] = j < a.n ? cmul(col[j], a.pre[j]) : make_float2(0.f, 0.f);
         }
         czt_pair_reg<L>(buf, v, a.chat, lane);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           const int m = lane + 64 * u;
-          if (m < a.nx) outs[cc * a.nx + m] = cmul(make_float2(v[u].x, -v[u].y), a.post[m]);
+          if (m < a.nx) col[m] = cmul(make_float2(v[u].x, -v[u].y), a.post[m]);
         }
+      } else {
+        for (int j = lane; j < L; j += 64)
+          buf[pidx(j)] = j < a.n ? cmul(col[j], a.pre[j]) : make_float2(0.f, 0.f);
+        wave_lds_order();
+        fft<L>(buf, lane);
+        for (int f = lane; f < L; f += 64) {
+          const float2 v = cmul(buf[pidx(f)], a.chat[f]);
+          buf[pidx(f)] = make_float2(v.x, -v.y);
+        }
+        wave_lds_order();
+        fft<L>(buf, lane);
+        for (int m = lane; m < a.nx; m += 64) {
+          const float2 b = buf[pidx(m)];
+          col[m] = cmul(make_float2(b.x, -b.y), a.post[m]);
+        }
+        wave_lds_order();
       }
-    } else
-    for (int r = 0; r < CB / 4; ++r) {
-      const int cc = 4 * r + wave;
-      for (int j = lane; j < L; j += 64)
-        buf[pidx(j)] = j < a.n ? cmul(stage[cc * a.n + j], a.pre[j]) : make_float2(0.f, 0.f);
-      wave_lds_order();
-      fft<L>(buf, lane);
-      for (int f = lane; f < L; f += 64) {
-        const float2 v = cmul(buf[pidx(f)], a.chat[f]);
-        buf[pidx(f)] = make_float2(v.x, -v.y);
-      }
-      wave_lds_order();
-      fft<L>(buf, lane);
-      for (int m = lane; m < a.nx; m += 64) {
-        const float2 b = buf[pidx(m)];
-        outs[cc * a.nx + m] = cmul(make_float2(b.x, -b.y), a.post[m]);
-      }
-      wave_lds_order();
     }
-    __syncthreads();   // every wave's columns are in outs
+    __syncthreads();   // every wave's columns are transformed
     // rows of E from LDS: CB consecutive columns per row
     float2* Ec = a.E ? a.E + ((gstk * a.nz + gz) * a.nc + c) * plane : nullptr;
-    for (int idx = tid; idx < a.nx * CB; idx += 256) {   // each thread keeps its own entries
-      const int m = idx / CB, cc = idx % CB;
-      const float2 v = outs[cc * a.nx + m];
+    for (int idx = tid; idx < a.nx * CB; idx += NT) {   // each thread keeps its own entries
+      const int m = idx >> lcb, cc = idx & (CB - 1);
+      const float2 v = cols[cc * S + m];
       isum[idx] += v.x * v.x + v.y * v.y;
       if (Ec && n0 + cc < a.ny) Ec[(size_t)m * a.ny + n0 + cc] = v;
     }
@@ -401,8 +419,8 @@ __global__ void __launch_bounds__(256) czt_cols_kernel(CztColArgs a) {
   }
   if (a.I) {
     float* Ip = a.I + (gstk * a.nz + gz) * plane;
-    for (int idx = tid; idx < a.nx * CB; idx += 256) {
-      const int m = idx / CB, cc = idx % CB;
+    for (int idx = tid; idx < a.nx * CB; idx += NT) {
+      const int m = idx >> lcb, cc = idx & (CB - 1);
       if (n0 + cc < a.ny) Ip[(size_t)m * a.ny + n0 + cc] = isum[idx];
     }
   }
@@ -411,9 +429,16 @@ __global__ void __launch_bounds__(256) czt_cols_kernel(CztColArgs a) {
 // --------------------------------------------------------------------------
 // Plan tables (FP64 on the host) and dispatch
 // --------------------------------------------------------------------------
-// LDS of the column kernel: T columns, transformed columns, 4 FFT buffers, |E|^2 sums
-static size_t czt_cols_lds(int cb, int N, int nx, int L) {
-  return (size_t)(cb * N + cb * nx + 4 * (L + L / 8)) * sizeof(float2) + (size_t)nx * cb * sizeof(float);
+// LDS of the column kernel: columns, an FFT buffer per wave, |E|^2 sums
+static size_t czt_cols_lds(int cb, int stride, int nx, int L) {
+  const int waves = L <= 512 ? czt_col_waves<512>() : czt_col_waves<1024>();
+  return (size_t)(cb * stride + waves * (L + L / 8)) * sizeof(float2) +
+         (size_t)nx * cb * sizeof(float);
+}
+// The envelope: plans whose four columns of the x pass would not fit LDS with input and output
+// columns side by side and four FFT buffers.
+static bool czt_unsupported(int N, int nx, int L) {
+  return (size_t)(4 * N + 4 * nx + 4 * (L + L / 8)) * sizeof(float2) + (size_t)nx * 4 * sizeof(float) > 160 * 1024;
 }
 
 // The limit belongs to the kernel, not to a plan: the column kernel's LDS depends on the
@@ -471,8 +496,11 @@ int czt_plan_init(rwpsf_plan* p) {
   p->czt_Lx = Lx;
   // columns per workgroup of the column pass: as many as fit 2 workgroups per CU, down to 4
   int cb = 16;
-  while (cb > 4 && czt_cols_lds(cb, N, nx, Lx) > 80 * 1024) cb /= 2;
-  if (czt_cols_lds(cb, N, nx, Lx) > 160 * 1024) return RWPSF_ERR_UNSUPPORTED;
+  while (cb > 4 && czt_cols_lds(cb, czt_col_stride(cb, N, nx), nx, Lx) > 80 * 1024) cb /= 2;
+  int stride = czt_col_stride(cb, N, nx);
+  if (czt_cols_lds(cb, stride, nx, Lx) > 160 * 1024) stride = std::max(N, nx);   // no room for the padding
+  if (czt_unsupported(N, nx, Lx)) return RWPSF_ERR_UNSUPPORTED;
+  p->czt_stride = stride;
   p->czt_cb = cb;
   const size_t tables = (size_t)N + ny + Ly + N + nx + Lx;
   int st;
@@ -512,7 +540,7 @@ static void launch_rows(const CztRowArgs& a, int blocks, hipStream_t st) {
 }
 template <int L>
 static void launch_cols(const CztColArgs& a, int blocks, size_t lds, hipStream_t st) {
-  hipLaunchKernelGGL(czt_cols_kernel<L>, dim3(blocks), dim3(256), lds, st, a);
+  hipLaunchKernelGGL(czt_cols_kernel<L>, dim3(blocks), dim3(64 * czt_col_waves<L>()), lds, st, a);
 }
 static int czt_slab(rwpsf_plan* p, int s_local, int ns, const double* zoff, int s_global, int z0, int nzs, float2* E,
                     float* I, hipStream_t st) {
@@ -560,12 +588,13 @@ static int czt_slab(rwpsf_plan* p, int s_local, int ns, const double* zoff, int 
   ca.ny = ny;
   ca.nz = p->grid.nz;
   ca.cb = p->czt_cb;
+  ca.stride = p->czt_stride;
   ca.nc = p->nc;
   ca.nstk = ns;
   ca.s_base = s_global;
   ca.z0 = z0;
   ca.nzs = nzs;
-  const size_t lds = czt_cols_lds(ca.cb, N, nx, p->czt_Lx);
+  const size_t lds = czt_cols_lds(ca.cb, ca.stride, nx, p->czt_Lx);
   const int cblocks = ns * nzs * ((ny + ca.cb - 1) / ca.cb);
   tr = p->time_begin(RWPSF_KERNEL_CZT_COLS, st);
 #define RW_COLS(LL) launch_cols<LL>(ca, cblocks, lds, st)
