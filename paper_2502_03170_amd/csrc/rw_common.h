@@ -210,6 +210,9 @@ struct rwpsf_plan {
   double* d_node = nullptr;     // [T][4] Bessel form: sin, cos, stack-independent amplitude, k cos of each node
   int bessel_mode = 0;          // 0 vectorial, 1 vectorial with Fresnel factors, 2 scalar
   float* d_btab = nullptr;      // [T][G][R] w_t h_g(t) J_{n_g}(k rho_r sin t)
+  uint4* d_bpanel = nullptr;    // d_btab as a split-f16 panel of btab_ld columns, times 2^tab_exp
+  int btab_ld = 0, tab_exp = 0;
+  int phi_exp = 0;              // Phi is split after multiplication by 2^phi_exp
   double* d_fq = nullptr;       // [T][4] Fresnel products q_s, q_p per node (Fresnel mode)
   float2* d_phi = nullptr;      // workspace [T][stacks][nz][V] pupil x defocus (x q_v)
   float2* d_In = nullptr;       // workspace [stacks][nz][V][re/im][G][R]
@@ -219,7 +222,9 @@ struct rwpsf_plan {
   double drho = 0;              // radial sample pitch
   // Bessel-form adjoint (built on first use)
   float* d_btabT = nullptr;     // [G][R][T] transposed table
-  float* d_GInT = nullptr;      // workspace [G][R][2 stacks nz V] gradients of the radial samples
+  uint4* d_bpanelT = nullptr;   // the same as a split-f16 panel
+  int* d_GInEx = nullptr;       // [stacks nz V] exponents of the row pairs of G_In
+  float* d_GIn = nullptr;       // workspace [2 stacks nz V][G][R] gradients of the radial samples
   float* d_GPhi = nullptr;      // workspace [2 stacks nz V][T] gradient of Phi
   double2* d_adjX = nullptr;    // workspace [stacks][T] sum_z conj(G_Phi) Phi
   double* d_adjnode = nullptr;  // [T][7] k cos t, dW/dt_s (re, im), 2 pi Z_{1,4,11,22}
