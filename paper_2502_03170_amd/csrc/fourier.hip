@@ -469,6 +469,66 @@ __global__ void __launch_bounds__(Cfg::NT, OCC) gemm_image_kernel(Gemm2Args a) {
   }
 }
 
+// K3 for launches of few tiles: the channels side by side in a workgroup, four waves and stage
+// buffers each, instead of one after the other; |E_c|^2 meet in LDS and are added in channel
+// order.  Such a launch is a chain of K / 32 stages on a part of the CUs: one 201 x 201 image on a
+// 256 x 256 pupil (32 tiles) 13.6 -> 11.4 us, the whole call 24.8 -> 22.4.  With more tiles than
+// CUs it is slower (1008 tiles 28 -> 49 us: one such workgroup fills a CU's LDS).
+template <class Cfg>
+__global__ void __launch_bounds__(3 * Cfg::NT, 1) gemm_image_few_kernel(Gemm2Args a) {
+  static_assert(Cfg::TM == 1 && Cfg::TN == 1, "one block a wave");
+  extern __shared__ __align__(16) char hlds[];
+  const int tiles_m = 2 * a.nyp / Cfg::BM, tiles_n = a.nxp / Cfg::BN;
+  int id = blockIdx.x;
+  const int tn = id % tiles_n; id /= tiles_n;
+  const int tm = id % tiles_m; id /= tiles_m;
+  const int zi = id % a.nzs, s = id / a.nzs;
+  const int row0 = tm * Cfg::BM, col0 = tn * Cfg::BN;
+  const int c = __builtin_amdgcn_readfirstlane(threadIdx.x / Cfg::NT), tid = threadIdx.x % Cfg::NT;
+  const int lane = tid & 63, wave = tid >> 6;
+  const int wrow = (wave / Cfg::WAVES_N) * Cfg::WM, wcol = (wave % Cfg::WAVES_N) * Cfg::WN;
+  const int w = 2 * a.nhp;
+  const size_t plane = (size_t)a.nx * a.ny;
+  const size_t at = (size_t)(a.s_base + s) * a.nz + a.z0 + zi;
+  HgPanelLoader<Cfg, Cfg::BM> la;
+  la.src = a.T + (((size_t)s * a.nzs + zi) * a.nc + c) * (hg_panel_bytes(w, 2 * a.nyp) / 16) + row0;
+  la.ld = 2 * a.nyp;
+  HgPanelLoader<Cfg, Cfg::BN> lb;
+  lb.src = a.A2 + col0;
+  lb.ld = a.nxp;
+  char* lds = hlds + c * Cfg::LDS_BYTES;
+  HgAcc<Cfg> acc;
+  acc.zero();
+  hg_mainloop<Cfg>(acc, la, lb, 0, w, lds, tid, wrow, wcol, lane);
+  const int m = col0 + wcol + (lane & 31);
+  const int n0 = (row0 + wrow) / 2 + 2 * (lane >> 5);
+  float* sq = reinterpret_cast<float*>(lds);   // [8][NT]: this channel's share of the lane's eight intensities
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const int n = n0 + 4 * g;
+    // E = -i E' = (Im E', -Re E')
+    const float4 e = make_float4(acc.c[0][0][4 * g + 1] * a.escale, acc.c[0][0][4 * g] * -a.escale,
+                                 acc.c[0][0][4 * g + 3] * a.escale, acc.c[0][0][4 * g + 2] * -a.escale);
+    sq[(2 * g) * Cfg::NT + tid] = e.x * e.x + e.y * e.y;
+    sq[(2 * g + 1) * Cfg::NT + tid] = e.z * e.z + e.w * e.w;
+    if (a.E && m < a.nx) {
+      float2* o = a.E + (at * a.nc + c) * plane + (size_t)m * a.ny + n;
+      if (n < a.ny) o[0] = make_float2(e.x, e.y);
+      if (n + 1 < a.ny) o[1] = make_float2(e.z, e.w);
+    }
+  }
+  __syncthreads();
+  if (!a.I || c > 0 || m >= a.nx) return;
+  float* I = a.I + at * plane + (size_t)m * a.ny;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    const int n = n0 + 4 * (q >> 1) + (q & 1);
+    float v = 0.f;
+    for (int k = 0; k < a.nc; ++k) v += reinterpret_cast<const float*>(hlds + k * Cfg::LDS_BYTES)[q * Cfg::NT + tid];
+    if (n < a.ny) I[n] = v;
+  }
+}
+
 // --------------------------------------------------------------------------
 // Host-side launchers
 // --------------------------------------------------------------------------
@@ -550,18 +610,25 @@ hipError_t launch_gemm_pupil(const Gemm1Args& a, hipStream_t st) {
 hipError_t launch_gemm_image(const Gemm2Args& a, hipStream_t st) {
   const long long work = (long long)a.nstk * a.nzs;
   const bool few = work * ((a.nxp + 127) / 128) * ((2 * a.nyp + 127) / 128) < 2LL * device_cus();
-  if (few) return gemm_image_launch<CfgImageS, 2>(a, st);
+  const long long blocks = work * (2 * a.nyp / CfgImageS::BM) * (a.nxp / CfgImageS::BN);
+  if (few && blocks > device_cus()) return gemm_image_launch<CfgImageS, 2>(a, st);
+  if (few) {
+    hipLaunchKernelGGL(gemm_image_few_kernel<CfgImageS>, dim3((unsigned)blocks), dim3(a.nc * CfgImageS::NT),
+                       a.nc * CfgImageS::LDS_BYTES, st, a);
+    return hipGetLastError();
+  }
   if (a.nxp % 128 == 0) return gemm_image_launch<CfgImage, 2>(a, st);
   return gemm_image_launch<CfgImageM, 2>(a, st);
 }
 
 hipError_t fourier_kernel_attributes() {
-  const void* k[6] = {(const void*)gemm_pupil_kernel<CfgPupil, 2, 2>, (const void*)gemm_pupil_kernel<CfgPupilN, 2, 2>,
+  const void* k[7] = {(const void*)gemm_pupil_kernel<CfgPupil, 2, 2>, (const void*)gemm_pupil_kernel<CfgPupilN, 2, 2>,
                       (const void*)gemm_pupil_kernel<CfgPupilS, 1, 2>, (const void*)gemm_image_kernel<CfgImage, 2>,
-                      (const void*)gemm_image_kernel<CfgImageM, 2>, (const void*)gemm_image_kernel<CfgImageS, 2>};
-  const int bytes[6] = {CfgPupil::LDS_BYTES, CfgPupilN::LDS_BYTES, CfgPupilS::LDS_BYTES,
-                        CfgImage::LDS_BYTES, CfgImageM::LDS_BYTES, CfgImageS::LDS_BYTES};
-  for (int i = 0; i < 6; ++i) {
+                      (const void*)gemm_image_kernel<CfgImageM, 2>, (const void*)gemm_image_kernel<CfgImageS, 2>,
+                      (const void*)gemm_image_few_kernel<CfgImageS>};
+  const int bytes[7] = {CfgPupil::LDS_BYTES, CfgPupilN::LDS_BYTES, CfgPupilS::LDS_BYTES,
+                        CfgImage::LDS_BYTES, CfgImageM::LDS_BYTES, CfgImageS::LDS_BYTES, 3 * CfgImageS::LDS_BYTES};
+  for (int i = 0; i < 7; ++i) {
     const hipError_t e = hipFuncSetAttribute(k[i], hipFuncAttributeMaxDynamicSharedMemorySize, bytes[i]);
     if (e != hipSuccess) return e;
   }
