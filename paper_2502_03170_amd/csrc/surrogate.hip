@@ -648,8 +648,9 @@ __global__ void sg_gate_predict_kernel(const float* __restrict__ coef, const flo
 //     the vector units (a thread owns 2 x 2 input pixels and their 4 x 4 outputs).
 // Layers 1 and 2 run v_mfma_f32_16x16x32_bf16: A lane l holds row l % 16 and eight
 // consecutive k of group l / 16, B lane l holds column l % 16 and the same eight k, C
-// register r of lane l holds row 4 (l / 16) + r, column l % 16.  Activations sit in LDS
-// channel-last with a zero border, so the eight k of a lane are eight consecutive
+// register r of lane l holds row 4 (l / 16) + r, column l % 16.  The weights are A and the
+// pixels B, so that a lane ends up with four channels of one pixel and writes them at once.
+// Activations sit in LDS channel-last with a zero border, so the eight k of a lane are eight consecutive
 // channels of one source pixel (two 16-byte reads), with no bounds tests.  Weights are
 // pre-arranged as B fragments ([class][k-step][lane][8] BF16 hi / lo) and held in
 // registers for all samples of the workgroup.  The inputs of the two matrix-core layers
@@ -659,6 +660,7 @@ constexpr int DC0 = 16, DC1 = 16, DC2 = 8;          // decoder channels (layer i
 // inputs of the matrix-core layers are held as BF16 hi / lo planes (split once, when
 // written), DXb BF16 per pixel (16-byte aligned, padded); the last layer's input in FP32
 constexpr int DX0b = DC0 + 8, DX1b = DC1 + 8, DX2 = DC2;
+constexpr int DX2H = 34 * 34 * 4;   // floats of one half of the last layer's channels: a pixel's four are 16 bytes
 constexpr int DL0b = 10 * 10 * DX0b, DL1b = 18 * 18 * DX1b, DL2 = 34 * 34 * DX2;   // elements per plane
 constexpr int DK1 = 4 * DC0 / 32, DK2 = 6 * DC1 / 32;    // k-steps of the layer-1 / layer-2 GEMMs
 constexpr int kDecLdsBytes = 2 * (DL0b + DL1b) * 2 + DL2 * 4;
@@ -697,6 +699,9 @@ __device__ void sg_dec_fragment(int i, const PlaneArgs& a) {
 // h3 [B][DC0][8][8] (relu applied) -> y [B][64][64] += T(T(T(h3))); d1 [B][DC1][16][16] and d2
 // [B][DC2][32][32] (post-relu) are also written when the pointers are not null (training).
 // Persistent: workgroup g serves samples g, g + gridDim.x, ...
+// LDS is busy 60% of the time, the vector units 52%, with two waves a SIMD to overlap them.  65536
+// samples: 1102 us with one channel of a pixel a store, 1000 us with four.  Even and odd columns
+// apart, which takes a sixth of the bank conflicts away, changed nothing more.
 template <int NSPLIT>
 __global__ void __launch_bounds__(256, 2) sg_decoder_kernel(const float* __restrict__ h3, int B,
                                                             const bf8_t* __restrict__ f1h,
@@ -714,7 +719,7 @@ __global__ void __launch_bounds__(256, 2) sg_decoder_kernel(const float* __restr
   __bf16* X0l = X0h + DL0b;
   __bf16* X1h = X0l + DL0b;                       // [18][18][DX1b] hi, then lo
   __bf16* X1l = X1h + DL1b;
-  float* X2 = reinterpret_cast<float*>(X1l + DL1b);   // [34][34][DX2] FP32
+  float* X2 = reinterpret_cast<float*>(X1l + DL1b);   // [channel half][34][34][4] FP32
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, g = lane >> 4, r16 = lane & 15;
   for (int i = tid; i < kDecLdsBytes / 4; i += 256) dls[i] = 0.f;   // zero borders (interiors are rewritten)
   // B fragments of this wave: layer-1 class p = w, layer-2 row class py2 = w / 2
@@ -730,8 +735,14 @@ __global__ void __launch_bounds__(256, 2) sg_decoder_kernel(const float* __restr
     w2h[s] = f2h[(py2 * DK2 + s) * 64 + lane];
     if (NSPLIT > 1) w2l[s] = f2l[(py2 * DK2 + s) * 64 + lane];
   }
-  const float bias1 = c1[r16];
-  const float bias2 = c2[r16 % DC2];
+  // accumulator register i of a lane is output channel 4 g + i (layer 2: channel (4 g + i) % DC2 of
+  // column class g / 2)
+  float bias1[4], bias2[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    bias1[i] = c1[4 * g + i];
+    bias2[i] = c2[(4 * g + i) % DC2];
+  }
   const float bias3 = c3[0];
   // staged h3 of the next sample: DC0 * 64 floats, 8 per thread as two float4
   constexpr int NV = DC0 * 64 / 4 / 256;
@@ -786,28 +797,31 @@ __global__ void __launch_bounds__(256, 2) sg_decoder_kernel(const float* __restr
           al[mt] = NSPLIT > 1 ? *reinterpret_cast<const bf8_t*>(X0l + at) : ah[mt];
         }
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt) acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[mt], w1h[s], acc[mt], 0, 0, 0);
+        for (int mt = 0; mt < 4; ++mt) acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1h[s], ah[mt], acc[mt], 0, 0, 0);
         if (NSPLIT > 1) {
 #pragma unroll
           for (int mt = 0; mt < 4; ++mt)
-            acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[mt], w1l[s], acc[mt], 0, 0, 0);
+            acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1l[s], ah[mt], acc[mt], 0, 0, 0);
 #pragma unroll
           for (int mt = 0; mt < 4; ++mt)
-            acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[mt], w1h[s], acc[mt], 0, 0, 0);
+            acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1h[s], al[mt], acc[mt], 0, 0, 0);
         }
       }
-      // C: rows 4 g + i (pixels), column r16 (output channel)
+      // C: rows 4 g + i (output channels), column r16 (pixel): four channels of a pixel in one store
 #pragma unroll
-      for (int mt = 0; mt < 4; ++mt)
+      for (int mt = 0; mt < 4; ++mt) {
+        const int mm = 16 * mt + r16, YY = mm >> 3, XX = mm & 7;
+        const int at = ((2 * YY + py + 1) * 18 + 2 * XX + px + 1) * DX1b + 4 * g;
+        bf4_t h, l;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const int mm = 16 * mt + 4 * g + i, YY = mm >> 3, XX = mm & 7;
-          const int at = ((2 * YY + py + 1) * 18 + 2 * XX + px + 1) * DX1b + r16;
-          const float v = fmaxf(acc[mt][i] + bias1, 0.f);
-          const __bf16 h = (__bf16)v;
-          X1h[at] = h;
-          X1l[at] = (__bf16)(v - (float)h);
+          const float v = fmaxf(acc[mt][i] + bias1[i], 0.f);
+          h[i] = (__bf16)v;
+          l[i] = (__bf16)(v - (float)h[i]);
         }
+        *reinterpret_cast<bf4_t*>(X1h + at) = h;
+        *reinterpret_cast<bf4_t*>(X1l + at) = l;
+      }
     }
     __syncthreads();
     if (d1g) {   // training: d1 [co][16][16]
@@ -840,24 +854,24 @@ __global__ void __launch_bounds__(256, 2) sg_decoder_kernel(const float* __restr
             al[u] = NSPLIT > 1 ? *reinterpret_cast<const bf8_t*>(X1l + at) : ah[u];
           }
 #pragma unroll
-          for (int u = 0; u < L2G; ++u) acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[u], w2h[s], acc[u], 0, 0, 0);
+          for (int u = 0; u < L2G; ++u) acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w2h[s], ah[u], acc[u], 0, 0, 0);
           if (NSPLIT > 1) {
 #pragma unroll
             for (int u = 0; u < L2G; ++u)
-              acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[u], w2l[s], acc[u], 0, 0, 0);
+              acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w2l[s], ah[u], acc[u], 0, 0, 0);
 #pragma unroll
             for (int u = 0; u < L2G; ++u)
-              acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[u], w2h[s], acc[u], 0, 0, 0);
+              acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w2h[s], al[u], acc[u], 0, 0, 0);
           }
         }
-        const int px = r16 / DC2, co = r16 % DC2;
+        const int px = g >> 1, half = g & 1;
 #pragma unroll
-        for (int u = 0; u < L2G; ++u)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int mm = 16 * (8 * (w & 1) + t0 + u) + 4 * g + i, YY = mm >> 4, XX = mm & 15;
-            X2[((2 * YY + py2 + 1) * 34 + 2 * XX + px + 1) * DX2 + co] = fmaxf(acc[u][i] + bias2, 0.f);
-          }
+        for (int u = 0; u < L2G; ++u) {
+          const int mm = 16 * (8 * (w & 1) + t0 + u) + r16, YY = mm >> 4, XX = mm & 15;
+          *reinterpret_cast<float4*>(X2 + half * DX2H + ((2 * YY + py2 + 1) * 34 + 2 * XX + px + 1) * 4) =
+              make_float4(fmaxf(acc[u][0] + bias2[0], 0.f), fmaxf(acc[u][1] + bias2[1], 0.f),
+                          fmaxf(acc[u][2] + bias2[2], 0.f), fmaxf(acc[u][3] + bias2[3], 0.f));
+        }
       }
     }
     __syncthreads();
@@ -865,7 +879,7 @@ __global__ void __launch_bounds__(256, 2) sg_decoder_kernel(const float* __restr
       float* o = d2g + (size_t)b * DC2 * 1024;
       for (int e = tid; e < DC2 * 1024; e += 256) {
         const int co = e / 1024, pix = e % 1024;
-        o[e] = X2[((pix / 32 + 1) * 34 + pix % 32 + 1) * DX2 + co];
+        o[e] = X2[co / 4 * DX2H + ((pix / 32 + 1) * 34 + pix % 32 + 1) * 4 + co % 4];
       }
     }
     // ---- layer 3 (FP32): thread owns input pixels (2 Yb + u, 2 Xb + v), u, v in {0, 1},
@@ -884,7 +898,7 @@ __global__ void __launch_bounds__(256, 2) sg_decoder_kernel(const float* __restr
         for (int i = 0; i < 4; ++i)
 #pragma unroll
           for (int j = 0; j < 4; ++j)
-            nb[i][j] = *reinterpret_cast<const float4*>(X2 + ((2 * Yb + i) * 34 + 2 * Xb + j) * DX2 + hc);
+            nb[i][j] = *reinterpret_cast<const float4*>(X2 + hc / 4 * DX2H + ((2 * Yb + i) * 34 + 2 * Xb + j) * 4);
 #pragma unroll
         for (int cc = 0; cc < 4; ++cc) {
           const int ci = hc + cc;
