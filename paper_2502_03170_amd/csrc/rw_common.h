@@ -207,7 +207,7 @@ struct rwpsf_plan {
   int n_theta_total = 0;        // nodes after the critical-angle split
   double* d_theta = nullptr;    // [T] nodes
   double* d_wtheta = nullptr;   // [T] weights
-  double* d_node = nullptr;     // [T][4] Bessel form: sin, cos, stack-independent amplitude, k cos of each node
+  double* d_node = nullptr;     // [T] BesselNode: what the pupil of a node takes from the plan
   int bessel_mode = 0;          // 0 vectorial, 1 vectorial with Fresnel factors, 2 scalar
   float* d_btab = nullptr;      // [T][G][R] w_t h_g(t) J_{n_g}(k rho_r sin t)
   uint4* d_bpanel = nullptr;    // d_btab as a split-f16 panel of btab_ld columns, times 2^tab_exp
