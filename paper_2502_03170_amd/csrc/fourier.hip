@@ -584,7 +584,7 @@ static hipError_t gemm_image_launch(const Gemm2Args& a, hipStream_t st) {
 }
 
 // Compute units of the current device (queried once per device).
-static int device_cus() {
+int device_cus() {
   static int cus[64] = {0};
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;

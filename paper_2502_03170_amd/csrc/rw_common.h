@@ -196,7 +196,8 @@ struct rwpsf_plan {
   int P_stacks = 0;             // capacity of d_P in stacks
 
   // chirp-z evaluation of the Fourier form
-  int czt_Ly = 0, czt_Lx = 0, czt_cb = 0, czt_stride = 0;   // FFT lengths, output columns per workgroup, their stride in LDS
+  // FFT lengths, most output columns per workgroup, their stride in LDS
+  int czt_Ly = 0, czt_Lx = 0, czt_cb = 0, czt_stride = 0;
   float2* d_czt = nullptr;       // tables: pre/post/chat along y, then along x
   float2 *czt_pre_y = nullptr, *czt_post_y = nullptr, *czt_chat_y = nullptr;
   float2 *czt_pre_x = nullptr, *czt_post_x = nullptr, *czt_chat_x = nullptr;

@@ -101,5 +101,6 @@ hipError_t launch_pupil_build_folded(const FoldArgs& a, const float2* Q, const f
 hipError_t launch_gemm_pupil(const Gemm1Args& a, hipStream_t st);
 hipError_t launch_gemm_image(const Gemm2Args& a, hipStream_t st);
 hipError_t fourier_kernel_attributes();
+int device_cus();   // compute units of the current device
 
 }  // namespace rw

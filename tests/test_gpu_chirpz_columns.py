@@ -29,3 +29,27 @@ def test_chirpz_column_blocks(lib, n_pupil, nx, ny):
                                x0=9.0, y0=-5.0)
     assert rel_l2(E[0].cpu().numpy(), ref) < TOL
     assert rel_l2(I[0].cpu().numpy(), (np.abs(ref) ** 2).sum(axis=1)) < TOL
+
+
+@pytest.mark.parametrize("n_pupil,nx,ny,nz", [(40, 30, 33, 90), (60, 24, 17, 129), (300, 260, 35, 90)])
+def test_chirpz_column_blocks_of_few_and_many_planes(lib, n_pupil, nx, ny, nz):
+    """A call of few planes takes fewer columns a workgroup; a plane does not depend on it."""
+    rw = lib
+    w = W.fourier_plain(n_stacks=1, seed=8)
+    z = np.linspace(-500.0, 500.0, nz)
+    o = w["optics"]
+    st = [dict(x0=9.0, y0=-5.0, zernike=w["zernike"][0])]
+
+    def fields(zz):
+        plan = rw.Plan(form=rw.FORM_CHIRPZ, na=o["na"], wavelength=o["wavelength"], n_i=o["n_i"], nx=nx, ny=ny,
+                       dx=15.0, dy=15.0, z=zz, e_inc=w["e_inc"], n_pupil=n_pupil)
+        E, I = plan.compute(st)
+        E, I = E[0].cpu().numpy(), I[0].cpu().numpy()
+        plan.close()
+        return E, I
+
+    E, I = fields(z)
+    E1, I1 = fields(z[:1])
+    assert np.array_equal(E[:1], E1) and np.array_equal(I[:1], I1)
+    En, In = fields(z[-3:])
+    assert np.array_equal(E[-3:], En) and np.array_equal(I[-3:], In)
