@@ -14,9 +14,9 @@
 //   E' = A2_S T             (S x S, T kept in LDS),  E = -i E'
 // and I = sum_c |E_c|^2.  A2_S / B1_S are the rows of one 96-row table that cover the
 // crop (pixel i of an S-crop is table row i - S/2 + 32).  Crops are evaluated on 32- or
-// 64-wide tiles, the two tile classes; the (emitter, plane) items of each class are dealt, emitter by emitter and longest first, to eight queues, one per XCD, and the
-// class's persistent kernel takes items from the queues' atomic counters until they are
-// exhausted.
+// 64-wide tiles, the two tile classes; the (emitter, plane) items of each class are dealt,
+// emitter by emitter and longest first, to eight queues, one per XCD, and the class's
+// persistent kernel takes items from the queues' atomic counters until they are exhausted.
 #include <algorithm>
 #include <cmath>
 #include <complex>
@@ -357,10 +357,10 @@ __device__ __forceinline__ void batch_plane(const BatchArgs& a, const BatchParam
 }
 
 // Persistent plane kernel of tile class cls (one launch per class), which serves queues 8 cls
-// .. 8 cls + 7.  Workgroup ids are dealt
-// round-robin over the 8 XCDs, so workgroup b serves queue b % 8 of the class: the (emitter,
-// plane) items of the emitters assigned to that queue, in order, so that the planes of one
-// emitter run at the same time on one XCD and its folded pupil is read from that XCD's L2.
+// .. 8 cls + 7.  Workgroup ids are dealt round-robin over the 8 XCDs, so workgroup b serves
+// queue b % 8 of the class: the (emitter, plane) items of the emitters assigned to that queue,
+// in order, so that the planes of one emitter run at the same time on one XCD and its folded
+// pupil is read from that XCD's L2.
 // The next item is drawn while the current one is computed.  A workgroup exits when its
 // queue is exhausted; the grid has at least 8 workgroups, one per queue.
 template <int N, int SP>

@@ -11,8 +11,7 @@
 //   K1  pupil_build_folded   mirror-folded pupils Pf (four parities per folded cell)
 //                     of up to 16 stacks, each cell's P_c formed on the way (FP64
 //                     phase: Gibson-Lanni, Zernike, free phase map, lateral emitter
-//                     shift); the chirp-z and adjoint paths take the unfolded P_c of
-//                     pupil_build
+//                     shift); the chirp-z path takes the unfolded P_c of pupil_build
 //   K2  gemm_pupil    T = Pf~ B1 (fold along y); the defocus factor is formed while the
 //                     pupil tile is staged (FP64 phase, reduced mod 2 pi, FP32 sincos)
 //   K3  gemm_image    E'_c = A2 T_c (fold along x) for c = x, y, z in one workgroup,
@@ -239,9 +238,9 @@ __global__ void __launch_bounds__(256) pupil_build_folded_kernel(FoldArgs a, con
 // K2, K3: the two GEMMs (the pupil operand's loader is in hfold.h).
 // --------------------------------------------------------------------------
 // Measured on 16 stacks of 128 x 128 x 64 at a 256 x 256 pupil (fields and intensity): the
-// call took 1313 us with FP32 MFMA tiles and takes 692 us (pupil GEMM 860 -> 345-400 us, image
+// call took 1305 us with FP32 MFMA tiles and takes 660 us (pupil GEMM 860 -> 345-400 us, image
 // GEMM 480 -> 310-340 us, whose 0.8 GB of T and 0.47 GB of output are 4 TB/s of HBM); one
-// 201 x 201 image 52 -> 25 us.  The pupil GEMM's pipes hardly overlap: its MFMAs alone need
+// 201 x 201 image 52 -> 22 us.  The pupil GEMM's pipes hardly overlap: its MFMAs alone need
 // 115 us, without them it takes 257 us, without global loads 247 us; one plane per tile
 // (the pupil then crosses L2 twice as often) 372 us, other tile shapes and occupancies
 // (128 x 128, eight waves, k-stages of 32) 372-450 us.

@@ -161,8 +161,9 @@ __device__ __forceinline__ void hg_stage_mma(HgAcc<Cfg>& acc, const char* a, con
 // flight: stage k+2 is requested while stage k is multiplied and stage k+1 (already in
 // registers) is prepared and written to the other LDS buffer (one stage in flight left a
 // wave waiting for it behind a third of its MFMAs: the pupil GEMM of 16 stacks 345 -> 323
-// us).  The last stages are peeled, so that no branch surrounds the loads and stores.  The caller's barrier must separate an earlier use of the LDS from this call; on
-// return every wave has left it.
+// us).  The last stages are peeled, so that no branch surrounds the loads and stores.  The
+// caller's barrier must separate an earlier use of the LDS from this call; on return every
+// wave has left it.
 template <class Cfg, class ALoader, class BLoader>
 __device__ __forceinline__ void hg_mainloop_pre(HgAcc<Cfg>& acc, const ALoader& la, const BLoader& lb,
                                                 const typename ALoader::Regs& ra0,

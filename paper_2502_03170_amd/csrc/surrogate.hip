@@ -940,13 +940,15 @@ __global__ void __launch_bounds__(256, 2) sg_decoder_kernel(const float* __restr
 // and the data gradient gin[ci][iy][ix] = sum_{co, ky, kx} g[co][..][..] K[ci][co][ky][kx],
 // masked by the relu of the layer's input.  Everything stays FP32, on
 // v_mfma_f32_16x16x4_f32 (which adds its four k in order): a weight gradient of one co is the
-// product [ci][pixel] x [pixel][tap], a data gradient [pixel][(tap, co)] x [(tap, co)][ci].  Every sum of a sample is one chain in pixel (or tap) order, added to the
-// workgroup's total afterwards, as a plain loop over the batch would: in training the sums
-// over a batch cancel to 1e-4 of their terms and feed back into the weights, so a different
-// order, no less exact, shows in the moments within tens of steps.  The long chains (layer
-// 3's weights and the biases) run on waves of their own beside the others' work.  Gradients sit in LDS with a zero
-// border, so that no tap needs a bounds test; rows are padded against bank conflicts.  A workgroup serves a run of samples and keeps the weight and bias gradients in
-// registers; the partial sums of the workgroups are added in a fixed order afterwards.
+// product [ci][pixel] x [pixel][tap], a data gradient [pixel][(tap, co)] x [(tap, co)][ci].
+// Every sum of a sample is one chain in pixel (or tap) order, added to the workgroup's total
+// afterwards, as a plain loop over the batch would: in training the sums over a batch cancel
+// to 1e-4 of their terms and feed back into the weights, so a different order, no less exact,
+// shows in the moments within tens of steps.  The long chains (layer 3's weights and the
+// biases) run on waves of their own beside the others' work.  Gradients sit in LDS with a zero
+// border, so that no tap needs a bounds test; rows are padded against bank conflicts.  A
+// workgroup serves a run of samples and keeps the weight and bias gradients in registers; the
+// partial sums of the workgroups are added in a fixed order afterwards.
 // Bound by latency: 256 samples are one workgroup per CU, a chain of six phases.  Measured at
 // 256 samples: 39 us and 5 us for the reduction, against 730 us for the separate kernels (weights 3
 // x 117 us, whose bias sums ran on one thread, their reduction 3 x 64, data 3 x 58, masks).
