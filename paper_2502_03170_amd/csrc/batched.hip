@@ -166,10 +166,12 @@ __global__ void __launch_bounds__(256) batch_fold_kernel(BatchArgs a) {
 // joined through LDS.  Waves own 64 pupil rows (N = 128) or 32.
 // Bound by the matrix cores and by what stands between their products (staging, the split of
 // T).  Measured on 4096 emitters (crops 24-64, 1-41 planes, N = 128), a whole call: 16.7 ms with
-// FP32 MFMA tiles (planes 16.1), 6.5 ms so (planes 5.4 + 1.1); a frame of 100 emitters of one
-// plane 87 -> 30 us.  Waves of 32 pupil rows (eight of them) took 7.0 + 1.55 ms; table rows
-// of the second product requested ahead of the split of T gave 2.75 -> 3.09 ms on the 64-row
-// tile (they spill) and 1.20 -> 1.12 ms on the 32-row tile, where they are.
+// FP32 MFMA tiles (planes 16.1), 6.0 ms so (planes 4.8 + 1.0); a frame of 100 emitters of one
+// plane 87 -> 30 us.  (Item, emitter and crop size in vector registers and the 64-bit offsets of a
+// lane's sixteen pixels, formed once per plane, spilled 44 registers on the 64-row tile: 2.5 GB
+// written and as much read per call, 6.5-6.7 ms.)  Waves of 32 pupil rows (eight of them) took 7.0
+// + 1.55 ms; table rows of the second product requested ahead of the split of T gave 2.75 -> 3.09
+// ms on the 64-row tile (they spill) and 1.20 -> 1.12 ms on the 32-row tile, where they are.
 template <int N, int SP>
 struct PlaneTile {
   static constexpr int WM = N >= 128 ? 64 : 32;
@@ -293,13 +295,24 @@ __device__ __forceinline__ void batch_plane(const BatchArgs& a, const BatchParam
         hg16 er, ei;
         fetch(blk >> 1, 0);
         product(blk & 1, 0, er, ei);
-        const int n = 32 * (blk & 1) + l32;
+        const int n = 32 * (blk & 1) + l32, m0 = 32 * (blk >> 1) + 4 * h;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int m = 32 * (blk >> 1) + 8 * (r >> 2) + 4 * h + (r & 3);
           const float x = ei[r] * a.escale, y = -er[r] * a.escale;
           isum[16 * q + r] += x * x + y * y;
-          if (Ec && m < S && n < S) Ec[m * S + n] = make_float2(x, y);
+          er[r] = x;
+          ei[r] = y;
+        }
+        if (Ec) {
+          // row steps formed here: the sixteen offsets, kept over the components, spilled
+          int step = __builtin_amdgcn_readfirstlane(S);
+          asm("" : "+s"(step));
+          const unsigned o = m0 * step + n;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int dm = 8 * (r >> 2) + (r & 3);
+            if (m0 + dm < S && n < S) Ec[o + dm * step] = make_float2(er[r], ei[r]);
+          }
         }
       }
       __syncthreads();   // T is consumed
@@ -340,10 +353,13 @@ __device__ __forceinline__ void batch_plane(const BatchArgs& a, const BatchParam
       for (int q = 0; q < P::COMBOS; ++q) {
         const int blk = w + q * P::NW;
         if (blk >= 4) break;
+        const int n = 32 * (blk & 1) + l32, m0 = 32 * (blk >> 1) + 4 * h;
+        const int step = S;
+        const unsigned o = m0 * step + n;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int m = 32 * (blk >> 1) + 8 * (r >> 2) + 4 * h + (r & 3), n = 32 * (blk & 1) + l32;
-          if (m < S && n < S) Ip[m * S + n] = isum[16 * q + r];
+          const int dm = 8 * (r >> 2) + (r & 3);
+          if (m0 + dm < S && n < S) Ip[o + dm * step] = isum[16 * q + r];
         }
       }
     } else {
@@ -354,6 +370,12 @@ __device__ __forceinline__ void batch_plane(const BatchArgs& a, const BatchParam
       }
     }
   }
+}
+
+// Memory that nothing writes while the kernel runs, read over the scalar path.
+template <class T>
+__device__ __forceinline__ auto as_constant(const T* p) {
+  return (const T __attribute__((address_space(4)))*)p;
 }
 
 // Persistent plane kernel of tile class cls (one launch per class), which serves queues 8 cls
@@ -369,12 +391,17 @@ __global__ void __launch_bounds__((PlaneTile<N, SP>::Cfg::NT), 2) batch_planes_k
   __shared__ long long item[2];
   const int tid = threadIdx.x;
   const int x = 8 * cls + (blockIdx.x & 7);
-  const int lo = a.qoff[x], hi = a.qoff[x + 1];
-  const long long end = a.pre[hi];
+  // the lists are uploaded before the launch and an item is the same in every lane: scalar loads
+  const auto pre = as_constant(a.pre);
+  const auto qoff = as_constant(a.qoff);
+  const int lo = qoff[x], hi = qoff[x + 1];
+  const long long end = pre[hi];
   if (tid == 0) item[0] = (long long)atomicAdd(&a.counter[x], 1ull);
   __syncthreads();
   for (int turn = 0;; turn ^= 1) {
-    const long long it = item[turn];
+    const long long vit = item[turn];
+    const int it_lo = __builtin_amdgcn_readfirstlane((int)vit), it_hi = __builtin_amdgcn_readfirstlane((int)(vit >> 32));
+    const long long it = (long long)((unsigned long long)(unsigned)it_hi << 32 | (unsigned)it_lo);
     if (it >= end) break;
     long long next = 0;
     if (tid == 0) next = (long long)atomicAdd(&a.counter[x], 1ull);
@@ -382,11 +409,16 @@ __global__ void __launch_bounds__((PlaneTile<N, SP>::Cfg::NT), 2) batch_planes_k
     int e0 = lo, e1 = hi - 1;
     while (e0 < e1) {
       const int mid = (e0 + e1 + 1) >> 1;
-      if (a.pre[mid] <= it) e0 = mid; else e1 = mid - 1;
+      if (pre[mid] <= it) e0 = mid; else e1 = mid - 1;
     }
-    const int slot = a.list[e0];
-    const int d = (int)(it - a.pre[e0]);
-    const BatchParam bp = a.params[slot];
+    const int slot = as_constant(a.list)[e0];
+    const int d = (int)(it - pre[e0]);
+    const auto p = as_constant(a.params) + slot;
+    BatchParam bp;
+    bp.zoff = p->zoff;
+    bp.off = p->off;
+    bp.S = p->S;
+    bp.D = p->D;
     batch_plane<N, SP>(a, bp, slot, d, blds, tid);
     if (tid == 0) item[turn ^ 1] = next;   // read after the barriers of the next plane, or below
     __syncthreads();
