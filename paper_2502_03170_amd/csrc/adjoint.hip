@@ -153,7 +153,9 @@ struct AdjArgs {
 // the scales.  Without the sum over planes 268, without G 190, without H 232.  The x table in
 // registers spilled (406 us: a spill's reload waits for the loads in flight); the two waves of a
 // SIMD in opposite order 370 against 328; all LDS reads of H first, or three chains, 305-307.
-// MULTI: more than one chunk along y, so that H and the y table pass from step to step.
+// MULTI: more than one chunk along y, so that H and the y table pass from step to step.  16 stacks
+// of 128 x 128 x 21 at N = 256, a whole adjoint: 555 us with 89 registers spilled, most of them
+// addresses kept over the planes, 366 with 30.
 template <bool MULTI>
 __global__ void __launch_bounds__(kAdjThreads, 2) adj_kernel(AdjArgs a) {
   extern __shared__ __align__(16) char alds[];
@@ -271,6 +273,9 @@ __global__ void __launch_bounds__(kAdjThreads, 2) adj_kernel(AdjArgs a) {
   store(cur);
   cur = load(zl, nl_c);
   const float hscale = ldexpf(1.f, -a.hshift);
+  // The lane half of an LDS read in its base, so that the reads of a loop are one address and
+  // constants; in its step with one chunk, where registers are left (328 us, in the base 357).
+  const int hbase = MULTI ? h : 0, hstep = MULTI ? 0 : h;
   const int hb = wave >> 1, hp = wave & 1;   // 16 pixel rows and the parity of this wave's block of H
   // Z += acc conj(D).  Blocks 0, 1 (2, 3) hold the parts of C* and S* at y parity 0 (1); even
   // registers are x parity 0, odd ones 1.
@@ -291,12 +296,12 @@ __global__ void __launch_bounds__(kAdjThreads, 2) adj_kernel(AdjArgs a) {
     }
   };
   auto transform_y = [&]() {
-    const hg8* ap = reinterpret_cast<const hg8*>(As) + 32 * hb + l32;
-    const hg8* bp = reinterpret_cast<const hg8*>(Ts) + 32 * hp + l32;
+    const hg8* ap = reinterpret_cast<const hg8*>(As) + 32 * hb + l32 + hbase * 128;
+    const hg8* bp = reinterpret_cast<const hg8*>(Ts) + 32 * hp + l32 + hbase * 64;
 #pragma unroll
     for (int u = 0; u < kAdjChunk / 16; ++u) {
-      const hg8 ah = ap[(4 * u + h) * 128], al = ap[(4 * u + 2 + h) * 128];
-      const hg8 bh = bp[(4 * u + h) * 64], bl = bp[(4 * u + 2 + h) * 64];
+      const hg8 ah = ap[(4 * u + hstep) * 128], al = ap[(4 * u + 2 + hstep) * 128];
+      const hg8 bh = bp[(4 * u + hstep) * 64], bl = bp[(4 * u + 2 + hstep) * 64];
       hx = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bl, hx, 0, 0, 0);
       hm = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bh, hm, 0, 0, 0);
       hx = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, bh, hx, 0, 0, 0);
@@ -339,9 +344,16 @@ __global__ void __launch_bounds__(kAdjThreads, 2) adj_kernel(AdjArgs a) {
     }
     __syncthreads();   // H is in LDS, the chunk is consumed
     // the defocus before the next chunk: loads return in order
-    const float2* Dz = a.D + ((size_t)zi * nhp + (active ? jf0 : 0)) * nhp + lf;
+    const float2* Dz = a.D + ((size_t)zi * nhp + (active ? jf0 : 0)) * nhp;
+    if constexpr (MULTI) {
+      unsigned o = 2 * h * nhp + lf;
+      asm("" : "+v"(o));   // formed for each plane: eight addresses kept spill (one chunk: 359 us)
 #pragma unroll
-    for (int q = 0; q < 8; ++q) d[q] = Dz[(size_t)(4 * (q >> 1) + 2 * h + (q & 1)) * nhp];
+      for (int q = 0; q < 8; ++q) d[q] = (Dz + (4 * (q >> 1) + (q & 1)) * nhp)[o];
+    } else {
+#pragma unroll
+      for (int q = 0; q < 8; ++q) d[q] = (Dz + lf)[(size_t)(4 * (q >> 1) + 2 * h + (q & 1)) * nhp];
+    }
     e_acc = e_cur;
     __builtin_amdgcn_sched_barrier(0);
     e_cur = cur.e;
@@ -351,16 +363,16 @@ __global__ void __launch_bounds__(kAdjThreads, 2) adj_kernel(AdjArgs a) {
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[j] = zero;
-    const hg8* bp = reinterpret_cast<const hg8*>(Hs) + l32;
-    const hg8* xp = reinterpret_cast<const hg8*>(Xs) + 32 * wave + l32;
+    const hg8* bp = reinterpret_cast<const hg8*>(Hs) + l32 + hbase * 128;
+    const hg8* xp = reinterpret_cast<const hg8*>(Xs) + 32 * wave + l32 + hbase * kAdjRows;
 #pragma unroll
     for (int k16 = 0; k16 < kAdjChunk / 16; ++k16) {
-      const hg8 xh = xp[(4 * k16 + h) * kAdjRows], xl = xp[(4 * k16 + 2 + h) * kAdjRows];
+      const hg8 xh = xp[(4 * k16 + hstep) * kAdjRows], xl = xp[(4 * k16 + 2 + hstep) * kAdjRows];
       hg8 bh[4], bl[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        bh[j] = bp[(4 * k16 + h) * 128 + 32 * j];
-        bl[j] = bp[(4 * k16 + 2 + h) * 128 + 32 * j];
+        bh[j] = bp[(4 * k16 + hstep) * 128 + 32 * j];
+        bl[j] = bp[(4 * k16 + 2 + hstep) * 128 + 32 * j];
       }
 #pragma unroll
       for (int j = 0; j < 4; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(xh, bl[j], acc[j], 0, 0, 0);
