@@ -1170,7 +1170,8 @@ __device__ __forceinline__ void adjb_project(const AdjRadArgs& a, bool scalar, f
 // 2^-40 of a bound of the plane's |P|: integer addition is associative, so the atomics give
 // a bitwise repeatable result whatever their order, and the quantisation error (2^-41 of
 // the bound per term) is far below FP32 rounding.  The bound, the largest part of 2 g E times
-// four times the sum of the polarisation's parts, needs no geometry.  A term is rounded to units
+// four times the sum of the polarisation's parts, needs no geometry; its maximum propagates NaN,
+// and a plane with a pixel that is not finite has NaN for every sample (a count has no such value).  A term is rounded to units
 // by adding 1.5 2^52 of them: its count is then the difference of the bit patterns.
 // Measured on 2112 planes of 65 x 65: 200 us with an exact |P| maximum (geometry and both reads of
 // E twice), 64-bit conversions and G_In written 8 bytes at a time down its columns; 136 us so.
@@ -1214,26 +1215,29 @@ __global__ void __launch_bounds__(kRadialThreads, 4) adjb_radial_kernel(AdjRadAr
   float mx = 0.f;
   auto bound = [&](const Pixel& v) {
 #pragma unroll
-    for (int c = 0; c < 3; ++c) mx = fmaxf(mx, fabsf(v.g2) * fmaxf(fabsf(v.e[c].x), fabsf(v.e[c].y)));
+    for (int c = 0; c < 3; ++c)
+      mx = __builtin_elementwise_maximum(
+          mx, fabsf(v.g2) * __builtin_elementwise_maximum(fabsf(v.e[c].x), fabsf(v.e[c].y)));
   };
 #pragma unroll
   for (int u = 0; u < kRadialPixels; ++u) bound(kept[u]);
   for (int pix = tid + kRadialPixels * kRadialThreads; pix < P; pix += kRadialThreads) bound(load(pix));
   auto block_max = [&](float v) {
 #pragma unroll
-    for (int d = 32; d > 0; d >>= 1) v = fmaxf(v, __shfl_xor(v, d));
+    for (int d = 32; d > 0; d >>= 1) v = __builtin_elementwise_maximum(v, __shfl_xor(v, d));
     __syncthreads();
     if ((tid & 63) == 0) red[tid >> 6] = v;
     __syncthreads();
     v = red[0];
 #pragma unroll
-    for (int i = 1; i < kRadialThreads / 64; ++i) v = fmaxf(v, red[i]);
+    for (int i = 1; i < kRadialThreads / 64; ++i) v = __builtin_elementwise_maximum(v, red[i]);
     return v;
   };
   mx = block_max(mx) * (4.f * (fabsf(a.exr) + fabsf(a.exi) + fabsf(a.eyr) + fabsf(a.eyi)));
-  const double unit = mx > 0.f ? ldexp(1.0, ilogbf(mx) - 40) : 0.0;
+  const bool finite = mx < INFINITY;   // false for NaN too
+  const double unit = !finite ? NAN : mx > 0.f ? ldexp(1.0, ilogbf(mx) - 40) : 0.0;
   const double magic = 6755399441055744.0 * unit;   // 1.5 2^52 units
-  if (mx > 0.f) {
+  if (finite && mx > 0.f) {
     const int di = kRadialThreads / a.ny, dj = kRadialThreads % a.ny;
     int i = tid / a.ny, j = tid % a.ny;
     auto add = [&](const Pixel& v) {
