@@ -1119,6 +1119,7 @@ int bessel_compute_noalloc(rwpsf_plan* p, int n, const rwpsf_stack* s, float2* E
 // --------------------------------------------------------------------------
 struct AdjRadArgs {
   int nx, ny, nz, R, mode, s_base, K;   // K: columns of G_In (G R)
+  int unit_exp;        // the integer sums' unit is 2^-unit_exp of the bound's power of two
   float dx, dy, inv_drho, drho;
   float exr, exi, eyr, eyi;
   float x0[kPhiStacks], y0[kPhiStacks];
@@ -1169,7 +1170,9 @@ __device__ __forceinline__ void adjb_project(const AdjRadArgs& a, bool scalar, f
 // the forward interpolation.  The sums are kept in LDS as 64-bit integers in units of
 // 2^-40 of a bound of the plane's |P|: integer addition is associative, so the atomics give
 // a bitwise repeatable result whatever their order, and the quantisation error (2^-41 of
-// the bound per term) is far below FP32 rounding.  The bound, the largest part of 2 g E times
+// the bound per term) is far below FP32 rounding.  A plane of more than 2^22 pixels takes a
+// unit so much larger that all of them together cannot leave 63 bits: |P| is at most half the
+// bound, and a pixel's weights on one sample add to less than 1.1.  The bound, the largest part of 2 g E times
 // four times the sum of the polarisation's parts, needs no geometry; its maximum propagates NaN,
 // and a plane with a pixel that is not finite has NaN for every sample (a count has no such value).  A term is rounded to units
 // by adding 1.5 2^52 of them: its count is then the difference of the bit patterns.
@@ -1233,11 +1236,13 @@ __global__ void __launch_bounds__(kRadialThreads, 4) adjb_radial_kernel(AdjRadAr
     for (int i = 1; i < kRadialThreads / 64; ++i) v = __builtin_elementwise_maximum(v, red[i]);
     return v;
   };
-  mx = block_max(mx) * (4.f * (fabsf(a.exr) + fabsf(a.exi) + fabsf(a.eyr) + fabsf(a.eyi)));
+  mx = block_max(mx);
   const bool finite = mx < INFINITY;   // false for NaN too
-  const double unit = !finite ? NAN : mx > 0.f ? ldexp(1.0, ilogbf(mx) - 40) : 0.0;
+  // (FP64: the bound can leave FP32's range where no |P| does)
+  const double bound_p = 4.0 * mx * ((double)fabsf(a.exr) + fabsf(a.exi) + fabsf(a.eyr) + fabsf(a.eyi));
+  const double unit = !finite ? NAN : bound_p > 0.0 ? ldexp(1.0, ilogb(bound_p) - a.unit_exp) : 0.0;
   const double magic = 6755399441055744.0 * unit;   // 1.5 2^52 units
-  if (finite && mx > 0.f) {
+  if (finite && bound_p > 0.0) {
     const int di = kRadialThreads / a.ny, dj = kRadialThreads % a.ny;
     int i = tid / a.ny, j = tid % a.ny;
     auto add = [&](const Pixel& v) {
@@ -1458,6 +1463,8 @@ int bessel_adjoint(rwpsf_plan* p, int n, const rwpsf_stack* s, const float2* E, 
     ra.mode = mode;
     ra.s_base = b0;
     ra.K = G * R;
+    ra.unit_exp = 40;
+    while (((long long)p->grid.nx * p->grid.ny - 1) >> (62 - ra.unit_exp)) --ra.unit_exp;   // >= 36
     ra.dx = (float)p->grid.dx_nm;
     ra.dy = (float)p->grid.dy_nm;
     ra.inv_drho = (float)(1.0 / p->drho);
