@@ -11,7 +11,12 @@
 namespace rw {
 
 static thread_local int g_last_hip = 0;
-void set_hip_error(hipError_t e) { g_last_hip = (int)e; }
+// The error is reported by the call that met it: the runtime forgets it, or the check after the next
+// launch would find it there.
+void set_hip_error(hipError_t e) {
+  g_last_hip = (int)e;
+  (void)hipGetLastError();
+}
 
 // n-point Gauss-Legendre rule on [a, b].  Newton's method on f(theta) = P_n(cos theta)
 // from theta_i = pi (i + 3/4) / (n + 1/2); P_n, P_{n-1} by the three-term recurrence

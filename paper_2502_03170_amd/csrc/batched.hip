@@ -781,7 +781,9 @@ int rwpsf_batch_create(const rwpsf_optics* o, int n_pupil, double pixel_nm, doub
     delete b;
     return rc;
   }
-  if (hipHostMalloc((void**)&b->h_staging, b->upload_bytes, hipHostMallocDefault) != hipSuccess) {
+  const hipError_t he = hipHostMalloc((void**)&b->h_staging, b->upload_bytes, hipHostMallocDefault);
+  if (he != hipSuccess) {
+    set_hip_error(he);
     b->h_staging = nullptr;
     delete b;
     return RWPSF_ERR_OOM;
