@@ -195,14 +195,15 @@ struct ContractArgs {
   int a_exp, c_exp;      // A is multiplied by 2^a_exp (2^ex), C by 2^c_exp (and 2^-ex)
 };
 
-// Split panel of a table in [K][N], scaled by 2^exp: one thread per (node, column) of the padded panel.
-__global__ void bessel_panel_kernel(const float* __restrict__ in, int K, int N, int ldb, int exp,
+// Split panel of a table, scaled by 2^exp: one thread per (k, column) of the padded panel, whose value
+// is in[k sk + column sn].
+__global__ void bessel_panel_kernel(const float* __restrict__ in, int K, int N, int sk, int sn, int ldb, int exp,
                                     _Float16* __restrict__ out) {
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
   const int kp = (K + 15) / 16 * 16;
   if (idx >= kp * ldb) return;
   const int q = idx / ldb, c = idx % ldb;
-  const float x = q < K && c < N ? ldexpf(in[(size_t)q * N + c], exp) : 0.f;
+  const float x = q < K && c < N ? ldexpf(in[(size_t)q * sk + (size_t)c * sn], exp) : 0.f;
   _Float16* o = out + ((size_t)(q / 16 * 4 + q % 16 / 8) * ldb + c) * 8 + q % 8;
   const _Float16 hi = (_Float16)x;
   o[0] = hi;
@@ -734,7 +735,7 @@ static int bessel_panels(rwpsf_plan* p, const std::vector<double>& th, const std
   int st;
   if ((st = dev_alloc(p, &p->d_bpanel, hg_panel_bytes(kp, p->btab_ld) / sizeof(uint4)))) return st;
   hipLaunchKernelGGL(bessel_panel_kernel, dim3((unsigned)((kp * p->btab_ld + 255) / 256)), dim3(256), 0, 0, p->d_btab, T,
-                     N, p->btab_ld, p->tab_exp, (_Float16*)p->d_bpanel);
+                     N, N, 1, p->btab_ld, p->tab_exp, (_Float16*)p->d_bpanel);
   return hip_check(hipGetLastError());
 }
 
@@ -1381,16 +1382,10 @@ __global__ void adjb_coef_kernel(const double* __restrict__ dcp, int n, float* _
   dc[j] = (float)acc;
 }
 
-__global__ void adjb_transpose_kernel(const float* __restrict__ in, float* __restrict__ out, int rows, int cols) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= rows * cols) return;
-  const int r = idx / cols, c = idx % cols;
-  out[(size_t)c * rows + r] = in[idx];
-}
-
-// Tables and workspace of the adjoint, built on first use.
+// Tables and workspace of the adjoint, built on first use and marked ready last, so that a call after
+// one that ran out of memory starts again (with what that one has allocated).
 static int bessel_adjoint_prepare(rwpsf_plan* p) {
-  if (p->d_btabT) return RWPSF_OK;
+  if (p->adjb_ready) return RWPSF_OK;
   const int T = p->n_theta_total, R = p->num.n_rho, nz = p->grid.nz;
   const int G = bessel_groups(p->bessel_mode), V = bessel_variants(p->bessel_mode);
   // per-sample sums, 6 R 64-bit integers in LDS
@@ -1418,29 +1413,27 @@ static int bessel_adjoint_prepare(rwpsf_plan* p) {
     for (int j = 0; j < 4; ++j) node[7 * q + 3 + j] = kTwoPi * zernike_noll(noll[j], sn / p->s_max, 1.0, 0.0);
   }
   const size_t M = 2 * (size_t)kPhiStacks * nz * V;
-  if ((st = dev_alloc(p, &p->d_btabT, (size_t)G * R * T))) return st;
-  const int kp = (G * R + 15) / 16 * 16, ldT = (T + kConPad - 1) / kConPad * kConPad;
-  if ((st = dev_alloc(p, &p->d_bpanelT, hg_panel_bytes(kp, ldT) / sizeof(uint4)))) return st;
-  if ((st = dev_alloc(p, &p->d_GInEx, (size_t)kPhiStacks * nz * V))) return st;
-  if ((st = dev_alloc(p, &p->d_GIn, (size_t)G * R * M))) return st;
-  if ((st = dev_alloc(p, &p->d_GPhi, M * T))) return st;
-  if ((st = dev_alloc(p, &p->d_adjX, (size_t)kPhiStacks * T))) return st;
-  if ((st = dev_alloc(p, &p->d_adjnode, node.size()))) return st;
-  if ((st = dev_alloc(p, &p->d_dcp, 4 * (size_t)RWPSF_MAX_STACKS_PER_CALL))) return st;
-
+  const int K = G * R, kp = (K + 15) / 16 * 16, ldT = (T + kConPad - 1) / kConPad * kConPad;
+  auto need = [&](auto** ptr, size_t count) { return *ptr ? (int)RWPSF_OK : dev_alloc(p, ptr, count); };
+  if ((st = need(&p->d_GIn, (size_t)K * M))) return st;
+  if ((st = need(&p->d_GPhi, M * T))) return st;
+  if ((st = need(&p->d_GInEx, (size_t)kPhiStacks * nz * V))) return st;
+  if ((st = need(&p->d_adjX, (size_t)kPhiStacks * T))) return st;
+  if ((st = need(&p->d_adjnode, node.size()))) return st;
+  if ((st = need(&p->d_dcp, 4 * (size_t)RWPSF_MAX_STACKS_PER_CALL))) return st;
+  if ((st = need(&p->d_bpanelT, hg_panel_bytes(kp, ldT) / sizeof(uint4)))) return st;
   if ((st = hip_check(hipMemcpy(p->d_adjnode, node.data(), node.size() * sizeof(double), hipMemcpyHostToDevice))))
     return st;
   // the limits are per kernel, not per plan: allow the whole LDS so plans of any size can launch
   if ((st = hip_check(hipFuncSetAttribute((const void*)adjb_radial_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                                           150 * 1024))))
     return st;
-  const int total = G * R * T;
-  hipLaunchKernelGGL(adjb_transpose_kernel, dim3((total + 255) / 256), dim3(256), 0, 0, p->d_btab, p->d_btabT, T,
-                     G * R);
-  hipLaunchKernelGGL(bessel_panel_kernel, dim3((unsigned)(((size_t)kp * ldT + 255) / 256)), dim3(256), 0, 0, p->d_btabT,
-                     G * R, T, ldT, p->tab_exp, (_Float16*)p->d_bpanelT);
+  hipLaunchKernelGGL(bessel_panel_kernel, dim3((unsigned)(((size_t)kp * ldT + 255) / 256)), dim3(256), 0, 0, p->d_btab,
+                     K, T, 1, K, ldT, p->tab_exp, (_Float16*)p->d_bpanelT);
   if ((st = hip_check(hipGetLastError()))) return st;
-  return hip_check(hipDeviceSynchronize());
+  if ((st = hip_check(hipDeviceSynchronize()))) return st;
+  p->adjb_ready = true;
+  return RWPSF_OK;
 }
 
 int bessel_adjoint(rwpsf_plan* p, int n, const rwpsf_stack* s, const float2* E, const float* dLdI, float* dc,

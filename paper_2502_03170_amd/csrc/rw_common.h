@@ -222,8 +222,8 @@ struct rwpsf_plan {
   float* scratch = nullptr;     // device address of the allocation-free entry point's fixed array
   double drho = 0;              // radial sample pitch
   // Bessel-form adjoint (built on first use)
-  float* d_btabT = nullptr;     // [G][R][T] transposed table
-  uint4* d_bpanelT = nullptr;   // the same as a split-f16 panel
+  bool adjb_ready = false;      // all of the following is complete
+  uint4* d_bpanelT = nullptr;   // the transposed table [G][R][T] as a split-f16 panel
   int* d_GInEx = nullptr;       // [stacks nz V] exponents of the row pairs of G_In
   float* d_GIn = nullptr;       // workspace [2 stacks nz V][G][R] gradients of the radial samples
   float* d_GPhi = nullptr;      // workspace [2 stacks nz V][T] gradient of Phi
