@@ -187,7 +187,7 @@ __global__ void bessel_phi_kernel(PhiArgs a, const BesselNode* __restrict__ node
 // --------------------------------------------------------------------------
 constexpr int kConRows = 64, kConK = 128, kConPad = 256;
 struct ContractArgs {
-  const float* A;
+  const float* A;        // BY_ROW: 16-byte aligned, lda a multiple of 4
   const uint4* B;
   float* C;
   const int* ex;         // [rows / 2] exponents of A's row pairs, or null
@@ -1119,7 +1119,7 @@ int bessel_compute_noalloc(rwpsf_plan* p, int n, const rwpsf_stack* s, float2* E
 //   with dW/dc_j = 2 pi Z_j, dW/dt_s = d W_GL / d t_s, dW/dz_offset = k cos t.
 // --------------------------------------------------------------------------
 struct AdjRadArgs {
-  int nx, ny, nz, R, mode, s_base, K;   // K: columns of G_In (G R)
+  int nx, ny, nz, R, mode, s_base, ld;   // ld: row stride of G_In
   int unit_exp;        // the integer sums' unit is 2^-unit_exp of the bound's power of two
   float dx, dy, inv_drho, drho;
   float exr, exi, eyr, eyi;
@@ -1300,9 +1300,9 @@ __global__ void __launch_bounds__(kRadialThreads, 4) adjb_radial_kernel(AdjRadAr
 #pragma unroll
     for (int e = 0; e < 6; ++e) g[e] = total(e * R + r);
     auto put = [&](int v, int gg, float re, float im) {
-      float* d = GIn + (size_t)(2 * (col + v)) * a.K + gg * R + r;
+      float* d = GIn + (size_t)(2 * (col + v)) * a.ld + gg * R + r;
       d[0] = re;
-      d[a.K] = im;
+      d[a.ld] = im;
     };
     if (a.mode == kModeFresnel) {
       put(0, 0, g[0], g[1]);
@@ -1382,6 +1382,10 @@ __global__ void adjb_coef_kernel(const double* __restrict__ dcp, int n, float* _
   dc[j] = (float)acc;
 }
 
+// Floats from one row of G_In to the next: rows of whole runs of eight, so that the contraction's
+// 16-byte reads of a row are aligned for every count of radial samples.
+static int adjb_row_stride(int K) { return (K + 7) / 8 * 8; }
+
 // Tables and workspace of the adjoint, built on first use and marked ready last, so that a call after
 // one that ran out of memory starts again (with what that one has allocated).
 static int bessel_adjoint_prepare(rwpsf_plan* p) {
@@ -1415,7 +1419,7 @@ static int bessel_adjoint_prepare(rwpsf_plan* p) {
   const size_t M = 2 * (size_t)kPhiStacks * nz * V;
   const int K = G * R, kp = (K + 15) / 16 * 16, ldT = (T + kConPad - 1) / kConPad * kConPad;
   auto need = [&](auto** ptr, size_t count) { return *ptr ? (int)RWPSF_OK : dev_alloc(p, ptr, count); };
-  if ((st = need(&p->d_GIn, (size_t)K * M))) return st;
+  if ((st = need(&p->d_GIn, adjb_row_stride(K) * M))) return st;
   if ((st = need(&p->d_GPhi, M * T))) return st;
   if ((st = need(&p->d_GInEx, (size_t)kPhiStacks * nz * V))) return st;
   if ((st = need(&p->d_adjX, (size_t)kPhiStacks * T))) return st;
@@ -1455,7 +1459,7 @@ int bessel_adjoint(rwpsf_plan* p, int n, const rwpsf_stack* s, const float2* E, 
     ra.R = R;
     ra.mode = mode;
     ra.s_base = b0;
-    ra.K = G * R;
+    ra.ld = adjb_row_stride(G * R);
     ra.unit_exp = 40;
     while (((long long)p->grid.nx * p->grid.ny - 1) >> (62 - ra.unit_exp)) --ra.unit_exp;   // >= 36
     ra.dx = (float)p->grid.dx_nm;
@@ -1478,7 +1482,7 @@ int bessel_adjoint(rwpsf_plan* p, int n, const rwpsf_stack* s, const float2* E, 
     // G_Phi[m][q] = sum_k G_In[m][k] B^T[k][q]
     const int K = G * R;
     tr = p->time_begin(RWPSF_KERNEL_ADJB_CONTRACT, st);
-    const ContractArgs ca{p->d_GIn, p->d_bpanelT, p->d_GPhi, p->d_GInEx, K,
+    const ContractArgs ca{p->d_GIn, p->d_bpanelT, p->d_GPhi, p->d_GInEx, adjb_row_stride(K),
                           (T + kConPad - 1) / kConPad * kConPad, T, M, T, K, 0, -p->tab_exp};
     if ((rc = hip_check(launch_contract<true>(ca, st)))) return rc;
     p->time_end(tr, st);

@@ -225,7 +225,7 @@ struct rwpsf_plan {
   bool adjb_ready = false;      // all of the following is complete
   uint4* d_bpanelT = nullptr;   // the transposed table [G][R][T] as a split-f16 panel
   int* d_GInEx = nullptr;       // [stacks nz V] exponents of the row pairs of G_In
-  float* d_GIn = nullptr;       // workspace [2 stacks nz V][G][R] gradients of the radial samples
+  float* d_GIn = nullptr;       // workspace [2 stacks nz V] rows of [G][R] gradients of the radial samples
   float* d_GPhi = nullptr;      // workspace [2 stacks nz V][T] gradient of Phi
   double2* d_adjX = nullptr;    // workspace [stacks][T] sum_z conj(G_Phi) Phi
   double* d_adjnode = nullptr;  // [T][7] k cos t, dW/dt_s (re, im), 2 pi Z_{1,4,11,22}
