@@ -34,6 +34,11 @@
 
 namespace rw {
 
+// Wide loads of the caller's arrays, which are aligned as their elements are (the hardware takes any
+// multiple of four bytes).
+typedef float any4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef float any2 __attribute__((ext_vector_type(2), aligned(4)));
+
 constexpr int kAdjStacks = 64;    // stacks per launch (their z offsets are passed by value)
 constexpr int kAdjThreads = 512;  // eight waves
 constexpr int kAdjCols = 32;      // folded y cells per workgroup
@@ -85,15 +90,15 @@ __global__ void adj_defocus_kernel(const double* __restrict__ kszf, const double
 __global__ void __launch_bounds__(256) adj_scale_kernel(const float2* __restrict__ E, const float* __restrict__ g,
                                                         int pixels, int* __restrict__ ex) {
   const size_t item = blockIdx.x;
-  const float4* e4 = reinterpret_cast<const float4*>(E + item * 3 * pixels);
-  const float2* g2 = reinterpret_cast<const float2*>(g + item * pixels);
+  const any4* e4 = reinterpret_cast<const any4*>(E + item * 3 * pixels);
+  const any2* g2 = reinterpret_cast<const any2*>(g + item * pixels);
   const int pairs = pixels / 2;
   float m[3] = {0.f, 0.f, 0.f};
   for (int i = threadIdx.x; i < pairs; i += 256) {
-    const float2 f = g2[i];
+    const any2 f = g2[i];
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      const float4 v = e4[(size_t)c * pairs + i];
+      const any4 v = e4[(size_t)c * pairs + i];
       m[c] = fmaxf(m[c], fmaxf(fmaxf(fabsf(2.f * f.x * v.x), fabsf(2.f * f.x * v.y)),
                                fmaxf(fabsf(2.f * f.y * v.z), fabsf(2.f * f.y * v.w))));
     }
@@ -196,12 +201,12 @@ __global__ void __launch_bounds__(kAdjThreads, 2) adj_kernel(AdjArgs a) {
     const size_t pl = gs * a.nz + zi;
     const bool ok = m < a.nx && n < a.ny;
     const size_t off = ok ? (size_t)m * a.ny + n : 0;
-    const float4* ep = reinterpret_cast<const float4*>(a.E + (pl * 3 + c) * plane + off);
-    const float4* gp = reinterpret_cast<const float4*>(a.g + pl * plane + off);
+    const any4* ep = reinterpret_cast<const any4*>(a.E + (pl * 3 + c) * plane + off);
+    const any4* gp = reinterpret_cast<const any4*>(a.g + pl * plane + off);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) r.v[i] = ep[i];
+    for (int i = 0; i < 4; ++i) r.v[i] = make_float4(ep[i].x, ep[i].y, ep[i].z, ep[i].w);
 #pragma unroll
-    for (int i = 0; i < 2; ++i) r.f[i] = gp[i];
+    for (int i = 0; i < 2; ++i) r.f[i] = make_float4(gp[i].x, gp[i].y, gp[i].z, gp[i].w);
     r.two = ok ? 2.f : 0.f;
     r.e = a.ex[pl * 3 + c];
     if constexpr (MULTI) {
