@@ -129,7 +129,7 @@ struct AdjArgs {
   const float2* D;     // [nz][nhp][nhp] exp(i k s_z z) of the plan's planes
   const float2* Pf;    // [launch's stacks][3][w][w] mirror-folded pupils (the forward's fold)
   const double* kszf;  // [nhp][nhp]
-  float* partial;      // [stacks * 3 * zgroups * MC][np][np], MC chunks along x
+  float* partial;      // [launch's stacks * 3 * zgroups * MC][np][np], MC chunks along x
   double zoff[kAdjStacks];
   int s0, nstk, nz, nx, ny, w, n, row_groups;
   int zgroups, zper;   // planes are split into zgroups runs of zper (the last may be shorter)
@@ -392,7 +392,7 @@ __global__ void __launch_bounds__(kAdjThreads, 2) adj_kernel(AdjArgs a) {
   const int nh = (a.n + 1) / 2;
   const size_t npp = (size_t)a.w * a.w;
   const float2* Pf = a.Pf + ((size_t)s * 3 + c) * npp;
-  float* out = a.partial + (((gs * 3 + c) * a.zgroups + zg) * MC + mc) * npp;
+  float* out = a.partial + ((((size_t)s * 3 + c) * a.zgroups + zg) * MC + mc) * npp;
 #pragma unroll
   for (int q = 0; q < 8; ++q) {
     const int jf = jf0 + 4 * (q >> 1) + 2 * h + (q & 1);
@@ -426,8 +426,9 @@ __global__ void __launch_bounds__(kAdjThreads, 2) adj_kernel(AdjArgs a) {
   }
 }
 
-// dL/dPhi on the N x N cells: the partials are summed in group order (FP64) in two
-// levels -- runs of kReduceRun groups (grid.y runs), then the runs in order.
+// dL/dPhi on the N x N cells: the partials of a launch are summed in group order (FP64) in two
+// levels -- runs of kReduceRun groups (grid.y runs) into rows 1, 2, .. of `runs`, then the rows in
+// order; row 0 is the sum over the launches before.
 constexpr int kReduceRun = 32;
 
 __global__ void adj_reduce_runs_kernel(const float* __restrict__ partial, int groups, int n, int np,
@@ -440,14 +441,24 @@ __global__ void adj_reduce_runs_kernel(const float* __restrict__ partial, int gr
   double s = 0.0;
 #pragma unroll 8
   for (int g = g0; g < g1; ++g) s += (double)partial[g * npp + pc];
-  runs[(size_t)blockIdx.y * n * n + cell] = s;
+  runs[(size_t)(blockIdx.y + 1) * n * n + cell] = s;
+}
+
+// The sum over the launches so far: rows row0 .. nruns into row 0.
+__global__ void adj_total_kernel(double* __restrict__ runs, int row0, int nruns, int nn) {
+  const int cell = blockIdx.x * blockDim.x + threadIdx.x;
+  if (cell >= nn) return;
+  double s = 0.0;
+#pragma unroll 8
+  for (int r = row0; r <= nruns; ++r) s += runs[(size_t)r * nn + cell];
+  runs[cell] = s;
 }
 
 // Second level, dL/dW0, and each workgroup's share of dL/dc_q = 2 pi sum_cells dL/dPhi Z_q
 // (a tree over the lanes, then the four waves in order).
 constexpr int kReduceThreads = 256;
-__global__ void __launch_bounds__(kReduceThreads) adj_reduce_kernel(const double* __restrict__ runs, int nruns, int n,
-                                                                    float* __restrict__ dW0,
+__global__ void __launch_bounds__(kReduceThreads) adj_reduce_kernel(const double* __restrict__ runs, int row0,
+                                                                    int nruns, int n, float* __restrict__ dW0,
                                                                     const float* __restrict__ ztab, int n_zernike,
                                                                     double* __restrict__ shares) {
   __shared__ double red[RWPSF_MAX_ZERNIKE][kReduceThreads / 64];
@@ -456,7 +467,7 @@ __global__ void __launch_bounds__(kReduceThreads) adj_reduce_kernel(const double
   double s = 0.0;
   if (in) {
 #pragma unroll 8
-    for (int r = 0; r < nruns; ++r) s += runs[(size_t)r * nn + cell];
+    for (int r = row0; r <= nruns; ++r) s += runs[(size_t)r * nn + cell];
     if (dW0) dW0[cell] = (float)s;
   }
   for (int q0 = 0; q0 < n_zernike; q0 += 6) {   // six terms' loads and trees in flight
@@ -493,15 +504,23 @@ __global__ void __launch_bounds__(kReduceThreads) adj_zernike_kernel(const doubl
   if (threadIdx.x == 0) dc[blockIdx.x] = (float)(kTwoPi * ((red[0] + red[1]) + (red[2] + red[3])));
 }
 
-// How a call is spread over workgroups.
+// How a call is spread over workgroups and launches.  The partial sums of a launch take at most
+// kAdjPartialBytes, or one run of all planes of one stack where that is more (1.5 GiB at the largest
+// image and pupil): wide images and large pupils take longer runs, then fewer stacks a launch.  (All
+// partial sums of a call at once were 41 GB for 1024 stacks of 256 x 256 x 21 at N = 512.)
+constexpr size_t kAdjPartialBytes = (size_t)1 << 30;
 struct AdjSplit {
   void (*k)(AdjArgs);
   int row_groups, zgroups, zper, chunks_x;
+  int stacks;   // of a launch, at most
+  int groups(int n) const { return 3 * std::min(n, stacks) * zgroups * chunks_x; }   // partial sums of a launch
 };
 static AdjSplit adjoint_split(const rwpsf_plan* p, int n) {
   const int w = 2 * p->nhp, nz = p->grid.nz;
   const int mc = (p->grid.nx + kAdjChunk - 1) / kAdjChunk, nc = (p->grid.ny + kAdjChunk - 1) / kAdjChunk;
-  AdjSplit r{nc > 1 ? adj_kernel<true> : adj_kernel<false>, (w + kAdjRows - 1) / kAdjRows, 1, nz, mc};
+  AdjSplit r{nc > 1 ? adj_kernel<true> : adj_kernel<false>, (w + kAdjRows - 1) / kAdjRows, 1, nz, mc, kAdjStacks};
+  const size_t fit = kAdjPartialBytes / ((size_t)3 * mc * p->np * p->np * sizeof(float));   // runs of planes of a launch
+  const int shortest = fit > 0 ? (int)((nz + fit - 1) / fit) : nz;
   // Runs of planes: one workgroup fits a CU (256 of them), a plane takes a step per chunk along y
   // and the pupil at the end of a run costs about three.  The shortest runs (they are summed in
   // FP32, the partial sums in FP64) within 15% of the least number of rounds times length.
@@ -510,9 +529,10 @@ static AdjSplit adjoint_split(const rwpsf_plan* p, int n) {
     return ((base * ((nz + zper - 1) / zper) + 255) / 256) * ((long long)zper * nc + 3);
   };
   long long best = cost(nz);
-  for (int zper = 1; zper < nz; ++zper) best = std::min(best, cost(zper));
-  for (r.zper = 1; 20 * cost(r.zper) > 23 * best;) ++r.zper;
+  for (int zper = shortest; zper < nz; ++zper) best = std::min(best, cost(zper));
+  for (r.zper = shortest; 20 * cost(r.zper) > 23 * best;) ++r.zper;
   r.zgroups = (nz + r.zper - 1) / r.zper;
+  r.stacks = (int)std::max<size_t>(1, std::min<size_t>(kAdjStacks, fit / r.zgroups));
   return r;
 }
 
@@ -552,15 +572,21 @@ static int adjoint_prepare(rwpsf_plan* p, int n_stacks, const AdjSplit& sp) {
     p->d_adjEx = d;
     p->adj_stacks = n_stacks;
   }
-  const int groups = 3 * n_stacks * sp.zgroups * sp.chunks_x;
-  if (p->partial_groups < groups) {
+  if (p->partial_stacks < std::min(n_stacks, kAdjStacks)) {
+    // Room for every call of up to that many stacks: one of fewer may have more runs of planes, and
+    // must not have to allocate after a larger one (it may be under capture).  In powers of two, as
+    // what is replaced stays with the plan.
+    int most = 1;
+    while (most < std::min(n_stacks, kAdjStacks)) most *= 2;
+    int groups = 0;
+    for (int n = 1; n <= most; ++n) groups = std::max(groups, adjoint_split(p, n).groups(n));
     float* d = nullptr;
     if ((st = dev_alloc(p, &d, (size_t)groups * np * np))) return st;
     double* r = nullptr;
-    if ((st = dev_alloc(p, &r, (size_t)((groups + kReduceRun - 1) / kReduceRun) * N * N))) return st;
+    if ((st = dev_alloc(p, &r, (size_t)((groups + kReduceRun - 1) / kReduceRun + 1) * N * N))) return st;
     p->d_partial = d;
     p->d_runs = r;
-    p->partial_groups = groups;
+    p->partial_stacks = most;
   }
   return RWPSF_OK;
 }
@@ -577,8 +603,9 @@ int fourier_adjoint(rwpsf_plan* p, int n, const rwpsf_stack* s, const float2* E,
   hipLaunchKernelGGL(adj_scale_kernel, dim3((unsigned)(n * nz)), dim3(256), 0, st, E, dLdI, nx * ny, p->d_adjEx);
   if ((rc = hip_check(hipGetLastError()))) return rc;
   p->time_end(tr, st);
-  for (int b0 = 0; b0 < n; b0 += kAdjStacks) {
-    const int nb = std::min(kAdjStacks, n - b0);
+  const int rblocks = (N * N + kReduceThreads - 1) / kReduceThreads;
+  for (int b0 = 0; b0 < n; b0 += sp.stacks) {
+    const int nb = std::min(sp.stacks, n - b0);
     if ((rc = fourier_build_folded(p, s + b0, nb, p->d_adjPf, st))) return rc;
     AdjArgs a{};
     a.E = E;
@@ -614,21 +641,26 @@ int fourier_adjoint(rwpsf_plan* p, int n, const rwpsf_stack* s, const float2* E,
     hipLaunchKernelGGL(sp.k, dim3(blocks), dim3(kAdjThreads), kAdjLds, st, a);
     if ((rc = hip_check(hipGetLastError()))) return rc;
     p->time_end(tr, st);
-  }
-  tr = p->time_begin(RWPSF_KERNEL_ADJ_REDUCE, st);
-  const int groups = 3 * n * sp.zgroups * sp.chunks_x, nruns = (groups + kReduceRun - 1) / kReduceRun;
-  hipLaunchKernelGGL(adj_reduce_runs_kernel, dim3((N * N + 255) / 256, nruns), dim3(256), 0, st, p->d_partial,
-                     groups, N, np, p->d_runs);
-  if ((rc = hip_check(hipGetLastError()))) return rc;
-  const int rblocks = (N * N + kReduceThreads - 1) / kReduceThreads;
-  hipLaunchKernelGGL(adj_reduce_kernel, dim3(rblocks), dim3(kReduceThreads), 0, st, p->d_runs, nruns, N, dW0, p->d_ztab,
-                     n_zernike, p->d_shares);
-  if ((rc = hip_check(hipGetLastError()))) return rc;
-  if (n_zernike > 0) {
-    hipLaunchKernelGGL(adj_zernike_kernel, dim3(n_zernike), dim3(kReduceThreads), 0, st, p->d_shares, rblocks, dc);
+    // this launch's partial sums, with those of the launches before
+    tr = p->time_begin(RWPSF_KERNEL_ADJ_REDUCE, st);
+    const int groups = sp.groups(nb), nruns = (groups + kReduceRun - 1) / kReduceRun, row0 = b0 == 0 ? 1 : 0;
+    hipLaunchKernelGGL(adj_reduce_runs_kernel, dim3((N * N + 255) / 256, nruns), dim3(256), 0, st, p->d_partial,
+                       groups, N, np, p->d_runs);
     if ((rc = hip_check(hipGetLastError()))) return rc;
+    if (b0 + nb < n) {
+      hipLaunchKernelGGL(adj_total_kernel, dim3((N * N + 255) / 256), dim3(256), 0, st, p->d_runs, row0, nruns, N * N);
+      if ((rc = hip_check(hipGetLastError()))) return rc;
+    } else {
+      hipLaunchKernelGGL(adj_reduce_kernel, dim3(rblocks), dim3(kReduceThreads), 0, st, p->d_runs, row0, nruns, N, dW0,
+                         p->d_ztab, n_zernike, p->d_shares);
+      if ((rc = hip_check(hipGetLastError()))) return rc;
+      if (n_zernike > 0) {
+        hipLaunchKernelGGL(adj_zernike_kernel, dim3(n_zernike), dim3(kReduceThreads), 0, st, p->d_shares, rblocks, dc);
+        if ((rc = hip_check(hipGetLastError()))) return rc;
+      }
+    }
+    p->time_end(tr, st);
   }
-  p->time_end(tr, st);
   return RWPSF_OK;
 }
 

@@ -188,11 +188,11 @@ struct rwpsf_plan {
   int* d_adjEx = nullptr;       // [adj_stacks][nz][3] power-of-two scales of 2 dL/dI E
   int adj_stacks = 0;
   float2* d_adjPf = nullptr;    // [64 stacks][3][2 nhp][2 nhp] folded pupils of an adjoint launch
-  float* d_partial = nullptr;   // [groups][np][np] per-(stack, component, run of planes, part) dL/dPhi
-  int partial_groups = 0;
+  float* d_partial = nullptr;   // [groups][np][np] a launch's per-(stack, component, run of planes, part) dL/dPhi
+  int partial_stacks = 0;       // calls of up to that many stacks (and of more) have room there
   double* d_shares = nullptr;   // [RWPSF_MAX_ZERNIKE][workgroups of the reduction] shares of dL/dc
   float2* d_adjD = nullptr;     // [nz][nhp][nhp] exp(i k s_z z) of the plan's planes on the folded cells
-  double* d_runs = nullptr;     // [partial runs][N][N] first level of the dL/dPhi reduction
+  double* d_runs = nullptr;     // [1 + partial runs][N][N] sum so far, first level of the dL/dPhi reduction
   int P_stacks = 0;             // capacity of d_P in stacks
 
   // chirp-z evaluation of the Fourier form
