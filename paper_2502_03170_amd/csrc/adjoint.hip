@@ -39,6 +39,7 @@ namespace rw {
 typedef float any4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef float any2 __attribute__((ext_vector_type(2), aligned(4)));
 
+constexpr int kScalePixels = 4096, kScaleGroups = 1024;   // scales of the planes: pixels of a workgroup, workgroups
 constexpr int kAdjStacks = 64;    // stacks per launch (their z offsets are passed by value)
 constexpr int kAdjThreads = 512;  // eight waves
 constexpr int kAdjCols = 32;      // folded y cells per workgroup
@@ -84,17 +85,30 @@ __global__ void adj_defocus_kernel(const double* __restrict__ kszf, const double
   D[idx] = make_float2(cs, sn);
 }
 
-// Scale of every (stack, plane, component): the exponent e that puts the largest part of
-// 2 g E 2^e in [2^13, 2^14), 0 for an empty or not finite plane.  One workgroup per
-// (stack, plane); pixels a multiple of 4.
+// Scale of every (stack, plane, component): the exponent e that puts the largest part x of 2 g E 2^e
+// in [2^13, 2^14), 0 for an empty or not finite plane.
+__device__ __forceinline__ int adj_exponent(float x) {
+  int b = 0;
+  if (!(x > 0.f && x < INFINITY)) return 0;
+  frexpf(x, &b);   // x in [2^(b-1), 2^b)
+  return 14 - b;
+}
+
+// The largest parts of a plane: `parts` workgroups per (stack, plane), each a run of its pixels
+// (a multiple of 4 in all).  One writes the plane's scales, several their maxima for adj_exponent_kernel.
+// Bound by its loads in flight: a call of few, large planes needs several workgroups a plane (2 planes
+// of 512 x 512 pixels: 181 us with one workgroup a plane, 6.4 with 64; 10 of 256 x 256: 49 us, 6.4
+// with 16).
 __global__ void __launch_bounds__(256) adj_scale_kernel(const float2* __restrict__ E, const float* __restrict__ g,
-                                                        int pixels, int* __restrict__ ex) {
-  const size_t item = blockIdx.x;
+                                                        int pixels, int parts, int* __restrict__ ex,
+                                                        float* __restrict__ maxima) {
+  const size_t item = blockIdx.x / parts;
   const any4* e4 = reinterpret_cast<const any4*>(E + item * 3 * pixels);
   const any2* g2 = reinterpret_cast<const any2*>(g + item * pixels);
-  const int pairs = pixels / 2;
+  const int pairs = pixels / 2, run = (pairs + parts - 1) / parts;
+  const int i0 = (blockIdx.x % parts) * run, i1 = min(pairs, i0 + run);
   float m[3] = {0.f, 0.f, 0.f};
-  for (int i = threadIdx.x; i < pairs; i += 256) {
+  for (int i = i0 + threadIdx.x; i < i1; i += 256) {
     const any2 f = g2[i];
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
@@ -114,10 +128,22 @@ __global__ void __launch_bounds__(256) adj_scale_kernel(const float2* __restrict
   if (threadIdx.x < 3) {
     const float* r = red[threadIdx.x];
     const float x = fmaxf(fmaxf(r[0], r[1]), fmaxf(r[2], r[3]));
-    int b = 0;
-    if (x > 0.f && x < INFINITY) frexpf(x, &b);   // x in [2^(b-1), 2^b)
-    ex[item * 3 + threadIdx.x] = x > 0.f && x < INFINITY ? 14 - b : 0;
+    if (parts == 1)
+      ex[item * 3 + threadIdx.x] = adj_exponent(x);
+    else
+      maxima[(size_t)blockIdx.x * 3 + threadIdx.x] = x;
   }
+}
+
+// The scales from the maxima of the runs: one thread per (stack, plane, component).
+__global__ void adj_exponent_kernel(const float* __restrict__ maxima, int parts, int count, int* __restrict__ ex) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= count) return;
+  const float* m = maxima + ((size_t)(i / 3) * parts) * 3 + i % 3;
+  float x = 0.f;
+#pragma unroll 8
+  for (int p = 0; p < parts; ++p) x = fmaxf(x, m[3 * p]);
+  ex[i] = adj_exponent(x);
 }
 
 struct AdjArgs {
@@ -552,6 +578,7 @@ static int adjoint_prepare(rwpsf_plan* p, int n_stacks, const AdjSplit& sp) {
     if ((st = dev_alloc(p, &p->d_adjPf, (size_t)kAdjStacks * 3 * w * w))) return st;
     const size_t cells = (size_t)nhp * nhp;
     if ((st = dev_alloc(p, &p->d_adjD, nz * cells))) return st;
+    if ((st = dev_alloc(p, &p->d_adjMax, (size_t)3 * kScaleGroups))) return st;
     hipLaunchKernelGGL(adj_panel_kernel, dim3((nx * nhp + 255) / 256), dim3(256), 0, 0, (_Float16*)tx, nx, N, w, k,
                        s_max, p->grid.dx_nm, 0);
     hipLaunchKernelGGL(adj_panel_kernel, dim3((ny * nhp + 255) / 256), dim3(256), 0, 0, (_Float16*)ty, ny, N, w, k,
@@ -600,8 +627,17 @@ int fourier_adjoint(rwpsf_plan* p, int n, const rwpsf_stack* s, const float2* E,
   if (rc) return rc;
   const int w = 2 * p->nhp;
   int tr = p->time_begin(RWPSF_KERNEL_ADJ_H, st);
-  hipLaunchKernelGGL(adj_scale_kernel, dim3((unsigned)(n * nz)), dim3(256), 0, st, E, dLdI, nx * ny, p->d_adjEx);
+  // workgroups per plane: runs of at least kScalePixels, while there are fewer than four for each of 256 CUs
+  const int items = n * nz;
+  const int parts = std::max(1, std::min(nx * ny / kScalePixels, kScaleGroups / items));
+  hipLaunchKernelGGL(adj_scale_kernel, dim3((unsigned)items * parts), dim3(256), 0, st, E, dLdI, nx * ny, parts,
+                     p->d_adjEx, p->d_adjMax);
   if ((rc = hip_check(hipGetLastError()))) return rc;
+  if (parts > 1) {
+    hipLaunchKernelGGL(adj_exponent_kernel, dim3((unsigned)(3 * items + 63) / 64), dim3(64), 0, st, p->d_adjMax, parts,
+                       3 * items, p->d_adjEx);
+    if ((rc = hip_check(hipGetLastError()))) return rc;
+  }
   p->time_end(tr, st);
   const int rblocks = (N * N + kReduceThreads - 1) / kReduceThreads;
   for (int b0 = 0; b0 < n; b0 += sp.stacks) {

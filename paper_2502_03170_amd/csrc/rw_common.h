@@ -187,6 +187,7 @@ struct rwpsf_plan {
   uint4* d_adjTy = nullptr;     // split-f16 panel of 2 nhp columns 64 (lf / 32) + 32 p + lf % 32, k = y pixel
   int* d_adjEx = nullptr;       // [adj_stacks][nz][3] power-of-two scales of 2 dL/dI E
   int adj_stacks = 0;
+  float* d_adjMax = nullptr;    // [workgroups][3] largest parts of 2 dL/dI E in runs of a plane's pixels
   float2* d_adjPf = nullptr;    // [64 stacks][3][2 nhp][2 nhp] folded pupils of an adjoint launch
   float* d_partial = nullptr;   // [groups][np][np] a launch's per-(stack, component, run of planes, part) dL/dPhi
   int partial_stacks = 0;       // calls of up to that many stacks (and of more) have room there
