@@ -567,22 +567,20 @@ static int adjoint_prepare(rwpsf_plan* p, int n_stacks, const AdjSplit& sp) {
   const int nx = p->grid.nx, ny = p->grid.ny, nz = p->grid.nz, N = p->num.n_pupil, np = p->np;
   const int nhp = p->nhp, w = 2 * nhp;
   int st;
-  if (!p->d_adjTx) {
+  if (!p->adj_ready) {   // set last; a try that failed on the way leaves what it has allocated to the next
     const double s_max = p->s_max, k = p->k;
-    uint4 *tx = nullptr, *ty = nullptr;
-    if ((st = dev_alloc(p, &tx, hg_panel_bytes(nx, w) / sizeof(uint4)))) return st;
-    if ((st = dev_alloc(p, &ty, hg_panel_bytes(ny, w) / sizeof(uint4)))) return st;
-    if ((st = dev_alloc(p, &p->d_shares, (size_t)RWPSF_MAX_ZERNIKE * ((N * N + kReduceThreads - 1) / kReduceThreads))))
-      return st;
-    // folded pupils of a whole launch
-    if ((st = dev_alloc(p, &p->d_adjPf, (size_t)kAdjStacks * 3 * w * w))) return st;
     const size_t cells = (size_t)nhp * nhp;
-    if ((st = dev_alloc(p, &p->d_adjD, nz * cells))) return st;
-    if ((st = dev_alloc(p, &p->d_adjMax, (size_t)3 * kScaleGroups))) return st;
-    hipLaunchKernelGGL(adj_panel_kernel, dim3((nx * nhp + 255) / 256), dim3(256), 0, 0, (_Float16*)tx, nx, N, w, k,
-                       s_max, p->grid.dx_nm, 0);
-    hipLaunchKernelGGL(adj_panel_kernel, dim3((ny * nhp + 255) / 256), dim3(256), 0, 0, (_Float16*)ty, ny, N, w, k,
-                       s_max, p->grid.dy_nm, 1);
+    if ((st = dev_need(p, &p->d_adjTx, hg_panel_bytes(nx, w) / sizeof(uint4)))) return st;
+    if ((st = dev_need(p, &p->d_adjTy, hg_panel_bytes(ny, w) / sizeof(uint4)))) return st;
+    if ((st = dev_need(p, &p->d_shares, (size_t)RWPSF_MAX_ZERNIKE * ((N * N + kReduceThreads - 1) / kReduceThreads))))
+      return st;
+    if ((st = dev_need(p, &p->d_adjPf, (size_t)kAdjStacks * 3 * w * w))) return st;   // of a whole launch
+    if ((st = dev_need(p, &p->d_adjD, nz * cells))) return st;
+    if ((st = dev_need(p, &p->d_adjMax, (size_t)3 * kScaleGroups))) return st;
+    hipLaunchKernelGGL(adj_panel_kernel, dim3((nx * nhp + 255) / 256), dim3(256), 0, 0, (_Float16*)p->d_adjTx, nx, N, w,
+                       k, s_max, p->grid.dx_nm, 0);
+    hipLaunchKernelGGL(adj_panel_kernel, dim3((ny * nhp + 255) / 256), dim3(256), 0, 0, (_Float16*)p->d_adjTy, ny, N, w,
+                       k, s_max, p->grid.dy_nm, 1);
     hipLaunchKernelGGL(adj_defocus_kernel, dim3((unsigned)((nz * cells + 255) / 256)), dim3(256), 0, 0, p->d_kszf,
                        p->d_z, nz, (int)cells, p->d_adjD);
     if ((st = hip_check(hipGetLastError()))) return st;
@@ -590,8 +588,7 @@ static int adjoint_prepare(rwpsf_plan* p, int n_stacks, const AdjSplit& sp) {
     if ((st = hip_check(hipDeviceSynchronize()))) return st;
     if ((st = hip_check(hipFuncSetAttribute((const void*)sp.k, hipFuncAttributeMaxDynamicSharedMemorySize, kAdjLds))))
       return st;
-    p->d_adjTy = ty;
-    p->d_adjTx = tx;
+    p->adj_ready = true;
   }
   if (p->adj_stacks < n_stacks) {
     int* d = nullptr;
@@ -610,7 +607,10 @@ static int adjoint_prepare(rwpsf_plan* p, int n_stacks, const AdjSplit& sp) {
     float* d = nullptr;
     if ((st = dev_alloc(p, &d, (size_t)groups * np * np))) return st;
     double* r = nullptr;
-    if ((st = dev_alloc(p, &r, (size_t)((groups + kReduceRun - 1) / kReduceRun + 1) * N * N))) return st;
+    if ((st = dev_alloc(p, &r, (size_t)((groups + kReduceRun - 1) / kReduceRun + 1) * N * N))) {
+      dev_release(p, d, (size_t)groups * np * np);
+      return st;
+    }
     p->d_partial = d;
     p->d_runs = r;
     p->partial_stacks = most;

@@ -1418,14 +1418,13 @@ static int bessel_adjoint_prepare(rwpsf_plan* p) {
   }
   const size_t M = 2 * (size_t)kPhiStacks * nz * V;
   const int K = G * R, kp = (K + 15) / 16 * 16, ldT = (T + kConPad - 1) / kConPad * kConPad;
-  auto need = [&](auto** ptr, size_t count) { return *ptr ? (int)RWPSF_OK : dev_alloc(p, ptr, count); };
-  if ((st = need(&p->d_GIn, adjb_row_stride(K) * M))) return st;
-  if ((st = need(&p->d_GPhi, M * T))) return st;
-  if ((st = need(&p->d_GInEx, (size_t)kPhiStacks * nz * V))) return st;
-  if ((st = need(&p->d_adjX, (size_t)kPhiStacks * T))) return st;
-  if ((st = need(&p->d_adjnode, node.size()))) return st;
-  if ((st = need(&p->d_dcp, 4 * (size_t)RWPSF_MAX_STACKS_PER_CALL))) return st;
-  if ((st = need(&p->d_bpanelT, hg_panel_bytes(kp, ldT) / sizeof(uint4)))) return st;
+  if ((st = dev_need(p, &p->d_GIn, adjb_row_stride(K) * M))) return st;
+  if ((st = dev_need(p, &p->d_GPhi, M * T))) return st;
+  if ((st = dev_need(p, &p->d_GInEx, (size_t)kPhiStacks * nz * V))) return st;
+  if ((st = dev_need(p, &p->d_adjX, (size_t)kPhiStacks * T))) return st;
+  if ((st = dev_need(p, &p->d_adjnode, node.size()))) return st;
+  if ((st = dev_need(p, &p->d_dcp, 4 * (size_t)RWPSF_MAX_STACKS_PER_CALL))) return st;
+  if ((st = dev_need(p, &p->d_bpanelT, hg_panel_bytes(kp, ldT) / sizeof(uint4)))) return st;
   if ((st = hip_check(hipMemcpy(p->d_adjnode, node.data(), node.size() * sizeof(double), hipMemcpyHostToDevice))))
     return st;
   // the limits are per kernel, not per plan: allow the whole LDS so plans of any size can launch

@@ -183,6 +183,7 @@ struct rwpsf_plan {
   uint4* d_T = nullptr;         // workspace [planes][3] split-f16 panels of 2 nyp rows 2n + ri, k = q
   size_t T_planes = 0;          // capacity of d_T in stack-planes
   // adjoint (built on first use)
+  bool adj_ready = false;       // the tables and d_shares, d_adjPf, d_adjD, d_adjMax are complete
   uint4* d_adjTx = nullptr;     // split-f16 panel of 2 nhp columns 2jf + p, k = x pixel
   uint4* d_adjTy = nullptr;     // split-f16 panel of 2 nhp columns 64 (lf / 32) + 32 p + lf % 32, k = y pixel
   int* d_adjEx = nullptr;       // [adj_stacks][nz][3] power-of-two scales of 2 dL/dI E

@@ -102,6 +102,20 @@ int dev_alloc(rwpsf_plan* p, T** ptr, size_t count) {
   return RWPSF_OK;
 }
 
+// Back at once what the last dev_alloc of the plan gave (nothing uses it yet).
+template <class T>
+void dev_release(rwpsf_plan* p, T* ptr, size_t count) {
+  p->allocations.pop_back();
+  p->device_bytes -= count * sizeof(T);
+  (void)hipFree(ptr);
+}
+
+// The same unless an earlier try, which failed later, has it already.
+template <class T>
+int dev_need(rwpsf_plan* p, T** ptr, size_t count) {
+  return *ptr ? (int)RWPSF_OK : dev_alloc(p, ptr, count);
+}
+
 inline int hip_check(hipError_t e) {
   if (e == hipSuccess) return RWPSF_OK;
   set_hip_error(e);
