@@ -87,7 +87,7 @@ __device__ __forceinline__ PupilCell<NZ> pupil_cell(const PupilGeom& a, const fl
 }
 
 // exp(i W) (times the evanescent decay of a Gibson-Lanni layer) at a cell, for stack st with the
-// coefficients 2 pi c in coef and the value w0 of its phase map (the table values of terms past
+// coefficients (waves) in coef and the value w0 of its phase map (the table values of terms past
 // max_zernike are 0).
 template <int NZ, class Stack>
 __device__ __forceinline__ float2 pupil_phase_factor(const PupilGeom& a, const Stack& st, const double* coef, float w0,
@@ -96,8 +96,10 @@ __device__ __forceinline__ float2 pupil_phase_factor(const PupilGeom& a, const S
   if (a.gibson_lanni) gl_opd(a.gl, st.t_s, p.sin_t, &w_re, &w_im);
   w_re -= a.k * (p.sx * st.x0 + p.sy * st.y0);
   w_re += (double)w0;
+  double waves = 0.0;
 #pragma unroll
-  for (int k = 0; k < NZ; ++k) w_re += coef[k] * (double)p.zv[k];
+  for (int k = 0; k < NZ; ++k) waves += coef[k] * (double)p.zv[k];
+  w_re += kTwoPi * waves;
   // the evanescent decay in FP32 (relative error ~1e-7, far below the tolerance); the phase
   // reduced in FP64
   const float amp = w_im > 0.0 ? expf((float)-w_im) : 1.f;

@@ -179,7 +179,7 @@ static void fill_pupil_geom(const rwpsf_plan* p, const rwpsf_stack* s, int nb, P
   for (int i = 0; i < nb; ++i) maxz = std::max(maxz, s[i].n_zernike);
   pa.max_zernike = maxz;
 }
-static double pupil_coef(const rwpsf_stack& x, int q) { return q < x.n_zernike ? kTwoPi * x.zernike_waves[q] : 0.0; }
+static double pupil_coef(const rwpsf_stack& x, int q) { return q < x.n_zernike ? x.zernike_waves[q] : 0.0; }
 template <class Stack>
 static void fill_pupil_stack(const rwpsf_stack& x, Stack& d) {
   d.t_s = x.t_s_nm;

@@ -14,7 +14,7 @@ constexpr int kGemmStacks = 64;  // stacks per GEMM launch (folded pupils of sev
 
 struct PupilStack {
   double t_s, x0, y0;
-  double coef[RWPSF_MAX_ZERNIKE];   // 2 pi c
+  double coef[RWPSF_MAX_ZERNIKE];   // waves
   const float* w0;
 };
 
@@ -31,14 +31,15 @@ struct PupilArgs : PupilGeom {
 static_assert(sizeof(PupilArgs) <= 4000, "kernel arguments are passed by value (4 KB limit)");
 
 // Arguments of the folded pupils: the coefficients are packed, max_zernike a stack (a read of
-// RWPSF_MAX_ZERNIKE from any stack's first stays inside).
+// RWPSF_MAX_ZERNIKE from any stack's first stays inside; past the stack's own terms it meets the next
+// stack's, which are finite as the caller gave them, times zero).
 struct FoldStack {
   double t_s, x0, y0;
   const float* w0;
 };
 struct FoldArgs : PupilGeom {
   FoldStack s[kFoldStacks];
-  double coef[kFoldTerms];          // 2 pi c
+  double coef[kFoldTerms];          // waves
 };
 static_assert(sizeof(FoldArgs) <= 4000, "kernel arguments are passed by value (4 KB limit)");
 
