@@ -160,7 +160,7 @@ struct AdjArgs {
   int s0, nstk, nz, nx, ny, w, n, row_groups;
   int zgroups, zper;   // planes are split into zgroups runs of zper (the last may be shorter)
   int hshift;          // H is stored with 2^-hshift
-  float gexp;          // power of two of the result
+  float gexp[3];       // powers of two of the result
 };
 
 // One (stack, component, run of planes, 64 pixel rows, 32 folded y cells, 256 folded x rows) per
@@ -430,7 +430,7 @@ __global__ void __launch_bounds__(kAdjThreads, 2) adj_kernel(AdjArgs a) {
     // stack's own defocus
     const float4 f0 = *reinterpret_cast<const float4*>(Pf + (size_t)(2 * jf) * a.w + 2 * lf);
     const float4 f1 = *reinterpret_cast<const float4*>(Pf + (size_t)(2 * jf + 1) * a.w + 2 * lf);
-    const float scale = (jf != j1 ? 0.5f : 1.f) * (lf != l1 ? 0.5f : 1.f) * a.gexp;
+    const float scale = (jf != j1 ? 0.5f : 1.f) * (lf != l1 ? 0.5f : 1.f) * a.gexp[c];
     float sn, cs;
     sincosf((float)reduce_2pi(a.kszf[(size_t)jf * nhp + lf] * a.zoff[s]), &sn, &cs);
     const float ccr = zacc[0][2 * q], cci = zacc[1][2 * q], scr = zacc[0][2 * q + 1], sci = zacc[1][2 * q + 1];
@@ -671,7 +671,7 @@ int fourier_adjoint(rwpsf_plan* p, int n, const rwpsf_stack* s, const float2* E,
     // 2^pf_exp
     int pref_exp = 0;
     std::frexp(p->opt.focal_length * p->k / kTwoPi, &pref_exp);
-    a.gexp = std::ldexp(1.f, pref_exp - p->pf_exp);
+    for (int c = 0; c < 3; ++c) a.gexp[c] = std::ldexp(1.f, pref_exp - p->scales.pf_exp[c]);
     const int blocks = nb * 3 * sp.zgroups * sp.chunks_x * sp.row_groups * (w / (2 * kAdjCols));
     tr = p->time_begin(RWPSF_KERNEL_ADJ_G, st);
     hipLaunchKernelGGL(sp.k, dim3(blocks), dim3(kAdjThreads), kAdjLds, st, a);

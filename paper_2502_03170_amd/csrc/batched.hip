@@ -58,7 +58,8 @@ struct BatchArgs {
   const double4* gl;         // [N*N] Gibson-Lanni phase W = t_s (g1.x + i g1.y) + (g0.x + i g0.y) as
                              // (g0.x, g0.y, g1.x, g1.y), or null without the layer
   const uint4* tab;          // split-f16 panel of 96 rows r, k = 2f + p: 2^kTabExp cos / sin (k s[f] x_r)
-  float tscale, escale;      // powers of two: on T, and fields per unit of the image product
+  float tscale;              // power of two on T
+  unsigned escale;           // packed powers of two: fields per unit of the image product
   float2* Pf;                // [n][3][N][N] folded pupils, slot order
   const int* list;           // [n] slots grouped by XCD queue
   const long long* pre;      // [n + 1] plane prefix sums over list
@@ -184,6 +185,9 @@ struct PlaneTile {
   static constexpr int T_BYTES = (int)hg_panel_bytes(N, 2 * SP);
   static constexpr int LDS_BYTES =
       Cfg::LDS_BYTES > T_BYTES ? (Cfg::LDS_BYTES > PART ? Cfg::LDS_BYTES : PART) : (T_BYTES > PART ? T_BYTES : PART);
+  // waves of a SIMD to leave registers for: at four (128 registers) two workgroups of six waves fit a
+  // CU, at 130 registers one (4096 crops of at most 16 pixels, 9 planes, N = 96: 1.14 ms, 1.69 with one)
+  static constexpr int OCC = SP == 32 && (N == 64 || N == 96) ? 4 : 2;
   static constexpr int PIX = SP == 64 ? 16 * COMBOS : (1024 + Cfg::NT - 1) / Cfg::NT;   // intensities per lane
 };
 
@@ -260,6 +264,7 @@ __device__ __forceinline__ void batch_plane(const BatchArgs& a, const BatchParam
         }
     }
     __syncthreads();
+    const float escale = component_scale(a.escale, c);
     float2* Ec = a.E ? a.E + 3 * bp.off + ((size_t)(d * 3 + c) * S) * S : nullptr;
     // E' block of columns nb over k-steps [ks0, ks0 + KPW).  The cross products of all k go
     // first: the accumulators are then 2^-11 of their final size and their roundings do not
@@ -298,7 +303,7 @@ __device__ __forceinline__ void batch_plane(const BatchArgs& a, const BatchParam
         const int n = 32 * (blk & 1) + l32, m0 = 32 * (blk >> 1) + 4 * h;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const float x = ei[r] * a.escale, y = -er[r] * a.escale;
+          const float x = ei[r] * escale, y = -er[r] * escale;
           isum[16 * q + r] += x * x + y * y;
           er[r] = x;
           ei[r] = y;
@@ -339,7 +344,7 @@ __device__ __forceinline__ void batch_plane(const BatchArgs& a, const BatchParam
           sr += part[ww * 2 * 32 * 33 + m * 33 + n];
           si += part[ww * 2 * 32 * 33 + 32 * 33 + m * 33 + n];
         }
-        const float x = si * a.escale, y = -sr * a.escale;
+        const float x = si * escale, y = -sr * escale;
         isum[q] += x * x + y * y;
         if (Ec && m < S && n < S) Ec[m * S + n] = make_float2(x, y);
       }
@@ -386,7 +391,8 @@ __device__ __forceinline__ auto as_constant(const T* p) {
 // The next item is drawn while the current one is computed.  A workgroup exits when its
 // queue is exhausted; the grid has at least 8 workgroups, one per queue.
 template <int N, int SP>
-__global__ void __launch_bounds__((PlaneTile<N, SP>::Cfg::NT), 2) batch_planes_kernel(BatchArgs a, int cls) {
+__global__ void __launch_bounds__((PlaneTile<N, SP>::Cfg::NT), (PlaneTile<N, SP>::OCC))
+    batch_planes_kernel(BatchArgs a, int cls) {
   extern __shared__ __align__(16) char blds[];
   __shared__ long long item[2];
   const int tid = threadIdx.x;
@@ -482,7 +488,7 @@ struct rwpsf_batch {
   double* d_ksz = nullptr;
   double4* d_gl = nullptr;      // [N*N] Gibson-Lanni phase tables, or null
   uint4* d_tab = nullptr;       // folded DFT table of both axes, a split-f16 panel of 96 rows
-  float tscale = 1.f, escale = 1.f;
+  rw::PupilScales scales;
   float2* d_pf = nullptr;       // [max][3][N][N] folded pupils
   long long items = 0;          // (emitter, plane) items of the staged call
   long long class_items[rw::kTileClasses] = {};   // of them, in the 32- and 64-row tile classes
@@ -637,8 +643,8 @@ static int batch_kernels(rwpsf_batch* b, int n, float* I, float2* E, hipStream_t
   a.basis = b->d_basis;
   a.gl = b->d_gl;
   a.tab = b->d_tab;
-  a.tscale = b->tscale;
-  a.escale = b->escale;
+  a.tscale = b->scales.tscale;
+  a.escale = b->scales.escale;
   a.Pf = b->d_pf;
   a.list = (const int*)(b->d_upload + off_list(b));
   a.pre = (const long long*)(b->d_upload + off_pre(b));
@@ -765,11 +771,7 @@ int rwpsf_batch_create(const rwpsf_optics* o, int n_pupil, double pixel_nm, doub
         bound[cell] = std::exp(std::min(std::max(0.0, -i0), 600.0));
       }
     }
-  const PupilScales ps = pupil_scales(Q, 3, N, N, bound.empty() ? nullptr : bound.data(), pref_exp);
-  b->tscale = ps.tscale;
-  b->escale = ps.escale;
-  const double sc = std::ldexp(1.0, ps.pf_exp);
-  for (float2& q : Q) q = make_float2((float)(sc * q.x), (float)(sc * q.y));
+  b->scales = pupil_scales(Q, 3, N, N, bound.empty() ? nullptr : bound.data(), pref_exp);
   b->upload_bytes = upload_size(b);
   int rc;
   if ((rc = balloc(b, &b->d_Q, 3 * NN)) || (rc = balloc(b, &b->d_ksz, NN)) ||

@@ -361,6 +361,7 @@ __device__ __forceinline__ void image_channel(const Gemm2Args& a, char* lds, int
   ra = la.load(0, tid);
   rb = lb.load(0, tid);
   __builtin_amdgcn_sched_barrier(0);
+  const float escale = component_scale(a.escale, c);
 #pragma unroll
   for (int i = 0; i < Cfg::TM; ++i)
 #pragma unroll
@@ -371,8 +372,8 @@ __device__ __forceinline__ void image_channel(const Gemm2Args& a, char* lds, int
       for (int g = 0; g < 4; ++g) {
         const int n = n0 + 4 * g;
         // E = -i E' = (Im E', -Re E')
-        const float4 e = make_float4(acc.c[i][jj][4 * g + 1] * a.escale, acc.c[i][jj][4 * g] * -a.escale,
-                                     acc.c[i][jj][4 * g + 3] * a.escale, acc.c[i][jj][4 * g + 2] * -a.escale);
+        const float4 e = make_float4(acc.c[i][jj][4 * g + 1] * escale, acc.c[i][jj][4 * g] * -escale,
+                                     acc.c[i][jj][4 * g + 3] * escale, acc.c[i][jj][4 * g + 2] * -escale);
         isum[i][jj][2 * g] += e.x * e.x + e.y * e.y;
         isum[i][jj][2 * g + 1] += e.z * e.z + e.w * e.w;
         if (HAS_E) {
@@ -503,13 +504,14 @@ __global__ void __launch_bounds__(3 * Cfg::NT, 1) gemm_image_few_kernel(Gemm2Arg
   hg_mainloop<Cfg>(acc, la, lb, 0, w, lds, tid, wrow, wcol, lane);
   const int m = col0 + wcol + (lane & 31);
   const int n0 = (row0 + wrow) / 2 + 2 * (lane >> 5);
+  const float escale = component_scale(a.escale, c);
   float* sq = reinterpret_cast<float*>(lds);   // [8][NT]: this channel's share of the lane's eight intensities
 #pragma unroll
   for (int g = 0; g < 4; ++g) {
     const int n = n0 + 4 * g;
     // E = -i E' = (Im E', -Re E')
-    const float4 e = make_float4(acc.c[0][0][4 * g + 1] * a.escale, acc.c[0][0][4 * g] * -a.escale,
-                                 acc.c[0][0][4 * g + 3] * a.escale, acc.c[0][0][4 * g + 2] * -a.escale);
+    const float4 e = make_float4(acc.c[0][0][4 * g + 1] * escale, acc.c[0][0][4 * g] * -escale,
+                                 acc.c[0][0][4 * g + 3] * escale, acc.c[0][0][4 * g + 2] * -escale);
     sq[(2 * g) * Cfg::NT + tid] = e.x * e.x + e.y * e.y;
     sq[(2 * g + 1) * Cfg::NT + tid] = e.z * e.z + e.w * e.w;
     if (a.E && m < a.nx) {

@@ -28,12 +28,14 @@ namespace rw {
 int bessel_plan_init(rwpsf_plan* p);
 
 // Power-of-two scales of the split-f16 GEMMs' operands (rw_fourier.h).
-PupilScales pupil_scales(const std::vector<float2>& Q, int nc, int N, int np, const double* amplitude, int pref_exp) {
+PupilScales pupil_scales(std::vector<float2>& Q, int nc, int N, int np, const double* amplitude, int pref_exp) {
   const int nh = (N + 1) / 2;
   const size_t npp = (size_t)np * np;
-  double cell_max = 0.0, row_max = 0.0;
   std::vector<double> m(N);   // one row of bounds and its mirror, added (plain loops over rows)
-  for (int c = 0; c < nc; ++c)
+  PupilScales s;
+  int t_exp = 0;   // (below 0: a row has more than one cell's terms)
+  for (int c = 0; c < nc; ++c) {
+    double cell_max = 0.0, row_max = 0.0;
     for (int jf = 0; jf < nh; ++jf) {
       const size_t r0 = (size_t)jf * np, r1 = (size_t)(N - 1 - jf) * np;
       const float2 *q0 = Q.data() + c * npp + r0, *q1 = Q.data() + c * npp + r1;
@@ -53,14 +55,19 @@ PupilScales pupil_scales(const std::vector<float2>& Q, int nc, int N, int np, co
       }
       row_max = std::max(row_max, row);
     }
-  int ec = 0, er = 0;   // cell_max < 2^ec, row_max < 2^er
-  std::frexp(cell_max, &ec);
-  std::frexp(row_max, &er);
-  PupilScales s;
-  s.pf_exp = cell_max > 0.0 ? 10 - ec : 0;
-  const int t_exp = row_max > 0.0 ? 15 - (er + s.pf_exp + kTabExp) : 0;
+    int ec = 0, er = 0;   // cell_max < 2^ec, row_max < 2^er
+    std::frexp(cell_max, &ec);
+    std::frexp(row_max, &er);
+    s.pf_exp[c] = cell_max > 0.0 ? 15 - ec : 0;
+    if (row_max > 0.0) t_exp = std::min(t_exp, 15 - (er + s.pf_exp[c] + kTabExp));
+    const double sc = std::ldexp(1.0, s.pf_exp[c]);
+    for (size_t i = c * npp; i < (c + 1) * npp; ++i) Q[i] = make_float2((float)(sc * Q[i].x), (float)(sc * Q[i].y));
+  }
   s.tscale = (float)std::ldexp(1.0, t_exp);
-  s.escale = (float)std::ldexp(1.0, pref_exp - (s.pf_exp + 2 * kTabExp + t_exp));
+  for (int c = 0; c < nc; ++c) {
+    const int e = pref_exp - (s.pf_exp[c] + 2 * kTabExp + t_exp);
+    s.escale |= (unsigned)(std::min(std::max(e, -512), 511) + 512) << 10 * c;
+  }
   return s;
 }
 
@@ -97,14 +104,7 @@ static int fourier_plan_init(rwpsf_plan* p) {
   std::vector<double> kszf((size_t)nhp * nhp, 0.0);
   for (int jf = 0; jf < nh; ++jf)
     for (int lf = 0; lf < nh; ++lf) kszf[(size_t)jf * nhp + lf] = ksz[(size_t)jf * np + lf];
-  if (folded) {
-    const PupilScales ps = pupil_scales(Q, p->nc, N, np, nullptr, pref_exp);
-    p->pf_exp = ps.pf_exp;
-    p->tscale = ps.tscale;
-    p->escale = ps.escale;
-    const double sc = std::ldexp(1.0, ps.pf_exp);
-    for (float2& q : Q) q = make_float2((float)(sc * q.x), (float)(sc * q.y));
-  }
+  if (folded) p->scales = pupil_scales(Q, p->nc, N, np, nullptr, pref_exp);
   int st;
   if ((st = dev_alloc(p, &p->d_Q, 3 * npp))) return st;
   if ((st = dev_alloc(p, &p->d_ksz, npp))) return st;
@@ -238,7 +238,7 @@ static int fourier_gemms(rwpsf_plan* p, int s_local, int ns, const double* zoff,
   g1.z = p->d_z;
   g1.B1 = p->d_B1;
   g1.T = p->d_T;
-  g1.tscale = p->tscale;
+  g1.tscale = p->scales.tscale;
   for (int i = 0; i < ns; ++i) g1.zoff[i] = zoff[i];
   g1.n = p->num.n_pupil;
   g1.nhp = p->nhp;
@@ -253,7 +253,7 @@ static int fourier_gemms(rwpsf_plan* p, int s_local, int ns, const double* zoff,
   p->time_end(tr, st);
   Gemm2Args g2{};
   g2.A2 = p->d_A2;
-  g2.escale = p->escale;
+  g2.escale = p->scales.escale;
   g2.vec = p->grid.ny % 2 == 0 && ((uintptr_t)E & 15) == 0 && ((uintptr_t)I & 7) == 0;
   g2.T = p->d_T;
   g2.E = E;

@@ -148,6 +148,13 @@ void set_hip_error(hipError_t e);
 
 struct PlanDevice;  // per-form device state
 
+// Power-of-two scales of the Fourier form's operands.
+struct PupilScales {
+  int pf_exp[3] = {0, 0, 0};              // Q and the folded pupils of a component carry 2^pf_exp
+  float tscale = 1.f;                     // T is multiplied by it when it is written
+  unsigned escale = 0;                    // fields per unit of the image product's sums: exponents + 512, 10 bits each
+};
+
 }  // namespace rw
 
 // ---------------------------------------------------------------------------
@@ -174,9 +181,7 @@ struct rwpsf_plan {
   double* d_kszf = nullptr;     // [nhp][nhp] k * s_z on the folded cells
   uint4* d_B1 = nullptr;        // split-f16 panel of nyp rows n, k = 2lf + p: cos / sin (k s_y[lf] y_n)
   uint4* d_A2 = nullptr;        // split-f16 panel of nxp rows m, k = 2jf + p: cos / sin (k s_x[jf] x_m)
-  int pf_exp = 0;               // Q and the folded pupils carry 2^pf_exp (Fourier form)
-  float tscale = 1.f;           // power of two that T is multiplied by when it is written
-  float escale = 1.f;           // power of two: fields per unit of the image GEMM's accumulators
+  rw::PupilScales scales;       // of the Fourier form's operands
   float* d_ztab = nullptr;      // [RWPSF_MAX_ZERNIKE][N][N] Noll basis on the pupil cells
   float2* d_P = nullptr;        // workspace [chunk][3][np][np]
   float2* d_Pf = nullptr;       // workspace [chunk][3][2 nhp][2 nhp] folded pupils

@@ -48,20 +48,24 @@ static_assert(sizeof(FoldArgs) <= 4000, "kernel arguments are passed by value (4
 // nhp = nh rounded up to 32 (so 2 nhp = np).
 
 // Operands of the two GEMMs are split in f16 halves (hgemm.h).  Their power-of-two scales
-// keep the halves in range: Q, and with it the folded pupils, carries 2^pf_exp, so that no
-// folded value (a sum over up to four mirrors, each of unit phase factor times the given
-// largest amplitude of the cell) exceeds 2^10; the DFT tables carry 2^kTabExp; T = Pf B1,
-// bounded by the largest row sum of |Pf|, is multiplied by tscale to stay under 2^15 when it
-// is split.  The halves then neither overflow nor, down to 2^-13 (Pf) or 2^-18 (T) of the
-// bounds, lose bits to subnormal halves.  escale, a power of two, turns the image GEMM's sums
-// into fields.
+// (PupilScales) keep the halves in range: Q, and with it the folded pupils, carries 2^pf_exp, so that no
+// folded value (a sum over up to four mirrors, each of unit phase factor times the given largest
+// amplitude of the cell) exceeds 2^15, each component by itself (at a numerical aperture of 0.02 the
+// y component of x-polarised light is 2^-14 of the x component; with one scale for both its halves were
+// subnormal, its error 5.1e-7 of its own norm, 1.7e-7 in FP32 products, 9.8e-8 so); the DFT tables carry
+// 2^kTabExp; T = Pf B1, bounded by the largest row sum of |Pf|, is multiplied by tscale to stay under 2^15
+// when it is split (rows over cells differ by a few bits from component to component: one tscale for
+// all).  The halves then neither overflow nor, down to about 2^-18 of the bounds, lose bits to subnormal
+// halves.  escale, a power of two, turns the image GEMM's sums into fields.
 constexpr int kTabExp = 6;
-struct PupilScales {
-  int pf_exp;
-  float tscale, escale;
-};
-// Q [nc][np][np] on the N x N cells, with the prefactor's mantissa; amplitude [np][np] or null
-PupilScales pupil_scales(const std::vector<float2>& Q, int nc, int N, int np, const double* amplitude, int pref_exp);
+// escale of component c, formed from the packed exponents on the scalar path (an array of three in the
+// arguments is a load on the critical path of a loop over components: 1 us of a call's 33).
+__device__ __forceinline__ float component_scale(unsigned exps, int c) {
+  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(ldexpf(1.f, (int)(exps >> 10 * c & 1023) - 512))));
+}
+// Scales of Q [nc][np][np] on the N x N cells, with the prefactor's mantissa; amplitude [np][np] or
+// null.  Multiplies Q by them.
+PupilScales pupil_scales(std::vector<float2>& Q, int nc, int N, int np, const double* amplitude, int pref_exp);
 
 struct Gemm1Args {
   const float2* Pf;    // [nstk][nc][2 nhp][2 nhp]
@@ -79,7 +83,7 @@ struct Gemm2Args {
   const uint4* T;      // [nstk][nzs][nc] panels of 2 nyp rows 2n + ri, k = q
   float2* E;           // [stacks][nz][nc][nx][ny] or null
   float* I;            // [stacks][nz][nx][ny] or null
-  float escale;        // power of two: the prefactor's over the operand scales
+  unsigned escale;     // packed powers of two: the prefactor's over the operand scales
   int vec;             // E and I rows allow 16- and 8-byte stores (ny even, aligned outputs)
   int nhp, nxp, nyp, nx, ny, nz, nstk, s_base, z0, nzs, nc;
 };
