@@ -176,8 +176,10 @@ __global__ void bessel_phi_kernel(PhiArgs a, const BesselNode* __restrict__ node
 // Bessel table; in the adjoint the rows of G_In, nodes contiguous (BY_ROW: A[row][q]), and the
 // transposed table.  The table is split once,
 // at plan time, into a panel of `ldb` columns (zero past N and K); A is split on its way into LDS.
-// The rows are scaled by powers of two: Phi by the plan's bound of its amplitude (so that a row
-// does not depend on its neighbours), G_In by the row's own exponent.
+// Both are scaled by powers of two: Phi by the plan's bound of its amplitude (so that a row does not
+// depend on its neighbours), G_In by the row's own exponent, the table group by group (the columns of
+// one integral; at a small aperture I_2 is orders of magnitude below I_0).  A group's scale is taken off
+// where its integrals are used: by the epilogue, and by the adjoint where it writes G_In.
 // A workgroup of four waves takes 64 rows and keeps a run of kConK nodes of them in LDS; each wave
 // owns WM x WN of the tile and reads its table fragments straight from L2.  Both shapes sum the
 // nodes in the same order, so a row's result does not depend on the call's size either.
@@ -185,7 +187,10 @@ __global__ void bessel_phi_kernel(PhiArgs a, const BesselNode* __restrict__ node
 // staged, 41 us so; the adjoint's 4224 x 200 over 768 43 -> 32 us (with one k-step of table
 // fragments on its way instead of four 41).
 // --------------------------------------------------------------------------
-constexpr int kConRows = 64, kConK = 128, kConPad = 256;
+constexpr int kConRows = 64, kConK = 128, kConPad = 256, kMaxGroups = 5;
+struct GroupExps {
+  int e[kMaxGroups];
+};
 struct ContractArgs {
   const float* A;        // BY_ROW: 16-byte aligned, lda a multiple of 4
   const uint4* B;
@@ -195,15 +200,15 @@ struct ContractArgs {
   int a_exp, c_exp;      // A is multiplied by 2^a_exp (2^ex), C by 2^c_exp (and 2^-ex)
 };
 
-// Split panel of a table, scaled by 2^exp: one thread per (k, column) of the padded panel, whose value
-// is in[k sk + column sn].
-__global__ void bessel_panel_kernel(const float* __restrict__ in, int K, int N, int sk, int sn, int ldb, int exp,
-                                    _Float16* __restrict__ out) {
+// Split panel of a table, scaled by the exponents of its groups of R (columns, or k where sk is 1): one
+// thread per (k, column) of the padded panel, whose value is in[k sk + column sn].
+__global__ void bessel_panel_kernel(const float* __restrict__ in, int K, int N, int sk, int sn, int ldb, GroupExps exps,
+                                    int R, _Float16* __restrict__ out) {
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
   const int kp = (K + 15) / 16 * 16;
   if (idx >= kp * ldb) return;
   const int q = idx / ldb, c = idx % ldb;
-  const float x = q < K && c < N ? ldexpf(in[(size_t)q * sk + (size_t)c * sn], exp) : 0.f;
+  const float x = q < K && c < N ? ldexpf(in[(size_t)q * sk + (size_t)c * sn], exps.e[(sk == 1 ? q : c) / R]) : 0.f;
   _Float16* o = out + ((size_t)(q / 16 * 4 + q % 16 / 8) * ldb + c) * 8 + q % 8;
   const _Float16 hi = (_Float16)x;
   o[0] = hi;
@@ -349,6 +354,11 @@ static hipError_t launch_contract(const ContractArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
+// What the contraction, which takes off group 0's scale of the table, leaves of each group's (at most 1).
+static void group_scales(const rwpsf_plan* p, float out[kMaxGroups]) {
+  for (int g = 0; g < kMaxGroups; ++g) out[g] = std::ldexp(1.f, p->tab_exp[0] - p->tab_exp[g]);
+}
+
 // --------------------------------------------------------------------------
 // Radial epilogue: one workgroup per (stack, plane).  The GEMM rows of this plane,
 // (variant, re/im) x [G][R], are combined into I_n and staged in LDS as [sample][n][re/im], the
@@ -370,6 +380,7 @@ struct EpiArgs {
   int nx, ny, nz, R, nstk, s_base, mode, split;   // split: workgroups per plane
   float dx, dy, inv_drho;
   float exr, exi, eyr, eyi;   // polarisation times -(i f k / 2); scalar: exr + i exi = -i f k
+  float gscale[kMaxGroups];   // I_n of a group is read times this power of two (group_scales)
   float x0[kEpiStacks], y0[kEpiStacks];
 };
 static_assert(sizeof(EpiArgs) <= 4000, "kernel arguments are passed by value (4 KB limit)");
@@ -393,12 +404,13 @@ __global__ void __launch_bounds__(256) bessel_epilogue_kernel(EpiArgs a, const f
     float2 v[3];
     if (!SCALAR && a.mode == kModeFresnel) {
       const float *sr = sp, *sm = sp + G * R, *pr = sp + 2 * G * R, *pm = sp + 3 * G * R;   // q_s, q_p
-      v[0] = make_float2(sr[0] + pr[R], sm[0] + pm[R]);
-      v[1] = make_float2(pr[2 * R], pm[2 * R]);
-      v[2] = make_float2(pr[3 * R] - sr[4 * R], pm[3 * R] - sm[4 * R]);
+      const float *w = a.gscale;
+      v[0] = make_float2(sr[0] + w[1] * pr[R], sm[0] + w[1] * pm[R]);
+      v[1] = make_float2(w[2] * pr[2 * R], w[2] * pm[2 * R]);
+      v[2] = make_float2(w[3] * pr[3 * R] - w[4] * sr[4 * R], w[3] * pm[3 * R] - w[4] * sm[4 * R]);
     } else {
 #pragma unroll
-      for (int n = 0; n < NI; ++n) v[n] = make_float2(sp[n * R], sp[(G + n) * R]);
+      for (int n = 0; n < NI; ++n) v[n] = make_float2(a.gscale[n] * sp[n * R], a.gscale[n] * sp[(G + n) * R]);
     }
     float2* d = reinterpret_cast<float2*>(sh) + (r + 1) * NI - 1;
 #pragma unroll
@@ -700,15 +712,16 @@ static void fused_plan_cost(rwpsf_plan* p) {
 
 int bessel_scratch_init(int dev, float** out);
 
-// Split table of the contraction and the exponents of its operands: the table's entries are
-// bounded by w_q h_g (|J_n| <= 1), Phi by the amplitude at t_s = 0 (the evanescent decay grows
+// Split table of the contraction and the exponents of its operands: the table's entries of a group are
+// bounded by w_q h_g (|J_n| <= 1; group 0 by 2 w_q sin t), Phi by the amplitude at t_s = 0 (the evanescent decay grows
 // with the depth) times the Fresnel products.
 static int bessel_panels(rwpsf_plan* p, const std::vector<double>& th, const std::vector<double>& wt) {
   const int T = p->n_theta_total, G = bessel_groups(p->bessel_mode), N = G * p->num.n_rho;
-  double tab = 0.0, amp = 0.0;
+  double tab[kMaxGroups] = {}, amp = 0.0;
   for (int q = 0; q < T; ++q) {
     const double sn = std::sin(th[q]), cs = std::cos(th[q]);
-    tab = std::max(tab, std::fabs(wt[q]) * 2.0 * sn);   // every h_g is at most 2 sin t
+    const double w = std::fabs(wt[q]), h[2][kMaxGroups] = {{2.0 * sn, sn * sn, sn * (1.0 - cs)}, {sn, sn, sn * sn, sn, sn}};
+    for (int g = 0; g < G; ++g) tab[g] = std::max(tab[g], w * h[p->bessel_mode == kModeFresnel][g]);
     double a = 1.0;
     if (p->opt.apodization) a *= std::sqrt(cs);
     if (p->opt.s_env > 0.0) a *= std::exp(-(sn * sn) / (p->opt.s_env * p->opt.s_env));
@@ -726,16 +739,19 @@ static int bessel_panels(rwpsf_plan* p, const std::vector<double>& th, const std
     amp = std::max(amp, a);
   }
   int et = 0, ea = 0;   // tab < 2^et, amp < 2^ea
-  std::frexp(tab, &et);
+  GroupExps exps{};
+  for (int g = 0; g < G; ++g) {
+    std::frexp(tab[g], &et);
+    exps.e[g] = p->tab_exp[g] = tab[g] > 0.0 ? 14 - et : p->tab_exp[0];
+  }
   std::frexp(amp, &ea);
-  p->tab_exp = tab > 0.0 ? 14 - et : 0;
   p->phi_exp = amp > 0.0 ? 14 - ea : 0;
   p->btab_ld = (N + kConPad - 1) / kConPad * kConPad;
   const size_t kp = (T + 15) / 16 * 16;
   int st;
   if ((st = dev_alloc(p, &p->d_bpanel, hg_panel_bytes(kp, p->btab_ld) / sizeof(uint4)))) return st;
   hipLaunchKernelGGL(bessel_panel_kernel, dim3((unsigned)((kp * p->btab_ld + 255) / 256)), dim3(256), 0, 0, p->d_btab, T,
-                     N, N, 1, p->btab_ld, p->tab_exp, (_Float16*)p->d_bpanel);
+                     N, N, 1, p->btab_ld, exps, p->num.n_rho, (_Float16*)p->d_bpanel);
   return hip_check(hipGetLastError());
 }
 
@@ -1023,7 +1039,7 @@ static int bessel_compute_ws(rwpsf_plan* p, int n, const rwpsf_stack* s, float2*
     const int M = 2 * cols * V, N = G * R;
     int tr = p->time_begin(RWPSF_KERNEL_BESSEL_CONTRACT, st);
     const ContractArgs ca{(const float*)phi, p->d_bpanel, In, nullptr, M, p->btab_ld, N, M, N, T,
-                          p->phi_exp, -p->phi_exp - p->tab_exp};
+                          p->phi_exp, -p->phi_exp - p->tab_exp[0]};
     if ((rc = hip_check(launch_contract<false>(ca, st)))) return rc;
     p->time_end(tr, st);
     EpiArgs ea{};
@@ -1037,6 +1053,7 @@ static int bessel_compute_ws(rwpsf_plan* p, int n, const rwpsf_stack* s, float2*
     ea.dx = (float)p->grid.dx_nm;
     ea.dy = (float)p->grid.dy_nm;
     ea.inv_drho = (float)(1.0 / p->drho);
+    group_scales(p, ea.gscale);
     ea.exr = pol[0];
     ea.exi = pol[1];
     ea.eyr = pol[2];
@@ -1120,6 +1137,7 @@ int bessel_compute_noalloc(rwpsf_plan* p, int n, const rwpsf_stack* s, float2* E
 // --------------------------------------------------------------------------
 struct AdjRadArgs {
   int nx, ny, nz, R, mode, s_base, ld;   // ld: row stride of G_In
+  float gscale[kMaxGroups];   // G_In of a group is written times this power of two (group_scales)
   int unit_exp;        // the integer sums' unit is 2^-unit_exp of the bound's power of two
   float dx, dy, inv_drho, drho;
   float exr, exi, eyr, eyi;
@@ -1301,8 +1319,8 @@ __global__ void __launch_bounds__(kRadialThreads, 4) adjb_radial_kernel(AdjRadAr
     for (int e = 0; e < 6; ++e) g[e] = total(e * R + r);
     auto put = [&](int v, int gg, float re, float im) {
       float* d = GIn + (size_t)(2 * (col + v)) * a.ld + gg * R + r;
-      d[0] = re;
-      d[a.ld] = im;
+      d[0] = re * a.gscale[gg];
+      d[a.ld] = im * a.gscale[gg];
     };
     if (a.mode == kModeFresnel) {
       put(0, 0, g[0], g[1]);
@@ -1431,8 +1449,10 @@ static int bessel_adjoint_prepare(rwpsf_plan* p) {
   if ((st = hip_check(hipFuncSetAttribute((const void*)adjb_radial_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                                           150 * 1024))))
     return st;
+  GroupExps exps{};
+  std::copy_n(p->tab_exp, G, exps.e);
   hipLaunchKernelGGL(bessel_panel_kernel, dim3((unsigned)(((size_t)kp * ldT + 255) / 256)), dim3(256), 0, 0, p->d_btab,
-                     K, T, 1, K, ldT, p->tab_exp, (_Float16*)p->d_bpanelT);
+                     K, T, 1, K, ldT, exps, R, (_Float16*)p->d_bpanelT);
   if ((st = hip_check(hipGetLastError()))) return st;
   if ((st = hip_check(hipDeviceSynchronize()))) return st;
   p->adjb_ready = true;
@@ -1459,6 +1479,7 @@ int bessel_adjoint(rwpsf_plan* p, int n, const rwpsf_stack* s, const float2* E, 
     ra.mode = mode;
     ra.s_base = b0;
     ra.ld = adjb_row_stride(G * R);
+    group_scales(p, ra.gscale);
     ra.unit_exp = 40;
     while (((long long)p->grid.nx * p->grid.ny - 1) >> (62 - ra.unit_exp)) --ra.unit_exp;   // >= 36
     ra.dx = (float)p->grid.dx_nm;
@@ -1482,7 +1503,7 @@ int bessel_adjoint(rwpsf_plan* p, int n, const rwpsf_stack* s, const float2* E, 
     const int K = G * R;
     tr = p->time_begin(RWPSF_KERNEL_ADJB_CONTRACT, st);
     const ContractArgs ca{p->d_GIn, p->d_bpanelT, p->d_GPhi, p->d_GInEx, adjb_row_stride(K),
-                          (T + kConPad - 1) / kConPad * kConPad, T, M, T, K, 0, -p->tab_exp};
+                          (T + kConPad - 1) / kConPad * kConPad, T, M, T, K, 0, -p->tab_exp[0]};
     if ((rc = hip_check(launch_contract<true>(ca, st)))) return rc;
     p->time_end(tr, st);
     tr = p->time_begin(RWPSF_KERNEL_ADJB_REDUCE, st);

@@ -218,8 +218,8 @@ struct rwpsf_plan {
   double* d_node = nullptr;     // [T] BesselNode: what the pupil of a node takes from the plan
   int bessel_mode = 0;          // 0 vectorial, 1 vectorial with Fresnel factors, 2 scalar
   float* d_btab = nullptr;      // [T][G][R] w_t h_g(t) J_{n_g}(k rho_r sin t)
-  uint4* d_bpanel = nullptr;    // d_btab as a split-f16 panel of btab_ld columns, times 2^tab_exp
-  int btab_ld = 0, tab_exp = 0;
+  uint4* d_bpanel = nullptr;    // d_btab as a split-f16 panel of btab_ld columns, group g times 2^tab_exp[g]
+  int btab_ld = 0, tab_exp[5] = {0, 0, 0, 0, 0};
   int phi_exp = 0;              // Phi is split after multiplication by 2^phi_exp
   double* d_fq = nullptr;       // [T][4] Fresnel products q_s, q_p per node (Fresnel mode)
   float2* d_phi = nullptr;      // workspace [T][stacks][nz][V] pupil x defocus (x q_v)
