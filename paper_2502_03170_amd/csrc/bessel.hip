@@ -365,10 +365,13 @@ static void group_scales(const rwpsf_plan* p, float out[kMaxGroups]) {
 // ghost of sample -1 in front (I_n(-rho) = (-1)^n I_n(rho)), so that a pixel's four samples are
 // 24 consecutive floats.  The ghost of I_0, which equals its sample 1, is left out: the longest
 // table then still fits.
-// Bound by its writes: 8448 planes of 65 x 65 (28 B a pixel, rows and planes off the cache lines)
-// take 191 us as plain stores and 141 us without them, 211-216 us together.  Several planes a
-// workgroup, sharing a pixel's stencil and angles, saved vector work and lost more on the writes
-// (two planes 249, seven 310 us).
+// Bound by its writes, 28 B a pixel in runs that start and end within cache lines.  A launch whose fields
+// leave the last-level cache runs neighbouring planes on one XCD, so that the lines they share meet in its
+// L2, and keeps few planes of a CU in flight (epi_lds): the fewer runs are open, the fewer of their lines
+// leave L2 half written.  8448 planes of 65 x 65 (1.0 GB): 262 us with eight workgroups a CU, 256 with neighbours on
+// one XCD, 232 with four a CU, 222 with three, 228 with two; with the samples of an integral side by side
+// and more instructions a pixel 245.  Several planes a workgroup, sharing a pixel's stencil and angles,
+// were slower (two planes 249, seven 310 us).
 // --------------------------------------------------------------------------
 constexpr int kEpiStacks = 256;   // stacks per contraction and epilogue launch
 // Workgroups per plane in the epilogue: a call with few planes splits each plane into 4
@@ -388,13 +391,27 @@ static_assert(sizeof(EpiArgs) <= 4000, "kernel arguments are passed by value (4 
 // floats of a plane's samples in LDS: R + 1 samples without I_0 of the first
 constexpr int epi_plane_floats(int NI, int R) { return (R + 1) * NI * 2 - 2; }
 
-template <bool SCALAR>
+// Fields and intensity of `out` bytes leave the last-level cache (256 MB).
+static bool epi_streams(size_t out, bool fields) { return fields && out > (size_t)256 << 20; }
+// LDS of the launch.  More than the samples need where the outputs leave the last-level cache: three
+// workgroups a CU then, four for planes of fewer than 2048 pixels, whose other phases need them (us of 256
+// stacks with eight, four, three: 33 x 33 x 65 133, 133, 149; 64 x 64 x 33 203, 196, 194; 65 x 65 x 33 256,
+// 232, 222; 200 of 129 x 129 x 33 839, 790, 719).  Below, and without fields, the waits of the other phases
+// count (64 stacks of 65 x 65 x 33 48, 51, 53; 200 of 129 x 129 x 33 without fields 348, 360, 381).
+static size_t epi_lds(int NI, int R, int pixels, bool streams) {
+  const size_t own = epi_plane_floats(NI, R) * sizeof(float);
+  if (!streams) return own;
+  return std::max<size_t>(own, 160 * 1024 / (pixels < 2048 ? 5 : 4) + 256);
+}
+
+template <bool SCALAR, bool STREAMS>   // STREAMS: epi_streams
 __global__ void __launch_bounds__(256) bessel_epilogue_kernel(EpiArgs a, const float* __restrict__ In,
                                                               float2* __restrict__ E,
                                                               float* __restrict__ I) {
   constexpr int NI = SCALAR ? 1 : 3;
   extern __shared__ __align__(16) float sh[];
-  const int part = blockIdx.x % a.split, pl = blockIdx.x / a.split;
+  const int id = STREAMS ? xcd_remap(blockIdx.x, gridDim.x) : blockIdx.x;
+  const int part = id % a.split, pl = id / a.split;
   const int si = pl / a.nz, zi = pl % a.nz;
   const int R = a.R;
   const int G = a.mode == kModeFresnel ? 5 : NI, V = a.mode == kModeFresnel ? 2 : 1;
@@ -874,7 +891,8 @@ int bessel_plan_init(rwpsf_plan* p) {
   if ((st = bessel_panels(p, th, wt))) return st;
   // the limit belongs to the kernel, not to this plan: allow the whole LDS, so that a later
   // plan with fewer radial samples cannot lower it below what this plan launches with
-  for (const void* k : {(const void*)bessel_epilogue_kernel<false>, (const void*)bessel_epilogue_kernel<true>})
+  for (const void* k : {(const void*)bessel_epilogue_kernel<false, false>, (const void*)bessel_epilogue_kernel<false, true>,
+                        (const void*)bessel_epilogue_kernel<true, false>, (const void*)bessel_epilogue_kernel<true, true>})
     if ((st = hip_check(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)))) return st;
   const void* fused[3] = {(const void*)bessel_fused_kernel<kModeVectorial>,
                           (const void*)bessel_fused_kernel<kModeFresnel>, (const void*)bessel_fused_kernel<kModeScalar>};
@@ -1064,9 +1082,14 @@ static int bessel_compute_ws(rwpsf_plan* p, int n, const rwpsf_stack* s, float2*
     }
     tr = p->time_begin(RWPSF_KERNEL_BESSEL_EPILOGUE, st);
     ea.split = nb * nz < kEpiFewPlanes ? kEpiSplitFew : 1;
-    const auto kernel = mode == kModeScalar ? bessel_epilogue_kernel<true> : bessel_epilogue_kernel<false>;
-    hipLaunchKernelGGL(kernel, dim3(nb * nz * ea.split), dim3(256),
-                       epi_plane_floats(mode == kModeScalar ? 1 : 3, R) * sizeof(float), st, ea, (const float*)In, E, I);
+    const int NI = mode == kModeScalar ? 1 : 3, pixels = p->grid.nx * p->grid.ny;
+    const size_t out = (size_t)nb * nz * pixels * ((E ? NI * sizeof(float2) : 0) + (I ? sizeof(float) : 0));
+    const bool streams = epi_streams(out, E != nullptr);
+    const auto kernel = mode == kModeScalar
+                            ? (streams ? bessel_epilogue_kernel<true, true> : bessel_epilogue_kernel<true, false>)
+                            : (streams ? bessel_epilogue_kernel<false, true> : bessel_epilogue_kernel<false, false>);
+    hipLaunchKernelGGL(kernel, dim3(nb * nz * ea.split), dim3(256), epi_lds(NI, R, pixels, streams), st, ea,
+                       (const float*)In, E, I);
     if ((rc = hip_check(hipGetLastError()))) return rc;
     p->time_end(tr, st);
   }
