@@ -212,19 +212,20 @@ __device__ __forceinline__ void czt_fft_reg(float2* buf, float2 (&v)[L / 64], in
   czt_last_reg<L>(buf, v, lane);
 }
 // v: in x (already multiplied by the pre-chirp), out conj(FFT(conj(FFT(x) chat)))
-template <int L>
+template <int L, bool AHEAD>
 __device__ __forceinline__ void czt_pair_reg(float2* buf, float2 (&v)[L / 64], const float2* __restrict__ chat, int lane) {
-  // at L = 512 the lane's spectrum factors are requested before the first transform (16
-  // registers); the longer transforms have no registers to spare and read them after it
-  constexpr int CH = L == 512 ? L / 64 : 1;
+  // AHEAD: the lane's spectrum factors are requested before the first transform (L / 32 registers) where
+  // registers are left (L = 512, and the columns at L = 1024: 44 -> 37 us for two planes of 300 x 200 on a
+  // 700-cell pupil, 42 with input and output columns side by side), otherwise read after it
+  constexpr int CH = AHEAD ? L / 64 : 1;
   float2 ch[CH];
-  if constexpr (L == 512)
+  if constexpr (AHEAD)
 #pragma unroll
     for (int u = 0; u < CH; ++u) ch[u] = chat[lane + 64 * u];
   czt_fft_reg<L>(buf, v, lane);
 #pragma unroll
   for (int u = 0; u < L / 64; ++u) {
-    const float2 t = cmul(v[u], L == 512 ? ch[u % CH] : chat[lane + 64 * u]);
+    const float2 t = cmul(v[u], AHEAD ? ch[u % CH] : chat[lane + 64 * u]);
     v[u] = make_float2(t.x, -t.y);
   }
   czt_fft_reg<L>(buf, v, lane);
@@ -278,7 +279,7 @@ __global__ void __launch_bounds__(256) czt_rows_kernel(CztRowArgs a) {
         const int l = lane + 64 * u;
         v[u] = (live && l < a.n) ? cmul(Pr[l], dz[u]) : make_float2(0.f, 0.f);
       }
-      czt_pair_reg<L>(buf, v, a.chat, lane);
+      czt_pair_reg<L, L == 512>(buf, v, a.chat, lane);
       if (live) {
         float2* Tr = a.T + (((size_t)s * a.nzs + zi) * a.nc + c) * (size_t)a.n * a.ny + (size_t)j * a.ny;
 #pragma unroll
@@ -382,7 +383,7 @@ __global__ void __launch_bounds__(64 * czt_col_waves<L>(), L <= 512 ? 4 : (L == 
           const int j = lane + 64 * u;
           v[u] = j < a.n ? cmul(col[j], a.pre[j]) : make_float2(0.f, 0.f);
         }
-        czt_pair_reg<L>(buf, v, a.chat, lane);
+        czt_pair_reg<L, L == 512 || L == 1024>(buf, v, a.chat, lane);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           const int m = lane + 64 * u;
