@@ -559,6 +559,14 @@ static size_t off_pre(const rwpsf_batch* b) {
 static size_t off_qoff(const rwpsf_batch* b) { return off_pre(b) + sizeof(long long) * (b->max_emitters + 1); }
 static size_t upload_size(const rwpsf_batch* b) { return off_qoff(b) + sizeof(int) * (kQueues + 1); }
 
+// Tile of a configuration's tile rows: 16 and 48 run on the next larger one.
+static int tile_of(int rows) { return rows > 32 ? 64 : 32; }
+
+static int class_grid(int num_cus, int wg_per_cu, long long items) {
+  const long long want = std::max<long long>(8, std::min<long long>(items, (long long)num_cus * wg_per_cu));
+  return items == 0 ? 0 : (int)std::min<long long>(want, (long long)num_cus * kMaxWgPerCu);
+}
+
 // Fill the pinned staging area: cost-sorted params, the coefficient matrix, and the
 // (emitter, plane) queues: per tile class, eight queues, the class's emitters dealt
 // longest first to its least-loaded queue.
@@ -567,8 +575,7 @@ static void batch_stage(rwpsf_batch* b, int n, const rwpsf_emitter* e) {
   for (int i = 0; i < n; ++i) off[i + 1] = off[i] + (long long)e[i].planes * e[i].crop * e[i].crop;
   std::vector<int> order(n);
   std::iota(order.begin(), order.end(), 0);
-  // tile rows of 16 and 48 run on the next larger tile
-  auto sp_of = [&](int i) { return b->cfg.tile_rows[(e[i].crop - 1) / 16] > 32 ? 64 : 32; };
+  auto sp_of = [&](int i) { return tile_of(b->cfg.tile_rows[(e[i].crop - 1) / 16]); };
   auto cost = [&](int i) { return (double)e[i].planes * sp_of(i) * (b->N + sp_of(i)); };
   std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return cost(x) > cost(y); });
   BatchParam* prm = (BatchParam*)b->h_staging;
@@ -612,12 +619,7 @@ static void batch_stage(rwpsf_batch* b, int n, const rwpsf_emitter* e) {
   b->items = pre[n];
   // persistent grid of each class: at least one workgroup per queue, no more than the
   // configured residency, none for an empty class
-  for (int t = 0; t < kTileClasses; ++t) {
-    const long long want =
-        std::max<long long>(8, std::min<long long>(b->class_items[t], (long long)b->num_cus * b->cfg.wg_per_cu));
-    b->class_grid[t] =
-        b->class_items[t] == 0 ? 0 : (int)std::min<long long>(want, (long long)b->num_cus * kMaxWgPerCu);
-  }
+  for (int t = 0; t < kTileClasses; ++t) b->class_grid[t] = class_grid(b->num_cus, b->cfg.wg_per_cu, b->class_items[t]);
 }
 
 // Copy the staged parameter block to the device and record upload_done right after it,
@@ -1018,10 +1020,27 @@ int rwpsf_batch_autotune(rwpsf_batch* b, int n, const rwpsf_emitter* e, float* I
     return rc;
   }
   // coordinate search from the default: workgroups per CU, then for each crop bucket the
-  // taller tile classes it could share (fewer, fuller launches against more padding)
+  // taller tile it could share (fewer, fuller launches against more padding).  A candidate that
+  // launches what another has launched is not timed again: the choice between the two would be noise.
+  long long bucket_items[4] = {};
+  for (int i = 0; i < n; ++i) bucket_items[(e[i].crop - 1) / 16] += e[i].planes;
+  std::vector<std::vector<int>> tried;
+  auto launches = [&](const rwpsf_batch_config& c) {   // grids of the classes, tile of each bucket in use
+    long long items[kTileClasses] = {};
+    std::vector<int> v;
+    for (int q = 0; q < 4; ++q) {
+      items[tile_of(c.tile_rows[q]) > 32] += bucket_items[q];
+      v.push_back(bucket_items[q] ? tile_of(c.tile_rows[q]) : 0);
+    }
+    for (long long k : items) v.push_back(class_grid(b->num_cus, c.wg_per_cu, k));
+    return v;
+  };
   rwpsf_batch_config best = default_config();
   float best_t = 1e30f;
   auto consider = [&](const rwpsf_batch_config& c) {
+    const std::vector<int> v = launches(c);
+    if (std::find(tried.begin(), tried.end(), v) != tried.end()) return (int)RWPSF_OK;
+    tried.push_back(v);
     float ms = 0.f;
     const int r = tune_trial(b, n, e, I, st, c, t0, t1, &ms);
     if (r == RWPSF_OK && ms < best_t) {
@@ -1037,16 +1056,10 @@ int rwpsf_batch_autotune(rwpsf_batch* b, int n, const rwpsf_emitter* e, float* I
     c.wg_per_cu = wg;
     rc = consider(c);
   }
-  bool used[4] = {false, false, false, false};
-  for (int i = 0; i < n; ++i) used[(e[i].crop - 1) / 16] = true;
   for (int q = 0; q < 3 && !rc; ++q) {
-    if (!used[q]) continue;
-    const rwpsf_batch_config base = best;
-    for (int rows = base.tile_rows[q] + 16; rows <= 64 && !rc; rows += 16) {
-      rwpsf_batch_config c = base;
-      c.tile_rows[q] = rows;
-      rc = consider(c);
-    }
+    rwpsf_batch_config c = best;
+    c.tile_rows[q] = 64;
+    rc = consider(c);
   }
   (void)hipEventDestroy(t0);
   (void)hipEventDestroy(t1);
