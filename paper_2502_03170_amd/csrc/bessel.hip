@@ -91,9 +91,7 @@ struct PhiStack {
 constexpr int kPhiStacks = 64;
 template <int NS>
 struct PhiArgsT {
-  int T, nz, nstk, V, max_zernike, gibson_lanni;   // V: variants per column
-  double s_max;
-  GLParams gl;
+  int T, nz, nstk, V, gibson_lanni;   // V: variants per column
   PhiStack s[NS];
 };
 using PhiArgs = PhiArgsT<kPhiStacks>;
@@ -911,18 +909,13 @@ static void fill_phi_args(const rwpsf_plan* p, const rwpsf_stack* s, int nb, Phi
   pa.nstk = nb;
   pa.V = bessel_variants(p->bessel_mode);
   pa.gibson_lanni = p->opt.gibson_lanni;
-  pa.s_max = p->s_max;
-  pa.gl = p->gl;
-  int maxz = 0;
   for (int i = 0; i < nb; ++i) {
     const rwpsf_stack& x = s[i];
     pa.s[i].t_s = x.t_s_nm;
     pa.s[i].zoff = x.z_offset_nm;
     for (int q = 0; q < kAxiTerms; ++q)
       pa.s[i].coef[q] = kAxiNoll[q] <= x.n_zernike ? x.zernike_waves[kAxiNoll[q] - 1] : 0.0;
-    maxz = std::max(maxz, x.n_zernike);
   }
-  pa.max_zernike = maxz;
 }
 
 static int bessel_phi(rwpsf_plan* p, const rwpsf_stack* s, int nb, float2* phi, int ld, hipStream_t st) {
@@ -1162,7 +1155,7 @@ struct AdjRadArgs {
   int nx, ny, nz, R, mode, s_base, ld;   // ld: row stride of G_In
   float gscale[kMaxGroups];   // G_In of a group is written times this power of two (group_scales)
   int unit_exp;        // the integer sums' unit is 2^-unit_exp of the bound's power of two
-  float dx, dy, inv_drho, drho;
+  float dx, dy, inv_drho;
   float exr, exi, eyr, eyi;
   float x0[kPhiStacks], y0[kPhiStacks];
 };
@@ -1508,7 +1501,6 @@ int bessel_adjoint(rwpsf_plan* p, int n, const rwpsf_stack* s, const float2* E, 
     ra.dx = (float)p->grid.dx_nm;
     ra.dy = (float)p->grid.dy_nm;
     ra.inv_drho = (float)(1.0 / p->drho);
-    ra.drho = (float)p->drho;
     ra.exr = pol[0];
     ra.exi = pol[1];
     ra.eyr = pol[2];
