@@ -212,8 +212,10 @@ int rwpsf_compute_noalloc(rwpsf_plan* plan, int n_stacks, const rwpsf_stack* sta
    Outputs are overwritten, never accumulated.  Fourier form, vectorial model, with
    nx, ny multiples of 16 (RWPSF_ERR_UNSUPPORTED otherwise).  Every reduction runs in a fixed order,
    so repeated calls give bitwise-identical results.  The first call allocates the adjoint's
-   tables, and a call with more stacks than any before it grows the partial-sum workspace
-   (device allocations; earlier buffers stay owned by the plan until it is destroyed). */
+   tables, and a call with more stacks than any before it may grow the partial-sum workspace,
+   which ends at 1 GiB, or at one stack's partial sums where these are more (at most 1.5 GiB)
+   (device allocations; earlier buffers stay owned by the plan until it is destroyed).  A call
+   that ran out of memory may be repeated. */
 int rwpsf_adjoint(rwpsf_plan* plan, int n_stacks, const rwpsf_stack* stacks, const void* E_in,
                   const float* dL_dI, int n_zernike, float* dL_dc, float* dL_dW0, void* stream);
 
@@ -232,7 +234,8 @@ int rwpsf_adjoint(rwpsf_plan* plan, int n_stacks, const rwpsf_stack* stacks, con
    (RWPSF_ERR_UNSUPPORTED for the other forms, or for n_rho > 3200, whose per-sample
    sums no longer fit one workgroup's LDS).  The gradient is that of the computed
    discrete model (theta rule, radial interpolation).  Every reduction runs in a fixed
-   order, so repeated calls give bitwise-identical results.  The first call on a plan
+   order, so repeated calls give bitwise-identical results.  A stack with a value of E_in or
+   dL_dI that is not finite has NaN gradients, and dL_dc with it.  The first call on a plan
    allocates the adjoint's tables and workspace and synchronises the device. */
 int rwpsf_adjoint_bessel(rwpsf_plan* plan, int n_stacks, const rwpsf_stack* stacks, const void* E_in,
                          const float* dL_dI, float* dL_dc, float* dL_dts, float* dL_dz, void* stream);
@@ -300,8 +303,8 @@ typedef struct rwpsf_batch_config {
 int rwpsf_batch_set_config(rwpsf_batch* batch, const rwpsf_batch_config* cfg);
 int rwpsf_batch_get_config(const rwpsf_batch* batch, rwpsf_batch_config* cfg);
 
-/* Time each candidate configuration on these emitters (outputs written to I_out)
-   and keep the fastest.  Synchronises the stream.  best_ms may be NULL.  If the
+/* Time the candidate configurations whose launches differ on these emitters (outputs
+   written to I_out) and keep the fastest.  Synchronises the stream.  best_ms may be NULL.  If the
    environment variable RWPSF_AUTOTUNE_CACHE names a file, a configuration stored there
    for the same key (pupil size, batch-size bucket, crop mix, mean plane count, CU
    count) is used without timing, and new results are added to it; a file that does

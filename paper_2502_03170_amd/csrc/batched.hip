@@ -170,9 +170,11 @@ __global__ void __launch_bounds__(256) batch_fold_kernel(BatchArgs a) {
 // FP32 MFMA tiles (planes 16.1), 6.0 ms so (planes 4.8 + 1.0); a frame of 100 emitters of one
 // plane 87 -> 30 us.  (Item, emitter and crop size in vector registers and the 64-bit offsets of a
 // lane's sixteen pixels, formed once per plane, spilled 44 registers on the 64-row tile: 2.5 GB
-// written and as much read per call, 6.5-6.7 ms.)  Waves of 32 pupil rows (eight of them) took 7.0
-// + 1.55 ms; table rows of the second product requested ahead of the split of T gave 2.75 -> 3.09
-// ms on the 64-row tile (they spill) and 1.20 -> 1.12 ms on the 32-row tile, where they are.
+// written and as much read per call, 6.5-6.7 ms.  The 64-row tile of N = 128, alone of all, still
+// spills 10, 44 bytes a lane: beside 620 MiB of intensities it writes 23 MiB at one workgroup a CU
+// and 119 at two.)  Waves of 32 pupil rows (eight of them) took 7.0 + 1.55 ms; table rows of the
+// second product requested ahead of the split of T gave 2.75 -> 3.09 ms on the 64-row tile (they
+// spill) and 1.20 -> 1.12 ms on the 32-row tile, where they are.
 template <int N, int SP>
 struct PlaneTile {
   static constexpr int WM = N >= 128 ? 64 : 32;
@@ -309,7 +311,7 @@ __device__ __forceinline__ void batch_plane(const BatchArgs& a, const BatchParam
           ei[r] = y;
         }
         if (Ec) {
-          // row steps formed here: the sixteen offsets, kept over the components, spilled
+          // row steps formed here: the sixteen offsets, kept over the components, spill
           int step = __builtin_amdgcn_readfirstlane(S);
           asm("" : "+s"(step));
           const unsigned o = m0 * step + n;

@@ -363,19 +363,19 @@ static void group_scales(const rwpsf_plan* p, float out[kMaxGroups]) {
 // ghost of sample -1 in front (I_n(-rho) = (-1)^n I_n(rho)), so that a pixel's four samples are
 // 24 consecutive floats.  The ghost of I_0, which equals its sample 1, is left out: the longest
 // table then still fits.
-// Bound by its writes, 28 B a pixel in runs that start and end within cache lines.  A launch whose fields
-// leave the last-level cache runs neighbouring planes on one XCD, so that the lines they share meet in its
-// L2, and keeps few planes of a CU in flight (epi_lds): the fewer runs are open, the fewer of their lines
-// leave L2 half written.  8448 planes of 65 x 65 (1.0 GB): 262 us with eight workgroups a CU, 256 with neighbours on
-// one XCD, 232 with four a CU, 222 with three, 228 with two; with the samples of an integral side by side
-// and more instructions a pixel 245.  Several planes a workgroup, sharing a pixel's stencil and angles,
-// were slower (two planes 249, seven 310 us).
+// Bound by its writes, 28 B a pixel in runs that start and end within cache lines.  A launch whose
+// fields leave the last-level cache runs neighbouring planes on one XCD, so that the lines they share
+// meet in its L2, and keeps few planes of a CU in flight (epi_lds): the fewer runs are open, the fewer
+// of their lines leave L2 half written.  8448 planes of 65 x 65 (1.0 GB): 262 us with eight workgroups
+// a CU, 256 with neighbours on one XCD, 232 with four a CU, 222 with three, 228 with two; with the
+// samples of an integral side by side and more instructions a pixel 245; the stores alone 191.  Several
+// planes a workgroup, sharing a pixel's stencil and angles, were slower (two planes 249, seven 310 us).
 // --------------------------------------------------------------------------
 constexpr int kEpiStacks = 256;   // stacks per contraction and epilogue launch
 // Workgroups per plane in the epilogue: a call with few planes splits each plane into 4
 // runs of pixels, so that more CUs work on it (one stack: 40 -> 31-34 us per call); a call
 // with many planes keeps one workgroup per plane (4 per plane made the 256-stack call's
-// epilogue 246 -> 303 us).  The split does not change any result.
+// epilogue 246 -> 303 us, both with eight workgroups a CU).  The split does not change any result.
 constexpr int kEpiSplitFew = 4, kEpiFewPlanes = 1024;
 struct EpiArgs {
   int nx, ny, nz, R, nstk, s_base, mode, split;   // split: workgroups per plane
@@ -509,9 +509,12 @@ __global__ void __launch_bounds__(256) bessel_epilogue_kernel(EpiArgs a, const f
 // host sets the band edges so that the bands cost about the same (contraction samples
 // against pixels).
 // --------------------------------------------------------------------------
-// Measured on the 65 x 65 x 33 stack: one stack 29.9 -> 21.7 us per call; two stacks
-// 30.9 us either way, three or more slower than the three launches, so only a single
-// stack of at most 64 planes takes this path (at least 8 bands per plane).
+// Bound by its own instructions (the kernel is 20 of the call's 20-odd us): 5.9e6 vector
+// instructions are half of that, most of them the 15 bands' walks over all pixels of a plane and the
+// 64-bit addresses of the table loads.  Measured on the 65 x 65 x 33 stack: one stack 29.9 us as
+// three launches, 21.7 so, 20.2 with Phi from the node table; two stacks 30.9 us either way, three or
+// more slower than the three launches, so only a single stack of at most 64 planes takes this path
+// (at least 8 bands per plane).
 constexpr int kFusedStacks = 1;      // a call of at most this many stacks ...
 constexpr int kFusedPlanes = 64;     // ... and planes takes the fused path
 constexpr int kFusedBands = 64;      // bands per plane, at most

@@ -241,7 +241,7 @@ __global__ void __launch_bounds__(256) pupil_build_folded_kernel(FoldArgs a, con
 // --------------------------------------------------------------------------
 // Measured on 16 stacks of 128 x 128 x 64 at a 256 x 256 pupil (fields and intensity): the
 // call took 1305 us with FP32 MFMA tiles and takes 660 us (pupil GEMM 860 -> 345-400 us, image
-// GEMM 480 -> 310-340 us, whose 0.8 GB of T and 0.47 GB of output are 4 TB/s of HBM); one
+// GEMM 480 -> 310-345 us, whose 0.8 GB of T and 0.47 GB of output are 4 TB/s of HBM); one
 // 201 x 201 image 52 -> 22 us.  The pupil GEMM's pipes hardly overlap: its MFMAs alone need
 // 115 us, without them it takes 257 us, without global loads 247 us; one plane per tile
 // (the pupil then crosses L2 twice as often) 372 us, other tile shapes and occupancies
